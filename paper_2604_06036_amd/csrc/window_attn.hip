@@ -23,8 +23,7 @@
 // sweeps of small batches are split over several items and merged by a second kernel.
 // head_dim 64: one workgroup per row tile, tiles staged through registers.
 //
-// fp32 kernel: plain SIMT, one wave per (query, head), keys strided over lanes, online softmax
-// per lane and a final cross-lane merge.  It exists for fp32 caches (small validation shapes).
+// fp32 kernel: the fp32 matrix instruction, 32 rows per workgroup, keys dealt to its waves.
 #include <math.h>
 
 #include "common.h"
@@ -1520,73 +1519,219 @@ __global__ __launch_bounds__(256) void window_attn_merge_kernel(AttnParams p) {
 }
 
 // ------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void window_attn_f32_kernel(AttnParams p) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t unit = static_cast<int64_t>(blockIdx.x) * 4 + wave;      // (query, head)
-  if (unit >= p.n_q * p.n_q_heads) return;
-  const int tok = static_cast<int>(unit / p.n_q_heads);
-  if (tok >= p.cu_q[p.n_streams]) return;               // n_q may be an upper bound
-  const int head = static_cast<int>(unit - static_cast<int64_t>(tok) * p.n_q_heads);
-  const int kvh = head / p.group;
-  int s = 0;
-  while (s + 1 < p.n_streams && p.cu_q[s + 1] <= tok) ++s;
-  const int32_t* bt = p.block_table + static_cast<int64_t>(s) * p.max_blocks;
-  const int lim = min(p.q_pos[tok], min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1);
-  if (lim < 0) return;                    // the stream defines no cache entry (or q_pos < 0): row left untouched
+// fp32: a workgroup = 8 waves = 32 rows (query token, query head of one kv group) of one stream; the
+// waves take every eighth tile of 32 keys and merge their partial results through LDS at the end, so
+// that a short window still puts eight waves on its few row tiles and the sums over the keys stay
+// short.  Both contractions run on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: products and
+// sums in fp32), fed from global memory / L2 without staging: its operands are one float per lane and
+// an instruction takes 64 cycles, so a wave's loads keep ahead of it.
+//   S^T = K Q^T    half h of the wave contributes d = 8 i + 4 h + j (16-byte loads of K and Q rows),
+//                  even and odd i in accumulators of their own (two chains of D/2 sums)
+//   O^T += V^T P^T step r contracts the two keys that register r of S^T holds in the two halves
+// A tile's P V is summed from zero and then added to the running output, so no chain of sums is longer
+// than 32 + (tiles of the wave).  What bounds it: matrix instructions on long windows, the chain
+// block table -> K -> S -> V of a wave's few tiles on short ones.
+// Measured against one token and head per wave with the keys dealt to lanes (which read every K/V row
+// once per query head, 64 rows scattered over the lanes of each load): 337 tokens, 2 heads of 64,
+// 452 keys 41.5 -> 19.6 us; 424 tokens, 28 heads of 128, 919 keys 959 -> 58.7 us; 2,082 tokens, 6,033
+// keys 30.1 -> 1.63 ms (83 TFLOP/s of the 157 the unit has).  Error against 64 bits 2.1e-7..3.0e-7
+// before, 1.6e-7..2.1e-7 now.
+constexpr int kF32Rows = 32, kF32Keys = 32, kF32Waves = 8;
 
-  const float* qrow = static_cast<const float*>(p.q) + (static_cast<int64_t>(tok) * p.n_q_heads + head) * D;
-  float qv[D], acc[D];
+// Stream and first row of the row tile with index x (tiles of BM rows, streams in order): 64 streams
+// per turn, one lane each.  Returns the stream or -1; all lanes of the wave take the same values.
+template <int BM>
+__device__ __forceinline__ int find_row_tile(const int32_t* cu_q, int n_streams, int group, int64_t x, int& q0,
+                                             int& rows_total, int64_t& tile, int64_t& n_tiles) {
+  const int lane = threadIdx.x & 63;
+  int64_t before = 0;
+  for (int s0 = 0; s0 < n_streams; s0 += 64) {
+    const int s = s0 + lane;
+    const int lo = s < n_streams ? cu_q[s] : 0, hi = s < n_streams ? cu_q[s + 1] : 0;
+    const int tiles = ((hi - lo) * group + BM - 1) / BM;
+    int incl = tiles;
 #pragma unroll
-  for (int c = 0; c < D; c += 4) {
-    const float4 t = *reinterpret_cast<const float4*>(qrow + c);
-    qv[c] = t.x; qv[c + 1] = t.y; qv[c + 2] = t.z; qv[c + 3] = t.w;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int t = __shfl_up(incl, off);
+      if (lane >= off) incl += t;
+    }
+    const unsigned long long found = __ballot(x < before + incl);
+    if (found) {
+      const int at = __ffsll(found) - 1;
+      q0 = __builtin_amdgcn_readlane(lo, at);
+      rows_total = (__builtin_amdgcn_readlane(hi, at) - q0) * group;
+      n_tiles = __builtin_amdgcn_readlane(tiles, at);
+      tile = x - (before + __builtin_amdgcn_readlane(incl, at) - n_tiles);
+      return s0 + at;
+    }
+    before += __builtin_amdgcn_readlane(incl, 63);
   }
+  return -1;
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves, 2) void window_attn_f32_kernel(AttnParams p) {
+  constexpr int DB = D / 32, VECS = D / 8;
+  __shared__ float s_o[kF32Waves / 2][DB * 16][64];
+  __shared__ float s_ml[kF32Waves / 2][2][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 31, h = lane >> 5;
+
+  int q0 = 0, rows_total = 0;
+  int64_t tile = 0, n_tiles = 0;
+  const int s = find_row_tile<kF32Rows>(p.cu_q, p.n_streams, p.group, blockIdx.x / p.n_kv_heads, q0, rows_total, tile, n_tiles);
+  if (s < 0) return;                                     // n_q may be an upper bound
+  const int r_tile = static_cast<int>(n_tiles - 1 - tile) * kF32Rows;     // longest sweeps first
+  const int kvh = blockIdx.x % p.n_kv_heads;
+  const int32_t* bt = p.block_table + static_cast<int64_t>(s) * p.max_blocks;
+  const int cap = min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1;
+
+  const int row = r_tile + n;
+  const bool valid = row < rows_total;
+  const int row_c = valid ? row : rows_total - 1;
+  const int tok = q0 + row_c / p.group;
+  const int head = kvh * p.group + row_c % p.group;
+  const int lim = valid ? min(p.q_pos[tok], cap) : -1;
+  int top = lim, low = valid ? lim : 0x7fffffff;         // highest and lowest frontier of the rows
 #pragma unroll
-  for (int c = 0; c < D; ++c) acc[c] = 0.f;
+  for (int off = 16; off > 0; off >>= 1) {
+    top = max(top, __shfl_xor(top, off));
+    low = min(low, __shfl_xor(low, off));
+  }
+  top = __builtin_amdgcn_readfirstlane(top);
+  low = __builtin_amdgcn_readfirstlane(low);
+  if (top < 0) return;                    // no row sees a cache entry (the same in every wave): rows left untouched
+  const int n_key_tiles = top / kF32Keys + 1;
+
+  const int64_t q_at = (static_cast<int64_t>(tok) * p.n_q_heads + head) * D;
+  const float* qrow = static_cast<const float*>(p.q) + q_at;
+  float4 qv[VECS];
+#pragma unroll
+  for (int i = 0; i < VECS; ++i) qv[i] = *reinterpret_cast<const float4*>(qrow + 8 * i + 4 * h);
+
+  f32x16 o[DB];
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int db = 0; db < DB; ++db) o[db] = zero16;
   float m = kNegInf, l = 0.f;
   const float* kb = static_cast<const float*>(p.k) + kvh * p.stride_head;
   const float* vb = static_cast<const float*>(p.v) + kvh * p.stride_head;
-  for (int j = lane; j <= lim; j += 64) {
-    const int64_t slot = static_cast<int64_t>(bt[j / CS_KV_BLOCK]) * CS_KV_BLOCK + j % CS_KV_BLOCK;
-    const float* kr = kb + slot * p.stride_slot;
-    const float* vr = vb + slot * p.stride_slot;
-    float dot = 0.f;
+  const int last_blk = top / CS_KV_BLOCK;
+
+  for (int kt = wave; kt < n_key_tiles; kt += kF32Waves) {
+    const int j0 = kt * kF32Keys;
+    // rows past the highest frontier may be unallocated: their lanes take the frontier row (weight 0)
+    const int64_t blk0 = bt[2 * kt], blk1 = bt[min(2 * kt + 1, last_blk)];
+    auto slot_of = [&](int j) {                          // j inside this tile
+      const int jc = min(j, top);
+      return (jc - j0 < CS_KV_BLOCK ? blk0 : blk1) * CS_KV_BLOCK + jc % CS_KV_BLOCK;
+    };
+    const float* kr = kb + slot_of(j0 + n) * p.stride_slot + 4 * h;
+    f32x16 sa = zero16, sb = zero16;
 #pragma unroll
-    for (int c = 0; c < D; c += 4) {
-      const float4 t = *reinterpret_cast<const float4*>(kr + c);
-      dot = fmaf(qv[c], t.x, dot); dot = fmaf(qv[c + 1], t.y, dot);
-      dot = fmaf(qv[c + 2], t.z, dot); dot = fmaf(qv[c + 3], t.w, dot);
+    for (int i = 0; i < VECS; ++i) {
+      const float4 t = *reinterpret_cast<const float4*>(kr + 8 * i);
+      f32x16& c = i & 1 ? sb : sa;
+      if (i == VECS / 2) __builtin_amdgcn_sched_barrier(0);            // half of the row in registers at a time
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(t.x, qv[i].x, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(t.y, qv[i].y, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(t.z, qv[i].z, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(t.w, qv[i].w, c, 0, 0, 0);
     }
-    const float sc = dot * p.scale;
-    const float m_new = fmaxf(m, sc);
-    const float a = expf(m - m_new);            // exp(-inf) = 0 on the first key
-    const float w = expf(sc - m_new);
-    l = fmaf(l, a, w);
+    // register r is key j0 + 8 (r / 4) + 4 h + r % 4 of query n
+    float sc[16], t_max = kNegInf;
+    const bool straddles = j0 + kF32Keys - 1 > low;
 #pragma unroll
-    for (int c = 0; c < D; c += 4) {
-      const float4 t = *reinterpret_cast<const float4*>(vr + c);
-      acc[c] = fmaf(acc[c], a, w * t.x); acc[c + 1] = fmaf(acc[c + 1], a, w * t.y);
-      acc[c + 2] = fmaf(acc[c + 2], a, w * t.z); acc[c + 3] = fmaf(acc[c + 3], a, w * t.w);
+    for (int r = 0; r < 16; ++r) {
+      sc[r] = (sa[r] + sb[r]) * p.scale;
+      if (straddles && j0 + 8 * (r / 4) + 4 * h + r % 4 > lim) sc[r] = kNegInf;
+      t_max = fmaxf(t_max, sc[r]);
     }
+    t_max = fmaxf(t_max, __shfl_xor(t_max, 32));
+    const float m_new = fmaxf(m, t_max);
+    const float m_ref = m_new == kNegInf ? 0.f : m_new;  // a row that sees none of these keys
+    const float alpha = expf(m - m_ref);                 // exp(-inf) = 0 on the first keys
+    float l_tile = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      sc[r] = expf(sc[r] - m_ref);
+      l_tile += sc[r];
+    }
+    l = fmaf(l, alpha, l_tile);
     m = m_new;
+    // a value row that is masked for some of the queries takes part in the product with weight 0: one
+    // that is not finite must not reach them
+    bool finite = true;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      float vv[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        vv[r] = vb[slot_of(j0 + 8 * (r / 4) + 4 * h + r % 4) * p.stride_slot + 32 * db + n];
+      f32x16 t = zero16;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) t = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[r], sc[r], t, 0, 0, 0);
+      if (straddles) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) finite = finite && fabsf(vv[r]) < INFINITY;
+        if (__any(!finite)) {
+          t = zero16;
+#pragma unroll 1
+          for (int key = 0; key < kF32Keys; ++key) {
+            const int r = 4 * (key / 8) + key % 4, hh = (key >> 2) & 1;
+            float mine = 0.f;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) mine = k == r ? sc[k] : mine;
+            const float w = __shfl(mine, n + 32 * hh);
+            const float* vr = vb + slot_of(j0 + key) * p.stride_slot + 32 * db;
+            if (j0 + key <= lim) {
+#pragma unroll
+              for (int k = 0; k < 16; ++k) t[k] = fmaf(w, vr[8 * (k / 4) + 4 * h + k % 4], t[k]);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[db][r] = fmaf(o[db][r], alpha, t[r]);
+    }
   }
-  // merge the 64 per-lane partial results
-  float m_all = m;
+
+  // ---- the waves' partial results: the upper half of the waves hands over to the lower half, three times
+  float l_all = l + __shfl_xor(l, 32);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m_all = fmaxf(m_all, __shfl_xor(m_all, off));
-  const float w = m == kNegInf ? 0.f : expf(m - m_all);
-  float l_all = l * w;
+  for (int half = kF32Waves / 2; half > 0; half >>= 1) {
+    if (wave >= half && wave < 2 * half) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) l_all += __shfl_xor(l_all, off);
-  const float inv = 1.f / l_all;
-  float* orow = static_cast<float*>(p.out) + (static_cast<int64_t>(tok) * p.n_q_heads + head) * D;
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
-  for (int c = 0; c < D; ++c) {
-    float t = acc[c] * w;
+        for (int r = 0; r < 16; ++r) s_o[wave - half][db * 16 + r][lane] = o[db][r];
+      s_ml[wave - half][0][lane] = m;
+      s_ml[wave - half][1][lane] = l_all;
+    }
+    __syncthreads();
+    if (wave < half) {
+      const float m_o = s_ml[wave][0][lane], l_o = s_ml[wave][1][lane];
+      const float m_new = fmaxf(m, m_o);
+      const float a = m == kNegInf ? 0.f : expf(m - m_new), b = m_o == kNegInf ? 0.f : expf(m_o - m_new);
+      l_all = fmaf(l_all, a, l_o * b);
+      m = m_new;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
-    if (lane == (c & 63)) orow[c] = t * inv;
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] = fmaf(o[db][r], a, s_o[wave][db * 16 + r][lane] * b);
+    }
+    __syncthreads();
+  }
+  if (wave == 0 && lim >= 0) {            // register r of block db is d = 32 db + 8 (r / 4) + 4 h + r % 4
+    const float inv = 1.f / l_all;
+    float* orow = static_cast<float*>(p.out) + q_at;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq)
+        *reinterpret_cast<float4*>(orow + 32 * db + 8 * rq + 4 * h) =
+            make_float4(o[db][4 * rq] * inv, o[db][4 * rq + 1] * inv, o[db][4 * rq + 2] * inv, o[db][4 * rq + 3] * inv);
   }
 }
 
@@ -1825,12 +1970,13 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       hipLaunchKernelGGL(window_attn_bf16_kernel<64>, grid, dim3(256), bt_bytes, st, p);
     }
   } else {
-    const int64_t units = n_q * n_q_heads;
-    const dim3 grid(static_cast<unsigned>((units + 3) / 4));
+    const int64_t tiles = ((n_q * group) / kF32Rows + n_streams) * n_kv_heads;       // upper bound on row tiles
+    if (tiles > 0x7fffffffll) return CS_EUNSUPPORTED;
+    const dim3 grid(static_cast<unsigned>(tiles)), block(64 * kF32Waves);
     if (head_dim == 128)
-      hipLaunchKernelGGL(window_attn_f32_kernel<128>, grid, dim3(256), 0, st, p);
+      hipLaunchKernelGGL(window_attn_f32_kernel<128>, grid, block, 0, st, p);
     else
-      hipLaunchKernelGGL(window_attn_f32_kernel<64>, grid, dim3(256), 0, st, p);
+      hipLaunchKernelGGL(window_attn_f32_kernel<64>, grid, block, 0, st, p);
   }
   return cs::note_hip(hipGetLastError());
 }
