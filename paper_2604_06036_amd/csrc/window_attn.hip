@@ -21,7 +21,7 @@
 // head_dim 128: a planning kernel lists the work items of the launch and persistent workgroups
 // stream K/V tiles from HBM straight into LDS (global_load_lds), across item boundaries; long key
 // sweeps of small batches are split over several items and merged by a second kernel.
-// head_dim 64: one workgroup per row tile, tiles staged through registers.
+// head_dim 64: one workgroup per row tile, no plan, key ranges shared inside it.
 //
 // fp32 kernel: the fp32 matrix instruction, 32 rows per workgroup, keys dealt to its waves.
 #include <math.h>
@@ -74,7 +74,7 @@ struct AttnParams {
 constexpr int kBM = 128;   // rows per workgroup (4 waves x 32)
 constexpr int kBN = 64;    // keys per LDS tile
 constexpr float kNegInf = -INFINITY;
-constexpr int kMaxBlocksInLds = 8192;   // block-table row staged in LDS: windows up to 131072 tokens
+constexpr int kMaxBlocks64 = 8192;      // head_dim 64: windows up to 131072 tokens
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -89,231 +89,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // raised (and the accumulators rescaled) when the tile maximum exceeds it by more than this, so
 // probabilities stay below 2^kMaxSlack and almost every tile skips the rescale.
 constexpr float kMaxSlack = 8.0f;
-
-template <int D>
-__global__ __launch_bounds__(256, 2) void window_attn_bf16_kernel(AttnParams p) {
-  constexpr int KP = D + 8;            // K tile pitch (elements): rows shift by 4 banks
-  constexpr int VP = D + 32;           // V tile pitch: rows shift by 16 banks (transpose reads)
-  constexpr int STEPS = D / 16;        // contraction steps of S^T
-  constexpr int DB = D / 32;           // 32-wide blocks of the head dimension in O^T
-  constexpr int CPR = D / 8;           // 16-byte chunks per cache row
-  constexpr int RPP = 256 / CPR;       // rows staged per pass by the whole workgroup
-  constexpr int RPW = 64 / CPR;        // rows staged per pass by one wave (inside one cache block)
-  constexpr int PASSES = kBN / RPP;
-  constexpr int BPT = kBN / CS_KV_BLOCK;   // cache blocks per key tile
-
-  __shared__ __attribute__((aligned(16))) uint16_t sK[kBN * KP];
-  __shared__ __attribute__((aligned(16))) uint16_t sV[kBN * VP];
-  extern __shared__ int32_t s_bt[];    // this stream's block-table row (max_blocks entries)
-
-  // ---- which (stream, row tile) is this workgroup?  longest tiles of a stream come first
-  int x = blockIdx.x, s = 0, q0 = 0, rows_total = 0, n_row_tiles = 0;
-  for (; s < p.n_streams; ++s) {
-    q0 = p.cu_q[s];
-    rows_total = (p.cu_q[s + 1] - q0) * p.group;
-    n_row_tiles = (rows_total + kBM - 1) / kBM;
-    if (x < n_row_tiles) break;
-    x -= n_row_tiles;
-  }
-  if (s == p.n_streams) return;
-  const int r_tile = (n_row_tiles - 1 - x) * kBM;
-  const int kvh = blockIdx.y;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = lane & 31, h = lane >> 5;
-
-  // ---- this lane's row (query token, head) and causal frontier
-  const int row = r_tile + wave * 32 + n;
-  const bool valid = row < rows_total;
-  const int row_c = valid ? row : rows_total - 1;
-  const int tok = q0 + row_c / p.group;
-  const int head = kvh * p.group + row_c % p.group;
-  // a frontier never lies past the entries the stream's block-table row defines
-  const int cap = min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1;
-  const int lim = valid ? min(p.q_pos[tok], cap) : -1;
-
-  const int wg_last = min(r_tile + kBM, rows_total) - 1;
-  const int wg_max = min(p.q_pos[q0 + wg_last / p.group], cap);
-  const int w_first = r_tile + wave * 32;
-  const bool wave_live = w_first < rows_total;
-  const int w_last = min(w_first + 31, rows_total - 1);
-  const int wave_min = wave_live ? min(p.q_pos[q0 + w_first / p.group], cap) : -1;
-  const int wave_max = wave_live ? min(p.q_pos[q0 + w_last / p.group], cap) : -1;
-  if (wg_max < 0) return;                 // the stream defines no cache entry: nothing to attend to
-  const int n_key_tiles = wg_max / kBN + 1;
-  const int last_blk = wg_max / CS_KV_BLOCK;
-
-  // ---- Q^T fragments: lane = (query n, half h) holds d-slice [16*step + 8h, +8)
-  const uint16_t* qrow = static_cast<const uint16_t*>(p.q) +
-                         (static_cast<int64_t>(tok) * p.n_q_heads + head) * D;
-  bf16x8 qf[STEPS];
-#pragma unroll
-  for (int st = 0; st < STEPS; ++st)
-    qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const cs::u32x4*>(qrow + 16 * st + 8 * h));
-
-  f32x16 o[DB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-  float m_run = kNegInf, l_run = 0.f;
-  const float slack = kMaxSlack / p.scale_log2e;          // in raw score units
-
-  // ---- staging of K/V tiles.  Thread -> row st_row + pass * RPP of the tile, chunk st_chunk.
-  // A wave's rows of one pass lie inside one 16-token cache block, so the block id is
-  // wave-uniform and the per-lane part of the address never changes.
-  const int st_row = tid / CPR, st_chunk = tid % CPR;
-  const int32_t* bt = p.block_table + static_cast<int64_t>(s) * p.max_blocks;
-  const int64_t lane_off = static_cast<int64_t>(st_row % CS_KV_BLOCK) * p.stride_slot +
-                           static_cast<int64_t>(kvh) * p.stride_head + st_chunk * 8;
-  const uint16_t* kbase = static_cast<const uint16_t*>(p.k) + lane_off;
-  const uint16_t* vbase = static_cast<const uint16_t*>(p.v) + lane_off;
-  const int64_t blk_stride = static_cast<int64_t>(CS_KV_BLOCK) * p.stride_slot;
-  cs::u32x4 kreg[PASSES], vreg[PASSES];
-
-  for (int i = tid; i <= last_blk; i += 256) s_bt[i] = bt[i];
-  __syncthreads();
-
-  // Full tiles: every row is a live cache entry.  The last tile may end inside a block (rows past
-  // the frontier are staged as zeros: they can hold anything) or before a block the table does
-  // not define (never read).
-  auto fetch = [&](int key_tile, bool last) {
-#pragma unroll
-    for (int i = 0; i < PASSES; ++i) {
-      const int bi = key_tile * BPT + (i * RPP + wave * RPW) / CS_KV_BLOCK;     // wave-uniform
-      if (!last || bi <= last_blk) {
-        const int64_t blk = __builtin_amdgcn_readfirstlane(s_bt[bi]);
-        kreg[i] = *reinterpret_cast<const cs::u32x4*>(kbase + blk * blk_stride);
-        vreg[i] = *reinterpret_cast<const cs::u32x4*>(vbase + blk * blk_stride);
-      }
-      if (last && (bi > last_blk || key_tile * kBN + st_row + i * RPP > wg_max)) {
-        kreg[i] = cs::u32x4{0, 0, 0, 0};
-        vreg[i] = cs::u32x4{0, 0, 0, 0};
-      }
-    }
-  };
-
-  if (n_key_tiles == 1) fetch(0, true); else fetch(0, false);
-  for (int kt = 0; kt < n_key_tiles; ++kt) {
-    __syncthreads();                       // everyone is done reading the previous tile
-#pragma unroll
-    for (int i = 0; i < PASSES; ++i) {
-      const int r = st_row + i * RPP;
-      *reinterpret_cast<cs::u32x4*>(&sK[r * KP + st_chunk * 8]) = kreg[i];
-      *reinterpret_cast<cs::u32x4*>(&sV[r * VP + st_chunk * 8]) = vreg[i];
-    }
-    __syncthreads();
-    if (kt + 2 < n_key_tiles) fetch(kt + 1, false);
-    else if (kt + 1 < n_key_tiles) fetch(kt + 1, true);
-
-    const int j0 = kt * kBN;
-    if (j0 > wave_max) continue;           // wholly above this wave's frontier (wave-uniform)
-
-    // ---- S^T = K Q^T for the 64 keys of the tile: two 32-key blocks, MFMAs alternate between
-    //      the two accumulators so that consecutive ones are independent
-    f32x16 sacc[2];
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        const bf16x8 a = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const cs::u32x4*>(&sK[(kb * 32 + n) * KP + 16 * st + 8 * h]));
-        sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[st], st == 0 ? zero16 : sacc[kb], 0, 0, 0);
-      }
-    }
-    // register r of block kb is key j0 + 32 kb + 8 (r / 4) + 4 h + r % 4 of query n
-    if (j0 + kBN - 1 > wave_min) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = j0 + 32 * kb + 8 * (r / 4) + 4 * h + (r % 4);
-          if (key > lim) sacc[kb][r] = kNegInf;
-        }
-    }
-    float t_max = kNegInf;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) t_max = fmaxf(t_max, sacc[kb][r]);
-    t_max = fmaxf(t_max, __shfl_xor(t_max, 32));
-    // raise the row's reference maximum only when the tile exceeds it by more than the slack
-    // (always on the first visible key: m_run = -inf); both half-waves take the same decision
-    if (__any(t_max > m_run + slack)) {
-      const bool up = t_max > m_run + slack;
-      const float m_new = up ? t_max : m_run;
-      const float alpha = up ? __builtin_amdgcn_exp2f((m_run - m_new) * p.scale_log2e) : 1.f;
-      m_run = m_new;
-      l_run *= alpha;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-    }
-    const float m_scaled = (m_run == kNegInf ? 0.f : m_run) * p.scale_log2e;
-
-    // ---- P = exp2(S c - m c), packed to bf16 in B-operand order.  MFMA (kb, mm) contracts S
-    //      registers 8mm..8mm+7 of block kb; slot 8h + i of the contraction is key
-    //      32 kb + 16 mm + 8 (i / 4) + 4 h + i % 4.  Row sums are taken over the rounded values.
-    bf16x8 pb[2][2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        cs::u32x4 w;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float e0 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * mm + 2 * c], p.scale_log2e, -m_scaled));
-          const float e1 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * mm + 2 * c + 1], p.scale_log2e, -m_scaled));
-          const uint32_t pk = pack_bf16x2(e0, e1);
-          l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk),
-                                                  __builtin_bit_cast(bf16x2, 0x3f803f80u), l_run, false);
-          w[c] = pk;
-        }
-        pb[kb][mm] = __builtin_bit_cast(bf16x8, w);
-      }
-
-    // ---- O^T += V^T P^T.  Transpose read: lane i of a 16-lane group supplies
-    //      &V[key0 + i / 4][col0 + 4 (i % 4)] and receives V[key0 + 0..3][col0 + i]
-    const int i16 = lane & 15, gid = (lane >> 4) & 1;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        const int key0 = 32 * kb + 16 * mm + 4 * h + (i16 >> 2);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const int col = 32 * db + 16 * gid + 4 * (i16 & 3);
-          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_s16x4*)(&sV[key0 * VP + col]));
-          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_s16x4*)(&sV[(key0 + 8) * VP + col]));
-          const s16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pb[kb][mm],
-                                                         o[db], 0, 0, 0);
-        }
-      }
-  }
-
-  // ---- normalise and store: register r of block db is d = 32 db + 8 (r / 4) + 4 h + r % 4
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  if (valid) {
-    const float inv = 1.f / l_tot;
-    uint16_t* orow = static_cast<uint16_t*>(p.out) +
-                     (static_cast<int64_t>(tok) * p.n_q_heads + head) * D;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        cs::u32x2 w;
-        w.x = pack_bf16x2(o[db][4 * rq + 0] * inv, o[db][4 * rq + 1] * inv);
-        w.y = pack_bf16x2(o[db][4 * rq + 2] * inv, o[db][4 * rq + 3] * inv);
-        *reinterpret_cast<cs::u32x2*>(orow + 32 * db + 8 * rq + 4 * h) = w;
-      }
-  }
-}
 
 // ------------------------------------------------------------------------------------------
 // Tile transport for head_dim 128 (the shape of every bf16 workload measured).
@@ -369,6 +144,385 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+typedef __attribute__((ext_vector_type(8))) int32_t i32x8;
+
+// Scalar loads issued by hand: the results are uniform, travel outside the vector-memory queue
+// (so waiting for them never drains tile requests) and are only read after the explicit wait.
+__device__ __forceinline__ i32x8 sload8(const void* ptr) {
+  i32x8 v;
+  asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
+  return v;
+}
+__device__ __forceinline__ int32_t sload1(const void* ptr) {
+  int32_t v;
+  asm volatile("s_load_dword %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
+  return v;
+}
+
+// One row tile of a launch without a plan: stream, kv head, first row.
+struct RowTile {
+  int s, kvh, q0, rows_total, r_tile;
+};
+
+// Which (stream, kv head, tile of BM rows) is workgroup b?  False: none (n_q may be an upper bound).  The streams'
+// tile counts are added up 64 streams per turn, one lane each; all lanes take the same values.  Longest sweeps of a
+// stream come first, the kv heads of a tile are neighbours, so each XCD (workgroups go round robin) serves a share
+// of every stream.  A list cut into one run per XCD, so that the tiles of a (stream, kv head) pair share its K and V
+// in one L2, was level when all streams are alike and 5-13 % slower when they differ: the runs then carry unequal
+// work (12 streams of 900 keys, head_dim 64: 33.4 against 30.5 us).
+template <int BM>
+__device__ __forceinline__ bool find_row_tile(const AttnParams& p, int b, RowTile& t) {
+  const int lane = threadIdx.x & 63;
+  const int x = b / p.n_kv_heads;
+  int64_t before = 0;
+  for (int s0 = 0; s0 < p.n_streams; s0 += 64) {
+    const int s = s0 + lane;
+    const int lo = s < p.n_streams ? p.cu_q[s] : 0;
+    const int rows = s < p.n_streams ? (p.cu_q[s + 1] - lo) * p.group : 0;
+    const int tiles = (rows + BM - 1) / BM;
+    int incl = tiles;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
+    }
+    const unsigned long long found = __ballot(x < before + incl);
+    if (found) {
+      const int at = __ffsll(found) - 1;
+      t.s = s0 + at;
+      t.kvh = b % p.n_kv_heads;
+      t.q0 = __builtin_amdgcn_readlane(lo, at);
+      t.rows_total = __builtin_amdgcn_readlane(rows, at);
+      t.r_tile = static_cast<int>(before + __builtin_amdgcn_readlane(incl, at) - 1 - x) * BM;
+      return true;
+    }
+    before += __builtin_amdgcn_readlane(incl, 63);
+  }
+  return false;
+}
+
+// bf16, one launch and no plan: a workgroup = one tile of 32 ROWW rows of one (stream, kv head), its waves
+// arranged as KG key groups of ROWW row waves.  Group g sweeps key tiles g, g + KG, ...; the groups' partial
+// results meet in LDS at the end, so a sweep is shared by KG times as many waves without a trip through memory
+// and without a merge launch.  head_dim 64 always runs here.
+// Tiles go to LDS by DMA with the persistent kernel's layout and swizzle idea.  STAGES 2: the next tile is requested
+// at the top of a tile, one workgroup barrier per tile.  STAGES 1 (half the LDS: more workgroups per CU, or more key
+// groups): K of the next tile is requested when S is done and lands behind P V, V when P V is done and lands behind
+// S and the softmax; two barriers per tile.
+// What bounds it: with few row tiles the serial chain of the longest sweep (per tile barrier, S, softmax, P V),
+// hence the key groups; with many the vector pipe (head_dim 64 has the softmax of 128 over half the MFMAs).
+// head_dim 64 against single-buffered tiles staged through registers, us a layer in a step: one stream of 900 keys,
+// 16/4 heads 20.0 -> 15.2; 4 streams, 28/4 heads 29.0 -> 23.5; 12 streams, 16/4 35.0 -> 26.9; 32 streams 62.0 -> 58.7;
+// 2 streams of 8,600 keys 231 -> 140.
+template <int D>
+__device__ __forceinline__ int k_swizzle(int r) { return D == 128 ? r & 15 : (r >> 1) & 7; }
+template <int D>
+__device__ __forceinline__ int v_swizzle(int r) {
+  return D == 128 ? 4 * (r & 3) + 2 * ((r >> 2) & 1) : 4 * ((r >> 1) & 1) + 2 * ((r >> 2) & 1);
+}
+
+template <int D, int ROWW, int KG, int STAGES>
+__global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_bf16_tile_kernel(AttnParams p) {
+  constexpr int BM = 32 * ROWW;
+  constexpr int STEPS = D / 16, DB = D / 32;
+  constexpr int TILE = kBN * D;        // elements of one K (or V) tile, unpadded
+  constexpr int CPR = D / 8;           // 16-byte chunks per row
+  constexpr int RPD = 64 / CPR;        // rows per 1-KiB DMA instruction
+  constexpr int IPW = CPR / ROWW;      // DMA instructions per wave, per tile, per tensor
+  constexpr int BPW = kBN / ROWW / CS_KV_BLOCK;      // cache blocks a wave requests per tile
+  constexpr int IPB = IPW / BPW;       // its DMA instructions per block
+  static_assert(BPW >= 1 && IPB * RPD == CS_KV_BLOCK, "a DMA instruction stays inside a cache block");
+
+  __shared__ __attribute__((aligned(1024))) uint16_t s_kv[KG][STAGES][2][TILE];
+  __shared__ float s_ml[KG > 1 ? KG / 2 : 1][ROWW][2][64];
+  static_assert(sizeof(s_kv) >= sizeof(float) * (KG / 2) * ROWW * DB * 16 * 64, "the merge reuses the tile buffers");
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rw = wave % ROWW, kg = wave / ROWW;
+  const int n = lane & 31, h = lane >> 5;
+
+  RowTile t;
+  if (!find_row_tile<BM>(p, blockIdx.x, t)) return;
+  const int s = __builtin_amdgcn_readfirstlane(t.s), kvh = __builtin_amdgcn_readfirstlane(t.kvh);
+  const int q0 = __builtin_amdgcn_readfirstlane(t.q0), rows_total = __builtin_amdgcn_readfirstlane(t.rows_total);
+  const int r_tile = __builtin_amdgcn_readfirstlane(t.r_tile);
+
+  // ---- this lane's row (query token, head) and causal frontier, kept inside the entries the stream's
+  //      block-table row defines
+  const int w_first = r_tile + rw * 32;
+  const int row = w_first + n;
+  const bool valid = row < rows_total;
+  const int row_c = valid ? row : rows_total - 1;
+  const int tok = q0 + row_c / p.group;
+  const int head = kvh * p.group + row_c % p.group;
+  const int cap = min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1;
+  const int lim = valid ? min(p.q_pos[tok], cap) : -1;
+  const int wg_max = min(p.q_pos[q0 + (min(r_tile + BM, rows_total) - 1) / p.group], cap);
+  if (wg_max < 0) return;                               // the stream defines no cache entry: rows left untouched
+  // positions do not decrease along the rows
+  const int rows_here = min(32, rows_total - w_first);
+  const int wave_min = rows_here > 0 ? __builtin_amdgcn_readlane(lim, 0) : -1;
+  const int wave_max = rows_here > 0 ? __builtin_amdgcn_readlane(lim, max(rows_here, 1) - 1) : -1;
+  const int n_key_tiles = wg_max / kBN + 1;
+  const int last_blk = wg_max / CS_KV_BLOCK;
+
+  // ---- tile requests.  This wave fetches rows [16 BPW rw, + 16 BPW) of its group's tiles; inside a cache block
+  //      a lane's source offset is constant.  The tile that holds the frontier takes per-lane addresses: rows past
+  //      the frontier may be unallocated or hold anything, they fetch the frontier row instead (finite data,
+  //      weight 0 after masking).  So does every tile when a block spans more than 32 bits of byte offset.
+  const int32_t* bt = p.block_table + static_cast<int64_t>(s) * p.max_blocks;
+  const uint16_t* kh = static_cast<const uint16_t*>(p.k) + static_cast<int64_t>(kvh) * p.stride_head;
+  const uint16_t* vh = static_cast<const uint16_t*>(p.v) + static_cast<int64_t>(kvh) * p.stride_head;
+  const int l_row = lane / CPR, l_pos = lane % CPR;
+  const bool wide = p.stride_slot >= (1ll << 26);
+  const int64_t blk_stride = static_cast<int64_t>(CS_KV_BLOCK) * p.stride_slot;
+  auto chunk_of = [&](int i, bool v) { return l_pos ^ (v ? v_swizzle<D>(RPD * i + l_row) : k_swizzle<D>(RPD * i + l_row)); };
+  uint32_t k_off[IPB], v_off[IPB];
+#pragma unroll
+  for (int i = 0; i < IPB; ++i) {
+    const uint32_t at = static_cast<uint32_t>((RPD * i + l_row) * p.stride_slot);
+    k_off[i] = (at + chunk_of(i, false) * 8) * 2;
+    v_off[i] = (at + chunk_of(i, true) * 8) * 2;
+  }
+  // cache blocks of this wave's share of a tile: scalar loads, so that waiting for them does not drain the tile
+  // requests; issued unconditionally (the last tile's blocks again when there is no next tile)
+  int ids[BPW], ids_next[BPW];
+  auto load_ids = [&](int kt) {
+#pragma unroll
+    for (int b = 0; b < BPW; ++b)
+      ids_next[b] = sload1(bt + min(min(kt, n_key_tiles - 1) * (kBN / CS_KV_BLOCK) + rw * BPW + b, last_blk));
+  };
+  auto wait_ids = [&]() {
+#pragma unroll
+    for (int b = 0; b < BPW; ++b) {
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(ids_next[b]));
+      ids[b] = ids_next[b];
+    }
+  };
+  int last_id = sload1(bt + last_blk);
+  auto request = [&](int kt, int stage, int which) {
+    const uint16_t* base = which ? vh : kh;
+    uint16_t* dst = &s_kv[kg][stage][which][rw * IPW * 512];
+    if (kt != n_key_tiles - 1 && !wide) {
+#pragma unroll
+      for (int b = 0; b < BPW; ++b) {
+        const uint16_t* src = base + ids[b] * blk_stride;
+#pragma unroll
+        for (int i = 0; i < IPB; ++i) dma16_s(which ? v_off[i] : k_off[i], src, dst + (b * IPB + i) * 512);
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < BPW; ++b)
+#pragma unroll
+        for (int i = 0; i < IPB; ++i) {
+          const int j_un = kt * kBN + (rw * BPW + b) * CS_KV_BLOCK + RPD * i + l_row;
+          const bool over = j_un > wg_max;
+          const int j = over ? wg_max : j_un;
+          const int64_t slot = static_cast<int64_t>(over ? last_id : ids[b]) * CS_KV_BLOCK + j % CS_KV_BLOCK;
+          dma16(base + slot * p.stride_slot + chunk_of(i, which == 1) * 8, dst + (b * IPB + i) * 512);
+        }
+    }
+  };
+
+  int kt = kg;
+  load_ids(kt);
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(last_id));
+  wait_ids();
+  if (kt < n_key_tiles) {
+    request(kt, 0, 0);
+    if (STAGES == 2) request(kt, 0, 1);
+  }
+  if (STAGES == 2) load_ids(kt + KG);
+
+  // ---- Q^T fragments: lane = (query n, half h) holds d-slice [16 step + 8 h, + 8)
+  const int64_t q_at = (static_cast<int64_t>(tok) * p.n_q_heads + head) * D;
+  const uint16_t* qrow = static_cast<const uint16_t*>(p.q) + q_at;
+  bf16x8 qf[STEPS];
+#pragma unroll
+  for (int st = 0; st < STEPS; ++st)
+    qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const cs::u32x4*>(qrow + 16 * st + 8 * h));
+
+  // ---- LDS byte addresses of this lane's fragments
+  uint32_t k_addr[STEPS], v_addr[DB];
+#pragma unroll
+  for (int st = 0; st < STEPS; ++st)
+    k_addr[st] = lds_address(&s_kv[kg][0][0][0]) + 2 * (n * D + (((2 * st + h) ^ k_swizzle<D>(n)) << 3));
+  const int i16 = lane & 15, gid = (lane >> 4) & 1;
+  const int v_row = 4 * h + (i16 >> 2);
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+    v_addr[db] = lds_address(&s_kv[kg][0][1][0]) +
+                 2 * (v_row * D + (((4 * db + 2 * gid + ((i16 & 3) >> 1)) ^ v_swizzle<D>(v_row)) << 3) + 4 * (i16 & 1));
+
+  f32x16 o[DB];
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int db = 0; db < DB; ++db) o[db] = zero16;
+  float m_run = kNegInf, l_run = 0.f;
+  const float slack = kMaxSlack / p.scale_log2e;          // in raw score units
+
+  const int n_trips = (n_key_tiles + KG - 1) / KG;
+  for (int trip = 0; trip < n_trips; ++trip, kt += KG) {
+    wait_vmcnt<0>();
+    __syncthreads();       // one stage: K has landed, every wave is done with the previous V; two: the tile, the other stage
+    const bool here = kt < n_key_tiles, computes = here && kt * kBN <= wave_max;
+    const int stage = STAGES == 2 ? trip & 1 : 0;
+    const uint32_t stage_off = stage * (2 * TILE * 2);
+    if (STAGES == 2) {
+      wait_ids();
+      if (kt + KG < n_key_tiles) {
+        request(kt + KG, stage ^ 1, 0);
+        request(kt + KG, stage ^ 1, 1);
+      }
+      load_ids(kt + 2 * KG);
+    } else {
+      if (here) request(kt, 0, 1);
+      load_ids(kt + KG);                                 // (used after the S phase)
+    }
+
+    bf16x8 pb[2][2];
+    if (computes) {
+      const int j0 = kt * kBN;
+      typedef __attribute__((address_space(3))) const cs::u32x4 lds_u32x4;
+      auto k_frag = [&](int st, int kb) {
+        return __builtin_bit_cast(bf16x8, reinterpret_cast<lds_u32x4*>(static_cast<uintptr_t>(k_addr[st] + stage_off))[kb * 32 * D * 2 / 16]);
+      };
+      f32x16 sacc[2];
+#pragma unroll
+      for (int st = 0; st < STEPS; ++st)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+          sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(st, kb), qf[st], st == 0 ? zero16 : sacc[kb], 0, 0, 0);
+      if (D == 128) {
+        // K fragments are read two steps ahead of their MFMAs (the scheduler would pull each read back to its use)
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int st = 0; st < STEPS - 2; ++st) {
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      }
+      // register r of block kb is key j0 + 32 kb + 8 (r / 4) + 4 h + r % 4 of query n
+      if (j0 + kBN - 1 > wave_min) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int key = j0 + 32 * kb + 8 * (r / 4) + 4 * h + (r % 4);
+            if (key > lim) sacc[kb][r] = kNegInf;
+          }
+      }
+      float t_max = kNegInf;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t_max = fmaxf(t_max, sacc[kb][r]);
+      {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t_max), __float_as_uint(t_max), false, false);
+        t_max = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      }
+      if (__any(t_max > m_run + slack)) {
+        const bool up = t_max > m_run + slack;
+        const float m_new = up ? t_max : m_run;
+        const float alpha = up ? __builtin_amdgcn_exp2f((m_run - m_new) * p.scale_log2e) : 1.f;
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      }
+      const float m_scaled = (m_run == kNegInf ? 0.f : m_run) * p.scale_log2e;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int mm = 0; mm < 2; ++mm) {
+          cs::u32x4 w;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const float e0 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * mm + 2 * c], p.scale_log2e, -m_scaled));
+            const float e1 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * mm + 2 * c + 1], p.scale_log2e, -m_scaled));
+            const uint32_t pk = pack_bf16x2(e0, e1);
+            l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk),
+                                                    __builtin_bit_cast(bf16x2, 0x3f803f80u), l_run, false);
+            w[c] = pk;
+          }
+          pb[kb][mm] = __builtin_bit_cast(bf16x8, w);
+        }
+    }
+    if (STAGES == 1) {
+      wait_ids();
+      wait_vmcnt<0>();
+      __syncthreads();                     // V has landed; every wave is done with this K tile
+      if (kt + KG < n_key_tiles) request(kt + KG, 0, 0);
+    }
+    if (computes) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int mm = 0; mm < 2; ++mm)
+#pragma unroll
+          for (int db = 0; db < DB; ++db) {
+            const int g0 = (32 * kb + 16 * mm) * D;
+            const uint32_t a0 = v_addr[db] + stage_off;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(((lds_s16x4*)(static_cast<uintptr_t>(a0))) + g0 * 2 / 8);
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(((lds_s16x4*)(static_cast<uintptr_t>(a0))) + (g0 + 8 * D) * 2 / 8);
+            const s16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pb[kb][mm], o[db], 0, 0, 0);
+          }
+    }
+  }
+
+  // ---- the groups' partial results: the upper half of the groups hands over to the lower half until one is left
+  //      (a group that met no visible key holds m = -inf, l = 0, O = 0)
+  float l_tot = l_run + __shfl_xor(l_run, 32);
+  float* s_o = reinterpret_cast<float*>(&s_kv[0][0][0][0]);
+#pragma unroll
+  for (int half = KG / 2; half > 0; half >>= 1) {
+    __syncthreads();                       // the tile buffers (or the previous hand-over) have been read
+    if (kg >= half && kg < 2 * half) {
+      float* at = s_o + ((kg - half) * ROWW + rw) * (DB * 16 * 64) + lane;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) at[(db * 16 + r) * 64] = o[db][r];
+      s_ml[kg - half][rw][0][lane] = m_run;
+      s_ml[kg - half][rw][1][lane] = l_tot;
+    }
+    __syncthreads();
+    if (kg < half) {
+      const float m_o = s_ml[kg][rw][0][lane], l_o = s_ml[kg][rw][1][lane];
+      const float m_new = fmaxf(m_run, m_o);
+      const float a = m_run == kNegInf ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * p.scale_log2e);
+      const float b = m_o == kNegInf ? 0.f : __builtin_amdgcn_exp2f((m_o - m_new) * p.scale_log2e);
+      l_tot = fmaf(l_tot, a, l_o * b);
+      m_run = m_new;
+      const float* at = s_o + (kg * ROWW + rw) * (DB * 16 * 64) + lane;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] = fmaf(o[db][r], a, at[(db * 16 + r) * 64] * b);
+    }
+  }
+
+  // ---- normalise and store: register r of block db is d = 32 db + 8 (r / 4) + 4 h + r % 4
+  if (kg == 0 && valid) {
+    const float inv = 1.f / l_tot;
+    uint16_t* orow = static_cast<uint16_t*>(p.out) + q_at;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq) {
+        cs::u32x2 w;
+        w.x = pack_bf16x2(o[db][4 * rq + 0] * inv, o[db][4 * rq + 1] * inv);
+        w.y = pack_bf16x2(o[db][4 * rq + 2] * inv, o[db][4 * rq + 3] * inv);
+        *reinterpret_cast<cs::u32x2*>(orow + 32 * db + 8 * rq + 4 * h) = w;
+      }
+  }
+}
+
 // =============================================================================================
 // bf16 / head_dim 128: planned, persistent kernel
 //
@@ -387,8 +541,6 @@ __device__ __forceinline__ void wait_vmcnt() {
 // ahead of their use, and the Q rows of the next item are requested before the finished item is
 // normalised and stored, so that the per-item latencies (descriptor -> block table -> first tile)
 // that dominate short key sweeps are paid once per workgroup instead of once per item.
-
-typedef __attribute__((ext_vector_type(8))) int32_t i32x8;
 
 // Item descriptor: 8 ints.  [0] first query token of the stream, [1] rows of the stream (tokens x
 // heads per kv group), [2] first row of the tile, [3] kv head | stream << 8, [4] highest visible
@@ -896,19 +1048,6 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
   }
 }
 
-
-// Scalar loads issued by hand: the results are uniform, travel outside the vector-memory queue
-// (so waiting for them never drains tile requests) and are only read after the explicit wait.
-__device__ __forceinline__ i32x8 sload8(const void* ptr) {
-  i32x8 v;
-  asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
-  return v;
-}
-__device__ __forceinline__ int32_t sload1(const void* ptr) {
-  int32_t v;
-  asm volatile("s_load_dword %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
-  return v;
-}
 
 // RB = 32-row blocks per wave.  RB = 1 is what runs: 128-row items, two workgroups per CU (two
 // waves per SIMD hide each other's latencies).  RB = 2 (256-row items, one workgroup per CU with
@@ -1538,37 +1677,6 @@ __global__ __launch_bounds__(256) void window_attn_merge_kernel(AttnParams p) {
 // before, 1.6e-7..2.1e-7 now.
 constexpr int kF32Rows = 32, kF32Keys = 32, kF32Waves = 8;
 
-// Stream and first row of the row tile with index x (tiles of BM rows, streams in order): 64 streams
-// per turn, one lane each.  Returns the stream or -1; all lanes of the wave take the same values.
-template <int BM>
-__device__ __forceinline__ int find_row_tile(const int32_t* cu_q, int n_streams, int group, int64_t x, int& q0,
-                                             int& rows_total, int64_t& tile, int64_t& n_tiles) {
-  const int lane = threadIdx.x & 63;
-  int64_t before = 0;
-  for (int s0 = 0; s0 < n_streams; s0 += 64) {
-    const int s = s0 + lane;
-    const int lo = s < n_streams ? cu_q[s] : 0, hi = s < n_streams ? cu_q[s + 1] : 0;
-    const int tiles = ((hi - lo) * group + BM - 1) / BM;
-    int incl = tiles;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int t = __shfl_up(incl, off);
-      if (lane >= off) incl += t;
-    }
-    const unsigned long long found = __ballot(x < before + incl);
-    if (found) {
-      const int at = __ffsll(found) - 1;
-      q0 = __builtin_amdgcn_readlane(lo, at);
-      rows_total = (__builtin_amdgcn_readlane(hi, at) - q0) * group;
-      n_tiles = __builtin_amdgcn_readlane(tiles, at);
-      tile = x - (before + __builtin_amdgcn_readlane(incl, at) - n_tiles);
-      return s0 + at;
-    }
-    before += __builtin_amdgcn_readlane(incl, 63);
-  }
-  return -1;
-}
-
 template <int D>
 __global__ __launch_bounds__(64 * kF32Waves, 2) void window_attn_f32_kernel(AttnParams p) {
   constexpr int DB = D / 32, VECS = D / 8;
@@ -1578,12 +1686,11 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void window_attn_f32_kernel(Attn
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
 
-  int q0 = 0, rows_total = 0;
-  int64_t tile = 0, n_tiles = 0;
-  const int s = find_row_tile<kF32Rows>(p.cu_q, p.n_streams, p.group, blockIdx.x / p.n_kv_heads, q0, rows_total, tile, n_tiles);
-  if (s < 0) return;                                     // n_q may be an upper bound
-  const int r_tile = static_cast<int>(n_tiles - 1 - tile) * kF32Rows;     // longest sweeps first
-  const int kvh = blockIdx.x % p.n_kv_heads;
+  RowTile rt;
+  if (!find_row_tile<kF32Rows>(p, blockIdx.x, rt)) return;
+  const int s = __builtin_amdgcn_readfirstlane(rt.s), kvh = __builtin_amdgcn_readfirstlane(rt.kvh);
+  const int q0 = __builtin_amdgcn_readfirstlane(rt.q0), rows_total = __builtin_amdgcn_readfirstlane(rt.rows_total);
+  const int r_tile = __builtin_amdgcn_readfirstlane(rt.r_tile);
   const int32_t* bt = p.block_table + static_cast<int64_t>(s) * p.max_blocks;
   const int cap = min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1;
 
@@ -1802,6 +1909,15 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
   return a;
 }
 
+template <int D, int ROWW, int KG, int STAGES>
+int launch_tiles(const AttnParams& p, hipStream_t st) {
+  const int64_t tiles = ((p.n_q * p.group) / (32 * ROWW) + p.n_streams) * p.n_kv_heads;      // upper bound
+  if (tiles > 0x7fffffffll) return CS_EUNSUPPORTED;
+  hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES>), dim3(static_cast<unsigned>(tiles)),
+                     dim3(64 * ROWW * KG), 0, st, p);
+  return cs::note_hip(hipGetLastError());
+}
+
 }  // namespace
 
 extern "C" size_t cs_window_prefill_attn_workspace(int64_t n_q, int32_t n_streams, int32_t n_q_heads,
@@ -1847,7 +1963,7 @@ int attn_validate(const void* q, const void* k_cache_layer, const void* v_cache_
       !cs::aligned16(v_cache_layer))
     return CS_EUNSUPPORTED;
   if (n_q * n_q_heads >= (1ll << 31)) return CS_EUNSUPPORTED;
-  if (dtype == CS_BF16 && head_dim == 64 && max_blocks > kMaxBlocksInLds) return CS_EUNSUPPORTED;
+  if (dtype == CS_BF16 && head_dim == 64 && max_blocks > kMaxBlocks64) return CS_EUNSUPPORTED;
   return CS_OK;
 }
 
@@ -1897,7 +2013,6 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
   p.ws_status = nullptr;
   hipStream_t st = cs::as_stream(stream);
   if (dtype == CS_BF16) {
-    const size_t bt_bytes = static_cast<size_t>(max_blocks) * sizeof(int32_t);
     if (head_dim == 128) {
       if (n_kv_heads > 256 || n_streams >= (1 << 23)) return CS_EUNSUPPORTED;
       if (plan_mode != CS_ATTN_PLAN_BUILD && plan_mode != CS_ATTN_PLAN_REUSE && plan_mode != CS_ATTN_PLAN_ONLY)
@@ -1963,11 +2078,12 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
                            dim3(256), 0, st, p);
       }
     } else {
-      if (max_blocks > kMaxBlocksInLds) return CS_EUNSUPPORTED;
-      const int64_t tiles = (n_q * group) / kBM + n_streams;           // upper bound on row tiles
-      if (tiles > 0x7fffffffll) return CS_EUNSUPPORTED;
-      const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(n_kv_heads));
-      hipLaunchKernelGGL(window_attn_bf16_kernel<64>, grid, dim3(256), bt_bytes, st, p);
+      // Two key groups while the launch is so small that its longest sweep is what it takes (all of its row tiles
+      // are resident together, 1,024 of them with one group).  One group / two, us a layer in a step: 4 streams,
+      // 28/4 heads 25.3 / 23.1; 12 streams, 16/4 heads 30.5 / 26.9; 32 streams 57.3 / 58.4 (the merge is extra work).
+      const int64_t tiles = ((n_q * group) / kBM + n_streams) * n_kv_heads;
+      if (tiles <= 1024) return launch_tiles<64, 4, 2, 2>(p, st);
+      return launch_tiles<64, 4, 1, 1>(p, st);
     }
   } else {
     const int64_t tiles = ((n_q * group) / kF32Rows + n_streams) * n_kv_heads;       // upper bound on row tiles
