@@ -21,7 +21,7 @@
 // head_dim 128: a planning kernel lists the work items of the launch and persistent workgroups
 // stream K/V tiles from HBM straight into LDS (global_load_lds), across item boundaries; long key
 // sweeps of small batches are split over several items and merged by a second kernel.
-// head_dim 64: one workgroup per row tile, no plan, key ranges shared inside it.
+// head_dim 64, and launches of few row tiles: one workgroup per row tile, no plan, key ranges shared inside it.
 //
 // fp32 kernel: the fp32 matrix instruction, 32 rows per workgroup, keys dealt to its waves.
 #include <math.h>
@@ -66,6 +66,7 @@ struct AttnParams {
   int32_t row_vecs, head_vecs;   // 16-byte vectors per new row / per head
   int32_t* ws_sync;      // counters of the fused launch's launch-wide barrier (see launch_barrier)
   int32_t* ws_status;    // its status word
+  int32_t clear_status;  // the launch without a plan zeroes it
   int32_t* ws_desc;      // [items][8]: q0, rows_total, r_tile, kvh, n_split
   float* ws_ml;          // [items][max_splits][bm][2]: running max (raw score units), row sum
   float* ws_o;           // [items][max_splits][bm][128]: un-normalised output rows
@@ -204,7 +205,7 @@ __device__ __forceinline__ bool find_row_tile(const AttnParams& p, int b, RowTil
 // bf16, one launch and no plan: a workgroup = one tile of 32 ROWW rows of one (stream, kv head), its waves
 // arranged as KG key groups of ROWW row waves.  Group g sweeps key tiles g, g + KG, ...; the groups' partial
 // results meet in LDS at the end, so a sweep is shared by KG times as many waves without a trip through memory
-// and without a merge launch.  head_dim 64 always runs here.
+// and without a merge launch.  head_dim 64 always runs here, head_dim 128 where tile_route_128 says so.
 // Tiles go to LDS by DMA with the persistent kernel's layout and swizzle idea.  STAGES 2: the next tile is requested
 // at the top of a tile, one workgroup barrier per tile.  STAGES 1 (half the LDS: more workgroups per CU, or more key
 // groups): K of the next tile is requested when S is done and lands behind P V, V when P V is done and lands behind
@@ -242,6 +243,7 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
   const int rw = wave % ROWW, kg = wave / ROWW;
   const int n = lane & 31, h = lane >> 5;
 
+  if (p.clear_status && blockIdx.x == 0 && threadIdx.x == 0) *p.ws_status = 0;
   RowTile t;
   if (!find_row_tile<BM>(p, blockIdx.x, t)) return;
   const int s = __builtin_amdgcn_readfirstlane(t.s), kvh = __builtin_amdgcn_readfirstlane(t.kvh);
@@ -1909,6 +1911,31 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
   return a;
 }
 
+// head_dim 128: which launches leave the plan and the persistent kernel for the tile kernel, by 128-row tiles x kv
+// heads (their upper bound, as the workspace is sized) and key tiles of the longest window.  Below 1,024 row tiles
+// the persistent kernel splits its sweeps and needs the merge launch, and its plan costs 15-50 us a step.
+// us a layer in a step, plan not counted, persistent + merge / tile kernel (28/4 heads unless noted; T: row tiles):
+//   1,024 tiles and more       the planned schedule balances better: T 1,196 116 / 123, T 1,632 66.5 / 77.7
+//   kRows128 (to 1,023)        T 520 40.3 / 35.0, T 808 54.5 / 42.9, T 624 with 59 key tiles 94.0 / 86.6; past 64 key
+//                              tiles the split wins: T 508 with 89 106 / 112, T 564 with 121 137 / 167
+//   kRows64Keys2 (to 440)      T 288 31.3 / 22.4; at T 520 it has two rounds of workgroups: 37.1 (kRows128 35.0); past
+//                              48 key tiles level
+//   kRows64Keys4 (to 128)      T 116 20.2 / 17.4, with 28 key tiles 28.3 / 24.9 (two groups 18.1, 28.7): every
+//                              workgroup runs at once and the longest sweep is the time; up to 8 key tiles two groups
+//                              are enough (300 keys 11.0 / 12.2, persistent 16.3)
+//   a few row tiles with long sweeps (2 key tiles > row tiles) keep the split over the whole chip (T 27 14.8 / 16.4)
+enum class TileRoute { kNone, kRows128, kRows64Keys2, kRows64Keys4 };
+
+TileRoute tile_route_128(int64_t row_tiles, int key_tiles) {
+  if (row_tiles >= 1024 || key_tiles > 64) return TileRoute::kNone;
+  if (row_tiles <= 128) {
+    if (2 * key_tiles > (row_tiles > 16 ? row_tiles : 16)) return TileRoute::kNone;
+    return key_tiles > 8 ? TileRoute::kRows64Keys4 : TileRoute::kRows64Keys2;
+  }
+  if (row_tiles <= 440) return key_tiles <= 48 ? TileRoute::kRows64Keys2 : TileRoute::kNone;
+  return TileRoute::kRows128;
+}
+
 template <int D, int ROWW, int KG, int STAGES>
 int launch_tiles(const AttnParams& p, hipStream_t st) {
   const int64_t tiles = ((p.n_q * p.group) / (32 * ROWW) + p.n_streams) * p.n_kv_heads;      // upper bound
@@ -2011,6 +2038,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
   p.row_vecs = n_kv_heads * p.head_vecs;
   p.ws_sync = nullptr;
   p.ws_status = nullptr;
+  p.clear_status = 0;
   hipStream_t st = cs::as_stream(stream);
   if (dtype == CS_BF16) {
     if (head_dim == 128) {
@@ -2018,6 +2046,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       if (plan_mode != CS_ATTN_PLAN_BUILD && plan_mode != CS_ATTN_PLAN_REUSE && plan_mode != CS_ATTN_PLAN_ONLY)
         return CS_EINVAL;
       const AttnPlan a = plan_attn(n_q, n_streams, group, n_kv_heads, max_blocks);
+      const TileRoute route = tile_route_128(a.rt_cap, a.max_tiles);
       if (a.items_cap * a.bm >= (1ll << 31)) return CS_EUNSUPPORTED;
       if (stride_slot >= (1ll << 26) || a.max_tiles >= (1 << 15)) return CS_EUNSUPPORTED;      // 32-bit byte offsets inside a cache block
       if (!workspace || workspace_bytes < a.total || !cs::aligned16(workspace)) return CS_EWORKSPACE;
@@ -2033,6 +2062,19 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       p.ws_desc = reinterpret_cast<int32_t*>(w + a.off_rt_desc);
       p.ws_ml = reinterpret_cast<float*>(w + a.off_ml);
       p.ws_o = reinterpret_cast<float*>(w + a.off_o);
+      if (route != TileRoute::kNone && plan_mode != CS_ATTN_PLAN_ONLY) {
+        // (the plan is neither needed nor made; the status word of a BUILD call still starts at zero)
+        p.clear_status = plan_mode == CS_ATTN_PLAN_BUILD ? 1 : 0;
+        if (fuse) {
+          const int e = cs_kv_refresh_scatter(k_new, v_new, new_slot, const_cast<void*>(k_cache_layer),
+                                              const_cast<void*>(v_cache_layer), n_new, n_kv_heads, head_dim, stride_slot,
+                                              stride_head, dtype, stream);
+          if (e != CS_OK) return e;
+        }
+        if (route == TileRoute::kRows128) return launch_tiles<128, 4, 1, 2>(p, st);
+        if (route == TileRoute::kRows64Keys2) return launch_tiles<128, 2, 2, 1>(p, st);
+        return launch_tiles<128, 2, 4, 1>(p, st);
+      }
       if (plan_mode != CS_ATTN_PLAN_REUSE) {
         PlanParams pp;
         pp.cu_q = cu_q;

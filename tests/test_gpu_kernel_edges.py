@@ -51,3 +51,66 @@ def test_f32_attention_masked_rows_do_not_reach_earlier_queries(cs, bad):
     got = out.cpu()
     hp.check_attention(got[:at], ref[:at], "f32")
     assert not torch.isfinite(got[at:]).any()
+
+
+# bf16 attention without a plan (head_dim 64, and head_dim 128 while the row tiles are few): key tiles of 64 shared by
+# one, two or four key groups; 64- or 128-row tiles
+TILE_ATTN = [
+    # Hq, Hkv, d, kv_lens, n_qs
+    (7, 1, 128, [63, 64, 65, 1], [9, 10, 65, 1]),                       # two key groups, one of them without a tile
+    (28, 4, 128, [580, 577, 513], [40, 150, 3]),                        # four key groups, 9 and 10 key tiles
+    (28, 4, 128, [1100], [470]),                                        # four key groups, row tiles of 64 with a remainder
+    (28, 4, 128, [900, 1, 830, 128], [420, 1, 333, 0]),                 # two key groups, a stream without queries
+    (32, 8, 128, [700 + 61 * i for i in range(7)], [190 + 17 * i for i in range(7)]),    # rows of 128
+    (16, 2, 128, [1500, 400, 1400], [600, 300, 777]),                   # two key groups, 24 key tiles
+    (4, 4, 64, [1, 63, 64, 65, 129], [1, 63, 30, 65, 2]),
+    (16, 1, 64, [2300], [100]),                                         # two key groups, 36 key tiles
+    (28, 4, 64, [300 + 7 * i for i in range(40)], [90 + i for i in range(40)]),   # one key group
+    (2, 2, 64, [20] * 130, [2] * 130),
+]
+
+
+@pytest.mark.parametrize("case", range(len(TILE_ATTN)))
+def test_unplanned_attention_tile_edges(cs, case):
+    hq, hkv, d, kv_lens, n_qs = TILE_ATTN[case]
+    say(f"unplanned attention {case}: heads={hq}/{hkv} d={d} kv={kv_lens[:4]} n_q={n_qs[:4]}")
+    for mult in (1.0, 6.0):                                             # (wide scores: maxima far apart between key groups)
+        say(f"  -> {_attn_case(cs, np.random.default_rng(9300 + case), 'bf16', hq, hkv, d, kv_lens, n_qs, scale_mult=mult)}")
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,kv_lens,n_qs", [
+    ("bf16", 14, 2, 128, [300, 77], [40, 77]), ("bf16", 28, 4, 128, [1100], [300]), ("bf16", 8, 2, 64, [300, 77], [40, 77]),
+    ("bf16", 28, 4, 128, [900, 700, 800, 640], [380, 500, 250, 400]), ("f32", 8, 2, 128, [300, 77], [40, 77])])
+def test_unplanned_attention_head_major_pool_and_row_capacity(cs, dtype, hq, hkv, d, kv_lens, n_qs):
+    """A head-major pool (slot stride d, head stride slots * d) and n_q beyond the rows the streams hold: rows past
+    cu_q stay as they were."""
+    say(f"unplanned attention, head-major pool: {dtype} heads={hq}/{hkv} d={d} kv={kv_lens}")
+    rng = np.random.default_rng(9400 + d)
+    n_streams, extra = len(kv_lens), 37
+    nb = [-(-k // 16) for k in kv_lens]
+    bt, ids, at = np.zeros((n_streams, max(nb)), np.int32), rng.permutation(sum(nb)), 0
+    for s in range(n_streams):
+        bt[s, : nb[s]] = ids[at: at + nb[s]]
+        at += nb[s]
+    slots = sum(nb) * 16
+    kc, vc = _pool(rng, (slots, hkv, d), dtype), _pool(rng, (slots, hkv, d), dtype)
+    cu = np.concatenate([[0], np.cumsum(n_qs)]).astype(np.int32)
+    q_pos = np.concatenate([np.sort(rng.choice(kv_lens[s], n_qs[s], replace=False)) for s in range(n_streams)]).astype(np.int32)
+    n_q = int(cu[-1])
+    q = _pool(rng, (n_q + extra, hq, d), dtype)
+    ref = oc.window_attn(hp.f64(q[:n_q]), hp.f64(kc), hp.f64(vc), cu, q_pos, bt, hq, 1 / math.sqrt(d))
+    head_major = lambda t: t.permute(1, 0, 2).contiguous().to(DEV)
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    kd, vd = head_major(kc), head_major(vc)
+    out = torch.full((n_q + extra, hq, d), 7.0, dtype=q.dtype, device=DEV)
+    code = cs.CS_BF16 if dtype == "bf16" else cs.CS_F32
+    wsb = cs.cs_window_prefill_attn_workspace(n_q + extra, n_streams, hq, hkv, d, max(nb), code)
+    ws = torch.randint(0, 255, (max(16, wsb),), dtype=torch.uint8, device=DEV)
+    pos = to(np.concatenate([q_pos, np.full(extra, 2 ** 30, np.int32)]))
+    cs.cs_window_prefill_attn(q.to(DEV), kd, vd, to(cu), pos, to(np.asarray(kv_lens, np.int32)), to(bt), max(nb), 16, out,
+                              n_q + extra, n_streams, hq, hkv, d, d, slots * d, 1 / math.sqrt(d), code, ws, wsb)
+    got = out.cpu()
+    hp.check_attention(got[:n_q], ref, dtype)
+    assert torch.all(got[n_q:] == 7.0)
+    if wsb:
+        assert cs.cs_attn_status(ws) == 0
