@@ -3,7 +3,8 @@
 // rectangles are rescaled and every patch gets the strongest motion (Eq. 1) among the blocks that
 // land on it.  Sec. 3.3.2: a patch touched by an intra-coded block is flagged.
 //
-// One workgroup per frame.  The frame's patch table lives in LDS as 64-bit keys
+// A workgroup per band of patch rows of a frame (one band in large batches).  The band's patch table
+// lives in LDS as 64-bit keys
 //     key = |v|^2 << 32 | (dx + 32768) << 16 | (dy + 32768)
 // so that "largest magnitude, ties to the lexicographically largest vector" is an unsigned
 // maximum and the winning vector comes back out of the key: blocks are streamed once (one 16-byte
@@ -13,6 +14,13 @@
 // blocks arrive cannot change the result.  Divisions by the two launch constants
 // patch * src_w and patch * src_h are multiplications by a precomputed reciprocal that is exact for
 // the numerators that can occur (below 2^29).
+//
+// A record's patch range, key and raises are some 150 vector instructions, 13 us for a 1920 x 1080
+// frame's 14 k blocks on one CU: with fewer frames than the chip has CUs the bands of a frame are
+// separate workgroups.  Each reads all of the frame's records (from L2 after the first) but leaves a
+// record after one comparison when it does not reach the band; blocks arrive in raster order, so
+// whole wavefronts leave together.  32 frames of 1920 x 1080: 14.5 us with a workgroup per frame,
+// 8.2 with eight.
 #include "common.h"
 
 namespace {
@@ -49,17 +57,24 @@ struct ProjectParams {
   uint32_t den_x, den_y;             // patch * src_w, patch * src_h
   ExactDiv div_x, div_y;
   int32_t grid_h, grid_w, n_patch;
+  int32_t n_frames, n_bands;
 };
 
 __global__ __launch_bounds__(kProjectThreads) void project_blocks_kernel(ProjectParams p) {
-  extern __shared__ unsigned long long s_key[];                         // [n_patch]
-  uint32_t* s_intra = reinterpret_cast<uint32_t*>(s_key + p.n_patch);  // bitmap, n_patch bits
+  extern __shared__ unsigned long long s_key[];                         // [patches of the band]
   const int tid = threadIdx.x;
-  const int frame = blockIdx.x;
-  for (int i = tid; i < p.n_patch; i += kProjectThreads) s_key[i] = 0ull;
-  for (int i = tid; i < (p.n_patch + 31) / 32; i += kProjectThreads) s_intra[i] = 0u;
+  // (the bands of a frame lie n_frames workgroups apart: with a multiple of 8 frames they share an XCD's L2)
+  const int frame = blockIdx.x % p.n_frames, band = blockIdx.x / p.n_frames;
+  const int row_lo = band * p.grid_h / p.n_bands, row_hi = (band + 1) * p.grid_h / p.n_bands;
+  const int n_cells = (row_hi - row_lo) * p.grid_w;
+  uint32_t* s_intra = reinterpret_cast<uint32_t*>(s_key + n_cells);    // bitmap, n_cells bits
+  for (int i = tid; i < n_cells; i += kProjectThreads) s_key[i] = 0ull;
+  for (int i = tid; i < (n_cells + 31) / 32; i += kProjectThreads) s_intra[i] = 0u;
   __syncthreads();
-
+  // source rows the band's patches overlap: a block reaches the band if hi_y > band_y0 and lo_y < band_y1
+  const uint64_t lo_num = static_cast<uint64_t>(row_lo) * p.den_y, hi_num = static_cast<uint64_t>(row_hi) * p.den_y;
+  const uint32_t band_y0 = static_cast<uint32_t>(min(lo_num / p.in_h, static_cast<uint64_t>(0xffffffffu)));
+  const uint32_t band_y1 = static_cast<uint32_t>(min((hi_num + p.in_h - 1u) / p.in_h, static_cast<uint64_t>(0xffffffffu)));
   const int begin = p.cu_blocks[frame], end = p.cu_blocks[frame + 1];
   auto apply = [&](const cs::u32x4 rec) {
     const uint32_t x = rec.x & 0xffffu, y = rec.x >> 16, w = rec.y & 0xffffu, h = rec.y >> 16;
@@ -67,6 +82,7 @@ __global__ __launch_bounds__(kProjectThreads) void project_blocks_kernel(Project
     const bool is_intra = (rec.w & 1u) != 0;
     const uint32_t mag = static_cast<uint32_t>(dx * dx) + static_cast<uint32_t>(dy * dy);   // up to 2^31
     if (!is_intra && mag == 0u) return;                       // a zero vector changes no patch
+    if (y + h <= band_y0 || y >= band_y1) return;
     // footprint clipped to the frame; nothing left -> no footprint
     const uint32_t lo_x = min(x, p.src_w), hi_x = min(x + w, p.src_w);
     const uint32_t lo_y = min(y, p.src_h), hi_y = min(y + h, p.src_h);
@@ -74,13 +90,13 @@ __global__ __launch_bounds__(kProjectThreads) void project_blocks_kernel(Project
     // patch columns c with lo*in < (c+1)*den and hi*in > c*den (positive overlap), same for rows
     const int c0 = static_cast<int>(div_by(lo_x * p.in_w, p.div_x));
     const int c1 = min(static_cast<int>(div_by(hi_x * p.in_w + p.den_x - 1u, p.div_x)) - 1, p.grid_w - 1);
-    const int r0 = static_cast<int>(div_by(lo_y * p.in_h, p.div_y));
-    const int r1 = min(static_cast<int>(div_by(hi_y * p.in_h + p.den_y - 1u, p.div_y)) - 1, p.grid_h - 1);
+    const int r0 = max(static_cast<int>(div_by(lo_y * p.in_h, p.div_y)), row_lo);
+    const int r1 = min(static_cast<int>(div_by(hi_y * p.in_h + p.den_y - 1u, p.div_y)), row_hi) - 1;
     const unsigned long long key = (static_cast<unsigned long long>(mag) << 32) |
                                    (static_cast<uint32_t>(dx + 32768) << 16) | static_cast<uint32_t>(dy + 32768);
     for (int r = r0; r <= r1; ++r)
       for (int c = c0; c <= c1; ++c) {
-        const int cell = r * p.grid_w + c;
+        const int cell = (r - row_lo) * p.grid_w + c;
         if (is_intra) {
           const uint32_t bit = 1u << (cell & 31);
           if (!(s_intra[cell >> 5] & bit)) atomicOr(&s_intra[cell >> 5], bit);
@@ -95,16 +111,17 @@ __global__ __launch_bounds__(kProjectThreads) void project_blocks_kernel(Project
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + u * kProjectThreads;
-      rec[u] = i < end ? __builtin_nontemporal_load(p.blocks + i) : cs::u32x4{0u, 0u, 0u, 0u};
+      rec[u] = i < end ? p.blocks[i] : cs::u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) apply(rec[u]);
   }
   __syncthreads();
 
-  uint32_t* mv = p.mv + static_cast<int64_t>(frame) * p.n_patch;
-  uint8_t* intra = p.intra + static_cast<int64_t>(frame) * p.n_patch;
-  for (int i = tid; i < p.n_patch; i += kProjectThreads) {
+  const int64_t first = static_cast<int64_t>(frame) * p.n_patch + row_lo * p.grid_w;
+  uint32_t* mv = p.mv + first;
+  uint8_t* intra = p.intra + first;
+  for (int i = tid; i < n_cells; i += kProjectThreads) {
     const unsigned long long key = s_key[i];                  // 0: no moving inter block here
     const uint32_t low = static_cast<uint32_t>(key);
     const uint32_t dx16 = key == 0ull ? 0u : ((low >> 16) - 32768u) & 0xffffu;
@@ -142,8 +159,16 @@ extern "C" int cs_project_blocks(const cs_block* blocks, const int32_t* cu_block
   p.div_y = exact_div(p.den_y);
   p.grid_h = grid_h; p.grid_w = grid_w;
   p.n_patch = static_cast<int32_t>(n_patch);
-  const size_t lds = static_cast<size_t>(n_patch) * 8 + static_cast<size_t>((n_patch + 31) / 32) * 4;
-  hipLaunchKernelGGL(project_blocks_kernel, dim3(static_cast<unsigned>(n_frames)), dim3(kProjectThreads),
+  // bands: two workgroups of this size fit a CU, so up to 512 in all; at most eight (past that the
+  // records every band reads cost more than its share of the work), one patch row at least
+  int bands = n_frames >= 512 ? 1 : 512 / n_frames;
+  if (bands > 8) bands = 8;
+  if (bands > grid_h) bands = grid_h;
+  p.n_frames = n_frames;
+  p.n_bands = bands;
+  const int64_t cells = static_cast<int64_t>((grid_h + bands - 1) / bands) * grid_w;
+  const size_t lds = static_cast<size_t>(cells) * 8 + static_cast<size_t>((cells + 31) / 32) * 4;
+  hipLaunchKernelGGL(project_blocks_kernel, dim3(static_cast<unsigned>(n_frames) * bands), dim3(kProjectThreads),
                      lds, cs::as_stream(stream), p);
   return cs::note_hip(hipGetLastError());
 }
