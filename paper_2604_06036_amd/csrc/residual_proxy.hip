@@ -3,19 +3,17 @@
 // compared with the current frame, and a patch is scored by the average absolute pixel difference
 // inside it (the per-patch counterpart of the block residual of Eq. 2; input of the rescue rule, Eq. 4).
 //
-// Three launches on the caller's stream; the output array doubles as the accumulator:
-//   1. clear the per-patch sums;
-//   2. residual_sum_kernel: a workgroup owns a run of source rows inside one patch row of one
-//      frame.  A thread owns a 4-pixel group of columns (consecutive lanes, consecutive groups:
-//      every load of a wave is one contiguous span) and walks down the rows a cell row of the
-//      motion field at a time: one vector, then for four pixel rows at once the current pixels
-//      (one dword) and the reference pixels as two aligned dwords joined by a byte funnel shift
-//      (per-pixel clamped byte loads only where the reference leaves the frame), twelve
-//      independent loads in flight.  |a - b| over four pixels is one v_sad_u8; a group that
-//      straddles a patch border is split by byte masks fixed per thread, so the row loop has no
-//      patch arithmetic at all.  Sums go thread -> LDS (per patch column) -> one global atomic
-//      per workgroup and patch;
-//   3. residual_mean_kernel: sum -> floor(256 * sum / pixels of the patch).
+// One launch where a patch is small enough (at most 128 source rows and 512 columns): a workgroup owns a run of
+// whole patches of one patch row, as many as its lanes take in one turn, sums them in LDS and writes their scores.
+// Larger patches keep three launches, the output array doubling as the accumulator: clear the sums, a workgroup per
+// run of source rows with one global atomic per workgroup and patch, then sum -> score.  In both a thread owns a
+// 4-pixel group of columns (consecutive lanes, consecutive groups: every load of a wave is one contiguous span) and
+// walks down the rows a cell row of the motion field at a time: one vector, then for four pixel rows at once the
+// current pixels (one dword) and the reference pixels (one 8-byte load and a byte permute that also clamps columns
+// outside the frame), eight independent loads in flight.  |a - b| over four pixels is one v_sad_u8; a group that
+// straddles a patch border is split by byte masks fixed per thread, so the row loop has no patch arithmetic at all.
+// HBM bound: 32 frames of 1920 x 1080, cell 4, 166 MB in 38.5 us (4.3 TB/s; 43.6 us as three launches with two dword
+// loads per reference and a path of byte loads at the frame's sides).
 // Integer adds commute, so the result is bit exact whatever the order.
 #include "common.h"
 
@@ -51,8 +49,10 @@ struct ResidualParams {
   int32_t n_frames, src_w, src_h, cell_shift, cells_w, cells_h;
   uint32_t in_w, in_h, den_x, den_y;      // den = patch * src size
   ExactDiv div_x;
-  int32_t grid_h, grid_w, n_sub;
+  int32_t grid_h, grid_w, n_sub, n_parts;
 };
+
+typedef cs::u32x2 __attribute__((aligned(4))) dword_pair;
 
 // first source coordinate of patch index i along an axis: ceil(i * den / n_in), capped at n_src
 __device__ __forceinline__ int first_coord(int i, uint32_t den, uint32_t n_in, int n_src) {
@@ -65,33 +65,54 @@ __global__ __launch_bounds__(256) void clear_sums_kernel(uint32_t* p, int64_t n)
   if (i < n) p[i] = 0u;
 }
 
+// 256 times the sum of a patch over its number of source pixels.
+__device__ __forceinline__ uint32_t patch_mean(const ResidualParams& p, int r, int c, uint32_t sum) {
+  const int64_t wide = first_coord(c + 1, p.den_x, p.in_w, p.src_w) - first_coord(c, p.den_x, p.in_w, p.src_w);
+  const int64_t tall = first_coord(r + 1, p.den_y, p.in_h, p.src_h) - first_coord(r, p.den_y, p.in_h, p.src_h);
+  const unsigned long long n = static_cast<unsigned long long>(wide * tall);
+  return n ? static_cast<uint32_t>((256ull * sum) / n) : 0u;
+}
+
+// kWhole: a workgroup owns a run of whole patches of one patch row (n_sub runs per row) and writes their means: one
+// launch.  Its waves are n_parts parts of the row's source rows times 4 / n_parts shares of the columns.
+// Otherwise a workgroup owns the source rows of one n_sub-th of a patch row and adds to sums that a launch before
+// this one clears and a launch after it divides.
+template <bool kWhole>
 __global__ __launch_bounds__(256) void residual_sum_kernel(ResidualParams p) {
-  extern __shared__ uint32_t s_sum[];                       // [grid_w]
+  extern __shared__ uint32_t s_sum[];                       // [patches of the workgroup]
   const int tid = threadIdx.x;
   const int sub = blockIdx.x % p.n_sub;
   const int band = (blockIdx.x / p.n_sub) % p.grid_h;
   const int frame = blockIdx.x / (p.n_sub * p.grid_h);
+  const int col_lo = kWhole ? static_cast<int>(static_cast<int64_t>(p.grid_w) * sub / p.n_sub) : 0;
+  const int col_hi = kWhole ? static_cast<int>(static_cast<int64_t>(p.grid_w) * (sub + 1) / p.n_sub) : p.grid_w;
+  const int n_parts = kWhole ? p.n_parts : p.n_sub;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = kWhole ? wave % n_parts : sub;
   const int y_lo = first_coord(band, p.den_y, p.in_h, p.src_h);
   const int y_hi = first_coord(band + 1, p.den_y, p.in_h, p.src_h);
-  if (y_lo >= y_hi) return;                                 // uniform for the workgroup
-  // the band's rows in quads (rows 4q .. 4q+3, the unit of the row loop), dealt to its n_sub workgroups
+  // the band's rows in quads (rows 4q .. 4q+3, the unit of the row loop), dealt to its parts
   const int q_lo = y_lo >> 2, n_quads = ((y_hi - 1) >> 2) + 1 - q_lo;
-  const int q_begin = q_lo + static_cast<int>(static_cast<int64_t>(n_quads) * sub / p.n_sub);
-  const int q_end = q_lo + static_cast<int>(static_cast<int64_t>(n_quads) * (sub + 1) / p.n_sub);
+  const int q_begin = q_lo + static_cast<int>(static_cast<int64_t>(n_quads) * part / n_parts);
+  const int q_end = q_lo + static_cast<int>(static_cast<int64_t>(n_quads) * (part + 1) / n_parts);
   const int y_begin = max(y_lo, 4 * q_begin), y_end = min(y_hi, 4 * q_end);
-  if (y_begin >= y_end) return;
+  if (!kWhole && (y_lo >= y_hi || y_begin >= y_end)) return;          // uniform for the workgroup
 
-  for (int i = tid; i < p.grid_w; i += 256) s_sum[i] = 0u;
+  for (int i = tid; i < col_hi - col_lo; i += 256) s_sum[i] = 0u;
   __syncthreads();
 
   const int W = p.src_w, H = p.src_h;
-  const int groups = (W + 3) / 4;                                    // 4-pixel groups along a row
+  const int all_groups = (W + 3) / 4;                                // 4-pixel groups along a row
+  const int k_lo = kWhole ? first_coord(col_lo, p.den_x, p.in_w, W) >> 2 : 0;
+  const int groups = kWhole ? min(all_groups, (first_coord(col_hi, p.den_x, p.in_w, W) + 3) >> 2) : all_groups;
+  const int k_step = kWhole ? 256 / n_parts : 256;
+  const int k_first = kWhole ? k_lo + 64 * (wave / n_parts) + (tid & 63) : tid;
   const uint8_t* cur = p.cur + static_cast<int64_t>(frame) * p.frame_stride;
   const uint8_t* prev = p.prev + static_cast<int64_t>(frame) * p.frame_stride;
   const uint32_t* field = p.field + static_cast<int64_t>(frame) * p.cells_h * p.cells_w;
   const int cell = 1 << p.cell_shift;
 
-  for (int k = tid; k < groups; k += 256) {
+  for (int k = k_first; k < groups && y_begin < y_end; k += k_step) {
     // ---- the group's patch column(s) and the byte masks that split it between them
     const int x = 4 * k;
     int col_a = static_cast<int>(div_by(static_cast<uint32_t>(x) * p.in_w, p.div_x)), col_b = 0;
@@ -104,8 +125,8 @@ __global__ __launch_bounds__(256) void residual_sum_kernel(ResidualParams p) {
         else { mask_b |= 0xffu << (8 * t); col_b = c; }     // columns are at least 4 pixels wide: one other column at most
       }
     }
-    if (col_a >= p.grid_w) mask_a = 0u;
-    if (col_b >= p.grid_w) mask_b = 0u;
+    if (col_a < col_lo || col_a >= col_hi) mask_a = 0u;
+    if (col_b < col_lo || col_b >= col_hi) mask_b = 0u;
     uint32_t acc_a = 0u, acc_b = 0u;
     // ---- down the rows, one cell row of the motion field at a time, four pixel rows per batch
     const int yc_last = (y_end - 1) >> p.cell_shift;
@@ -117,11 +138,18 @@ __global__ __launch_bounds__(256) void residual_sum_kernel(ResidualParams p) {
       const int ox = (static_cast<int>(static_cast<int16_t>(mv & 0xffffu)) + 2) >> 2;
       const int oy = (static_cast<int>(static_cast<int16_t>(mv >> 16)) + 2) >> 2;
       const int xs = x + ox;
-      const bool fast = xs >= 0 && xs + 3 <= W - 1;         // the reference group lies inside the row
-      const int a0 = fast ? (xs & ~3) : 0;                   // two aligned dwords, both inside the row
-      const int a1 = fast && (xs & 3) ? a0 + 4 : a0;
+      // the reference group's four bytes, columns clamped to the frame, lie in one 8-byte load inside the row's pitch
+      // and are picked out of it by one byte permute
+      const int a0 = min(max(min(xs, W - 1) & ~3, 0), static_cast<int>(p.pitch) - 8);
+      uint32_t pick = 0x03020100u + 0x01010101u * static_cast<uint32_t>(xs - a0);
+      if (xs < 0 || xs + 3 > W - 1) {
+        pick = 0u;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) pick |= static_cast<uint32_t>(min(max(xs + t, 0), W - 1) - a0) << (8 * t);
+      }
       for (int r4 = 0; r4 < cell; r4 += 4) {
-        uint32_t c4[4], lo[4], hi[4];
+        uint32_t c4[4];
+        dword_pair ref[4];
         bool live[4];
 #pragma unroll
         for (int dy = 0; dy < 4; ++dy) {
@@ -131,33 +159,26 @@ __global__ __launch_bounds__(256) void residual_sum_kernel(ResidualParams p) {
           const int yy = min(max(yv + oy, 0), H - 1);
           const uint8_t* prow = prev + static_cast<int64_t>(yy) * p.pitch;
           c4[dy] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(cur + static_cast<int64_t>(yv) * p.pitch + x));
-          lo[dy] = *reinterpret_cast<const uint32_t*>(prow + a0);
-          hi[dy] = *reinterpret_cast<const uint32_t*>(prow + a1);
+          ref[dy] = *reinterpret_cast<const dword_pair*>(prow + a0);
         }
 #pragma unroll
         for (int dy = 0; dy < 4; ++dy) {
-          uint32_t pred = __builtin_amdgcn_alignbyte(hi[dy], lo[dy], static_cast<uint32_t>(xs & 3));
-          if (!fast) {                                       // reference leaves the frame: clamp per pixel
-            const int y = (yc << p.cell_shift) + r4 + dy;
-            const int yv = min(max(y, y_begin), y_end - 1);
-            const uint8_t* prow = prev + static_cast<int64_t>(min(max(yv + oy, 0), H - 1)) * p.pitch;
-            pred = 0u;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) pred |= static_cast<uint32_t>(prow[min(max(xs + t, 0), W - 1)]) << (8 * t);
-          }
+          const uint32_t pred = __builtin_amdgcn_perm(ref[dy].y, ref[dy].x, pick);
           const uint32_t ma = live[dy] ? mask_a : 0u, mb = live[dy] ? mask_b : 0u;
           acc_a = __builtin_amdgcn_sad_u8(c4[dy] & ma, pred & ma, acc_a);
           acc_b = __builtin_amdgcn_sad_u8(c4[dy] & mb, pred & mb, acc_b);
         }
       }
     }
-    if (acc_a) atomicAdd(&s_sum[col_a], acc_a);
-    if (acc_b) atomicAdd(&s_sum[col_b], acc_b);
+    if (acc_a) atomicAdd(&s_sum[col_a - col_lo], acc_a);
+    if (acc_b) atomicAdd(&s_sum[col_b - col_lo], acc_b);
   }
   __syncthreads();
   uint32_t* out = p.res + (static_cast<int64_t>(frame) * p.grid_h + band) * p.grid_w;
-  for (int i = tid; i < p.grid_w; i += 256)
-    if (s_sum[i]) atomicAdd(out + i, s_sum[i]);
+  for (int i = tid; i < col_hi - col_lo; i += 256) {
+    if constexpr (kWhole) out[col_lo + i] = patch_mean(p, band, col_lo + i, s_sum[i]);
+    else if (s_sum[i]) atomicAdd(out + i, s_sum[i]);
+  }
 }
 
 __global__ __launch_bounds__(256) void residual_mean_kernel(ResidualParams p) {
@@ -166,10 +187,7 @@ __global__ __launch_bounds__(256) void residual_mean_kernel(ResidualParams p) {
   if (i >= static_cast<int64_t>(p.n_frames) * n_patch) return;
   const int cell = static_cast<int>(i % n_patch);
   const int r = cell / p.grid_w, c = cell - r * p.grid_w;
-  const int64_t wide = first_coord(c + 1, p.den_x, p.in_w, p.src_w) - first_coord(c, p.den_x, p.in_w, p.src_w);
-  const int64_t tall = first_coord(r + 1, p.den_y, p.in_h, p.src_h) - first_coord(r, p.den_y, p.in_h, p.src_h);
-  const unsigned long long n = static_cast<unsigned long long>(wide * tall);
-  p.res[i] = n ? static_cast<uint32_t>((256ull * p.res[i]) / n) : 0u;
+  p.res[i] = patch_mean(p, r, c, p.res[i]);
 }
 
 }  // namespace
@@ -214,19 +232,32 @@ extern "C" int cs_residual_proxy(const uint8_t* cur, const uint8_t* prev, const 
   p.div_x = exact_div(p.den_x);
   p.grid_h = grid_h;
   p.grid_w = grid_w;
-  // enough workgroups to fill the chip: split a patch row's source rows among n_sub workgroups
   const int64_t bands = static_cast<int64_t>(n_frames) * grid_h;
   const int64_t band_rows = (static_cast<int64_t>(p.den_y) + in_h - 1) / in_h + 1;
+  hipStream_t st = cs::as_stream(stream);
+  const int64_t col_groups = (static_cast<int64_t>(p.den_x) + 4ll * in_w - 1) / (4ll * in_w);    // of one patch
+  if (band_rows <= 128 && col_groups <= 128) {
+    // patches small enough for a workgroup of their own: at least four quads of rows per part (the set-up of a
+    // thread is paid once), as many patches as the lanes of a part's waves take in one turn
+    p.n_parts = band_rows >= 64 ? 4 : band_rows >= 32 ? 2 : 1;
+    const int64_t lanes = 256 / p.n_parts;
+    const int64_t cols = col_groups >= lanes ? 1 : (lanes - 1) / col_groups;
+    p.n_sub = static_cast<int32_t>((grid_w + cols - 1) / cols);
+    if (bands * p.n_sub >= (1ll << 31)) return CS_EUNSUPPORTED;
+    hipLaunchKernelGGL(residual_sum_kernel<true>, dim3(static_cast<unsigned>(bands * p.n_sub)), dim3(256),
+                       static_cast<size_t>((grid_w + p.n_sub - 1) / p.n_sub) * sizeof(uint32_t), st, p);
+    return cs::note_hip(hipGetLastError());
+  }
+  // larger ones: enough workgroups to fill the chip, a patch row's source rows split among n_sub workgroups
   int64_t n_sub = (8192 + bands - 1) / bands;               // a few rounds of workgroups per CU
   if (n_sub > band_rows / 16) n_sub = band_rows / 16;        // at least four quads of rows each: the per-thread set-up is paid once per workgroup
   if (n_sub < 1) n_sub = 1;
   p.n_sub = static_cast<int32_t>(n_sub);
   if (bands * n_sub >= (1ll << 31)) return CS_EUNSUPPORTED;
 
-  hipStream_t st = cs::as_stream(stream);
   const int64_t n_out = static_cast<int64_t>(n_frames) * grid_h * grid_w;
   hipLaunchKernelGGL(clear_sums_kernel, dim3(static_cast<unsigned>((n_out + 255) / 256)), dim3(256), 0, st, res, n_out);
-  hipLaunchKernelGGL(residual_sum_kernel, dim3(static_cast<unsigned>(bands * n_sub)), dim3(256),
+  hipLaunchKernelGGL(residual_sum_kernel<false>, dim3(static_cast<unsigned>(bands * n_sub)), dim3(256),
                      static_cast<size_t>(grid_w) * sizeof(uint32_t), st, p);
   hipLaunchKernelGGL(residual_mean_kernel, dim3(static_cast<unsigned>((n_out + 255) / 256)), dim3(256), 0, st, p);
   return cs::note_hip(hipGetLastError());

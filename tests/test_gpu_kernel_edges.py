@@ -8,7 +8,7 @@ import torch
 
 from oracle import codecsight_oracle as oc
 from tests import helpers as hp
-from tests.test_gpu_parity import DEV, _attn_case, _pool, cs, say        # noqa: F401  (cs is a fixture)
+from tests.test_gpu_parity import DEV, _attn_case, _pool, _project_gpu, _random_block_frames, _residual_gpu, cs, say   # noqa: F401  (cs is a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +114,45 @@ def test_unplanned_attention_head_major_pool_and_row_capacity(cs, dtype, hq, hkv
     assert torch.all(got[n_q:] == 7.0)
     if wsb:
         assert cs.cs_attn_status(ws) == 0
+
+
+# residual proxy: workgroups of whole patches with their rows in 1, 2 or 4 parts, and patches too large for that
+RESIDUAL_RUNS = [
+    # frames, h, w, cell, in_w, in_h, patch, gh, gw, pad
+    (2, 64, 640, 4, 640, 64, 31, 2, 20, 0),            # 31 rows per patch: one part
+    (2, 200, 636, 4, 448, 112, 28, 4, 16, 16),         # 50 rows: two parts; patch borders inside 4-pixel groups
+    (1, 303, 500, 8, 140, 84, 28, 3, 5, 0),            # 101 rows: four parts
+    (1, 128, 1030, 16, 1030, 128, 127, 1, 8, 0),       # the last patch cut off, 128 rows with the rounding
+    (1, 290, 520, 4, 56, 28, 28, 1, 2, 0),             # 290 rows per patch: rows split among workgroups
+    (1, 40, 1600, 4, 80, 40, 40, 1, 2, 0),             # 800 pixels wide
+    (2, 48, 96, 4, 48, 24, 8, 5, 7, 0),                # patches past the frame: no pixel, score 0
+]
+
+
+@pytest.mark.parametrize("case", range(len(RESIDUAL_RUNS)))
+def test_residual_proxy_work_splits(cs, case):
+    from oracle import residual_oracle as ro
+    f, h, w, cell, in_w, in_h, patch, gh, gw, pad = RESIDUAL_RUNS[case]
+    say(f"residual_proxy split {case}: {f} frames {w}x{h} cell {cell} -> grid {gh}x{gw}")
+    rng = np.random.default_rng(9500 + case)
+    cur, prev = (rng.integers(0, 256, size=(f, h, w), dtype=np.uint8) for _ in range(2))
+    field = rng.integers(-60, 61, size=(f, -(-h // cell), -(-w // cell), 2)).astype(np.int16)
+    field[:, ::3, ::5] *= 40                                        # some references leave the frame on every side
+    want = ro.residual_proxy(cur, prev, field, cell, in_w, in_h, patch, gh, gw)
+    assert np.array_equal(_residual_gpu(cs, cur, prev, field, cell, in_w, in_h, patch, gh, gw, pad), want)
+
+
+@pytest.mark.parametrize("geom,counts", [
+    ((640, 360, 448, 448, 28, 16, 16), [300] * 3),                  # eight bands of two patch rows
+    ((640, 360, 1288, 728, 28, 26, 46), [700]),                     # eight bands of three or four
+    ((640, 360, 448, 140, 28, 5, 16), [200, 0, 90]),                # as many bands as patch rows
+    ((640, 360, 448, 448, 28, 16, 16), [9] * 130),                  # three bands
+    ((64, 48, 32, 24, 8, 3, 4), [5] * 520),                         # one band
+])
+def test_project_blocks_bands(cs, geom, counts):
+    from oracle import projection_oracle as po
+    say(f"project_blocks bands: geometry {geom}, {len(counts)} frames")
+    blocks, cu = _random_block_frames(np.random.default_rng(9600 + len(counts)), counts, geom[0], geom[1], 64, 40)
+    mv_w, intra_w = po.project_blocks(blocks, cu, *geom)
+    mv_g, intra_g = _project_gpu(cs, blocks, cu, geom)
+    assert np.array_equal(mv_g, mv_w) and np.array_equal(intra_g, intra_w)
