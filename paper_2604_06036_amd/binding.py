@@ -101,11 +101,12 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     if not t.is_cuda:
         raise ValueError("device tensor expected")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle of torch's current stream (building the Stream object around it costs as much as the call it is for)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _need(fn: str, t: Optional[torch.Tensor], n: int, what: str):

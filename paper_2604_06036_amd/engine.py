@@ -300,18 +300,23 @@ class DeviceStep:
                                self.cs.CS_ROPE_HALF_SPLIT, self.dtype)
 
     def refresh_scatter(self, layer: int):
+        self._refresh_scatter(self.k_new[layer], self.v_new[layer], self.k_pool[layer], self.v_pool[layer])
+
+    def _refresh_scatter(self, k_new, v_new, k, v):
         w = self.data.workload
-        self.cs.cs_kv_refresh_scatter(self.k_new[layer], self.v_new[layer], self.q_slot,
-                                      self.k_pool[layer], self.v_pool[layer], self.n_q, w.n_kv_heads,
+        self.cs.cs_kv_refresh_scatter(k_new, v_new, self.q_slot, k, v, self.n_q, w.n_kv_heads,
                                       w.head_dim, self.stride_slot, self.stride_head, self.dtype)
 
     def attention(self, layer: int, reuse_plan: bool = False):
         """Attention of one layer.  The work plan depends only on cu_q / q_pos: `run` builds it at
         the first layer and lets the other layers reuse it."""
+        self._attention(self.q[layer], self.k_pool[layer], self.v_pool[layer], self.out[layer], reuse_plan)
+
+    def _attention(self, q, k, v, out, reuse_plan):
         w = self.data.workload
-        self.cs.cs_window_prefill_attn(self.q[layer], self.k_pool[layer], self.v_pool[layer], self.cu_q,
+        self.cs.cs_window_prefill_attn(q, k, v, self.cu_q,
                                        self.q_pos, self.kv_len, self.block_table, self.max_blocks,
-                                       self.cs.CS_KV_BLOCK, self.out[layer], self.n_q, w.n_streams,
+                                       self.cs.CS_KV_BLOCK, out, self.n_q, w.n_streams,
                                        w.n_q_heads, w.n_kv_heads, w.head_dim, self.stride_slot,
                                        self.stride_head, self.data.softmax_scale, self.dtype,
                                        self.ws_d if self.ws_d_bytes else None, self.ws_d_bytes,
@@ -367,6 +372,8 @@ class DeviceStep:
                     ready[l0] = ev
         else:
             self.rerotate()
+        # (the views of all layers at once: indexing six tensors in every layer costs more than the two calls of a layer)
+        views = () if self.fused else [t.unbind(0) for t in (self.k_new, self.v_new, self.k_pool, self.v_pool, self.q, self.out)]
         for layer in range(n_layers):
             if layer in ready:
                 # the refresh write touches other rows than the correction, but the fused call reads the cache too
@@ -375,10 +382,11 @@ class DeviceStep:
             if self.fused:
                 self.refresh_and_attention(layer, reuse_plan=layer > 0)
             else:
-                self.refresh_scatter(layer)
+                k_new, v_new, k, v, q, out = (t[layer] for t in views)
+                self._refresh_scatter(k_new, v_new, k, v)
                 if layer in ready:
                     torch.cuda.current_stream().wait_event(ready[layer])
-                self.attention(layer, reuse_plan=layer > 0)
+                self._attention(q, k, v, out, layer > 0)
         if ready:
             torch.cuda.current_stream().wait_stream(self.side)
 
