@@ -9,6 +9,7 @@ import torch
 from oracle import codecsight_oracle as oc
 from tests import helpers as hp
 from tests.test_gpu_parity import DEV, _attn_case, _pool, _project_gpu, _random_block_frames, _residual_gpu, cs, say   # noqa: F401  (cs is a fixture)
+from tests.test_gpu_parity import test_attention_plan_is_a_valid_schedule as _plan_is_valid
 
 pytestmark = pytest.mark.gpu
 
@@ -156,3 +157,13 @@ def test_project_blocks_bands(cs, geom, counts):
     mv_w, intra_w = po.project_blocks(blocks, cu, *geom)
     mv_g, intra_g = _project_gpu(cs, blocks, cu, geom)
     assert np.array_equal(mv_g, mv_w) and np.array_equal(intra_g, intra_w)
+
+
+@pytest.mark.parametrize("hq,hkv,kv_lens,n_qs", [
+    (28, 4, [2300, 1900, 2100, 900, 2200], [900, 1000, 800, 300, 1100]),        # 20 pairs: two whole rounds of the XCDs, four left over
+    (16, 1, [700 + 9 * i for i in range(23)], [480 + 3 * i for i in range(23)]),  # 23 pairs
+    (8, 8, [900, 40, 1000], [6000, 0, 7000]),                                   # 24 pairs, a third of them empty
+])
+def test_attention_plan_pairs_left_over_by_whole_rounds(cs, hq, hkv, kv_lens, n_qs):
+    kv_lens = [max(k, n) for k, n in zip(kv_lens, n_qs)]
+    _plan_is_valid(cs, hq, hkv, kv_lens, n_qs)
