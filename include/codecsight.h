@@ -405,7 +405,8 @@ int cs_kv_refresh_scatter(const void* k_new, const void* v_new, const int32_t* s
  *                the others); the planning launch is skipped.  CS_ATTN_PLAN_ONLY: plan and return
  *                (q, the caches and out are not touched and may be NULL), for callers that
  *                prefer every layer to run in REUSE mode.  Ignored where no plan is used (CS_F32, head_dim 64: an
- *                ONLY call then computes like any other).
+ *                ONLY call then computes like any other).  Launches of few row tiles run without a plan as
+ *                well: a BUILD call of such a shape makes none, a REUSE call of it reads none.
  * Errors: CS_EINVAL (null pointer, negative size, n_q_heads not a multiple of n_kv_heads, unknown
  *         plan_mode, softmax_scale not a positive finite number), CS_EUNSUPPORTED (head_dim not in {64,128}, block_size != 16,
  *         n_q_heads/n_kv_heads > 16, strides not multiples of 16 bytes, unknown dtype; CS_BF16:
@@ -435,7 +436,8 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  *
  * Exactly cs_kv_refresh_scatter(k_new, v_new, slot, ..., n_tok, ...) followed by
  * cs_window_prefill_attn(q, ..., plan_mode, ...) on the same layer, same arguments, same results
- * bit for bit.  CS_BF16 with head_dim 128: ONE launch: every workgroup of the persistent attention
+ * bit for bit.  CS_BF16 with head_dim 128, where attention runs from a plan (below 1,024 row tiles it
+ * may not, see cs_window_prefill_attn): ONE launch: every workgroup of the persistent attention
  * grid first moves its share of the new rows (stores written through to memory at device scope),
  * the grid meets at a launch-wide barrier, then attention proceeds as in cs_window_prefill_attn; a
  * CS_ATTN_PLAN_BUILD call is preceded by the planning launch, a CS_ATTN_PLAN_ONLY call plans and
@@ -449,11 +451,10 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  * counters: after a call that raised the word, plan again with CS_ATTN_PLAN_BUILD before the
  * workspace serves another call).
  *
- * Measured on MI355X as eager calls the one launch is 17 % shorter than the two calls for a single
- * stream (26 against 32 us) and within 3 % of them for batches of 32-64 streams (there the row move
- * is bandwidth-bound, so the launch saved is about what the barrier adds); replayed from a HIP
- * graph, where a kernel boundary costs about 2 us, the step built on it is 3-12 % longer than the
- * step of separate calls.
+ * Measured on MI355X as eager calls the one launch is within 3 % of the two calls for batches of
+ * 32-64 streams (the row move is bandwidth-bound, so the launch saved is about what the barrier
+ * adds); replayed from a HIP graph, where a kernel boundary costs about 2 us, the step built on it
+ * is 3-6 % longer than the step of separate calls.
  *
  *  k_new, v_new, slot, n_tok    as in cs_kv_refresh_scatter (slot < 0 skips the row)
  *  k_cache_layer, v_cache_layer i/o
