@@ -288,7 +288,9 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
     v_off[i] = (at + chunk_of(i, true) * 8) * 2;
   }
   // cache blocks of this wave's share of a tile: scalar loads, so that waiting for them does not drain the tile
-  // requests; issued unconditionally (the last tile's blocks again when there is no next tile)
+  // requests; issued unconditionally (the last tile's blocks again when there is no next tile).  Every load is waited
+  // for in the trip that issued it, also where nothing reads it: the compiler does not know that the register is
+  // still to be written, and is free to reuse a dead one
   int ids[BPW], ids_next[BPW];
   auto load_ids = [&](int kt) {
 #pragma unroll
@@ -364,6 +366,8 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
   float m_run = kNegInf, l_run = 0.f;
   const float slack = kMaxSlack / p.scale_log2e;          // in raw score units
 
+  if (STAGES == 2) wait_ids();
+
   const int n_trips = (n_key_tiles + KG - 1) / KG;
   for (int trip = 0; trip < n_trips; ++trip, kt += KG) {
     wait_vmcnt<0>();
@@ -372,7 +376,6 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
     const int stage = STAGES == 2 ? trip & 1 : 0;
     const uint32_t stage_off = stage * (2 * TILE * 2);
     if (STAGES == 2) {
-      wait_ids();
       if (kt + KG < n_key_tiles) {
         request(kt + KG, stage ^ 1, 0);
         request(kt + KG, stage ^ 1, 1);
@@ -475,6 +478,7 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
             o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pb[kb][mm], o[db], 0, 0, 0);
           }
     }
+    if (STAGES == 2) wait_ids();
   }
 
   // ---- the groups' partial results: the upper half of the groups hands over to the lower half until one is left
