@@ -3,7 +3,7 @@
 // rectangles are rescaled and every patch gets the strongest motion (Eq. 1) among the blocks that
 // land on it.  Sec. 3.3.2: a patch touched by an intra-coded block is flagged.
 //
-// A workgroup per band of patch rows of a frame (one band in large batches).  The band's patch table
+// A workgroup per band of patch rows of a frame (one band in large batches and for small frames).  The band's patch table
 // lives in LDS as 64-bit keys
 //     key = |v|^2 << 32 | (dx + 32768) << 16 | (dy + 32768)
 // so that "largest magnitude, ties to the lexicographically largest vector" is an unsigned
@@ -16,11 +16,12 @@
 // the numerators that can occur (below 2^29).
 //
 // A record's patch range, key and raises are some 150 vector instructions, 13 us for a 1920 x 1080
-// frame's 14 k blocks on one CU: with fewer frames than the chip has CUs the bands of a frame are
+// frame's 14 k blocks on one CU: with at most half as many frames as the chip has CUs the bands of a frame are
 // separate workgroups.  Each reads all of the frame's records (from L2 after the first) but leaves a
 // record after one comparison when it does not reach the band; blocks arrive in raster order, so
-// whole wavefronts leave together.  32 frames of 1920 x 1080: 14.5 us with a workgroup per frame,
-// 8.2 with eight.
+// whole wavefronts leave together.  32 frames of 1920 x 1080: 13.7 us with a workgroup per frame,
+// 8.3 with eight.  With one band a record is read once and past the caches: 1,376 frames, 304 MB,
+// 60.4 us (5.0 TB/s), 68.3 with the cached loads and the comparison that bands need.
 #include "common.h"
 
 namespace {
@@ -60,12 +61,15 @@ struct ProjectParams {
   int32_t n_frames, n_bands;
 };
 
+// kBands: a workgroup owns one band of a frame, not all of it.
+template <bool kBands>
 __global__ __launch_bounds__(kProjectThreads) void project_blocks_kernel(ProjectParams p) {
   extern __shared__ unsigned long long s_key[];                         // [patches of the band]
   const int tid = threadIdx.x;
   // (the bands of a frame lie n_frames workgroups apart: with a multiple of 8 frames they share an XCD's L2)
-  const int frame = blockIdx.x % p.n_frames, band = blockIdx.x / p.n_frames;
-  const int row_lo = band * p.grid_h / p.n_bands, row_hi = (band + 1) * p.grid_h / p.n_bands;
+  const int frame = kBands ? blockIdx.x % p.n_frames : blockIdx.x, band = kBands ? blockIdx.x / p.n_frames : 0;
+  const int row_lo = kBands ? band * p.grid_h / p.n_bands : 0;
+  const int row_hi = kBands ? (band + 1) * p.grid_h / p.n_bands : p.grid_h;
   const int n_cells = (row_hi - row_lo) * p.grid_w;
   uint32_t* s_intra = reinterpret_cast<uint32_t*>(s_key + n_cells);    // bitmap, n_cells bits
   for (int i = tid; i < n_cells; i += kProjectThreads) s_key[i] = 0ull;
@@ -82,7 +86,7 @@ __global__ __launch_bounds__(kProjectThreads) void project_blocks_kernel(Project
     const bool is_intra = (rec.w & 1u) != 0;
     const uint32_t mag = static_cast<uint32_t>(dx * dx) + static_cast<uint32_t>(dy * dy);   // up to 2^31
     if (!is_intra && mag == 0u) return;                       // a zero vector changes no patch
-    if (y + h <= band_y0 || y >= band_y1) return;
+    if (kBands && (y + h <= band_y0 || y >= band_y1)) return;
     // footprint clipped to the frame; nothing left -> no footprint
     const uint32_t lo_x = min(x, p.src_w), hi_x = min(x + w, p.src_w);
     const uint32_t lo_y = min(y, p.src_h), hi_y = min(y + h, p.src_h);
@@ -111,7 +115,8 @@ __global__ __launch_bounds__(kProjectThreads) void project_blocks_kernel(Project
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + u * kProjectThreads;
-      rec[u] = i < end ? p.blocks[i] : cs::u32x4{0u, 0u, 0u, 0u};
+      // (only the other bands of a frame read a record again)
+      rec[u] = i >= end ? cs::u32x4{0u, 0u, 0u, 0u} : kBands ? p.blocks[i] : __builtin_nontemporal_load(p.blocks + i);
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) apply(rec[u]);
@@ -159,16 +164,20 @@ extern "C" int cs_project_blocks(const cs_block* blocks, const int32_t* cu_block
   p.div_y = exact_div(p.den_y);
   p.grid_h = grid_h; p.grid_w = grid_w;
   p.n_patch = static_cast<int32_t>(n_patch);
-  // bands: two workgroups of this size fit a CU, so up to 512 in all; at most eight (past that the
-  // records every band reads cost more than its share of the work), one patch row at least
-  int bands = n_frames >= 512 ? 1 : 512 / n_frames;
+  // Bands: one workgroup per CU, at most eight (past that the records every band reads cost more than its share of
+  // the work), one patch row at least.  us with one band / 256 / 512 workgroups in all, 1920 x 1080: 32 frames
+  // 13.7 / 8.3 / 8.3, 96 14.2 / 12.6 / 13.5, 255 16.4 / 16.4 / 23.5.  A frame of few blocks and patches is one
+  // band: 640 x 360 to 16 x 16 patches, 64 frames, 4.2 / 4.4 / 5.2 (to 26 x 46 5.3 / 5.1 / 6.0).
+  int bands = n_frames < 256 ? 256 / n_frames : 1;
+  if (static_cast<int64_t>(src_w) * src_h / 256 + 2 * n_patch < 2048) bands = 1;        // macroblocks + 2 patches
   if (bands > 8) bands = 8;
   if (bands > grid_h) bands = grid_h;
   p.n_frames = n_frames;
   p.n_bands = bands;
   const int64_t cells = static_cast<int64_t>((grid_h + bands - 1) / bands) * grid_w;
   const size_t lds = static_cast<size_t>(cells) * 8 + static_cast<size_t>((cells + 31) / 32) * 4;
-  hipLaunchKernelGGL(project_blocks_kernel, dim3(static_cast<unsigned>(n_frames) * bands), dim3(kProjectThreads),
-                     lds, cs::as_stream(stream), p);
+  const dim3 grid(static_cast<unsigned>(n_frames) * bands), block(kProjectThreads);
+  if (bands > 1) hipLaunchKernelGGL(project_blocks_kernel<true>, grid, block, lds, cs::as_stream(stream), p);
+  else hipLaunchKernelGGL(project_blocks_kernel<false>, grid, block, lds, cs::as_stream(stream), p);
   return cs::note_hip(hipGetLastError());
 }

@@ -144,11 +144,16 @@ def test_residual_proxy_work_splits(cs, case):
 
 
 @pytest.mark.parametrize("geom,counts", [
-    ((640, 360, 448, 448, 28, 16, 16), [300] * 3),                  # eight bands of two patch rows
+    ((640, 360, 448, 448, 28, 16, 16), [300] * 3),                  # few blocks and patches: one band
     ((640, 360, 1288, 728, 28, 26, 46), [700]),                     # eight bands of three or four
-    ((640, 360, 448, 140, 28, 5, 16), [200, 0, 90]),                # as many bands as patch rows
-    ((640, 360, 448, 448, 28, 16, 16), [9] * 130),                  # three bands
+    ((640, 360, 448, 140, 28, 5, 16), [200, 0, 90]),
+    ((640, 360, 448, 448, 28, 16, 16), [9] * 130),
     ((64, 48, 32, 24, 8, 3, 4), [5] * 520),                         # one band
+    ((1280, 720, 448, 448, 28, 16, 16), [2000] * 2),                # 3,600 macroblocks: eight bands of two patch rows
+    ((1280, 720, 448, 140, 28, 5, 16), [200, 0, 90]),               # as many bands as patch rows
+    ((1280, 720, 448, 448, 28, 16, 16), [9] * 80),                  # three bands, five or six patch rows each
+    ((1280, 720, 448, 448, 28, 16, 16), [9] * 128),                 # two bands
+    ((1280, 720, 448, 448, 28, 16, 16), [9] * 129),                 # one band
 ])
 def test_project_blocks_bands(cs, geom, counts):
     from oracle import projection_oracle as po
