@@ -12,8 +12,10 @@
 // current pixels (one dword) and the reference pixels (one 8-byte load and a byte permute that also clamps columns
 // outside the frame), eight independent loads in flight.  |a - b| over four pixels is one v_sad_u8; a group that
 // straddles a patch border is split by byte masks fixed per thread, so the row loop has no patch arithmetic at all.
-// HBM bound: 32 frames of 1920 x 1080, cell 4, 166 MB in 38.5 us (4.3 TB/s; 43.6 us as three launches with two dword
-// loads per reference and a path of byte loads at the frame's sides).
+// HBM bound.  Runs of patches that share lines of the planes go to one XCD, so that its L2 serves the second, and in
+// large batches a run is a whole patch row (512 lanes), read front to back.  us for 1920 x 1080, 16 x 16 patches, with
+// short runs dealt round the XCDs / as three launches / now: cell 4, 32 frames, 149 MB 42.2 / 47.0 / 41.7; 96 frames,
+// 448 MB 110 / 105 / 98.6 (4.5 TB/s); 200 frames 223 / 186 / 184 (5.1 TB/s); cell 16, 96 frames 140 / 125 / 91.4.
 // Integer adds commute, so the result is bit exact whatever the order.
 #include "common.h"
 
@@ -73,17 +75,20 @@ __device__ __forceinline__ uint32_t patch_mean(const ResidualParams& p, int r, i
   return n ? static_cast<uint32_t>((256ull * sum) / n) : 0u;
 }
 
-// kWhole: a workgroup owns a run of whole patches of one patch row (n_sub runs per row) and writes their means: one
-// launch.  Its waves are n_parts parts of the row's source rows times 4 / n_parts shares of the columns.
+// kWhole: a workgroup of T threads owns a run of whole patches of one patch row (n_sub runs per row) and writes their
+// means: one launch.  Its waves are n_parts parts of the row's source rows times T / 64 / n_parts shares of the columns.
 // Otherwise a workgroup owns the source rows of one n_sub-th of a patch row and adds to sums that a launch before
 // this one clears and a launch after it divides.
-template <bool kWhole>
-__global__ __launch_bounds__(256) void residual_sum_kernel(ResidualParams p) {
+template <bool kWhole, int T>
+__global__ __launch_bounds__(T) void residual_sum_kernel(ResidualParams p) {
   extern __shared__ uint32_t s_sum[];                       // [patches of the workgroup]
   const int tid = threadIdx.x;
-  const int sub = blockIdx.x % p.n_sub;
-  const int band = (blockIdx.x / p.n_sub) % p.grid_h;
-  const int frame = blockIdx.x / (p.n_sub * p.grid_h);
+  // workgroups go to the XCDs round robin: an XCD's workgroups take consecutive runs
+  const int xcd = blockIdx.x & 7;
+  const int run = kWhole ? (blockIdx.x >> 3) + xcd * (gridDim.x >> 3) + min(xcd, static_cast<int>(gridDim.x & 7)) : blockIdx.x;
+  const int sub = run % p.n_sub;
+  const int band = (run / p.n_sub) % p.grid_h;
+  const int frame = run / (p.n_sub * p.grid_h);
   const int col_lo = kWhole ? static_cast<int>(static_cast<int64_t>(p.grid_w) * sub / p.n_sub) : 0;
   const int col_hi = kWhole ? static_cast<int>(static_cast<int64_t>(p.grid_w) * (sub + 1) / p.n_sub) : p.grid_w;
   const int n_parts = kWhole ? p.n_parts : p.n_sub;
@@ -98,14 +103,14 @@ __global__ __launch_bounds__(256) void residual_sum_kernel(ResidualParams p) {
   const int y_begin = max(y_lo, 4 * q_begin), y_end = min(y_hi, 4 * q_end);
   if (!kWhole && (y_lo >= y_hi || y_begin >= y_end)) return;          // uniform for the workgroup
 
-  for (int i = tid; i < col_hi - col_lo; i += 256) s_sum[i] = 0u;
+  for (int i = tid; i < col_hi - col_lo; i += T) s_sum[i] = 0u;
   __syncthreads();
 
   const int W = p.src_w, H = p.src_h;
   const int all_groups = (W + 3) / 4;                                // 4-pixel groups along a row
   const int k_lo = kWhole ? first_coord(col_lo, p.den_x, p.in_w, W) >> 2 : 0;
   const int groups = kWhole ? min(all_groups, (first_coord(col_hi, p.den_x, p.in_w, W) + 3) >> 2) : all_groups;
-  const int k_step = kWhole ? 256 / n_parts : 256;
+  const int k_step = kWhole ? T / n_parts : T;
   const int k_first = kWhole ? k_lo + 64 * (wave / n_parts) + (tid & 63) : tid;
   const uint8_t* cur = p.cur + static_cast<int64_t>(frame) * p.frame_stride;
   const uint8_t* prev = p.prev + static_cast<int64_t>(frame) * p.frame_stride;
@@ -147,13 +152,14 @@ __global__ __launch_bounds__(256) void residual_sum_kernel(ResidualParams p) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) pick |= static_cast<uint32_t>(min(max(xs + t, 0), W - 1) - a0) << (8 * t);
       }
-      for (int r4 = 0; r4 < cell; r4 += 4) {
+      const int y_cell = yc << p.cell_shift;                 // (a part may begin and end inside a cell row)
+      for (int r4 = max((y_begin & ~3) - y_cell, 0); r4 < min(y_end - y_cell, cell); r4 += 4) {
         uint32_t c4[4];
         dword_pair ref[4];
         bool live[4];
 #pragma unroll
         for (int dy = 0; dy < 4; ++dy) {
-          const int y = (yc << p.cell_shift) + r4 + dy;
+          const int y = y_cell + r4 + dy;
           live[dy] = y >= y_begin && y < y_end;
           const int yv = min(max(y, y_begin), y_end - 1);    // a row of this workgroup in any case
           const int yy = min(max(yv + oy, 0), H - 1);
@@ -175,7 +181,7 @@ __global__ __launch_bounds__(256) void residual_sum_kernel(ResidualParams p) {
   }
   __syncthreads();
   uint32_t* out = p.res + (static_cast<int64_t>(frame) * p.grid_h + band) * p.grid_w;
-  for (int i = tid; i < col_hi - col_lo; i += 256) {
+  for (int i = tid; i < col_hi - col_lo; i += T) {
     if constexpr (kWhole) out[col_lo + i] = patch_mean(p, band, col_lo + i, s_sum[i]);
     else if (s_sum[i]) atomicAdd(out + i, s_sum[i]);
   }
@@ -237,15 +243,30 @@ extern "C" int cs_residual_proxy(const uint8_t* cur, const uint8_t* prev, const 
   hipStream_t st = cs::as_stream(stream);
   const int64_t col_groups = (static_cast<int64_t>(p.den_x) + 4ll * in_w - 1) / (4ll * in_w);    // of one patch
   if (band_rows <= 128 && col_groups <= 128) {
-    // patches small enough for a workgroup of their own: at least four quads of rows per part (the set-up of a
-    // thread is paid once), as many patches as the lanes of a part's waves take in one turn
-    p.n_parts = band_rows >= 64 ? 4 : band_rows >= 32 ? 2 : 1;
-    const int64_t lanes = 256 / p.n_parts;
-    const int64_t cols = col_groups >= lanes ? 1 : (lanes - 1) / col_groups;
-    p.n_sub = static_cast<int32_t>((grid_w + cols - 1) / cols);
+    // patches small enough for a workgroup of their own.  A run is as many of them as the lanes of a part's waves take
+    // in one turn.
+    auto runs = [&](int64_t lanes) {
+      const int64_t cols = col_groups >= lanes ? 1 : (lanes - 1) / col_groups;
+      return (grid_w + cols - 1) / cols;
+    };
+    // Large batches: 512 lanes and one part, where a row keeps three quarters of them busy and there are three such
+    // workgroups per CU.  us with 256 threads / 512, 1920 x 1080, cell 4, 16 x 16 patches: 16 frames (256 workgroups)
+    // 24.0 / 25.7, 32 41.7 / 42.4, 64 73.7 / 68.7, 96 104.1 / 98.6; 1280 x 720 (320 lanes of 512) 52.1 / 55.0.
+    const int64_t wide_sub = runs(512);
+    const bool wide = bands * wide_sub >= 768 && (src_w + 3) / 4 >= 384 * wide_sub;
+    if (wide) {
+      p.n_parts = 1;
+      p.n_sub = static_cast<int32_t>(wide_sub);
+    } else {
+      // at least four quads of rows per part: the set-up of a thread is paid once
+      p.n_parts = band_rows >= 64 ? 4 : band_rows >= 32 ? 2 : 1;
+      p.n_sub = static_cast<int32_t>(runs(256 / p.n_parts));
+    }
     if (bands * p.n_sub >= (1ll << 31)) return CS_EUNSUPPORTED;
-    hipLaunchKernelGGL(residual_sum_kernel<true>, dim3(static_cast<unsigned>(bands * p.n_sub)), dim3(256),
-                       static_cast<size_t>((grid_w + p.n_sub - 1) / p.n_sub) * sizeof(uint32_t), st, p);
+    const dim3 grid(static_cast<unsigned>(bands * p.n_sub));
+    const size_t lds = static_cast<size_t>((grid_w + p.n_sub - 1) / p.n_sub) * sizeof(uint32_t);
+    if (wide) hipLaunchKernelGGL((residual_sum_kernel<true, 512>), grid, dim3(512), lds, st, p);
+    else hipLaunchKernelGGL((residual_sum_kernel<true, 256>), grid, dim3(256), lds, st, p);
     return cs::note_hip(hipGetLastError());
   }
   // larger ones: enough workgroups to fill the chip, a patch row's source rows split among n_sub workgroups
@@ -257,7 +278,7 @@ extern "C" int cs_residual_proxy(const uint8_t* cur, const uint8_t* prev, const 
 
   const int64_t n_out = static_cast<int64_t>(n_frames) * grid_h * grid_w;
   hipLaunchKernelGGL(clear_sums_kernel, dim3(static_cast<unsigned>((n_out + 255) / 256)), dim3(256), 0, st, res, n_out);
-  hipLaunchKernelGGL(residual_sum_kernel<false>, dim3(static_cast<unsigned>(bands * n_sub)), dim3(256),
+  hipLaunchKernelGGL((residual_sum_kernel<false, 256>), dim3(static_cast<unsigned>(bands * n_sub)), dim3(256),
                      static_cast<size_t>(grid_w) * sizeof(uint32_t), st, p);
   hipLaunchKernelGGL(residual_mean_kernel, dim3(static_cast<unsigned>((n_out + 255) / 256)), dim3(256), 0, st, p);
   return cs::note_hip(hipGetLastError());

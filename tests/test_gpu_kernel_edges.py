@@ -127,6 +127,10 @@ RESIDUAL_RUNS = [
     (1, 290, 520, 4, 56, 28, 28, 1, 2, 0),             # 290 rows per patch: rows split among workgroups
     (1, 40, 1600, 4, 80, 40, 40, 1, 2, 0),             # 800 pixels wide
     (2, 48, 96, 4, 48, 24, 8, 5, 7, 0),                # patches past the frame: no pixel, score 0
+    (2, 270, 500, 16, 140, 112, 28, 4, 5, 16),         # four parts that begin and end inside a cell row
+    (49, 48, 1540, 4, 154, 128, 8, 16, 20, 0),         # 784 patch rows of 385 groups: a workgroup of 512 lanes per row
+    (26, 45, 3100, 8, 160, 120, 8, 15, 20, 16),        # two runs of 10 patches per row, 780 workgroups
+    (47, 48, 1540, 16, 154, 128, 8, 16, 20, 0),        # 752 patch rows: short runs
 ]
 
 
