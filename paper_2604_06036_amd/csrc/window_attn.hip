@@ -796,6 +796,7 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
   __shared__ int s_wave[kPlanThreads / 64];
   __shared__ unsigned long long s_key[kSortMax];
   __shared__ int s_list_off[9];
+  __shared__ int s_left_tiles[8], s_left_end[8];   // pairs left over by whole rounds: row tiles; last row tile + pair
   __shared__ int s_by_rank[8][64];      // deal: lane (and length) of the item of each rank, per XCD
   __shared__ int s_cut[8][kSlotsPerXcd + 1];   // span plan: first tile position of every workgroup's span
   const int tid = threadIdx.x;
@@ -885,10 +886,29 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
   //      bucket = position class in the list (counting sort), XCD chosen alongside.
   //      Pairs beyond the last whole round of eight (the ones with the least work) have their row
   //      tiles dealt to all XCDs instead, behind the whole pairs: one XCD's list would carry a pair
-  //      more than another's (20 pairs: three against two).  5 streams of 3,200 keys, 4 kv heads:
-  //      169.7 -> 153.1 us a layer; 11 streams of 1,000 keys 57.5 -> 56.3.
-  const bool grouped = pp.n_streams * pp.n_kv_heads >= 16;
-  const int whole_pairs = (pp.n_streams * pp.n_kv_heads) & ~7;
+  //      more than another's (20 pairs: three against two).  On its XCD a row tile's place among
+  //      them goes by its distance from its stream's end, longest first.  us a layer without /
+  //      with: 5 streams of 3,200 keys, 4 kv heads 171.9 / 151.1; 25 streams of 2,900 keys, one
+  //      kv head 165.0 / 155.9; 21 streams of 1,000 keys, 4 kv heads 98.4 / 96.1.
+  const int n_pairs = pp.n_streams * pp.n_kv_heads, whole_pairs = n_pairs & ~7;
+  const bool grouped = n_pairs >= 16;
+  if (grouped && tid < n_pairs - whole_pairs) {
+    const int rank = (whole_pairs + tid) / pp.n_kv_heads;
+    const int s = pp.n_streams <= kSortMax ? static_cast<int>(s_key[rank] & 0xffffffffu) : rank;
+    s_left_tiles[tid] = pp.st_toff[s + 1] - pp.st_toff[s];
+    s_left_end[tid] = pp.st_toff[s + 1] - 1 + whole_pairs + tid;
+  }
+  __syncthreads();
+  // the row tiles of these pairs that XCD x takes before the given one (`level` from its stream's end)
+  auto left_before = [&](int pair, int level, int x) {
+    int at = 0;
+    for (int i = 0; i < n_pairs - whole_pairs; ++i) {
+      const int nearer = min(s_left_tiles[i], level + (i < pair - whole_pairs ? 1 : 0));
+      const int first = (s_left_end[i] - x) & 7;           // level of the pair's first tile on this XCD; every eighth follows
+      at += nearer > first ? (nearer - first + 7) >> 3 : 0;
+    }
+    return at;
+  };
   auto place = [&](int r, int s, int kvh, int split, int len, int& bucket) {
     if (grouped) {
       const int pair = pp.st_rank[s] * pp.n_kv_heads + kvh;
@@ -972,10 +992,12 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
         int bucket;
         const int x = place(r, s, kvh, c, ke - kb, bucket);
         int* cursor = &pp.hist[x * hist_pitch + bucket];
-        // a pair's bucket holds its row tiles only: the longest (last) row tile goes first; where
-        // sweeps are split or buckets are shared, arrival order decides
-        const bool in_order = grouped && pp.max_splits == 1 && pp.st_rank[s] * pp.n_kv_heads + kvh < whole_pairs;
-        const int within = in_order ? tiles_s - 1 - t : atomicAdd(cursor, 1);
+        // a pair's bucket holds its row tiles only, the last bucket those of the pairs left over:
+        // the longest (last) row tile goes first; where sweeps are split or buckets are shared by
+        // length, arrival order decides
+        const bool in_order = grouped && pp.max_splits == 1;
+        const int pair = pp.st_rank[s] * pp.n_kv_heads + kvh, level = tiles_s - 1 - t;
+        const int within = !in_order ? atomicAdd(cursor, 1) : pair < whole_pairs ? level : left_before(pair, level, x);
         const int start = in_order ? __hip_atomic_load(cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
         const int pos = s_list_off[x] + start + within;
         int32_t* it = pp.items + static_cast<int64_t>(pos) * 8;

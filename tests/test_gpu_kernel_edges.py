@@ -8,7 +8,7 @@ import torch
 
 from oracle import codecsight_oracle as oc
 from tests import helpers as hp
-from tests.test_gpu_parity import DEV, _attn_case, _pool, _project_gpu, _random_block_frames, _residual_gpu, cs, say   # noqa: F401  (cs is a fixture)
+from tests.test_gpu_parity import DEV, _attention_plan, _attn_case, _pool, _project_gpu, _random_block_frames, _residual_gpu, cs, say   # noqa: F401  (cs is a fixture)
 from tests.test_gpu_parity import test_attention_plan_is_a_valid_schedule as _plan_is_valid
 
 pytestmark = pytest.mark.gpu
@@ -169,10 +169,46 @@ def test_project_blocks_bands(cs, geom, counts):
 
 
 @pytest.mark.parametrize("hq,hkv,kv_lens,n_qs", [
-    (28, 4, [2300, 1900, 2100, 900, 2200], [900, 1000, 800, 300, 1100]),        # 20 pairs: two whole rounds of the XCDs, four left over
+    (28, 4, [2300, 1900, 2100, 900, 2200], [900, 1000, 800, 300, 1100]),        # 20 pairs, below 1,024 row tiles: split sweeps
     (16, 1, [700 + 9 * i for i in range(23)], [480 + 3 * i for i in range(23)]),  # 23 pairs
-    (8, 8, [900, 40, 1000], [6000, 0, 7000]),                                   # 24 pairs, a third of them empty
+    (8, 8, [900, 40, 1000], [6000, 0, 7000]),                                   # 24 pairs, a third of them empty, split sweeps
 ])
 def test_attention_plan_pairs_left_over_by_whole_rounds(cs, hq, hkv, kv_lens, n_qs):
     kv_lens = [max(k, n) for k, n in zip(kv_lens, n_qs)]
     _plan_is_valid(cs, hq, hkv, kv_lens, n_qs)
+
+
+@pytest.mark.parametrize("hq,hkv,kv_lens,n_qs", [
+    (28, 4, [2300, 1900, 2100, 900, 2200], [1200, 1300, 1100, 600, 1500]),      # 20 pairs: two whole rounds of the XCDs, four left over
+    (16, 1, [700 + 9 * i for i in range(23)], [480 + 3 * i for i in range(23)]),  # 23 pairs
+    (12, 3, [2000 + 90 * i for i in range(7)], [1500, 1700, 1900, 2000, 1800, 1990, 0]),  # 21 pairs, three of those left over empty
+    (16, 1, [300] * 2052, [20 + i % 9 for i in range(2052)]),                   # more streams than are sorted by work
+])
+def test_attention_plan_deals_the_left_over_pairs_in_order(cs, hq, hkv, kv_lens, n_qs):
+    """The row tiles of the pairs beyond the last whole round of eight: on all XCDs in like numbers, behind the whole
+    pairs, those nearest their stream's end first, and the same plan from one call to the next."""
+    group, n_pairs = hq // hkv, len(kv_lens) * hkv
+    say(f"attention plan, {n_pairs % 8} of {n_pairs} pairs left over")
+    assert (sum(n_qs) * group // 128 + len(kv_lens)) * hkv >= 1024              # whole sweeps, not split ones
+    _plan_is_valid(cs, hq, hkv, kv_lens, n_qs)
+    cu = np.concatenate([[0], np.cumsum(n_qs)])
+    q_pos = np.concatenate([np.arange(k - n, k) for k, n in zip(kv_lens, n_qs)])
+    bt = np.arange(len(kv_lens) * (max(kv_lens) // 16 + 1)).reshape(len(kv_lens), -1)
+    hdr, items = _attention_plan(cs, cu, q_pos, np.asarray(kv_lens), bt, hq, hkv)
+    again = _attention_plan(cs, cu, q_pos, np.asarray(kv_lens), bt, hq, hkv)
+    assert np.array_equal(hdr[:9], again[0][:9]) and np.array_equal(items, again[1])
+    tiles = [-(-n * group // 128) for n in n_qs]
+    work = [sum(int(q_pos[cu[s] + (min((t + 1) * 128, n_qs[s] * group) - 1) // group]) // 64 + 1 for t in range(tiles[s]))
+            for s in range(len(kv_lens))]
+    rank = np.argsort(np.argsort([-w for w in work], kind="stable"), kind="stable")
+    if len(kv_lens) > 2048:
+        rank = np.arange(len(kv_lens))
+    counts = []
+    for x in range(8):
+        part = items[hdr[x]: hdr[x + 1]]
+        stream, kvh = part[:, 3] >> 8, part[:, 3] & 255
+        left = rank[stream] * hkv + kvh >= n_pairs // 8 * 8
+        level = np.asarray(tiles)[stream] - 1 - part[:, 2] // 128
+        assert not np.any(left[:-1] & ~left[1:]) and np.all(np.diff(level[left]) >= 0)
+        counts.append(int(left.sum()))
+    assert max(counts) - min(counts) <= n_pairs % 8                             # each pair's are shared evenly
