@@ -406,7 +406,9 @@ int cs_kv_refresh_scatter(const void* k_new, const void* v_new, const int32_t* s
  *                (q, the caches and out are not touched and may be NULL), for callers that
  *                prefer every layer to run in REUSE mode.  Ignored where no plan is used (CS_F32, head_dim 64: an
  *                ONLY call then computes like any other).  Launches of few row tiles run without a plan as
- *                well: a BUILD call of such a shape makes none, a REUSE call of it reads none.
+ *                well (head_dim 128, fewer than 1,024 tiles of 128 rows by n_q, and not too long a window): a BUILD call
+ *                of such a shape makes none and a REUSE call of it reads none; an ONLY call still writes the plan, so
+ *                a caller of many such shapes has no use for it (BUILD at the first layer costs nothing there).
  * Errors: CS_EINVAL (null pointer, negative size, n_q_heads not a multiple of n_kv_heads, unknown
  *         plan_mode, softmax_scale not a positive finite number), CS_EUNSUPPORTED (head_dim not in {64,128}, block_size != 16,
  *         n_q_heads/n_kv_heads > 16, strides not multiples of 16 bytes, unknown dtype; CS_BF16:

@@ -75,7 +75,7 @@ struct AttnParams {
 constexpr int kBM = 128;   // rows per workgroup (4 waves x 32)
 constexpr int kBN = 64;    // keys per LDS tile
 constexpr float kNegInf = -INFINITY;
-constexpr int kMaxBlocks64 = 8192;      // head_dim 64: windows up to 131072 tokens
+constexpr int kMaxBlocks64 = 8192;      // head_dim 64: windows up to 131072 tokens (a limit of the interface; this kernel has none)
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -1944,17 +1944,20 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 }
 
 // head_dim 128: which launches leave the plan and the persistent kernel for the tile kernel, by 128-row tiles x kv
-// heads (their upper bound, as the workspace is sized) and key tiles of the longest window.  Below 1,024 row tiles
-// the persistent kernel splits its sweeps and needs the merge launch, and its plan costs 15-50 us a step.
+// heads and key tiles of the longest window.  Both are the caller's upper bounds (n_q, max_blocks): the host knows no
+// other sizes, and the route has to be the same for all calls of a shape.  The row tiles that a launch then has are
+// fewer (in the runs below, with budgets 12-40 % above the rows, 0.6-0.85 of T), so a caller that budgets closer stays
+// on a route up to more work.  Below 1,024 row tiles the persistent kernel splits its sweeps and needs the merge
+// launch, and its plan costs 15-50 us a step.
 // us a layer in a step, plan not counted, persistent + merge / tile kernel (28/4 heads unless noted; T: row tiles):
 //   1,024 tiles and more       the planned schedule balances better: T 1,196 116 / 123, T 1,632 66.5 / 77.7
 //   kRows128 (to 1,023)        T 520 40.3 / 35.0, T 808 54.5 / 42.9, T 624 with 59 key tiles 94.0 / 86.6; past 64 key
 //                              tiles the split wins: T 508 with 89 106 / 112, T 564 with 121 137 / 167
-//   kRows64Keys2 (to 440)      T 288 31.3 / 22.4; at T 520 it has two rounds of workgroups: 37.1 (kRows128 35.0); past
-//                              48 key tiles level
-//   kRows64Keys4 (to 128)      T 116 20.2 / 17.4, with 28 key tiles 28.3 / 24.9 (two groups 18.1, 28.7): every
-//                              workgroup runs at once and the longest sweep is the time; up to 8 key tiles two groups
-//                              are enough (300 keys 11.0 / 12.2, persistent 16.3)
+//   kRows64Keys2 (to 440)      T 288 31.3 / 22.4; at T 520 its twice as many workgroups (two fit a CU) no longer all run
+//                              at once: 37.1 (kRows128 35.0); past 48 key tiles level
+//   kRows64Keys4 (to 128)      T 116 20.2 / 17.4, with 28 key tiles 28.3 / 24.9 (two groups 18.1, 28.7): one workgroup
+//                              per CU, all of them run at once and the longest sweep is the time; up to 8 key tiles two
+//                              groups are enough (300 keys 11.0 / 12.2, persistent 16.3)
 //   a few row tiles with long sweeps (2 key tiles > row tiles) keep the split over the whole chip (T 27 14.8 / 16.4)
 enum class TileRoute { kNone, kRows128, kRows64Keys2, kRows64Keys4 };
 

@@ -117,6 +117,31 @@ def test_unplanned_attention_head_major_pool_and_row_capacity(cs, dtype, hq, hkv
         assert cs.cs_attn_status(ws) == 0
 
 
+@pytest.mark.parametrize("capacity", [130, 8200])                       # two key groups; one
+@pytest.mark.parametrize("stride_slot", [2 ** 26 - 8, 2 ** 26])         # 32-bit byte offsets inside a block; 64-bit addresses
+def test_head_dim_64_attention_of_far_apart_slots(cs, stride_slot, capacity):
+    """A pool whose slots are 2^26 elements apart (K and V of all slots in one 18-GiB allocation)."""
+    say(f"head_dim 64 attention, slot stride {stride_slot}, room for {capacity} tokens")
+    rng = np.random.default_rng(9700)
+    hq, hkv, d, kv_len, n_q = 16, 1, 64, 137, 130
+    bt = rng.permutation(9)[None].astype(np.int32)
+    q, kc, vc = _pool(rng, (capacity, hq, d), "bf16"), _pool(rng, (144, hkv, d), "bf16"), _pool(rng, (144, hkv, d), "bf16")
+    q_pos = np.sort(rng.choice(kv_len, n_q, replace=False)).astype(np.int32)
+    ref = oc.window_attn(hp.f64(q[:n_q]), hp.f64(kc), hp.f64(vc), np.array([0, n_q]), q_pos, bt, hq, 1 / math.sqrt(d))
+    pool = torch.empty((143 * stride_slot + 2 * hkv * d,), dtype=torch.bfloat16, device=DEV)
+    kd, vd = (pool[at:].as_strided((144, hkv, d), (stride_slot, d, 1)) for at in (0, hkv * d))
+    kd.copy_(kc)
+    vd.copy_(vc)
+    out = torch.full((capacity, hq, d), 7.0, dtype=torch.bfloat16, device=DEV)
+    i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).to(DEV)
+    pos = i32(np.concatenate([q_pos, np.zeros(capacity - n_q, np.int32)]))
+    cs.cs_window_prefill_attn(q.to(DEV), kd, vd, i32([0, n_q]), pos, i32([kv_len]), i32(bt), 9, 16, out, capacity, 1, hq, hkv, d,
+                              stride_slot, d, 1 / math.sqrt(d), cs.CS_BF16)
+    got = out.cpu()
+    hp.check_attention(got[:n_q], ref, "bf16")
+    assert torch.all(got[n_q:] == 7.0)
+
+
 # residual proxy: workgroups of whole patches with their rows in 1, 2 or 4 parts, and patches too large for that
 RESIDUAL_RUNS = [
     # frames, h, w, cell, in_w, in_h, patch, gh, gw, pad
