@@ -450,9 +450,10 @@ def kernel_rooflines(w, work, t_a, t_plan, t_b, t_c, t_d, traffic_for):
     t = traffic_for("cs_window_prefill_attn")
     tm = traffic_for("attn_merge")
     traffic = None if t is None else t["read_bytes"] + t["write_bytes"] + (0 if tm is None else tm["read_bytes"] + tm["write_bytes"])
-    name = ("window_attn_bf16_stream_kernel (+ window_attn_merge_kernel where the key sweep is split; the planning "
+    name = ("window_attn_bf16_tile_kernel where row tiles are few and the window is short, else "
+            "window_attn_bf16_stream_kernel (+ window_attn_merge_kernel where the key sweep is split; the planning "
             "kernel runs once per step)" if w.dtype == "bf16" and w.head_dim == 128 else
-            "window_attn_bf16_kernel" if w.dtype == "bf16" else "window_attn_f32_kernel")
+            "window_attn_bf16_tile_kernel" if w.dtype == "bf16" else "window_attn_f32_kernel")
     out["cs_window_prefill_attn"] = dict(kernel=name, bound="mfma", ms=t_d, launches_per_step=L,
                                          flops_per_launch=work["d_flops"], algorithmic_bytes=work["d_bytes"],
                                          achieved=ach, peak=PEAK_MFMA_BF16_TFLOPS, unit="TFLOP/s",
