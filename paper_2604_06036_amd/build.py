@@ -11,10 +11,13 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcodecsight.so")
 SOURCES = ["library.hip", "calibrate.hip", "project_blocks.hip", "residual_proxy.hip", "score_compact.hip", "plan_refresh.hip", "kv_rerotate.hip", "window_attn.hip"]
 
-# Packed-fp32 VALU forms are switched off for device code (scalar fp32 code generation only).
+# Packed-fp32 VALU forms are switched off for device code (scalar fp32 code generation only).  Matrix instructions keep
+# their results in the vector registers unless the source says otherwise: the persistent attention kernel fills the
+# accumulation registers with what it names itself, and its scores are read by vector instructions.
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wno-unused-command-line-argument",
 ]
 

@@ -4,17 +4,16 @@
 // causal attention reads a cache that mixes reused (position-corrected) states with states
 // written in the current pass.  Causality follows the window-sequence index of each query.
 //
-// bf16 kernels (matrix cores).  A workgroup = 4 waves = a tile of 128 "rows", a row being one
-// (query token, query head of one kv group) pair, so the K/V tiles a workgroup stages in LDS are
-// shared by all query heads of the group.  Keys are swept in tiles of 64 through LDS:
+// bf16 kernels (matrix cores).  A "row" is one (query token, query head of one kv group) pair, so the K/V tiles a
+// workgroup stages in LDS are shared by all query heads of the group.  Keys are swept in tiles of 64 through LDS:
 //   S^T = K Q^T      v_mfma_f32_32x32x16_bf16, A = K fragment from LDS (ds_read_b128),
 //                    B = Q^T fragment held in registers for the whole sweep;
 //   online softmax   fp32, per-lane statistics: in the S^T layout a lane owns one query and 16
-//                    of its 32 keys, the two half-waves exchange the running max once per tile;
+//                    of its 32 keys, the two half-waves exchange the running max;
 //   O^T += V^T P^T   P^T is already in B-operand layout (no LDS round trip); the V^T fragment is
 //                    fetched from the row-major V tile with the LDS transpose read
 //                    (ds_read_b64_tr_b16), so V is never transposed in memory.
-// Tiles that lie wholly above a wave's causal frontier are skipped by that wave; only tiles that
+// Key ranges that lie wholly above a wave's causal frontier are skipped by that wave; only ranges that
 // straddle a frontier pay for masking.  Cache rows past the workgroup's frontier are never read
 // (they may be unallocated): the lanes that would fetch them fetch the frontier row instead.
 //
@@ -25,6 +24,8 @@
 //
 // fp32 kernel: the fp32 matrix instruction, 32 rows per workgroup, keys dealt to its waves.
 #include <math.h>
+
+#include <type_traits>
 
 #include "common.h"
 
@@ -50,12 +51,11 @@ struct AttnParams {
   int32_t max_blocks, n_streams, n_q_heads, n_kv_heads, group;
   float scale, scale_log2e;
   int64_t n_q;
-  // split-KV (max_splits > 1): a row tile whose key sweep is longer than chunk_tiles key tiles is
-  // shared by several work items; their un-normalised partial results go to the workspace and a
-  // second kernel merges them (merging in the last workgroup to finish was built twice and is far
-  // slower here, also with write-through stores in place of an L2 write-back: single stream,
-  // 919 keys, 42 against 23 us per call; 6,033 keys 133 against 117; 17,630 keys 310 against 290)
-  int32_t chunk_tiles, max_splits, bm, span;
+  // Split sweeps (AttnPlan::span): a row tile's keys may be shared by several work items; their un-normalised partial
+  // results go to the workspace and a second kernel merges them.  (Merging in the last workgroup to finish was built
+  // twice and is far slower here, also with write-through stores in place of an L2 write-back: single stream, 919 keys,
+  // 42 against 23 us per call; 6,033 keys 133 against 117; 17,630 keys 310 against 290.)
+  int32_t bm;
   const int32_t* ws_plan;   // plan header (list offsets per XCD, row-tile count, end item, first items)
   const int32_t* ws_items;  // item descriptors, 8 ints each, the 8 XCD lists back to back
   // refresh write fused into the launch (cs_refresh_prefill_attn): rows to write before attention
@@ -67,12 +67,12 @@ struct AttnParams {
   int32_t* ws_sync;      // counters of the fused launch's launch-wide barrier (see launch_barrier)
   int32_t* ws_status;    // its status word
   int32_t clear_status;  // the launch without a plan zeroes it
-  int32_t* ws_desc;      // [items][8]: q0, rows_total, r_tile, kvh, n_split
-  float* ws_ml;          // [items][max_splits][bm][2]: running max (raw score units), row sum
-  float* ws_o;           // [items][max_splits][bm][128]: un-normalised output rows
+  int32_t* ws_desc;      // [row tiles][8]: q0, rows_total, r_tile, kvh, n_split, list position of the first piece, see plan_spans
+  float* ws_ml;          // [items][bm][2]: running max (raw score units), row sum
+  float* ws_o;           // [items][bm][128]: un-normalised output rows
 };
 
-constexpr int kBM = 128;   // rows per workgroup (4 waves x 32)
+constexpr int kBM = 128;   // rows per row tile
 constexpr int kBN = 64;    // keys per LDS tile
 constexpr float kNegInf = -INFINITY;
 constexpr int kMaxBlocks64 = 8192;      // head_dim 64: windows up to 131072 tokens (a limit of the interface; this kernel has none)
@@ -138,6 +138,14 @@ __device__ __forceinline__ void dma16_sa(uint32_t off, const void* sbase, uint32
                : "memory", "m0");
 }
 
+// 4 bytes per lane: lane l lands at lds_addr + 4 l
+__device__ __forceinline__ void dma4_sa(uint32_t off, const void* sbase, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+               :
+               : "v"(off), "s"(sbase), "s"(lds_addr)
+               : "memory", "m0");
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt in bits
@@ -149,11 +157,6 @@ typedef __attribute__((ext_vector_type(8))) int32_t i32x8;
 
 // Scalar loads issued by hand: the results are uniform, travel outside the vector-memory queue
 // (so waiting for them never drains tile requests) and are only read after the explicit wait.
-__device__ __forceinline__ i32x8 sload8(const void* ptr) {
-  i32x8 v;
-  asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
-  return v;
-}
 __device__ __forceinline__ int32_t sload1(const void* ptr) {
   int32_t v;
   asm volatile("s_load_dword %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
     if (computes) {
       const int j0 = kt * kBN;
       typedef __attribute__((address_space(3))) const cs::u32x4 lds_u32x4;
-      auto k_frag = [&](int st, int kb) {
+      auto k_frag = [&](int st, int kb) __attribute__((always_inline)) {
         return __builtin_bit_cast(bf16x8, reinterpret_cast<lds_u32x4*>(static_cast<uintptr_t>(k_addr[st] + stage_off))[kb * 32 * D * 2 / 16]);
       };
       f32x16 sacc[2];
@@ -539,14 +542,12 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 // decreasing key-range length.  The plan depends only on cu_q and q_pos, so one plan serves
 // every decoder layer of a step.
 //
-// The attention kernel is persistent: workgroup b serves XCD b % 8 (workgroups are dealt to XCDs
-// round robin by the hardware) and takes the items at positions j, 2S-1-j, 2S+j, ... of that list
-// (j = b / 8, S workgroups per XCD): with a sorted list this alternation evens out the totals
-// without any run-time queue.  Its K/V tile requests run one tile ahead of the computation ACROSS
-// item boundaries, item descriptors and cache-block ids arrive through scalar loads issued a tile
-// ahead of their use, and the Q rows of the next item are requested before the finished item is
-// normalised and stored, so that the per-item latencies (descriptor -> block table -> first tile)
-// that dominate short key sweeps are paid once per workgroup instead of once per item.
+// The attention kernel is persistent: workgroup b serves XCD b % 8 (workgroups are dealt to XCDs round robin by the
+// hardware) and follows its chain of items.  Where two items that follow each other are row tiles of one sweep and
+// begin at the same key tile, it takes them as ONE job of 256 rows: every K/V tile that it fetches, and every fragment
+// that a wave reads from LDS, then serves twice the rows (see window_attn_bf16_stream_kernel).  The plan makes
+// chains of such units: two neighbouring row tiles of a stream counted from its end, or, of a pair whose row tiles go
+// to all XCDs, two that the same XCD takes.
 
 // Item descriptor: 8 ints.  [0] first query token of the stream, [1] rows of the stream (tokens x
 // heads per kv group), [2] first row of the tile, [3] kv head | stream << 8, [4] highest visible
@@ -557,8 +558,9 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 // then one 32-int entry per workgroup j of XCD x at [32 + 32 (64 x + j)]: [0..2] its first three
 // items (-1: none), [3] cache block of its first item's frontier, [4..7] cache blocks of its first
 // tile request (one per wave), [8..15] a copy of its first item's descriptor, [16] its item count.
-// With the entry a workgroup can send its first tile request after ONE dependent load.
-constexpr int kSlotsPerXcd = 64;      // persistent workgroups per XCD: 32 CUs x 2
+// Entries from kWorkgroupsPerXcd on name no item.
+constexpr int kSlotsPerXcd = 64;      // header entries per XCD
+constexpr int kWorkgroupsPerXcd = 32; // persistent workgroups per XCD: one per CU
 constexpr int kHdrEndItem = 16, kHdrHeads = 32;
 constexpr int kHdrEntryInts = 32;
 constexpr int kHdrStatus = 14;        // status word of the fused launch's launch-wide wait
@@ -568,7 +570,10 @@ constexpr int kSyncGroups = 16, kSyncPitch = 64;
 constexpr int kHdrSyncBase = (kHdrHeads + kHdrEntryInts * 8 * kSlotsPerXcd + kSyncPitch - 1) / kSyncPitch * kSyncPitch;
 constexpr int kSyncInts = (kSyncGroups + 2) * kSyncPitch;
 constexpr int kPlanHeaderInts = kHdrSyncBase + kSyncInts;
-constexpr int kItemFixedCostHalves = 3;  // per-item overhead in half key tiles, for the planner's balance
+// What a job costs besides its key tiles, in half tiles, for the planner's balance: measured 8,300 cycles (results of the
+// job before, queries, first scores) beside 1,600 for a half tile.  3 instead: 2,100 tokens over 17,600 keys 258 against
+// 244 us a layer, over 6,000 keys 111 against 104.
+constexpr int kItemFixedCostHalves = 5;
 constexpr int kPlanThreads = 1024;
 constexpr int kSortMax = 2048;        // streams sorted by work in LDS; beyond, stream order is kept
 
@@ -578,15 +583,17 @@ struct PlanParams {
   const int32_t* __restrict__ block_table;
   const int32_t* __restrict__ kv_len;
   int32_t max_blocks;
-  int32_t n_streams, group, n_kv_heads, chunk_tiles, max_splits, max_tiles, r_cap, bm, n_slots, hist_pitch;   // n_slots: workgroups per XCD
+  int32_t n_streams, group, n_kv_heads, max_tiles, r_cap, bm, n_slots, hist_pitch;   // n_slots: workgroups per XCD
   int32_t* header;      // [kPlanHeaderInts]
   int32_t* items;       // [items_cap][8]
   int32_t* rt_desc;     // [r_cap * n_kv_heads][8]: q0, rows_total, r_tile, kvh, n_split
   int32_t* st_toff;     // [n_streams + 1] first row tile of each stream
+  int32_t* st_uoff;     // [n_streams] first unit of each stream
   int32_t* st_work;     // [n_streams] key tiles summed over the stream's row tiles
   int32_t* st_rank;     // [n_streams] rank by decreasing work
   int32_t* rt_stream;   // [r_cap]
   int32_t* rt_wgmax;    // [r_cap]
+  int32_t* un_head;     // [r_cap] first row tile of each unit
   int32_t* hist;        // [8][hist_pitch] items per (XCD, bucket), then list cursors
   int32_t span;         // 1: sweeps are cut into contiguous spans of equal cost (few, long sweeps)
   int32_t pref_pitch;   // ints per XCD in sw_pref
@@ -632,22 +639,32 @@ __device__ __forceinline__ int plan_xcd_of_pair(int pair) {
 // share.  Here every XCD gets every eighth sweep (sweep = row tile * kv heads + kv head, so with
 // four or eight kv heads an XCD serves one kv head), lays its sweeps end to end, and the sequence
 // is cut into one contiguous span per workgroup, of equal COST: 2 n_kt + kItemFixedCostHalves per
-// sweep, in half key tiles, the second workgroup of a CU (slots 32..63) getting 3/4 of the first
-// one's share because the issue arbiter serves it less often.  A sweep that a cut crosses becomes
+// sweep, in half key tiles.  A sweep is that of a unit of two row tiles, the longer one's; the shorter one
+// takes part as far as it goes.  A sweep that a cut crosses becomes
 // several items whose partial results the merge kernel combines; cuts closer than kMinPieceTiles to
 // a sweep's end move onto it.  Items of a workgroup are consecutive in the list, pieces of a sweep
 // are consecutive too, and the position of an item in the list also names its partial-result slot.
 constexpr int kMinSpanTiles = 3;     // fewer workgroups are used rather than give one less than this
 constexpr int kMinPieceTiles = 2;
-constexpr int kSpanWeightFirst = 4, kSpanWeightSecond = 3;
 
 constexpr int kSpanPrefInLds = 8 * 136;   // the span plan runs with fewer than 1,024 sweeps: at most 130 ints per XCD
 
-__device__ void plan_spans(const PlanParams& pp, int n_rt, int* s_wave, int (*s_cut)[kSlotsPerXcd + 1], int* s_pref) {
+// What a unit's items need to know: first query token, rows of the stream, first row and stream of its first row tile, the
+// frontiers of its two (-1: there is no second).
+struct PlanUnit { int q0, rows, r_tile, stream, wg_max, wg_max2; };
+constexpr int kSpanUnits = 1024;         // the span plan runs with fewer than 1,024 row tiles
+
+__device__ void plan_spans(const PlanParams& pp, int n_rt, int n_un, int* s_wave, int (*s_cut)[kSlotsPerXcd + 1], int* s_pref, PlanUnit* s_unit) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int n_kv = pp.n_kv_heads;
-  const int n_sw = n_rt * n_kv;
-  auto sweep_tiles = [&](int sw) { return max(pp.rt_wgmax[sw / n_kv], 0) / kBN + 1; };
+  const int n_sw = n_un * n_kv;
+  auto tiles_of = [&](int wg_max) { return wg_max < 0 ? 0 : wg_max / kBN + 1; };
+  for (int u = tid; u < n_un; u += kPlanThreads) {
+    const int r = pp.un_head[u], st = pp.rt_stream[r], t = r - pp.st_toff[st];
+    s_unit[u] = PlanUnit{pp.cu_q[st], plan_stream_rows(pp, st), t * pp.bm, st, pp.rt_wgmax[r], t > 0 ? pp.rt_wgmax[r - 1] : -1};
+  }
+  __syncthreads();
+  auto sweep_tiles = [&](int sw) { return tiles_of(s_unit[sw / n_kv].wg_max); };
   // ---- cost prefix of every XCD's sweeps (one wave per XCD)
   if (w < 8) {
     int32_t* pref = pp.sw_pref + w * pp.pref_pitch;
@@ -693,16 +710,15 @@ __device__ void plan_spans(const PlanParams& pp, int n_rt, int* s_wave, int (*s_
   };
   // ---- cuts: thread (x, j) places the start of workgroup j's span
   const int x = tid >> 6, j = tid & 63;          // threads 0..511: one per (XCD, workgroup)
-  const int n_wg = min(pp.n_slots, kSlotsPerXcd);
+  const int n_wg = pp.n_slots;
   if (tid < 512) {
     const int n_x = n_of(x);
     const int total_tiles = n_x > 0 ? tile_pref(x, n_x) : 0;
     const int total_cost = n_x > 0 ? cost_pref(x, n_x) : 0;
     const int spans = total_tiles > 0 ? max(1, min(n_wg, total_tiles / kMinSpanTiles)) : 0;
-    auto weight_before = [&](int k) { return k <= 32 ? kSpanWeightFirst * k : kSpanWeightFirst * 32 + kSpanWeightSecond * (k - 32); };
     int cut = total_tiles;
     if (j < spans) {
-      const int64_t c = static_cast<int64_t>(total_cost) * weight_before(j) / weight_before(spans);   // cost position
+      const int64_t c = static_cast<int64_t>(total_cost) * j / spans;   // cost position
       int lo = 0, hi = n_x;                       // largest i with cost_pref(i) <= c
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -729,53 +745,77 @@ __device__ void plan_spans(const PlanParams& pp, int n_rt, int* s_wave, int (*s_
       i_hi = sweep_at_tile(x, hi_t - 1);
     }
   }
-  const int count = i_hi - i_lo + 1;
+  // the piece [kb, ke) of sweep i that belongs to this workgroup, and the key tiles of its second row tile (0: none)
+  auto piece = [&](int i, int& kb, int& ke, int& n_kt, int& n_kt2) {
+    const int begin = tile_pref(x, i);
+    n_kt = tile_pref(x, i + 1) - begin;
+    kb = max(lo_t, begin) - begin;
+    ke = min(hi_t, begin + n_kt) - begin;
+    n_kt2 = tiles_of(s_unit[(8 * i + x) / n_kv].wg_max2);
+  };
+  int count = 0;
+  for (int i = i_lo; i <= i_hi; ++i) {
+    int kb, ke, n_kt, n_kt2;
+    piece(i, kb, ke, n_kt, n_kt2);
+    count += kb < n_kt2 ? 2 : 1;
+  }
   int total_items;
   const int first = plan_block_scan(tid < 512 ? count : 0, s_wave, total_items);
   if (tid < 512 && j == 0) pp.header[x] = first;
   if (tid == 0) {
     pp.header[8] = total_items;
-    pp.header[9] = n_sw;
+    pp.header[9] = n_rt * n_kv;
     for (int i = 10; i < kHdrHeads; ++i) pp.header[i] = 0;
     pp.header[kHdrEndItem + 4] = -1;                    // end item: no key tiles, nothing visible
     pp.header[kHdrEndItem + 6] = -1;
     pp.header[kHdrEndItem + 7] = -1;
   }
   for (int i = tid; i < kSyncInts; i += kPlanThreads) pp.header[kHdrSyncBase + i] = 0;
-  for (int i = n_sw + tid; i < pp.r_cap * n_kv; i += kPlanThreads)
+  for (int i = n_rt * n_kv + tid; i < pp.r_cap * n_kv; i += kPlanThreads)
     pp.rt_desc[static_cast<int64_t>(i) * 8 + 4] = 0;
   if (tid >= 512) return;
   // ---- write the items of workgroup (x, j) and its header entry
   int32_t d_first[8] = {0, 0, 0, 0, -1, 0, -1, -1};     // the end item
+  int pos = first;
   for (int i = i_lo; i <= i_hi; ++i) {
     const int sw = 8 * i + x;
-    const int r = sw / n_kv, kvh = sw - r * n_kv;
-    const int s = pp.rt_stream[r];
-    const int t = r - pp.st_toff[s];
-    const int q0 = pp.cu_q[s];
-    const int rows = plan_stream_rows(pp, s);
-    const int wg_max = pp.rt_wgmax[r];
-    const int begin = tile_pref(x, i), n_kt = tile_pref(x, i + 1) - begin;
-    const int kb = max(lo_t, begin) - begin, ke = min(hi_t, begin + n_kt) - begin;
-    const int pos = first + (i - i_lo);
-    const bool split = kb > 0 || ke < n_kt;
-    int32_t d[8] = {q0, rows, t * pp.bm, kvh | (s << 8), wg_max, kb | (ke << 16), i < i_hi ? pos + 1 : -1,
-                    split ? pos * pp.bm : -1};
-    int32_t* it = pp.items + static_cast<int64_t>(pos) * 8;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) it[k] = d[k];
-    if (i == i_lo) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) d_first[k] = d[k];
-    }
-    if (kb == 0) {                                       // the sweep's first piece describes it to the merge kernel
-      int pieces = 1;
-      for (int k = 1; k < kSlotsPerXcd; ++k) {
+    const int u = sw / n_kv, kvh = sw - u * n_kv;
+    const PlanUnit un = s_unit[u];
+    const int s = un.stream;
+    int kb, ke, n_kt, n_kt2;
+    piece(i, kb, ke, n_kt, n_kt2);
+    const bool two = kb < n_kt2;
+    int pieces = 1, pieces2 = 1;                         // of the sweep's two row tiles
+    if (kb == 0 && ke < n_kt) {
+      const int begin = tile_pref(x, i);
+      for (int k = j + 1; k < kSlotsPerXcd; ++k) {
         const int c = s_cut[x][k];
-        pieces += (c > begin && c < begin + n_kt && c != s_cut[x][k - 1]) ? 1 : 0;
+        if (c >= begin + n_kt) break;
+        if (c <= begin || c == s_cut[x][k - 1]) continue;
+        ++pieces;
+        pieces2 += c < begin + n_kt2 ? 1 : 0;
       }
-      int32_t* rd = pp.rt_desc + static_cast<int64_t>(sw) * 8;
-      rd[0] = q0; rd[1] = rows; rd[2] = t * pp.bm; rd[3] = kvh; rd[4] = pieces; rd[5] = pos;
+    }
+    for (int second = 0; second < (two ? 2 : 1); ++second) {
+      const int n_mine = second ? n_kt2 : n_kt, ke_mine = min(ke, n_mine);
+      const bool split = kb > 0 || ke_mine < n_mine;
+      int32_t d[8] = {un.q0, un.rows, un.r_tile - second * pp.bm, kvh | (s << 8), second ? un.wg_max2 : un.wg_max, kb | (ke_mine << 16),
+                      i < i_hi || second < (two ? 1 : 0) ? pos + 1 : -1, split ? pos * pp.bm : -1};
+      int32_t* it = pp.items + static_cast<int64_t>(pos) * 8;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) it[k] = d[k];
+      if (pos == first) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) d_first[k] = d[k];
+      }
+      // the sweep's first piece describes it to the merge kernel: piece c of either row tile stands at the list
+      // position [5] + c + min(c, [6]), since the pieces of the two alternate until the second's are used up
+      if (kb == 0) {
+        int32_t* rd = pp.rt_desc + static_cast<int64_t>((pp.un_head[u] - second) * n_kv + kvh) * 8;
+        rd[0] = un.q0; rd[1] = un.rows; rd[2] = un.r_tile - second * pp.bm; rd[3] = kvh; rd[4] = second ? pieces2 : pieces; rd[5] = pos;
+        rd[6] = n_kt2 > 0 ? pieces2 : 0;
+      }
+      ++pos;
     }
   }
   int32_t* hd = pp.header + kHdrHeads + kHdrEntryInts * (x * kSlotsPerXcd + j);
@@ -798,11 +838,14 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
   __shared__ int s_list_off[9];
   __shared__ int s_left_tiles[8], s_left_end[8];   // pairs left over by whole rounds: row tiles; last row tile + pair
   __shared__ int s_by_rank[8][64];      // deal: lane (and length) of the item of each rank, per XCD
+  __shared__ PlanUnit s_unit[kSpanUnits];
+  __shared__ int s_units[8];            // units in each XCD's list
   __shared__ int s_cut[8][kSlotsPerXcd + 1];   // span plan: first tile position of every workgroup's span
   const int tid = threadIdx.x;
   const int hist_pitch = pp.hist_pitch;
 
   // ---- clear counters; row tiles per stream
+  if (tid < 8) s_units[tid] = 0;
   for (int i = tid; i < 8 * hist_pitch; i += kPlanThreads) pp.hist[i] = 0;
   int carry = 0;
   for (int s0 = 0; s0 < pp.n_streams; s0 += kPlanThreads) {
@@ -820,6 +863,16 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
   }
   const int n_rt = carry;                // row tiles per kv head
   if (tid == 0) pp.st_toff[pp.n_streams] = n_rt;
+  // units: two neighbouring row tiles of a stream, counted from its end (an odd one out is the stream's first)
+  int n_un = 0;
+  for (int s0 = 0; s0 < pp.n_streams; s0 += kPlanThreads) {
+    const int s = s0 + tid;
+    const int tiles = s < pp.n_streams ? (plan_stream_rows(pp, s) + pp.bm - 1) / pp.bm : 0;
+    int total;
+    const int excl = plan_block_scan((tiles + 1) >> 1, s_wave, total);
+    if (s < pp.n_streams) pp.st_uoff[s] = n_un + excl;
+    n_un += total;
+  }
   __threadfence_block();
   __syncthreads();
 
@@ -839,13 +892,15 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
     const int wg_max = max(0, min(pp.q_pos[q0 + last_row / pp.group], min(pp.kv_len[s], pp.max_blocks * CS_KV_BLOCK) - 1));
     pp.rt_stream[r] = s;
     pp.rt_wgmax[r] = wg_max;
+    const int tiles_s = pp.st_toff[s + 1] - pp.st_toff[s];
+    if (((tiles_s - 1 - t) & 1) == 0) pp.un_head[pp.st_uoff[s] + (t >> 1)] = r;
     atomicAdd(&pp.st_work[s], max(wg_max, 0) / kBN + 1);
   }
   __threadfence_block();
   __syncthreads();
 
   if (pp.span) {
-    plan_spans(pp, n_rt, s_wave, s_cut, reinterpret_cast<int*>(s_key));    // s_key is unused on this route
+    plan_spans(pp, n_rt, n_un, s_wave, s_cut, reinterpret_cast<int*>(s_key), s_unit);    // s_key is unused on this route
     return;
   }
 
@@ -909,27 +964,23 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
     }
     return at;
   };
-  auto place = [&](int r, int s, int kvh, int split, int len, int& bucket) {
+  auto place = [&](int r, int s, int kvh, int& bucket) {
     if (grouped) {
       const int pair = pp.st_rank[s] * pp.n_kv_heads + kvh;
       bucket = pair >> 3;
       return pair < whole_pairs ? plan_xcd_of_pair(pair) : (r + pair) & 7;
     }
-    bucket = pp.max_tiles + 1 - min(len, pp.max_tiles + 1);
-    return (r * pp.n_kv_heads + kvh + split) & 7;
+    // (both row tiles of a unit by the longer one)
+    const int head = r + ((pp.st_toff[s + 1] - 1 - r) & 1);
+    bucket = pp.max_tiles + 1 - min(max(pp.rt_wgmax[head], 0) / kBN + 1, pp.max_tiles + 1);
+    return ((pp.st_uoff[s] + ((head - pp.st_toff[s]) >> 1)) * pp.n_kv_heads + kvh) & 7;
   };
-  for (int r = tid; r < n_rt; r += kPlanThreads) {
-    const int s = pp.rt_stream[r];
-    const int n_kt = max(pp.rt_wgmax[r], 0) / kBN + 1;
-    const int n_split = pp.max_splits > 1 ? min((n_kt + pp.chunk_tiles - 1) / pp.chunk_tiles, pp.max_splits) : 1;
-    for (int kvh = 0; kvh < pp.n_kv_heads; ++kvh)
-      for (int c = 0; c < n_split; ++c) {
-        const int len = n_split > 1 ? min(pp.chunk_tiles, n_kt - c * pp.chunk_tiles) : n_kt;
-        int bucket;
-        const int x = place(r, s, kvh, c, len, bucket);
-        atomicAdd(&pp.hist[x * hist_pitch + bucket], 1);
-      }
-  }
+  for (int r = tid; r < n_rt; r += kPlanThreads)
+    for (int kvh = 0; kvh < pp.n_kv_heads; ++kvh) {
+      int bucket;
+      const int x = place(r, pp.rt_stream[r], kvh, bucket);
+      atomicAdd(&pp.hist[x * hist_pitch + bucket], 1);
+    }
   __threadfence_block();
   __syncthreads();
 
@@ -978,32 +1029,36 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
     const int t = r - pp.st_toff[s];
     const int q0 = pp.cu_q[s];
     const int rows = plan_stream_rows(pp, s);
-    const int tiles_s = (rows + pp.bm - 1) / pp.bm;
-    const int wg_max = pp.rt_wgmax[r];
-    const int n_kt = max(wg_max, 0) / kBN + 1;
-    const int n_split = pp.max_splits > 1 ? min((n_kt + pp.chunk_tiles - 1) / pp.chunk_tiles, pp.max_splits) : 1;
+    const int level = pp.st_toff[s + 1] - 1 - r;         // row tiles from the stream's end
     for (int kvh = 0; kvh < pp.n_kv_heads; ++kvh) {
-      const int rt_id = r * pp.n_kv_heads + kvh;
-      int32_t* rd = pp.rt_desc + static_cast<int64_t>(rt_id) * 8;
-      rd[0] = q0; rd[1] = rows; rd[2] = t * pp.bm; rd[3] = kvh; rd[4] = n_split;
-      for (int c = 0; c < n_split; ++c) {
-        const int kb = n_split > 1 ? c * pp.chunk_tiles : 0;
-        const int ke = n_split > 1 ? min(n_kt, kb + pp.chunk_tiles) : n_kt;
-        int bucket;
-        const int x = place(r, s, kvh, c, ke - kb, bucket);
-        int* cursor = &pp.hist[x * hist_pitch + bucket];
-        // a pair's bucket holds its row tiles only, the last bucket those of the pairs left over:
-        // the longest (last) row tile goes first; where sweeps are split or buckets are shared by
-        // length, arrival order decides
-        const bool in_order = grouped && pp.max_splits == 1;
-        const int pair = pp.st_rank[s] * pp.n_kv_heads + kvh, level = tiles_s - 1 - t;
-        const int within = !in_order ? atomicAdd(cursor, 1) : pair < whole_pairs ? level : left_before(pair, level, x);
-        const int start = in_order ? __hip_atomic_load(cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-        const int pos = s_list_off[x] + start + within;
-        int32_t* it = pp.items + static_cast<int64_t>(pos) * 8;
-        it[0] = q0; it[1] = rows; it[2] = t * pp.bm; it[3] = kvh | (s << 8); it[4] = wg_max;
-        it[5] = kb | (ke << 16); it[6] = -1;
-        it[7] = n_split > 1 ? (rt_id * pp.max_splits + c) * pp.bm : -1;
+      int32_t* rd = pp.rt_desc + static_cast<int64_t>(r * pp.n_kv_heads + kvh) * 8;
+      rd[0] = q0; rd[1] = rows; rd[2] = t * pp.bm; rd[3] = kvh; rd[4] = 1;
+      if (!grouped && (level & 1)) continue;             // written with the other row tile of its unit
+      int bucket;
+      const int x = place(r, s, kvh, bucket);
+      int* cursor = &pp.hist[x * hist_pitch + bucket];
+      // a pair's bucket holds its row tiles only, the last bucket those of the pairs left over: the longest (last)
+      // row tile goes first; where buckets are shared by length, arrival order decides
+      const int n_here = !grouped && t > 0 ? 2 : 1;
+      const int pair = pp.st_rank[s] * pp.n_kv_heads + kvh;
+      const int within = !grouped ? atomicAdd(cursor, n_here) : pair < whole_pairs ? level : left_before(pair, level, x);
+      const int start = grouped ? __hip_atomic_load(cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+      const int pos = s_list_off[x] + start + within;
+      // units: the first item of one says where its second is ([6], for the deal below: -1 not a first one, -2 alone,
+      // -3 - i with item i).  Of a whole pair two neighbours make a unit; of a pair left over the row tiles that this
+      // XCD takes, two by two
+      int unit = -1;
+      if (!grouped || pair < whole_pairs) {
+        if ((level & 1) == 0) unit = t > 0 ? -4 - pos : -2;
+      } else if ((level & 8) == 0) {
+        unit = t >= 8 ? -3 - (s_list_off[x] + start + left_before(pair, level + 8, x)) : -2;
+      }
+      if (unit < -1) atomicAdd(&s_units[x], 1);
+      for (int second = 0; second < n_here; ++second) {
+        const int wg_max = pp.rt_wgmax[r - second];
+        int32_t* it = pp.items + static_cast<int64_t>(pos + second) * 8;
+        it[0] = q0; it[1] = rows; it[2] = (t - second) * pp.bm; it[3] = kvh | (s << 8); it[4] = wg_max;
+        it[5] = (max(wg_max, 0) / kBN + 1) << 16; it[6] = second ? -1 : unit; it[7] = -1;
       }
     }
   }
@@ -1020,24 +1075,28 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
     const int w = tid >> 6, lane = tid & 63;
     if (w < 8) {
       const int begin = s_list_off[w], end = s_list_off[w + 1];
-      const int n_wg = min(pp.n_slots, 64);
+      const int n_wg = pp.n_slots;
       int load = lane < n_wg ? 0 : 0x7fffffff;          // half key tiles; lanes beyond the grid rank last
       int last = -1, first3[3] = {-1, -1, -1}, taken = 0;
+      auto field = [&](int i, int k) {
+        return __hip_atomic_load(&pp.items[static_cast<int64_t>(i) * 8 + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      };
       // (a pair-ordered list that is not a whole number of batches starts with the short batch:
       // the full batches that follow even the loads out again, which a short batch at the end
       // cannot.  A list ordered by length keeps its batches aligned instead: workgroups that start
       // equal-length items together sweep the same key ranges together and share them in L2,
       // which is worth more there: 6 % on the dense long-window case.)
-      int n_batch = grouped ? (end - begin) % n_wg : 0;
-      if (n_batch == 0) n_batch = n_wg;
-      for (int base = begin; base < end; base += n_batch, n_batch = n_wg) {
-        const int n_here = min(n_batch, end - base);      // the last batch of a length-ordered list may be short
-        int len = -1;                                     // lanes without an item rank last
-        if (lane < n_here) {
-          const int kbe = __hip_atomic_load(&pp.items[static_cast<int64_t>(base + lane) * 8 + 5], __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
-          len = (kbe >> 16) - (kbe & 0xffff);
-        }
+      int n_batch = grouped && s_units[w] % n_wg ? s_units[w] % n_wg : n_wg;
+      for (int base = begin; base < end; n_batch = n_wg) {
+        // of whole pairs the next n_batch units lie within the next 64 items
+        const int unit = base + lane < end ? field(base + lane, 6) : -1, keys = base + lane < end ? field(base + lane, 5) : 0;
+        const bool first = unit < -1;
+        const int second = unit < -2 ? -3 - unit : -1;
+        const unsigned long long firsts = __ballot(first);
+        const int rank = __popcll(firsts & ((1ull << lane) - 1)), n_seen = __popcll(firsts), n_here = min(n_seen, n_batch);
+        const unsigned long long stop = __ballot(first && rank == n_batch);
+        int len = -1;                                     // lanes without a unit rank last
+        if (first && rank < n_batch) len = keys >> 16;
         int item_rank = 0, load_rank = 0;                 // by decreasing length / increasing load, ties by lane
 #pragma unroll 8
         for (int j = 0; j < 64; ++j) {
@@ -1047,19 +1106,23 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
         }
         s_by_rank[w][item_rank] = lane | (len << 8);
         __builtin_amdgcn_wave_barrier();
+        const int got = load_rank < n_here ? s_by_rank[w][load_rank] : 0;
+        const int got_second = __shfl(second, got & 63);
         if (load_rank < n_here) {
-          const int got = s_by_rank[w][load_rank];
-          const int idx = base + (got & 255);
-          if (last >= 0) pp.items[static_cast<int64_t>(last) * 8 + 6] = idx;
-          if (taken == 0) first3[0] = idx;
-          if (taken == 1) first3[1] = idx;
-          if (taken == 2) first3[2] = idx;
-          ++taken;
-          last = idx;
-          load += (2 * (got >> 8) + kItemFixedCostHalves) * (lane >= 32 ? kSpanWeightFirst : kSpanWeightSecond);
+          for (int k = 0; k < (got_second >= 0 ? 2 : 1); ++k, ++taken) {
+            const int idx = k ? got_second : base + (got & 63);
+            if (last >= 0) pp.items[static_cast<int64_t>(last) * 8 + 6] = idx;
+            if (taken == 0) first3[0] = idx;
+            if (taken == 1) first3[1] = idx;
+            if (taken == 2) first3[2] = idx;
+            last = idx;
+          }
+          load += 2 * (got >> 8) + kItemFixedCostHalves;
         }
         __builtin_amdgcn_wave_barrier();
+        base = stop ? base + __ffsll(stop) - 1 : min(base + 64, end);
       }
+      if (last >= 0) pp.items[static_cast<int64_t>(last) * 8 + 6] = -1;
       if (lane < kSlotsPerXcd) {
         int32_t* hd = pp.header + kHdrHeads + kHdrEntryInts * (w * kSlotsPerXcd + lane);
         int32_t d[8] = {0, 0, 0, 0, -1, 0, -1, -1};       // the end item
@@ -1083,11 +1146,6 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
 }
 
 
-// RB = 32-row blocks per wave.  RB = 1 is what runs: 128-row items, two workgroups per CU (two
-// waves per SIMD hide each other's latencies).  RB = 2 (256-row items, one workgroup per CU with
-// the whole register file, every K and V fragment read from LDS feeding two MFMAs) passes the same
-// tests but measured 15-25 % slower as it stands: with one wave per SIMD nothing hides the softmax
-// arithmetic unless the loop is software-pipelined by hand, and half the scores land in AGPRs.
 // 16-byte store that is written through the XCD's L2 to memory (agent scope), the cache policy an
 // agent-scope atomic store carries: its acknowledgement (vmcnt) comes when the other XCDs can read
 // the bytes, so a wait on vmcnt stands in for an L2 write-back.  The s_nop belongs to the store: a
@@ -1156,17 +1214,70 @@ __device__ __forceinline__ void launch_barrier(int32_t* sync, int32_t* status, i
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-template <int RB, bool FUSE>
-__global__ __launch_bounds__(256, RB == 1 ? 2 : 1) void window_attn_bf16_stream_kernel(AttnParams p) {
+// ---- loads of data that does not change during the launch: through the constant address space they are scalar loads
+typedef const __attribute__((address_space(4))) i32x8 const_i32x8;
+__device__ __forceinline__ i32x8 const_load8(const int32_t* at) { return *(const_i32x8*)reinterpret_cast<uintptr_t>(at); }
+// A scalar load that the compiler knows of turns every wait for an LDS read into a wait for all: it is waited for on the spot.
+__device__ __forceinline__ void wait_scalar() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+
+// f(Begin), f(Begin + 1), ... f(End - 1) with the index as a compile-time constant.
+template <int Begin, int End, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (Begin < End) {
+    f(std::integral_constant<int, Begin>{});
+    unrolled<Begin + 1, End>(f);
+  }
+}
+
+// One matrix instruction that accumulates in the accumulation registers, spelled out so that they stay there: the
+// compiler does not know it for one, so whoever reads the accumulators waits first (mfma_settle).
+__device__ __forceinline__ void mfma_acc(f32x16& acc, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_settle(f32x16 (&o)[2][4]) {
+  asm volatile("s_nop 15\n\ts_nop 7"
+               : "+a"(o[0][0]), "+a"(o[0][1]), "+a"(o[0][2]), "+a"(o[0][3]), "+a"(o[1][0]), "+a"(o[1][1]), "+a"(o[1][2]), "+a"(o[1][3]));
+}
+
+// The persistent kernel: 4 waves of 64 rows (two blocks of 32), one workgroup per CU, one wave per SIMD.
+//
+// What bounds it: power.  The matrix cores toggle enough for the device to run at 1.6-2.1 GHz instead of 2.4, so
+// cycles saved by overlap alone come back as a lower clock, and what counts is work per matrix instruction.  Timing
+// builds of the kernel before (32 rows a wave, 128 a workgroup, two workgroups per CU) with half the LDS reads, with
+// half the tile requests and with both left out ran 13, 8 and 20 % shorter at level cycles.  Hence 64 rows a wave
+// (each K and V fragment read from LDS feeds two matrix instructions) and 256 a workgroup (each tile is fetched once
+// for twice the rows).  The price is that no second wave hides anything: a half tile (32 keys) is laid out by hand as
+// 32 slots of one matrix instruction, 16 for the scores of the NEXT half tile and 16 for P V of this one, and between
+// them go the softmax of this half tile, the LDS reads two to three slots ahead and the next requests.  1,190 cycles a half
+// tile of 1,024 cycles of matrix instructions, 1,400 with the tile's barrier; the kernel before took 3,530 for 64 rows and 64 keys.
+// * Registers: O (128) and Q (64) live in the accumulation registers, scores and weights in the others; the matrix
+//   instructions of P V are spelled out so that O stays there.
+// * Row sums: v_dot2 waits for the matrix pipe to drain (48 cycles instead of 32 per matrix instruction when one
+//   follows each, and a second wave's stall it too); the 4x4 matrix instruction with ones sums the same rounded weights.
+// * Requests run three slots ahead through four LDS stages of 32 KiB; queries come by the same way.  A tile takes one
+//   barrier.  Sweeps inside a job change one index per slot; everything else (frontier tile, next job's queries, next
+//   job) is set up when the walk enters it.
+// * Frontiers: rows that see nothing more of a sweep get an infinite reference maximum once; only half tiles that hold
+//   some row's frontier are masked score by score.
+// * The scores of a job's first half tiles are formed ahead of its sweep, those of the second again inside it: 2 % of a sweep
+//   of 13 tiles, but the reference is then the maximum over 64 keys.  Over 32 the largest weight of a row is less often
+//   the exact one: error against 64 bits 2.130e-3 instead of 2.111e-3 (32 streams), 2.161 instead of 2.142 (64).
+// us a layer, two builds in turn (32 rows a wave / this one): 64 streams of 560 keys, 32/8 heads 278 / 263; 32 streams of
+// 860 keys, 28/4 heads 150 / 140; 2,100 tokens over 6,000 keys 118 / 105, over 17,600 keys 273 / 242 (0.94 PFLOP/s).
+template <bool FUSE>
+__global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnParams p) {
+  constexpr int RB = 2;                 // 32-row blocks per wave
   constexpr int WROWS = 32 * RB;        // rows per wave
   constexpr int D = 128;
   constexpr int STEPS = D / 16, DB = D / 32;
   constexpr int TILE = kBN * D;         // elements of one K (or V) tile: 16 KiB, unpadded
   constexpr int IPW = 4;                // 1-KiB DMA instructions per wave, per tile, per tensor
+  constexpr int STAGES = 4;
+  constexpr int kStageBytes = 2 * TILE * 2, kHalfBytes = 32 * D * 2;
 
-  __shared__ __attribute__((aligned(1024))) uint16_t sK[2][TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t sV[2][TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t s_sink[4][512];   // see request_part
+  __shared__ __attribute__((aligned(1024))) uint16_t s_kv[STAGES][2][TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t s_sink[4][512];
+  __shared__ int32_t s_pos[2][4][64];   // query positions of the waves' rows, every other job
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1197,448 +1308,554 @@ __global__ __launch_bounds__(256, RB == 1 ? 2 : 1) void window_attn_bf16_stream_
     launch_barrier(p.ws_sync, p.ws_status, static_cast<int>(gridDim.x));
   }
 
-  // ---- this workgroup's items: a chain through the `next` field of the descriptors, dealt by the
-  //      planning kernel; three descriptors of look-ahead are kept loaded
+  // ---- this workgroup's items: a chain through the `next` field of the descriptors, dealt by the planning kernel
   const int xcd = blockIdx.x & 7, slot_j = blockIdx.x >> 3;
   auto item_at = [&](int idx) -> const int32_t* {
     return idx >= 0 ? p.ws_items + static_cast<int64_t>(idx) * 8 : p.ws_plan + kHdrEndItem;
   };
   const int32_t* entry = p.ws_plan + kHdrHeads + kHdrEntryInts * (xcd * kSlotsPerXcd + slot_j);
-  i32x8 e0 = sload8(entry), d0 = sload8(entry + 8);
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(e0), "+s"(d0));
-  if ((d0[5] >> 16) == 0) return;       // nothing for this workgroup
-  i32x8 d1 = sload8(item_at(e0[1])), d2 = sload8(item_at(e0[2]));   // waited for after the first tile request
-  int seq0 = 0;                         // d0 is the seq0-th item of this workgroup
+  const i32x8 e0 = const_load8(entry);
+  i32x8 d = const_load8(entry + 8);
+  if ((d[5] >> 16) == 0) return;        // nothing for this workgroup
 
-  // ---- constants of the lane: DMA sources inside a cache block, LDS read addresses
-  const uint16_t* kall = static_cast<const uint16_t*>(p.k);
-  const uint16_t* vall = static_cast<const uint16_t*>(p.v);
-  const int64_t blk_stride = static_cast<int64_t>(CS_KV_BLOCK) * p.stride_slot;
+  // Two items that follow each other in the chain, are row tiles of one sweep and start at the same key tile (the second
+  // no longer than the first) are taken as one job of 256 rows: waves 0-1 the second, waves 2-3 the first.
+  auto couple = [&](const i32x8& a, const i32x8& b) {
+    return a[3] == b[3] && a[0] == b[0] && (a[5] & 0xffff) == (b[5] & 0xffff) && (b[5] >> 16) > 0 && (b[5] >> 16) <= (a[5] >> 16);
+  };
+  auto mine = [&](const i32x8& a, const i32x8& b, bool both) { return wave < 2 && both ? b : a; };
+  auto takes_part = [&](bool both) { return both || wave >= 2; };
+
+  // ---- constants of the lane
+  const uint32_t blk_bytes = static_cast<uint32_t>(CS_KV_BLOCK * 2 * p.stride_slot);     // (stride_slot < 2^26: the host checks)
+  const uint32_t row_bytes = static_cast<uint32_t>(p.stride_slot * 2);
   const int l_row = lane >> 4, l_pos = lane & 15;
-  uint32_t k_off[IPW], v_off[IPW];      // byte offsets inside a cache block (the host checks the range)
-  int k_chunk[IPW], v_chunk[IPW];
+  // tile requests: instruction i of a tensor moves rows 4 i + l_row of this wave's cache block; which 16-byte chunk
+  auto k_chunk = [&](int i) __attribute__((always_inline)) { return static_cast<uint32_t>((l_pos ^ (4 * i + l_row)) * 16); };
+  auto v_chunk = [&](int i) __attribute__((always_inline)) { return static_cast<uint32_t>((l_pos ^ (4 * l_row + 2 * (i & 1))) * 16); };
+  uint32_t kv_off[2 * IPW];
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
-    const int trow = 4 * (wave * IPW + i) + l_row;          // row of the tile, 0..63
-    k_chunk[i] = l_pos ^ (trow & 15);
-    v_chunk[i] = l_pos ^ (4 * (trow & 3) + 2 * ((trow >> 2) & 1));
-    k_off[i] = static_cast<uint32_t>(((trow & 15) * p.stride_slot + k_chunk[i] * 8) * 2);
-    v_off[i] = static_cast<uint32_t>(((trow & 15) * p.stride_slot + v_chunk[i] * 8) * 2);
+    kv_off[i] = (4 * i + l_row) * row_bytes + k_chunk(i);
+    kv_off[IPW + i] = (4 * i + l_row) * row_bytes + v_chunk(i);
   }
-  int k_rd[STEPS];
+  uint32_t k_addr[STEPS], v_addr[DB];   // LDS byte addresses of this lane's fragments in the current stage
 #pragma unroll
-  for (int st = 0; st < STEPS; ++st) k_rd[st] = n * D + (((2 * st + h) ^ (n & 15)) << 3);
+  for (int st = 0; st < STEPS; ++st)
+    k_addr[st] = lds_address(&s_kv[0][0][0]) + 2 * (n * D + (((2 * st + h) ^ (n & 15)) << 3));
   const int i16 = lane & 15, gid = (lane >> 4) & 1;
   const int v_row = 4 * h + (i16 >> 2);
   const int v_swz = 4 * (v_row & 3) + 2 * (v_row >> 2);
-  int v_rd[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
-    v_rd[db] = v_row * D + (((4 * db + 2 * gid + ((i16 & 3) >> 1)) ^ v_swz) << 3) + 4 * (i16 & 1);
+    v_addr[db] = lds_address(&s_kv[0][1][0]) +
+                 2 * (v_row * D + (((4 * db + 2 * gid + ((i16 & 3) >> 1)) ^ v_swz) << 3) + 4 * (i16 & 1));
 
-  uint32_t k_addr[STEPS], v_addr[DB];   // LDS byte addresses of this lane's fragments in stage 0
-#pragma unroll
-  for (int st = 0; st < STEPS; ++st) k_addr[st] = lds_address(&sK[0][0]) + 2 * k_rd[st];
-#pragma unroll
-  for (int db = 0; db < DB; ++db) v_addr[db] = lds_address(&sV[0][0]) + 2 * v_rd[db];
-
-  // ---- a slot of the tile stream: one key tile of one item, with the cache-block ids its
-  //      request needs (this wave's quarter of the tile, and the block of the item's frontier)
-  struct Slot {
-    int kt, ke, kvh, wg_max, seq;
-    const int32_t* row;  // the stream's block-table row
-    int64_t head_off;    // element offset of the kv head inside a cache row
-    int id, last_id;
-    int live;            // an int: a bool would leave tail padding that struct copies drag through memory
+  // ---- requests run three slots ahead of the computation, across jobs, on a walk of their own along the chain.  A slot
+  // is a key tile, or 32 query rows of each wave: two of these stand ahead of a job's tiles.  Every wave fetches its own
+  // queries, the first 16 rows of a slot to its share of the K half, the others to its share of the V half.  Each slot
+  // takes a wave eight DMA instructions; past the last one they go to a sink, so that their number stays the same.
+  struct Rows { int tok0, rem0, last; };                // of a wave's first row: token and head; rows after it
+  const uint32_t group_inv = 65535u / p.group + 1;      // x * group_inv >> 16 = x / group for x < 80
+  auto rows_of = [&](const i32x8& it) __attribute__((always_inline)) {
+    const int r0 = min(it[2] + (wave & 1) * WROWS, it[1] - 1);
+    const int t0 = r0 / p.group;
+    return Rows{it[0] + t0, r0 - t0 * p.group, it[1] - 1 - r0};
   };
-  auto first_slot = [&](const i32x8& d, int seq) {
-    Slot s;
-    s.kt = d[5] & 0xffff; s.ke = d[5] >> 16; s.kvh = d[3] & 255; s.wg_max = d[4]; s.seq = seq;
-    s.row = p.block_table + static_cast<int64_t>(d[3] >> 8) * p.max_blocks;
-    s.head_off = static_cast<int64_t>(d[3] & 255) * p.stride_head;
-    s.id = 0; s.last_id = 0;
-    s.live = (d[5] >> 16) > 0 ? 1 : 0;
-    return s;
+  auto row_offset = [&](const Rows& r, int row) __attribute__((always_inline)) {       // bytes from the first row's token and the kv head's first query head; past the last row, that row again
+    const uint32_t x = r.rem0 + min(row, r.last);
+    const uint32_t t = (x * group_inv) >> 16;
+    return (t * p.n_q_heads + (x - t * p.group)) * (D * 2);
   };
-  auto successor = [&](const Slot& c) {
-    if (c.kt + 1 < c.ke) {
-      Slot s = c;
-      s.kt = c.kt + 1;
-      return s;
-    }
-    const int rel = c.seq + 1 - seq0;                       // 1 or 2
-    return first_slot(rel == 1 ? d1 : d2, c.seq + 1);
-  };
-  auto request_ids = [&](Slot& s) {
-    const int last_blk = max(s.wg_max, 0) >> 4;           // CS_KV_BLOCK = 16
-    s.id = sload1(s.row + min(s.kt * 4 + wave, last_blk));
-    s.last_id = sload1(s.row + last_blk);
-  };
-  // A tile request is 8 DMA instructions per wave (4 for K, 4 for V), each moving 1 KiB.  The
-  // memory pipeline takes them at 64 bytes per clock, so issued back to back they hold the wave
-  // for hundreds of cycles: regular tiles are issued one instruction at a time between the MFMAs
-  // of the S phase instead (request_part), with a wave-uniform base in SGPRs and the lane's
-  // constant 32-bit offset.  The S phase always issues its eight parts, so that no branch or
-  // predicate splits the block of MFMAs: when there is nothing to request (the next tile holds a
-  // frontier and went out at once, or there is no next tile) the parts re-read the current
-  // tile's cache block into a 1-KiB sink.
-  const uint16_t *req_k = nullptr, *req_v = nullptr;
-  uint32_t req_dst_k = 0, req_dst_v = 0, req_step = 0;
-  const uint32_t lds_k0 = lds_address(&sK[0][wave * IPW * 512]), lds_v0 = lds_address(&sV[0][wave * IPW * 512]);
+  i32x8 r_cur = d, r_x1 = const_load8(item_at(d[6]));
+  int r_q = 2, r_kt = 0, r_ke = 0, r_live = 1, r_stage = 0;    // r_q: query slots before the next tile
+  int r_parity = 1;                     // the job's half of s_pos (the walk may be at the next but one before a job has read its own)
+  int r_last = 0;                       // the cache block of the item's frontier
+  uint32_t r_hi = 0;                    // the frontier's row in it
+  const int32_t* r_row = nullptr;
+  int r_id = 0;
+  const char *r_k = nullptr, *r_v = nullptr;                      // the kv head's cache
+  const char *src_k = nullptr, *src_v = nullptr;                  // the slot: base (of cache block 0)
+  uint32_t src_id = 0;                                            // ... block ids count (all ones) or not (0)
+  uint32_t req_off[2 * IPW];                                      // ... offsets of the lane
+  const char *req_k = nullptr, *req_v = nullptr;
+  uint32_t req_dst = 0, req_step = 0, req_v_at = 0;
+  const uint32_t lds_mine = lds_address(&s_kv[0][0][wave * IPW * 512]);
   const uint32_t lds_sink = lds_address(&s_sink[wave][0]);
-  auto request_part = [&](int part) {
-    const int i = part & 3;
-    if (part < 4) dma16_sa(k_off[i], req_k, req_dst_k + i * req_step);
-    else dma16_sa(v_off[i], req_v, req_dst_v + i * req_step);
+  auto enter_job = [&]() __attribute__((always_inline)) {
+    r_kt = r_cur[5] & 0xffff; r_ke = r_cur[5] >> 16;
+    r_last = max(r_cur[4], 0) >> 4;
+    r_hi = (max(r_cur[4], 0) & 15) * row_bytes;
+    r_row = p.block_table + static_cast<int64_t>(r_cur[3] >> 8) * p.max_blocks;
+    const int64_t head = static_cast<int64_t>(r_cur[3] & 255) * p.stride_head * 2;
+    r_k = static_cast<const char*>(p.k) + head;
+    r_v = static_cast<const char*>(p.v) + head;
+    r_q = 2;
+    r_parity ^= 1;
   };
-  auto prepare_sink = [&](const Slot& s) {
-    const int64_t at = s.head_off + static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(s.id)) *
-                                                         static_cast<uint32_t>(blk_stride));
-    req_k = kall + at;
-    req_v = vall + at;
-    req_dst_k = req_dst_v = lds_sink;
-    req_step = 0;
+  auto enter_queries = [&]() __attribute__((always_inline)) {
+    const i32x8 it = mine(r_cur, r_x1, couple(r_cur, r_x1));
+    const Rows r = rows_of(it);
+    src_k = src_v = static_cast<const char*>(p.q) + (static_cast<int64_t>(r.tok0) * p.n_q_heads + (it[3] & 255) * p.group) * (D * 2);
+    src_id = 0;
+#pragma unroll
+    for (int i = 0; i < 2 * IPW; ++i) req_off[i] = row_offset(r, (2 - r_q) * 32 + 4 * i + l_row) + k_chunk(i & 3);
+    if (r_q == 2) {
+      const uint32_t x = r.rem0 + min(lane, r.last);
+      dma4_sa(((x * group_inv) >> 16) * 4, p.q_pos + r.tok0, lds_address(&s_pos[r_parity][wave][0]));
+    }
   };
-  auto prepare_regular = [&](const Slot& s, int stage) {
-    // (a block spans fewer than 2^31 elements: the host checks the slot stride)
-    const int64_t at = s.head_off + static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(s.id)) *
-                                                         static_cast<uint32_t>(blk_stride));
-    req_k = kall + at;
-    req_v = vall + at;
-    req_dst_k = lds_k0 + stage * (TILE * 2);
-    req_dst_v = lds_v0 + stage * (TILE * 2);
-    req_step = 1024;
-  };
-  auto issue_frontier = [&](const Slot& s, int stage) {
-    // the tile that holds the frontier of its item (one per item, issued at once): rows past the
-    // frontier may be unallocated or hold anything, they fetch the frontier row instead (finite
-    // data, weight 0 after masking)
-    const uint16_t* kg = kall + s.head_off;
-    const uint16_t* vg = vall + s.head_off;
+  // Rows past the item's frontier may be unallocated or hold anything: their lanes fetch the frontier row instead
+  // (finite data, weight 0 after masking).
+  auto enter_tile = [&]() __attribute__((always_inline)) {
+    src_k = r_k; src_v = r_v; src_id = ~0u;
+    const int blk = 4 * r_kt + wave;
+    const uint32_t hi = blk < r_last ? 15 * row_bytes : r_hi, lo = blk > r_last ? r_hi : 0;
 #pragma unroll
     for (int i = 0; i < IPW; ++i) {
-      const int q = wave * IPW + i;
-      const int j_un = s.kt * kBN + 4 * q + l_row;
-      const bool over = j_un > s.wg_max;
-      const int j = over ? s.wg_max : j_un;
-      const int64_t slot = static_cast<int64_t>(over ? s.last_id : s.id) * CS_KV_BLOCK + j % CS_KV_BLOCK;
-      dma16(kg + slot * p.stride_slot + k_chunk[i] * 8, &sK[stage][q * 512]);
-      dma16(vg + slot * p.stride_slot + v_chunk[i] * 8, &sV[stage][q * 512]);
+      const uint32_t row = max(lo, min((4 * i + l_row) * row_bytes, hi));
+      req_off[i] = row + k_chunk(i);
+      req_off[IPW + i] = row + v_chunk(i);
     }
   };
-  auto issue = [&](const Slot& s, int stage) {     // the whole request at once
-    if (s.kt != s.wg_max / kBN) {
-      prepare_regular(s, stage);
-#pragma unroll
-      for (int part = 0; part < 2 * IPW; ++part) request_part(part);
+  // addresses of the slot's request, in four parts for four slots of a block
+  uint64_t r_at = 0;
+  auto prepare = [&](int part) __attribute__((always_inline)) {
+    if (part == 0) r_at = static_cast<uint64_t>(static_cast<uint32_t>(r_id) & src_id) * blk_bytes;
+    if (part == 1) req_k = src_k + r_at;
+    if (part == 2) req_v = src_v + r_at;
+    if (part == 3) {
+      req_dst = r_live ? lds_mine + r_stage * kStageBytes : lds_sink;
+      req_step = r_live ? 1024 : 0;
+      req_v_at = r_live ? TILE * 2 : 0;
+    }
+  };
+  auto request_part = [&](int part) __attribute__((always_inline)) {
+    if (part < IPW) dma16_sa(req_off[part], req_k, req_dst + part * req_step);
+    else dma16_sa(req_off[part], req_v, req_dst + req_v_at + (part - IPW) * req_step);
+  };
+  // ... and on to the next slot: inside a sweep only the tile changes
+  auto advance = [&]() __attribute__((always_inline)) {
+    r_stage = (r_stage + 1) & (STAGES - 1);
+    if (__builtin_expect(r_q == 0 && r_kt + 2 < r_ke, 1)) {
+      ++r_kt;
     } else {
-      issue_frontier(s, stage);
+      if (r_q) {
+        --r_q;
+      } else if (r_kt + 1 < r_ke) {
+        ++r_kt;
+      } else if (r_live) {
+        i32x8 to = r_x1;
+        if (couple(r_cur, r_x1)) {
+          to = const_load8(item_at(r_x1[6]));
+          wait_scalar();
+        }
+        if ((to[5] >> 16) > 0) {
+          r_cur = to;
+          r_x1 = const_load8(item_at(to[6]));
+          wait_scalar();
+          enter_job();
+        } else {
+          r_live = 0;
+        }
+      }
+      if (r_live) {
+        if (r_q) enter_queries();
+        else enter_tile();
+      }
     }
   };
+  // the block id of the tile that the walker stands at: asked for in every slot, behind its request, and waited for at
+  // the end of the slot (by hand, so that the waits for LDS reads in between need not be waits for it)
+  auto ask = [&]() __attribute__((always_inline)) { r_id = sload1(r_row + min(4 * r_kt + wave, r_last)); };
+  auto asked = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r_id)); };
+  auto send = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int part = 0; part < 4; ++part) prepare(part);
+#pragma unroll
+    for (int part = 0; part < 2 * IPW; ++part) request_part(part);
+    advance();
+    ask();
+  };
+  // waits until the tile after the current one has landed for every wave; after it every wave has left the previous one
+  auto gate = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory"); };
 
-  // ---- per-item state of the lane
+  // ---- per-job state of the lane
   bf16x8 qf[RB][STEPS];
-  int lim_raw[RB];
-  int it_tok_head[RB], it_part = -1;
-  bool it_valid[RB];
-  int it_rows_left = 0;                 // rows of the stream at and after this wave's first row
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    lim_raw[rb] = 0;
-    it_tok_head[rb] = 0;
-    it_valid[rb] = false;
-  }
-  auto load_item = [&](const i32x8& d) {
-    it_part = d[7];
-    it_rows_left = d[1] - (d[2] + wave * WROWS);
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int row = d[2] + wave * WROWS + rb * 32 + n;
-      it_valid[rb] = row < d[1];
-      const int row_c = it_valid[rb] ? row : d[1] - 1;
-      const int tq = row_c / p.group;
-      const int tok = d[0] + tq;
-      it_tok_head[rb] = tok * p.n_q_heads + (d[3] & 255) * p.group + (row_c - tq * p.group);
-      const uint16_t* qrow = static_cast<const uint16_t*>(p.q) + static_cast<int64_t>(it_tok_head[rb]) * D;
-#pragma unroll
-      for (int st = 0; st < STEPS; ++st)
-        qf[rb][st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const cs::u32x4*>(qrow + 16 * st + 8 * h));
-      lim_raw[rb] = min(p.q_pos[tok], d[4]);      // d[4]: the tile's frontier, already inside the stream's entries
-    }
-  };
-
-  f32x16 o[RB][DB];
-  float m_run[RB], l_run[RB];
   int lim[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[rb][db][r] = 0.f;
-    m_run[rb] = kNegInf;
-    l_run[rb] = 0.f;
-    lim[rb] = -1;
-  }
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  const s16x4 ones4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 o[RB][DB];
+  f32x4 lacc[RB][2];
+  float m_run[RB], m_scaled[RB], m_top[RB], t_max[RB];
+  uint64_t need = 0;                    // rows whose maximum has to be raised before the next half tile
+  int k_step = 0;                       // from this stage to the next
   const float slack = kMaxSlack / p.scale_log2e;
-  int wave_min = -1, wave_max = -1;
-
-  auto compute = [&](int kt, int stage) {
-    const int j0 = kt * kBN;
-    f32x16 sacc[RB][2];
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    constexpr int KPF = 2;        // K fragments are read two steps ahead of their MFMAs
-    bf16x8 ka[KPF + 1][2];
-    typedef __attribute__((address_space(3))) const cs::u32x4 lds_u32x4;
-    // LDS addresses of this tile's fragments: one add per address and tile; pinning them in
-    // registers lets every read fold its row-group offset into the instruction's immediate field
-    // (formed at each use they cost two vector instructions per pair of reads)
-    const uint32_t stage_off = static_cast<uint32_t>(stage) * (TILE * 2);
-    uint32_t kad[STEPS], va[DB];
+  f32x16 sa[RB], sb[RB];                // scores of the current and of the next half tile
+  bf16x8 ka[4];                         // K fragments in flight
+  typedef __attribute__((address_space(3))) const cs::u32x4 lds_u32x4;
+  auto k_frag = [&](int st, int half) {
+    ka[st & 3] = __builtin_bit_cast(bf16x8, reinterpret_cast<lds_u32x4*>(static_cast<uintptr_t>(k_addr[st]))[half * kHalfBytes / 16]);
+  };
+  auto row_max = [&](const f32x16 (&s)[RB], int rb) __attribute__((always_inline)) {
+    float t = kNegInf;
 #pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-      kad[st] = k_addr[st] + stage_off;
-      asm volatile("" : "+v"(kad[st]));
-    }
+    for (int r = 0; r < 16; ++r) t = fmaxf(t, s[rb][r]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+    t_max[rb] = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  };
+  auto mask = [&](f32x16 (&s)[RB], int half_tile) __attribute__((always_inline)) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      va[db] = v_addr[db] + stage_off;
-      asm volatile("" : "+v"(va[db]));
-    }
-    auto k_frag = [&](int st, int kb) {
-      return __builtin_bit_cast(bf16x8, reinterpret_cast<lds_u32x4*>(static_cast<uintptr_t>(kad[st]))[kb * 32 * D * 2 / 16]);
-    };
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int st = 0; st < KPF; ++st) {
-      ka[st][0] = k_frag(st, 0);
-      ka[st][1] = k_frag(st, 1);
-    }
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-      if (st + KPF < STEPS) {
-        ka[(st + KPF) % (KPF + 1)][0] = k_frag(st + KPF, 0);
-        ka[(st + KPF) % (KPF + 1)][1] = k_frag(st + KPF, 1);
+      for (int r = 0; r < 16; ++r) {
+        const int key = 32 * half_tile + 8 * (r / 4) + 4 * h + (r % 4);
+        if (key > lim[rb]) s[rb][r] = kNegInf;
       }
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-          sacc[rb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[st % (KPF + 1)][kb], qf[rb][st],
-                                                                 st == 0 ? zero16 : sacc[rb][kb], 0, 0, 0);
-      request_part(st);
-    }
-    // pin that order (the scheduler would otherwise pull each read back to just before its use)
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * KPF, 0);
-#pragma unroll
-    for (int st = 0; st < STEPS - KPF; ++st) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 2 * RB, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * RB * KPF, 0);
-    bf16x8 pb[RB][2][2];
+  };
+  // The scores of a half tile past some row's frontier.  Rows that see none of its keys (nor any later one) are out of
+  // the sweep: their reference maximum becomes infinite for the weights, which are 0 from here on.  Only where a
+  // frontier lies inside the half tile are scores masked one by one.  (A wave whose rows belong to two frames has
+  // frontiers thousands of keys apart, and all half tiles between them pass through here.)
+  auto past_frontier = [&](f32x16 (&s)[RB], int half_tile) __attribute__((always_inline)) {
+    const int j0 = 32 * half_tile;
+    bool straddles = false;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      if (j0 + kBN - 1 > wave_min) {
+      if (lim[rb] < j0) m_scaled[rb] = m_top[rb] = INFINITY;
+      straddles |= lim[rb] >= j0 && lim[rb] < j0 + 31;
+    }
+    if (__ballot(straddles)) {
+      mask(s, half_tile);
+      row_max(s, 0);
+      row_max(s, 1);
+    }
+    need = __ballot(t_max[0] > m_top[0] || t_max[1] > m_top[1]);
+  };
+  // the reference maximum: in log2 units as the weights need it, and where it is raised
+  auto set_max = [&](int rb, bool here, float m) __attribute__((always_inline)) {
+    m_run[rb] = here ? m : m_run[rb];
+    m_scaled[rb] = here ? (m == kNegInf ? 0.f : m) * p.scale_log2e : m_scaled[rb];
+    m_top[rb] = here ? m + slack : m_top[rb];
+  };
+  auto raise_max = [&]() __attribute__((always_inline)) {
+    if (__builtin_expect(need != 0, 0)) {
+      mfma_settle(o);
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = j0 + 32 * kb + 8 * (r / 4) + 4 * h + (r % 4);
-            if (key > lim[rb]) sacc[rb][kb][r] = kNegInf;
-          }
-      }
-      float t_max = kNegInf;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) t_max = fmaxf(t_max, sacc[rb][kb][r]);
-      {
-        // the two half-waves hold the same queries: v_permlane32_swap hands each half the other's
-        // value (no trip through LDS as a cross-lane shuffle would take)
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t_max), __float_as_uint(t_max), false, false);
-        t_max = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-      }
-      if (__any(t_max > m_run[rb] + slack)) {
-        const bool up = t_max > m_run[rb] + slack;
-        const float m_new = up ? t_max : m_run[rb];
+      for (int rb = 0; rb < RB; ++rb) {
+        const bool up = t_max[rb] > m_top[rb];
+        const float m_new = up ? t_max[rb] : m_run[rb];
         const float alpha = up ? __builtin_amdgcn_exp2f((m_run[rb] - m_new) * p.scale_log2e) : 1.f;
-        m_run[rb] = m_new;
-        l_run[rb] *= alpha;
+        set_max(rb, up, m_new);
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) lacc[rb][i][r] *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) o[rb][db][r] *= alpha;
-      }
-      const float m_scaled = (m_run[rb] == kNegInf ? 0.f : m_run[rb]) * p.scale_log2e;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int mm = 0; mm < 2; ++mm) {
-          cs::u32x4 w;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const float e0 = __builtin_amdgcn_exp2f(fmaf(sacc[rb][kb][8 * mm + 2 * c], p.scale_log2e, -m_scaled));
-            const float e1 = __builtin_amdgcn_exp2f(fmaf(sacc[rb][kb][8 * mm + 2 * c + 1], p.scale_log2e, -m_scaled));
-            const uint32_t pk = pack_bf16x2(e0, e1);
-            l_run[rb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk),
-                                                        __builtin_bit_cast(bf16x2, 0x3f803f80u), l_run[rb], false);
-            w[c] = pk;
-          }
-          pb[rb][kb][mm] = __builtin_bit_cast(bf16x8, w);
+          asm volatile("" : "+a"(o[rb][db]));
         }
-    }
-    // 16 MFMAs, m = (key block, key half, d block); V^T fragments are read VPF MFMAs ahead
-    constexpr int VPF = 3;
-    s16x4 vlo[VPF + 1], vhi[VPF + 1];
-    auto v_frag = [&](int m) {
-      const int g0 = (32 * (m >> 3) + 16 * ((m >> 2) & 1)) * D, db = m & 3;
-      const uint32_t a = va[db];
-      vlo[m % (VPF + 1)] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(((lds_s16x4*)(static_cast<uintptr_t>(a))) + g0 * 2 / 8);
-      vhi[m % (VPF + 1)] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(((lds_s16x4*)(static_cast<uintptr_t>(a))) + (g0 + 8 * D) * 2 / 8);
-    };
-#pragma unroll
-    for (int m = 0; m < VPF; ++m) v_frag(m);
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      if (m + VPF < 16) v_frag(m + VPF);
-      const s16x8 a = __builtin_shufflevector(vlo[m % (VPF + 1)], vhi[m % (VPF + 1)], 0, 1, 2, 3, 4, 5, 6, 7);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-        o[rb][m & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                              pb[rb][m >> 3][(m >> 2) & 1], o[rb][m & 3], 0, 0, 0);
+      }
     }
   };
+#define FENCE() __builtin_amdgcn_sched_barrier(0)
 
-  // Normalises and stores the rows of the finished item (or its un-normalised partial rows when
-  // the key sweep is shared), then clears the accumulators.
-  auto finish_item = [&](const int (&tok_head)[RB], const bool (&valid)[RB], int part) {
+  // One half tile (32 keys): softmax and P V of the scores `sc`, and the scores `sn` of the next half tile, as 32 slots
+  // of one matrix instruction and what its 32 cycles leave room for.  The fences keep the slots as they are written.
+  auto block = [&](auto half_c, const f32x16 (&sc)[RB], f32x16 (&sn)[RB]) __attribute__((always_inline)) {
+    constexpr int HALF = decltype(half_c)::value;
+    cs::u32x4 w[RB][2];
+    // the weights, two at a time (unit u = 8 mm + 4 rb + c): v_fma, v_exp, pack, each some instructions behind the other
+    float f[17][2], e[16][2];
+    auto form = [&](int u, int i) {
+      if (u < 16) f[u][i] = fmaf(sc[(u >> 2) & 1][8 * (u >> 3) + 2 * (u & 3) + i], p.scale_log2e, -m_scaled[(u >> 2) & 1]);
+    };
+    auto pack = [&](int u) { w[(u >> 2) & 1][u >> 3][u & 3] = pack_bf16x2(e[u][0], e[u][1]); };
+    auto op = [&](int k) {
+      const int u = k / 5, j = k % 5;
+      if (j == 0 || j == 2) e[u][j >> 1] = __builtin_amdgcn_exp2f(f[u][j >> 1]);
+      else if (j == 1 || j == 3) form(u + 1, j >> 1);
+      else if (u > 0) pack(u - 1);
+    };
+    s16x4 vlo[4], vhi[4];
+    auto v_frag = [&](int m) {
+      const int g0 = HALF * kHalfBytes / 8 + 16 * (m >> 2) * D * 2 / 8, db = m & 3;
+      vlo[m & 3] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(((lds_s16x4*)(static_cast<uintptr_t>(v_addr[db]))) + g0);
+      vhi[m & 3] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(((lds_s16x4*)(static_cast<uintptr_t>(v_addr[db]))) + g0 + 8 * D * 2 / 8);
+    };
+    auto part_max = [&](int rb, int part) {
+      float t = part ? t_max[rb] : kNegInf;
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const float l_tot = l_run[rb] + __shfl_xor(l_run[rb], 32);
-      if (part >= 0) {
-        const int64_t prow = static_cast<int64_t>(part) + wave * WROWS + rb * 32 + n;
-        if (h == 0) {
-          p.ws_ml[prow * 2] = m_run[rb];
-          p.ws_ml[prow * 2 + 1] = l_tot;
+      for (int r = 0; r < 8; ++r) t = fmaxf(t, sn[rb][8 * part + r]);
+      t_max[rb] = t;
+    };
+    auto swap_max = [&](int rb) {
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t_max[rb]), __float_as_uint(t_max[rb]), false, false);
+      asm("v_max_f32 %0, %1, %2" : "=v"(t_max[rb]) : "v"(sw[0]), "v"(sw[1]));      // (fmaxf would quiet each operand first)
+    };
+    FENCE();
+    form(0, 0);
+    form(0, 1);
+    unrolled<0, 32>([&](auto slot_c) {
+      constexpr int slot = decltype(slot_c)::value, rb = slot & 1, st = slot >> 1, m = st - 8;
+      if (HALF == 0 && slot == 16) gate();
+      if constexpr (slot < 16) {
+        sn[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[st & 3], qf[rb][st & 7], st == 0 ? zero16 : sn[rb], 0, 0, 0);
+        if (rb == 0 && st + 3 < STEPS) k_frag((st + 3) & 7, HALF ^ 1);
+        if (slot >= 11 && rb == 1) v_frag((slot - 11) >> 1);
+        if (HALF == 0 && slot >= 2 && slot < 6) prepare(slot - 2);
+      } else {
+        const s16x8 a = __builtin_shufflevector(vlo[m & 3], vhi[m & 3], 0, 1, 2, 3, 4, 5, 6, 7);
+        mfma_acc(o[rb][m & 3], __builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, w[rb][(m >> 2) & 1]));
+        if (rb == 0 && m + 3 < 8) v_frag(m + 3);
+        if (HALF == 0 && rb == 1) request_part(m & 7);
+        if (HALF == 0 && slot >= 20 && slot < 24) {
+          k_addr[2 * (slot - 20)] += k_step;
+          k_addr[2 * (slot - 20) + 1] += k_step;
         }
-        float* po = p.ws_o + prow * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int rq = 0; rq < 4; ++rq) {
-            const cs::u32x4 w = {__float_as_uint(o[rb][db][4 * rq + 0]), __float_as_uint(o[rb][db][4 * rq + 1]),
-                                 __float_as_uint(o[rb][db][4 * rq + 2]), __float_as_uint(o[rb][db][4 * rq + 3])};
-            *reinterpret_cast<cs::u32x4*>(po + 32 * db + 8 * rq + 4 * h) = w;
-          }
-      } else if (valid[rb]) {
-        const float inv = __builtin_amdgcn_rcpf(l_tot);      // 1 ulp: far below the bf16 result's rounding
-        uint16_t* orow = static_cast<uint16_t*>(p.out) + static_cast<int64_t>(tok_head[rb]) * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int rq = 0; rq < 4; ++rq) {
-            cs::u32x2 w;
-            w.x = pack_bf16x2(o[rb][db][4 * rq + 0] * inv, o[rb][db][4 * rq + 1] * inv);
-            w.y = pack_bf16x2(o[rb][db][4 * rq + 2] * inv, o[rb][db][4 * rq + 3] * inv);
-            *reinterpret_cast<cs::u32x2*>(orow + 32 * db + 8 * rq + 4 * h) = w;
-          }
+        if (HALF == 1 && slot >= 28) v_addr[slot - 28] += k_step;
+        if (slot >= 24 && slot < 28) part_max((slot >> 1) & 1, slot & 1);
+        if (slot == 28 || slot == 29) swap_max(slot & 1);
+        if (slot == 30) need = __ballot(t_max[0] > m_top[0] || t_max[1] > m_top[1]);
+        if (slot >= 26 && rb == 0) k_frag((slot - 26) >> 1, HALF);        // of the half tile after the next one
       }
+      if constexpr (slot < 24) {
+        unrolled<80 * slot / 24, 80 * (slot + 1) / 24>([&](auto k) { op(decltype(k)::value); });
+        if constexpr (slot == 23) pack(15);
+      }
+      FENCE();
+    });
+    // row sums of the rounded weights: the 4x4 instruction with ones adds a lane's own four.  All at once: the change
+    // from the large instruction and back costs 16 cycles
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int mm = 0; mm < 2; ++mm)
+          lacc[rb][mm] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones4, __builtin_bit_cast(s16x4, cs::u32x2{w[rb][mm][2 * i], w[rb][mm][2 * i + 1]}), lacc[rb][mm], 0, 0, 0);
+    FENCE();
+  };
+
+  bool out = false;                     // this wave holds results of the job before
+  Rows out_rows = {0, 0, 0};
+  int out_kvh = 0, out_part = -1;
+  // Normalises and stores the rows of the finished job (or their un-normalised partial results when the key sweep is
+  // shared).  The two halves of the wave exchange every other group of four, so that a lane stores 16 bytes.
+  auto finish = [&](int rb, const Rows& r, int kvh, int part, auto between) __attribute__((always_inline)) {
+    const float l_half = lacc[rb][0][0] + lacc[rb][1][0];
+    const auto lsw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_half), __float_as_uint(l_half), false, false);
+    const float l_tot = __uint_as_float(lsw[0]) + __uint_as_float(lsw[1]);
+    if (part >= 0) {
+      const int64_t prow = static_cast<int64_t>(part) + (wave & 1) * WROWS + rb * 32 + n;
+      if (h == 0) {
+        p.ws_ml[prow * 2] = m_run[rb];
+        p.ws_ml[prow * 2 + 1] = l_tot;
+      }
+      float* po = p.ws_o + prow * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[rb][db][r] = 0.f;
-      m_run[rb] = kNegInf;
-      l_run[rb] = 0.f;
+        for (int rq = 0; rq < 4; ++rq) {
+          const cs::u32x4 w = {__float_as_uint(o[rb][db][4 * rq + 0]), __float_as_uint(o[rb][db][4 * rq + 1]),
+                               __float_as_uint(o[rb][db][4 * rq + 2]), __float_as_uint(o[rb][db][4 * rq + 3])};
+          *reinterpret_cast<cs::u32x4*>(po + 32 * db + 8 * rq + 4 * h) = w;
+        }
+      unrolled<0, DB>(between);
+    } else {
+      // (a lane whose row is past the stream's last one holds that row's result and stores it once more)
+      const float inv = __builtin_amdgcn_rcpf(l_tot);      // 1 ulp: far below the bf16 result's rounding
+      const uint32_t at = row_offset(r, rb * 32 + n) + 16 * h;
+      char* base = static_cast<char*>(p.out) + (static_cast<int64_t>(r.tok0) * p.n_q_heads + kvh * p.group) * (D * 2);
+      unrolled<0, DB>([&](auto db_c) {
+        constexpr int db = decltype(db_c)::value;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          uint32_t w[2][2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+              w[i][c] = pack_bf16x2(o[rb][db][8 * k + 4 * i + 2 * c] * inv, o[rb][db][8 * k + 4 * i + 2 * c + 1] * inv);
+          const auto lo = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+          const auto hi = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+          *reinterpret_cast<cs::u32x4*>(base + at + 64 * db + 32 * k) = cs::u32x4{lo[0], hi[0], lo[1], hi[1]};
+        }
+        between(db_c);
+      });
     }
   };
-
-  // ---- prologue: first item, first tile request, block ids of the second slot
-  Slot cur = first_slot(d0, 0);
-  cur.id = wave == 0 ? e0[4] : wave == 1 ? e0[5] : wave == 2 ? e0[6] : e0[7];
-  cur.last_id = e0[3];
-  issue(cur, 0);
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(d1), "+s"(d2));
-  Slot nxt = successor(cur);
-  request_ids(nxt);
-  load_item(d0);
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(nxt.id), "+s"(nxt.last_id));
-  bool new_item = true, ep_pending = false, ep_valid[RB];
-  int ep_tok_head[RB], ep_part = -1;
+  auto send_between = [&](auto db) __attribute__((always_inline)) {
+    request_part(2 * decltype(db)::value);
+    request_part(2 * decltype(db)::value + 1);
+  };
+  auto results = [&](int rb) __attribute__((always_inline)) {           // with a slot's request between the stores
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    ep_valid[rb] = false;
-    ep_tok_head[rb] = 0;
+    for (int part = 0; part < 4; ++part) prepare(part);
+    if (out) finish(rb, out_rows, out_kvh, out_part, send_between);
+    else unrolled<0, DB>(send_between);
+    advance();
+    ask();
+    asked();
+  };
+
+  // ---- prologue: the requests of the first three slots
+  enter_job();
+  enter_queries();
+#pragma unroll 1
+  for (int i = 0; i < STAGES - 1; ++i) {
+    send();
+    asked();
   }
+  i32x8 x1 = const_load8(item_at(d[6]));
   int stage = 0;
+  const uint32_t q_delta = wave * (IPW * 1024) + (n >> 4) * (TILE * 2 - IPW * 1024);
+  uint32_t pos_at = lds_address(&s_pos[0][wave][n]), pos_next = lds_address(&s_pos[1][wave][n]);
+  auto next_stage = [&](bool k, bool v) __attribute__((always_inline)) {
+    k_step = stage == STAGES - 1 ? -(STAGES - 1) * kStageBytes : kStageBytes;
+    if (k)
+#pragma unroll
+      for (int st = 0; st < STEPS; ++st) k_addr[st] += k_step;
+    if (v)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) v_addr[db] += k_step;
+  };
 
   for (;;) {
-    // everything requested so far has landed: the tile of `cur`, and at an item boundary the Q
-    // rows and frontier of its item (telling the compiler so here keeps it from waiting for them
-    // later, when that wait would also cover the tile request issued below)
-    wait_vmcnt<0>();
+    // ---- from job to job: the query slots (wave by wave: their regions are the wave's own), the results of the job
+    // before, the requests of the second and third tile.  The second takes the last tile's stage: all waves have left it
+    asm volatile("s_barrier" ::: "memory");
+    mfma_settle(o);
+    results(0);
+    const bool stored = out && out_part < 0;            // 8 + 8 stores, then
+    const bool paired = couple(d, x1);
+    const i32x8 my = mine(d, x1, paired);
+    const int kb = d[5] & 0xffff, ke = d[5] >> 16;
+    const bool works = takes_part(paired) && my[2] + (wave & 1) * WROWS < my[1];
+    // (the requests of queries are older than 16 others: the first tile's and the second's)
+    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-      for (int st = 0; st < STEPS; ++st) asm volatile("" : "+v"(qf[rb][st]));
-      asm volatile("" : "+v"(lim_raw[rb]));
-    }
-    __syncthreads();                     // every wave's share landed; every wave left the other stage
-    if (new_item) {
+      for (int st = 0; st < STEPS; ++st)
+        qf[rb][st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<lds_u32x4*>(static_cast<uintptr_t>(k_addr[st] + q_delta)));
+      if (rb == 0) {
+        typedef __attribute__((address_space(3))) const int32_t lds_i32;
+        lim[0] = reinterpret_cast<lds_i32*>(static_cast<uintptr_t>(pos_at))[0];
+        lim[1] = reinterpret_cast<lds_i32*>(static_cast<uintptr_t>(pos_at))[32];
+        asm volatile("" : "+v"(lim[0]), "+v"(lim[1]));
+        const uint32_t t = pos_at;
+        pos_at = pos_next;
+        pos_next = t;
+      }
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) lim[rb] = it_valid[rb] ? lim_raw[rb] : -1;
-      const int rows_here = min(WROWS, it_rows_left);     // rows of this wave that exist
-      const int last = max(rows_here, 1) - 1;             // positions do not decrease along the rows
-      wave_min = rows_here > 0 ? __builtin_amdgcn_readlane(lim[0], 0) : -1;
-      wave_max = rows_here > 0 ? __builtin_amdgcn_readlane(lim[RB > 1 && last >= 32 ? RB - 1 : 0], last & 31) : -1;
-      new_item = false;
+      for (int st = 0; st < STEPS; ++st) asm volatile("" : "+a"(qf[rb][st]));
+      next_stage(true, true);
+      stage = (stage + 1) & (STAGES - 1);
+      if (rb == 0) {
+        results(1);
+      }
     }
-    // request the next tile: at once if it holds the frontier of its item or if this wave has
-    // nothing to compute in this step, else spread over the S phase of this step
-    const bool computes = cur.kt * kBN <= wave_max;
-    if (nxt.live && computes && nxt.kt != nxt.wg_max / kBN) {
-      prepare_regular(nxt, stage ^ 1);
-    } else {
-      if (nxt.live) issue(nxt, stage ^ 1);
-      prepare_sink(cur);
+    // the first tile: its request is older than those of the next two and the stores
+    if (stored) asm volatile("s_waitcnt vmcnt(32)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
+    const i32x8 nd = const_load8(item_at(paired ? x1[6] : d[6]));     // the next job
+    // positions do not decrease along the rows
+    lim[0] = min(lim[0], my[4]);                          // my[4]: the row tile's frontier, already inside the stream's entries
+    lim[1] = min(lim[1], my[4]);
+    const int wave_min = __builtin_amdgcn_readlane(lim[0], 0), wave_max = __builtin_amdgcn_readlane(lim[1], 31);
+    const int h_end = works && wave_max >= 0 ? min(2 * (my[5] >> 16), wave_max / 32 + 1) : 0;     // half tiles this wave computes
+    const int h_plain = min(h_end, wave_min >= 31 ? (wave_min - 31) / 32 + 1 : 0);                // ... that all its rows see
+    auto clear = [&](int i) __attribute__((always_inline)) {
+      o[i >> 2][i & 3] = zero16;
+      asm volatile("" : "+a"(o[i >> 2][i & 3]));
+    };
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      lacc[rb][0] = lacc[rb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      set_max(rb, true, kNegInf);
     }
-
-    // scalar requests for later steps: block ids of the slot after next; at the last tile of an
-    // item also the descriptor three items ahead
-    const bool cur_last = cur.kt + 1 == cur.ke;
-    // (always issued, towards harmless addresses when there is nothing to fetch: a conditional
-    // request would let the compiler merge the pending register with another value before the wait)
-    Slot nn = nxt.live ? successor(nxt) : nxt;
-    request_ids(nn);
-    i32x8 d3 = sload8(cur_last ? item_at(d2[6]) : p.ws_plan + kHdrEndItem);
-
-    if (ep_pending) {
-      finish_item(ep_tok_head, ep_valid, ep_part);
-      ep_pending = false;
-    }
-    if (computes) compute(cur.kt, stage);
-
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(nn.id), "+s"(nn.last_id), "+s"(d3));
-    if (cur_last) {
-      ep_pending = true;
+    if (2 * kb < h_end) {
+      // the scores of the whole first tile: their maximum is the rows' reference (the weight of the largest is then
+      // exact in bf16 for most of them)
+#pragma unroll
+      for (int st = 0; st < 3; ++st) k_frag(st, 0);
+      unrolled<0, 2 * STEPS>([&](auto i_c) {
+        constexpr int i = decltype(i_c)::value, st = i & 7, half = i >> 3;
+        constexpr int ahead = (i + 3) & 7;
+        if constexpr (i + 3 < 2 * STEPS) k_frag(ahead, (i + 3) >> 3);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          f32x16& to = half ? sb[rb] : sa[rb];
+          to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[st & 3], qf[rb][st], st == 0 ? zero16 : to, 0, 0, 0);
+        }
+        if constexpr (half == 0) clear(st);
+        FENCE();
+      });
+      if (2 * kb + 1 >= h_plain) mask(sb, 2 * kb + 1);
+      if (2 * kb >= h_plain) mask(sa, 2 * kb);
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
-        ep_tok_head[rb] = it_tok_head[rb];
-        ep_valid[rb] = it_valid[rb];
+        row_max(sb, rb);
+        const float t = t_max[rb];
+        row_max(sa, rb);
+        set_max(rb, true, fmaxf(t, t_max[rb]));
       }
-      ep_part = it_part;
-      if ((d1[5] >> 16) > 0) {
-        load_item(d1);
-        new_item = true;
-      }
-      d0 = d1; d1 = d2; d2 = d3;
-      ++seq0;
+#pragma unroll
+      for (int st = 0; st < 3; ++st) k_frag(st, 1);
+    } else {
+      unrolled<0, 8>([&](auto i) { clear(decltype(i)::value); });
     }
-    if (!nxt.live) break;
-    cur = nxt;
-    nxt = nn;
-    stage ^= 1;
+    wait_scalar();
+#pragma unroll 1
+    for (int kt = kb; kt < ke; ++kt) {
+      k_step = stage == STAGES - 1 ? -(STAGES - 1) * kStageBytes : kStageBytes;
+      const int h0 = 2 * kt;
+      if (__builtin_expect(h0 < h_end, 1)) {
+        if (__builtin_expect(h0 >= h_plain, 0)) past_frontier(sa, h0);
+        raise_max();
+        block(std::integral_constant<int, 0>{}, sa, sb);
+      } else {
+#pragma unroll
+        for (int part = 0; part < 4; ++part) prepare(part);
+        gate();
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) k_addr[st] += k_step;
+#pragma unroll
+        for (int i = 0; i < 2 * IPW; ++i) request_part(i);
+      }
+      advance();
+      ask();
+      if (__builtin_expect(h0 + 1 < h_end, 1)) {
+        if (__builtin_expect(h0 + 1 >= h_plain, 0)) past_frontier(sb, h0 + 1);
+        raise_max();
+        block(std::integral_constant<int, 1>{}, sb, sa);
+      } else {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) v_addr[db] += k_step;
+      }
+      stage = (stage + 1) & (STAGES - 1);
+      asked();
+    }
+    out = works;
+    out_rows = rows_of(my);
+    out_kvh = my[3] & 255;
+    out_part = my[7];
+    d = nd;
+    if ((d[5] >> 16) <= 0) break;
+    x1 = const_load8(item_at(d[6]));
   }
-  finish_item(ep_tok_head, ep_valid, ep_part);
+  mfma_settle(o);
+  if (out) {
+    auto nothing = [](auto) {};
+    finish(0, out_rows, out_kvh, out_part, nothing);
+    finish(1, out_rows, out_kvh, out_part, nothing);
+  }
+  // no request may land after the workgroup's LDS has been given on, no scalar load be left in flight
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
 // Merges the partial results of split row tiles: out = sum_c w_c O_c / sum_c w_c l_c with
@@ -1655,7 +1872,7 @@ __global__ __launch_bounds__(256) void window_attn_merge_kernel(AttnParams p) {
   const int rl = (blockIdx.x - item * groups) * 8 + (threadIdx.x >> 5);
   const int row = r_tile + rl;
   if (row >= rows_total) return;
-  const int64_t base = (p.span ? static_cast<int64_t>(d[5]) : static_cast<int64_t>(item) * p.max_splits) * p.bm + rl;
+  const int first = d[5], doubled = d[6];              // see plan_spans
   // one pass, four key ranges at a time: all loads of a batch are independent of each other and
   // of the running maximum (rows a range did not see hold m = -inf, l = 0, O = 0)
   float m_all = kNegInf, l_all = 0.f;
@@ -1665,7 +1882,8 @@ __global__ __launch_bounds__(256) void window_attn_merge_kernel(AttnParams p) {
     float4 t[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int64_t pr = base + static_cast<int64_t>(min(c0 + u, n_split - 1)) * p.bm;
+      const int c = min(c0 + u, n_split - 1);
+      const int64_t pr = static_cast<int64_t>(first + c + min(c, doubled)) * p.bm + rl;
       ml[u] = *reinterpret_cast<const float2*>(p.ws_ml + pr * 2);
       t[u] = *reinterpret_cast<const float4*>(p.ws_o + pr * D + 4 * sub);
     }
@@ -1882,43 +2100,29 @@ struct AttnPlan {
   int64_t r_cap;         // upper bound on row tiles per kv head
   int64_t rt_cap;        // ... times kv heads
   int64_t items_cap;     // upper bound on work items
-  int chunk_tiles;       // key tiles per item when a row tile's sweep is split
-  int max_splits, max_tiles;
-  int grid;              // persistent workgroups: 8 XCDs x up to 64
+  int max_tiles;         // key tiles of the longest sweep
+  int grid;              // persistent workgroups: 8 XCDs x up to kWorkgroupsPerXcd
   int bm;                // rows per item
-  int rb;                // 32-row blocks per wave
   int hist_pitch;        // buckets of the planner's counting sort, per XCD
   int span, pref_pitch;  // span plan (see plan_spans) and the ints per XCD of its prefix array
   size_t off_pref;
   size_t off_items, off_rt_desc, off_st_toff, off_st_work, off_st_rank, off_rt_stream, off_rt_wgmax,
-      off_hist, off_ml, off_o, total;
+      off_un_head, off_st_uoff, off_hist, off_ml, off_o, total;
 };
 
 AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int32_t max_blocks) {
   AttnPlan a;
-  a.rb = 1;
-  a.bm = kBM * a.rb;
+  a.bm = kBM;
   a.r_cap = (n_q * group) / a.bm + n_streams;
   a.rt_cap = a.r_cap * n_kv_heads;
   a.max_tiles = static_cast<int>((static_cast<int64_t>(max_blocks) * CS_KV_BLOCK + kBN - 1) / kBN);
   // split long key sweeps when the row tiles alone cannot fill the chip a couple of times over
-  const int64_t target = 1024;
-  a.chunk_tiles = 1 << 30;
-  a.max_splits = 1;
-  if (a.rt_cap < target && a.max_tiles > 4) {
-    const int wanted = static_cast<int>((target + a.rt_cap - 1) / a.rt_cap);
-    a.chunk_tiles = a.max_tiles / wanted;
-    if (a.chunk_tiles < 4) a.chunk_tiles = 4;
-    a.max_splits = (a.max_tiles + a.chunk_tiles - 1) / a.chunk_tiles;
-    if (a.max_splits <= 1) { a.max_splits = 1; a.chunk_tiles = 1 << 30; }
-  }
-  a.span = a.max_splits > 1 ? 1 : 0;
-  // span plan: every cut adds one item, and an item's list position names its partial-result slot
-  a.items_cap = a.span ? a.rt_cap + 8 * kSlotsPerXcd : a.rt_cap * a.max_splits;
+  a.span = a.rt_cap < kSpanUnits && a.max_tiles > 4 ? 1 : 0;
+  // span plan: every cut adds an item to each row tile of a unit, and an item's list position names its partial-result slot
+  a.items_cap = a.span ? a.rt_cap + 2 * 8 * kWorkgroupsPerXcd : a.rt_cap;
   a.pref_pitch = static_cast<int>(a.rt_cap / 8 + 2);
   const int64_t per_xcd = (a.items_cap + 7) / 8;
-  const int64_t cap = a.rb == 2 ? 32 : 64;
-  a.grid = 8 * static_cast<int>(per_xcd < cap ? per_xcd : cap);
+  a.grid = 8 * static_cast<int>(per_xcd < kWorkgroupsPerXcd ? per_xcd : kWorkgroupsPerXcd);
   size_t at = kPlanHeaderInts * sizeof(int32_t);
   auto take = [&](size_t bytes) {
     const size_t here = (at + 255) & ~static_cast<size_t>(255);
@@ -1932,13 +2136,14 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
   a.off_st_rank = take(static_cast<size_t>(n_streams) * sizeof(int32_t));
   a.off_rt_stream = take(static_cast<size_t>(a.r_cap) * sizeof(int32_t));
   a.off_rt_wgmax = take(static_cast<size_t>(a.r_cap) * sizeof(int32_t));
+  a.off_un_head = take(static_cast<size_t>(a.r_cap) * sizeof(int32_t));
+  a.off_st_uoff = take(static_cast<size_t>(n_streams) * sizeof(int32_t));
   const int64_t pair_rounds = (static_cast<int64_t>(n_streams) * n_kv_heads + 7) / 8;
   a.hist_pitch = static_cast<int>((a.max_tiles + 2 > pair_rounds ? a.max_tiles + 2 : pair_rounds) + 1);
   a.off_hist = take(static_cast<size_t>(8) * a.hist_pitch * sizeof(int32_t));
   a.off_pref = take(static_cast<size_t>(8) * a.pref_pitch * sizeof(int32_t));
-  const bool split = a.max_splits > 1;
-  a.off_ml = take(split ? static_cast<size_t>(a.items_cap) * a.bm * 2 * sizeof(float) : 0);
-  a.off_o = take(split ? static_cast<size_t>(a.items_cap) * a.bm * 128 * sizeof(float) : 0);
+  a.off_ml = take(a.span ? static_cast<size_t>(a.items_cap) * a.bm * 2 * sizeof(float) : 0);
+  a.off_o = take(a.span ? static_cast<size_t>(a.items_cap) * a.bm * 128 * sizeof(float) : 0);
   a.total = (at + 255) & ~static_cast<size_t>(255);
   return a;
 }
@@ -1950,9 +2155,9 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 // on a route up to more work.  Below 1,024 row tiles the persistent kernel splits its sweeps and needs the merge
 // launch, and its plan costs 15-50 us a step.
 // us a layer in a step, plan not counted, persistent + merge / tile kernel (28/4 heads unless noted; T: row tiles):
-//   1,024 tiles and more       the planned schedule balances better: T 1,196 116 / 123, T 1,632 66.5 / 77.7
-//   kRows128 (to 1,023)        T 520 40.3 / 35.0, T 808 54.5 / 42.9, T 624 with 59 key tiles 94.0 / 86.6; past 64 key
-//                              tiles the split wins: T 508 with 89 106 / 112, T 564 with 121 137 / 167
+//   1,024 tiles and more       whole sweeps, no merge: T 1,044 48 / 51 (with the merge 53), T 1,076 with 50 key tiles 89 / 98
+//   kRows128 (to 1,023)        T 520 43.4 / 36.2, T 752 49.3 / 39.2, T 928 66.0 / 53.6, T 632 with 22 key tiles 50.0 / 43.5;
+//                              past 64 key tiles the split wins: T 508 with 89 91 / 112, T 564 with 121 (32 rows a wave) 137 / 167
 //   kRows64Keys2 (to 440)      T 288 31.3 / 22.4; at T 520 its twice as many workgroups (two fit a CU) no longer all run
 //                              at once: 37.1 (kRows128 35.0); past 48 key tiles level
 //   kRows64Keys4 (to 128)      T 116 20.2 / 17.4, with 28 key tiles 28.3 / 24.9 (two groups 18.1, 28.7): one workgroup
@@ -2087,9 +2292,6 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       if (!workspace || workspace_bytes < a.total || !cs::aligned16(workspace)) return CS_EWORKSPACE;
       char* w = static_cast<char*>(workspace);
       p.bm = a.bm;
-      p.chunk_tiles = a.chunk_tiles;
-      p.max_splits = a.max_splits;
-      p.span = a.span;
       p.ws_plan = reinterpret_cast<const int32_t*>(w);
       p.ws_sync = reinterpret_cast<int32_t*>(w) + kHdrSyncBase;
       p.ws_status = reinterpret_cast<int32_t*>(w) + kHdrStatus;
@@ -2120,8 +2322,6 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
         pp.n_streams = n_streams;
         pp.group = group;
         pp.n_kv_heads = n_kv_heads;
-        pp.chunk_tiles = a.chunk_tiles;
-        pp.max_splits = a.max_splits;
         pp.max_tiles = a.max_tiles;
         pp.r_cap = static_cast<int32_t>(a.r_cap);
         pp.bm = a.bm;
@@ -2135,6 +2335,8 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
         pp.st_rank = reinterpret_cast<int32_t*>(w + a.off_st_rank);
         pp.rt_stream = reinterpret_cast<int32_t*>(w + a.off_rt_stream);
         pp.rt_wgmax = reinterpret_cast<int32_t*>(w + a.off_rt_wgmax);
+        pp.un_head = reinterpret_cast<int32_t*>(w + a.off_un_head);
+        pp.st_uoff = reinterpret_cast<int32_t*>(w + a.off_st_uoff);
         pp.hist = reinterpret_cast<int32_t*>(w + a.off_hist);
         pp.span = a.span;
         pp.pref_pitch = a.pref_pitch;
@@ -2145,10 +2347,10 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
         if (plan_mode == CS_ATTN_PLAN_ONLY) return CS_OK;
       }
       if (fuse)
-        hipLaunchKernelGGL((window_attn_bf16_stream_kernel<1, true>), dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((window_attn_bf16_stream_kernel<true>), dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);
       else
-        hipLaunchKernelGGL((window_attn_bf16_stream_kernel<1, false>), dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);
-      if (a.max_splits > 1) {
+        hipLaunchKernelGGL((window_attn_bf16_stream_kernel<false>), dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);
+      if (a.span) {
         const int e = cs::note_hip(hipGetLastError());
         if (e != CS_OK) return e;
         hipLaunchKernelGGL(window_attn_merge_kernel, dim3(static_cast<unsigned>(a.rt_cap * (a.bm / 8))),

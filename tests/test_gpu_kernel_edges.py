@@ -79,6 +79,26 @@ def test_unplanned_attention_tile_edges(cs, case):
         say(f"  -> {_attn_case(cs, np.random.default_rng(9300 + case), 'bf16', hq, hkv, d, kv_lens, n_qs, scale_mult=mult)}")
 
 
+# bf16 attention from a plan, head_dim 128: jobs of one or two 128-row tiles, four waves of 64 rows, 32 keys at a time
+PLANNED_ATTN = [
+    # Hq, Hkv, kv_lens, n_qs
+    (8, 8, [1 + 9 * i % 71 for i in range(132)], [1 + 5 * i % (1 + 9 * i % 71) for i in range(132)]),   # one head a group, jobs of one or two key tiles
+    (32, 2, [40 + i % 90 for i in range(516)], [1 + i % 11 for i in range(516)]),                        # 16 heads a group
+    (12, 4, [33 * (1 + i % 6) for i in range(260)], [22 * (1 + i % 6) for i in range(260)]),             # ends of half tiles, one to four row tiles
+    (7, 1, [6100], [42]),                                                                                # split sweeps, three row tiles
+    (8, 2, [7000, 64, 4200], [150, 64, 31]),                                                             # split and whole, frontiers far apart
+    (28, 4, [4300], [19]),                                                                               # two row tiles, 5 rows in the second
+]
+
+
+@pytest.mark.parametrize("case", range(len(PLANNED_ATTN)))
+def test_planned_attention_job_edges(cs, case):
+    hq, hkv, kv_lens, n_qs = PLANNED_ATTN[case]
+    say(f"planned attention {case}: heads={hq}/{hkv} kv={kv_lens[:4]} n_q={n_qs[:4]} streams={len(kv_lens)}")
+    for mult in (1.0, 6.0):                                             # (wide scores: the reference maximum is raised along the sweep)
+        say(f"  -> {_attn_case(cs, np.random.default_rng(9350 + case), 'bf16', hq, hkv, 128, kv_lens, n_qs, scale_mult=mult)}")
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,d,kv_lens,n_qs", [
     ("bf16", 14, 2, 128, [300, 77], [40, 77]), ("bf16", 28, 4, 128, [1100], [300]), ("bf16", 8, 2, 64, [300, 77], [40, 77]),
     ("bf16", 28, 4, 128, [900, 700, 800, 640], [380, 500, 250, 400]), ("f32", 8, 2, 128, [300, 77], [40, 77])])
