@@ -1259,9 +1259,9 @@ __device__ __forceinline__ void mfma_settle(f32x16 (&o)[2][4]) {
 //   job) is set up when the walk enters it.
 // * Frontiers: rows that see nothing more of a sweep get an infinite reference maximum once; only half tiles that hold
 //   some row's frontier are masked score by score.
-// * The scores of a job's first half tiles are formed ahead of its sweep, those of the second again inside it: 2 % of a sweep
-//   of 13 tiles, but the reference is then the maximum over 64 keys.  Over 32 the largest weight of a row is less often
-//   the exact one: error against 64 bits 2.130e-3 instead of 2.111e-3 (32 streams), 2.161 instead of 2.142 (64).
+// * The scores of a job's first tile are formed ahead of its sweep, and again inside it: 8,000 of 462,000 cycles of a
+//   workgroup at 64 streams.  The reference is then the maximum over 64 keys.  Over 32 the error against 64 bits was larger:
+//   2.130e-3 instead of 2.111e-3 (32 streams of 860 keys), 2.161e-3 instead of 2.142e-3 (64 of 560).
 // us a layer, two builds in turn (32 rows a wave / this one): 64 streams of 560 keys, 32/8 heads 278 / 263; 32 streams of
 // 860 keys, 28/4 heads 150 / 140; 2,100 tokens over 6,000 keys 118 / 105, over 17,600 keys 273 / 242 (0.94 PFLOP/s).
 template <bool FUSE>
