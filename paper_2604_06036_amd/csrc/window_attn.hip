@@ -33,6 +33,7 @@
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -443,6 +444,12 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
           for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
       }
       const float m_scaled = (m_run == kNegInf ? 0.f : m_run) * p.scale_log2e;
+      // Row sums of the rounded weights.  head_dim 64: the 4x4 matrix instruction with ones adds a lane's own four, since
+      // v_dot2 waits for the matrix pipe.  us a step, two runs each (v_dot2 / this): 2 streams of 8,700 keys 1,773-1,780 /
+      // 1,739-1,744, 4 streams of 1,000 keys 769-775 / 747-748, one 549-551 / 543-544, 12 of 1,100 level.  head_dim 128, with
+      // twice the matrix work for each weight, keeps v_dot2: 4 streams 1,126 / 1,133, of 1,400 keys 1,402 / 1,417.
+      f32x4 l_sum[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+      const s16x4 ones4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -453,12 +460,18 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
             const float e0 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * mm + 2 * c], p.scale_log2e, -m_scaled));
             const float e1 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * mm + 2 * c + 1], p.scale_log2e, -m_scaled));
             const uint32_t pk = pack_bf16x2(e0, e1);
-            l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk),
-                                                    __builtin_bit_cast(bf16x2, 0x3f803f80u), l_run, false);
+            if (D != 64)
+              l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk),
+                                                      __builtin_bit_cast(bf16x2, 0x3f803f80u), l_run, false);
             w[c] = pk;
           }
           pb[kb][mm] = __builtin_bit_cast(bf16x8, w);
+          if (D == 64) {
+            l_sum[0] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones4, __builtin_bit_cast(s16x4, cs::u32x2{w.x, w.y}), l_sum[0], 0, 0, 0);
+            l_sum[1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones4, __builtin_bit_cast(s16x4, cs::u32x2{w.z, w.w}), l_sum[1], 0, 0, 0);
+          }
         }
+      if (D == 64) l_run += l_sum[0][0] + l_sum[1][0];
     }
     if (STAGES == 1) {
       wait_ids();
@@ -1483,7 +1496,6 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
   // ---- per-job state of the lane
   bf16x8 qf[RB][STEPS];
   int lim[RB];
-  typedef __attribute__((ext_vector_type(4))) float f32x4;
   const s16x4 ones4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   f32x16 o[RB][DB];
