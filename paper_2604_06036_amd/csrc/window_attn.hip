@@ -1665,6 +1665,8 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
   // writes 8 rows of 128 bytes.  Straight from the registers it wrote 32 rows of 32 bytes: a job's results took 3,100 and
   // 3,700 cycles (its two blocks of 32 rows, 64 streams of 560 keys) instead of 2,300 and 2,500, a layer of 64 streams with
   // its refresh write 264.5 us instead of 258.5, of 32 streams 127.8 instead of 124.6.
+  // Partial results likewise: 1,800 and 2,050 cycles instead of 2,300 and 2,700 (2,100 tokens over 6,000 keys; a layer with
+  // merge and refresh write 94.3 us instead of 97.1).
   auto finish = [&](int rb, const Rows& r, int kvh, int part, auto between) __attribute__((always_inline)) {
     const float l_half = lacc[rb][0][0] + lacc[rb][1][0];
     const auto lsw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_half), __float_as_uint(l_half), false, false);
@@ -1675,15 +1677,20 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
         p.ws_ml[prow * 2] = m_run[rb];
         p.ws_ml[prow * 2 + 1] = l_tot;
       }
-      float* po = p.ws_o + prow * D;
+      float* po = p.ws_o + (static_cast<int64_t>(part) + (wave & 1) * WROWS + rb * 32 + (lane >> 3)) * D + 4 * (lane & 7);
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+      for (int db = 0; db < DB; ++db) {
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-          const cs::u32x4 w = {__float_as_uint(o[rb][db][4 * rq + 0]), __float_as_uint(o[rb][db][4 * rq + 1]),
-                               __float_as_uint(o[rb][db][4 * rq + 2]), __float_as_uint(o[rb][db][4 * rq + 3])};
-          *reinterpret_cast<cs::u32x4*>(po + 32 * db + 8 * rq + 4 * h) = w;
-        }
+        for (int rq = 0; rq < 4; ++rq)
+          *reinterpret_cast<lds_out*>(static_cast<uintptr_t>(out_write ^ (32 * rq))) =
+              cs::u32x4{__float_as_uint(o[rb][db][4 * rq + 0]), __float_as_uint(o[rb][db][4 * rq + 1]),
+                        __float_as_uint(o[rb][db][4 * rq + 2]), __float_as_uint(o[rb][db][4 * rq + 3])};
+        cs::u32x4 row[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) row[i] = reinterpret_cast<lds_out*>(static_cast<uintptr_t>(out_read))[i * 64];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<cs::u32x4*>(po + i * 8 * D + 32 * db) = row[i];
+      }
       unrolled<0, DB>(between);
     } else {
       // (a row past the stream's last one holds that row's result and stores it once more)
