@@ -239,8 +239,10 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
   static_assert(BPW >= 1 && IPB * RPD == CS_KV_BLOCK, "a DMA instruction stays inside a cache block");
 
   __shared__ __attribute__((aligned(1024))) uint16_t s_kv[KG][STAGES][2][TILE];
-  __shared__ float s_ml[KG > 1 ? KG / 2 : 1][ROWW][2][64];
-  static_assert(sizeof(s_kv) >= sizeof(float) * (KG / 2) * ROWW * DB * 16 * 64, "the merge reuses the tile buffers");
+  constexpr bool SPREAD = KG > 2;      // the merge of the groups is shared by all waves (see there)
+  __shared__ float s_ml[SPREAD ? KG : 1][ROWW][2][64];
+  static_assert(KG == 1 || KG == 2 || KG == DB, "of four groups each finishes one block of columns");
+  static_assert(sizeof(s_kv) >= sizeof(float) * (SPREAD ? KG : KG / 2) * ROWW * DB * 16 * 64, "the merge reuses the tile buffers");
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -497,9 +499,52 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
     if (STAGES == 2) wait_ids();
   }
 
-  // ---- the groups' partial results: the upper half of the groups hands over to the lower half until one is left
-  //      (a group that met no visible key holds m = -inf, l = 0, O = 0)
+  // ---- the groups' partial results (a group that met no visible key holds m = -inf, l = 0, O = 0).  Of two groups the
+  //      second hands over to the first.  Of four, every wave leaves all of its columns in LDS and finishes one block of its
+  //      rows' columns: two rounds of hand-over left six of the eight waves idle in the end.  us a step before / after (28
+  //      layers): one stream of 900 keys, 28/4 heads 656 / 635, 3 streams, 8/1 heads 637 / 620, one stream of 1,800 keys
+  //      902 / 885; one of 1,400 keys, and two groups merged this way, level.
   float l_tot = l_run + __shfl_xor(l_run, 32);
+  if constexpr (SPREAD) {
+    float4* s_o4 = reinterpret_cast<float4*>(&s_kv[0][0][0][0]);
+    __syncthreads();                       // the tile buffers have been read
+    float4* mine = s_o4 + (kg * ROWW + rw) * (DB * 4 * 64) + lane;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq)
+        mine[(db * 4 + rq) * 64] = make_float4(o[db][4 * rq], o[db][4 * rq + 1], o[db][4 * rq + 2], o[db][4 * rq + 3]);
+    s_ml[kg][rw][0][lane] = m_run;
+    s_ml[kg][rw][1][lane] = l_tot;
+    __syncthreads();
+    float w[KG], m_all = kNegInf, l_all = 0.f;
+#pragma unroll
+    for (int g = 0; g < KG; ++g) m_all = fmaxf(m_all, s_ml[g][rw][0][lane]);
+#pragma unroll
+    for (int g = 0; g < KG; ++g) {
+      const float m = s_ml[g][rw][0][lane];
+      w[g] = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f((m - m_all) * p.scale_log2e);
+      l_all = fmaf(w[g], s_ml[g][rw][1][lane], l_all);
+    }
+    const float inv = 1.f / l_all;
+    uint16_t* orow = static_cast<uint16_t*>(p.out) + q_at + 32 * kg + 4 * h;
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int g = 0; g < KG; ++g) {
+        const float4 x = s_o4[((g * ROWW + rw) * DB * 4 + kg * 4 + rq) * 64 + lane];
+        t.x = fmaf(w[g], x.x, t.x); t.y = fmaf(w[g], x.y, t.y); t.z = fmaf(w[g], x.z, t.z); t.w = fmaf(w[g], x.w, t.w);
+      }
+      if (valid) {                         // register r of a block is d = 32 db + 8 (r / 4) + 4 h + r % 4
+        cs::u32x2 pk;
+        pk.x = pack_bf16x2(t.x * inv, t.y * inv);
+        pk.y = pack_bf16x2(t.z * inv, t.w * inv);
+        *reinterpret_cast<cs::u32x2*>(orow + 8 * rq) = pk;
+      }
+    }
+    return;
+  }
   float* s_o = reinterpret_cast<float*>(&s_kv[0][0][0][0]);
 #pragma unroll
   for (int half = KG / 2; half > 0; half >>= 1) {
