@@ -445,7 +445,7 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  * CS_ATTN_PLAN_BUILD call is preceded by the planning launch, a CS_ATTN_PLAN_ONLY call plans and
  * moves nothing.  Other shapes: the two calls are queued one after the other.
  *
- * The barrier needs the whole grid (at most 512 workgroups, two per CU) resident at once, which a
+ * The barrier needs the whole grid (at most 256 workgroups, one per CU) resident at once, which a
  * device with all 256 CUs free for the launch gives.  Its wait is bounded so that every wave exits;
  * if it ever expires (part of the grid could not become resident) the 32-bit word at byte offset
  * CS_ATTN_STATUS_OFFSET of the workspace is 1 after the call has completed and the call's results

@@ -628,8 +628,8 @@ constexpr int kSyncGroups = 16, kSyncPitch = 64;
 constexpr int kHdrSyncBase = (kHdrHeads + kHdrEntryInts * 8 * kSlotsPerXcd + kSyncPitch - 1) / kSyncPitch * kSyncPitch;
 constexpr int kSyncInts = (kSyncGroups + 2) * kSyncPitch;
 constexpr int kPlanHeaderInts = kHdrSyncBase + kSyncInts;
-// What a job costs besides its key tiles, in half tiles, for the planner's balance: measured 8,300 cycles (results of the
-// job before, queries, first scores) beside 1,600 for a half tile.  3 instead: 2,100 tokens over 17,600 keys 258 against
+// What a job costs besides its key tiles, in half tiles, for the planner's balance: measured 7,300-8,900 cycles (results of
+// the job before, queries, first scores) beside 1,510-1,730 for a half tile.  3 instead: 2,100 tokens over 17,600 keys 258 against
 // 244 us a layer, over 6,000 keys 111 against 104.
 constexpr int kItemFixedCostHalves = 5;
 constexpr int kPlanThreads = 1024;
@@ -1220,7 +1220,7 @@ __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)
 
 constexpr uint32_t kBarrierSpinLimit = 1u << 24;
 
-// Launch-wide barrier of a grid whose workgroups are all resident (at most 2 per CU on 256 CUs, by
+// Launch-wide barrier of a grid whose workgroups are all resident (at most one per CU on 256 CUs, by
 // construction of the persistent grid).  Arrivals are counted in two levels so that no counter takes
 // more than n/16 + 16 read-modify-writes in a row (they execute at the memory side, one after the
 // other per address): workgroup b adds to group counter b & 15; whoever completes a group resets it
@@ -1302,12 +1302,13 @@ __device__ __forceinline__ void mfma_settle(f32x16 (&o)[2][4]) {
 // What bounds it: power.  The matrix cores toggle enough for the device to run at 1.6-2.1 GHz instead of 2.4, so
 // cycles saved by overlap alone come back as a lower clock, and what counts is work per matrix instruction.  Timing
 // builds of the kernel before (32 rows a wave, 128 a workgroup, two workgroups per CU) with half the LDS reads, with
-// half the tile requests and with both left out ran 13, 8 and 20 % shorter at level cycles.  Hence 64 rows a wave
+// half the tile requests and with both left out ran 13, 8 and 20 % shorter.  Hence 64 rows a wave
 // (each K and V fragment read from LDS feeds two matrix instructions) and 256 a workgroup (each tile is fetched once
 // for twice the rows).  The price is that no second wave hides anything: a half tile (32 keys) is laid out by hand as
 // 32 slots of one matrix instruction, 16 for the scores of the NEXT half tile and 16 for P V of this one, and between
-// them go the softmax of this half tile, the LDS reads two to three slots ahead and the next requests.  1,190 cycles a half
-// tile of 1,024 cycles of matrix instructions, 1,400 with the tile's barrier; the kernel before took 3,530 for 64 rows and 64 keys.
+// them go the softmax of this half tile, the LDS reads two to three slots ahead and the next requests.  A tile (64 keys)
+// takes 3,020 cycles in sweeps of 58 tiles and 3,460 in sweeps of 9, of which 2,048 are matrix instructions; a job takes
+// 8,900 more with whole results, 7,300 with partial ones.
 // * Registers: O (128) and Q (64) live in the accumulation registers, scores and weights in the others; the matrix
 //   instructions of P V are spelled out so that O stays there.
 // * Row sums: v_dot2 waits for the matrix pipe to drain (48 cycles instead of 32 per matrix instruction when one
@@ -1320,8 +1321,9 @@ __device__ __forceinline__ void mfma_settle(f32x16 (&o)[2][4]) {
 // * The scores of a job's first tile are formed ahead of its sweep, and again inside it: 8,000 of 462,000 cycles of a
 //   workgroup at 64 streams.  The reference is then the maximum over 64 keys.  Over 32 the error against 64 bits was larger:
 //   2.130e-3 instead of 2.111e-3 (32 streams of 860 keys), 2.161e-3 instead of 2.142e-3 (64 of 560).
-// us a layer, two builds in turn (32 rows a wave / this one): 64 streams of 560 keys, 32/8 heads 278 / 263; 32 streams of
-// 860 keys, 28/4 heads 150 / 140; 2,100 tokens over 6,000 keys 118 / 105, over 17,600 keys 273 / 242 (0.94 PFLOP/s).
+// us a layer, two builds in turn (32 rows a wave / this one): 64 streams of 560 keys, 32/8 heads 244 / 235; 32 streams of
+// 860 keys, 28/4 heads 127 / 117; 2,100 tokens over 6,000 keys 102 / 89, over 17,600 keys 249 / 214 (1.07 PFLOP/s); 5 ragged
+// streams of 2,600 keys 109 / 110 (1.5 jobs a workgroup, the longest 1.4 times the mean: the cycles saved are not on it).
 template <bool FUSE>
 __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnParams p) {
   constexpr int RB = 2;                 // 32-row blocks per wave
