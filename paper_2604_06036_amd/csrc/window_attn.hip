@@ -374,6 +374,11 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 
   if (STAGES == 2) wait_ids();
 
+  // Four groups: a SIMD holds a wave of group g and one of g + 2.  The upper groups run one barrier behind, so that one of
+  // the two is at its matrix instructions while the other forms weights (a barrier more here for them, behind the sweep for
+  // the others: all waves meet the same number).  us a step in step / behind: one stream of 900 keys 642 / 635, of 1,800
+  // keys 883 / 865, 3 streams, 8/1 heads 617 / 608; one stream, 32/8 heads level.
+  if (SPREAD && kg >= KG / 2) __syncthreads();
   const int n_trips = (n_key_tiles + KG - 1) / KG;
   for (int trip = 0; trip < n_trips; ++trip, kt += KG) {
     wait_vmcnt<0>();
@@ -498,6 +503,7 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
     }
     if (STAGES == 2) wait_ids();
   }
+  if (SPREAD && kg < KG / 2) __syncthreads();
 
   // ---- the groups' partial results (a group that met no visible key holds m = -inf, l = 0, O = 0).  Of two groups the
   //      second hands over to the first.  Of four, every wave leaves all of its columns in LDS and finishes one block of its
