@@ -639,6 +639,7 @@ constexpr int kPlanHeaderInts = kHdrSyncBase + kSyncInts;
 // 244 us a layer, over 6,000 keys 111 against 104.
 constexpr int kItemFixedCostHalves = 5;
 constexpr int kPlanThreads = 1024;
+constexpr int kDealAtOnce = 72;       // units of an XCD that are dealt by length over the whole list (at most two a lane)
 constexpr int kSortMax = 2048;        // streams sorted by work in LDS; beyond, stream order is kept
 
 struct PlanParams {
@@ -898,12 +899,14 @@ __device__ void plan_spans(const PlanParams& pp, int n_rt, int n_un, int* s_wave
 
 __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanParams pp) {
   __shared__ int s_wave[kPlanThreads / 64];
-  __shared__ unsigned long long s_key[kSortMax];
+  __shared__ __attribute__((aligned(16))) unsigned long long s_key[kSortMax];
+  static_assert(kDealAtOnce <= 128 && sizeof(int4) * 8 * 128 <= sizeof(s_key), "the deal keeps its units there");
   __shared__ int s_list_off[9];
   __shared__ int s_left_tiles[8], s_left_end[8];   // pairs left over by whole rounds: row tiles; last row tile + pair
   __shared__ int s_by_rank[8][64];      // deal: lane (and length) of the item of each rank, per XCD
   __shared__ PlanUnit s_unit[kSpanUnits];
   __shared__ int s_units[8];            // units in each XCD's list
+  __shared__ int s_deal[8][128];       // deal at once: units by length
   __shared__ int s_cut[8][kSlotsPerXcd + 1];   // span plan: first tile position of every workgroup's span
   const int tid = threadIdx.x;
   const int hist_pitch = pp.hist_pitch;
@@ -1145,46 +1148,92 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
       auto field = [&](int i, int k) {
         return __hip_atomic_load(&pp.items[static_cast<int64_t>(i) * 8 + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       };
-      // (a pair-ordered list that is not a whole number of batches starts with the short batch:
-      // the full batches that follow even the loads out again, which a short batch at the end
-      // cannot.  A list ordered by length keeps its batches aligned instead: workgroups that start
-      // equal-length items together sweep the same key ranges together and share them in L2,
-      // which is worth more there: 6 % on the dense long-window case.)
-      int n_batch = grouped && s_units[w] % n_wg ? s_units[w] % n_wg : n_wg;
-      for (int base = begin; base < end; n_batch = n_wg) {
-        // of whole pairs the next n_batch units lie within the next 64 items
-        const int unit = base + lane < end ? field(base + lane, 6) : -1, keys = base + lane < end ? field(base + lane, 5) : 0;
-        const bool first = unit < -1;
-        const int second = unit < -2 ? -3 - unit : -1;
-        const unsigned long long firsts = __ballot(first);
-        const int rank = __popcll(firsts & ((1ull << lane) - 1)), n_seen = __popcll(firsts), n_here = min(n_seen, n_batch);
-        const unsigned long long stop = __ballot(first && rank == n_batch);
-        int len = -1;                                     // lanes without a unit rank last
-        if (first && rank < n_batch) len = keys >> 16;
-        int item_rank = 0, load_rank = 0;                 // by decreasing length / increasing load, ties by lane
+      auto take = [&](int first_item, int second_item, int tiles) {
+        for (int k = 0; k < (second_item >= 0 ? 2 : 1); ++k, ++taken) {
+          const int idx = k ? second_item : first_item;
+          if (last >= 0) pp.items[static_cast<int64_t>(last) * 8 + 6] = idx;
+          if (taken == 0) first3[0] = idx;
+          if (taken == 1) first3[1] = idx;
+          if (taken == 2) first3[2] = idx;
+          last = idx;
+        }
+        load += 2 * tiles + kItemFixedCostHalves;
+      };
+      // A pair-ordered list of up to two and a quarter rounds is dealt by length over the whole list: its pairs are under
+      // way together in any case, and batches in list order let long units meet.  us a step in list order / by length: 12
+      // streams of 1,000 keys (71 units an XCD) 1,157 / 1,069, 11 (67) 1,847 / 1,713, 5 of 3,200 (71) 2,564 / 2,504, 5 ragged
+      // (54) 3,415 / 3,337, 9 and 10 of 1,000 (53, 57) 1,597 / 1,566, 963 / 947.  Longer lists keep their order, so that few
+      // pairs at a time share an L2: 12 of 1,000, eight kv heads (81) 1,337 / 1,386, 15 of 1,000 (88) 2,177 / 2,182, 16 of 900
+      // (90) 2,035 / 2,069, 9 of 2,000 (107) 2,595 / 2,681.  Some of them would gain (16 of 1,000 (92) 1,372 / 1,328, 25 of
+      // 2,900, one kv head (100) 2,519 / 2,400) and working both deals out tells which, but that costs 15-30 us a plan.
+      if (grouped && s_units[w] <= kDealAtOnce) {
+        int4* unit_at = reinterpret_cast<int4*>(s_key) + w * 128;     // first item, second (or -1), key tiles
+        int* by_len = s_deal[w];
+        int n_units = 0;
+        for (int base = begin; base < end; base += 64) {
+          const int at = base + lane;
+          const int unit = at < end ? field(at, 6) : -1;
+          const unsigned long long firsts = __ballot(unit < -1);
+          if (unit < -1)
+            unit_at[n_units + __popcll(firsts & ((1ull << lane) - 1))] = make_int4(at, unit < -2 ? -3 - unit : -1, field(at, 5) >> 16, 0);
+          n_units += __popcll(firsts);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int len0 = lane < n_units ? unit_at[lane].z : -1, len1 = lane + 64 < n_units ? unit_at[lane + 64].z : -1;
+        int rank0 = 0, rank1 = 0;                         // by decreasing length, ties in list order
 #pragma unroll 8
         for (int j = 0; j < 64; ++j) {
-          const int lj = __builtin_amdgcn_readlane(len, j), wj = __builtin_amdgcn_readlane(load, j);
-          item_rank += (lj > len || (lj == len && j < lane)) ? 1 : 0;
-          load_rank += (wj < load || (wj == load && j < lane)) ? 1 : 0;
+          const int l0 = __builtin_amdgcn_readlane(len0, j), l1 = __builtin_amdgcn_readlane(len1, j);
+          rank0 += (l0 > len0 || (l0 == len0 && j < lane) ? 1 : 0) + (l1 > len0 ? 1 : 0);
+          rank1 += (l0 >= len1 ? 1 : 0) + (l1 > len1 || (l1 == len1 && j < lane) ? 1 : 0);
         }
-        s_by_rank[w][item_rank] = lane | (len << 8);
+        by_len[rank0] = lane;
+        by_len[rank1] = lane + 64;
         __builtin_amdgcn_wave_barrier();
-        const int got = load_rank < n_here ? s_by_rank[w][load_rank] : 0;
-        const int got_second = __shfl(second, got & 63);
-        if (load_rank < n_here) {
-          for (int k = 0; k < (got_second >= 0 ? 2 : 1); ++k, ++taken) {
-            const int idx = k ? got_second : base + (got & 63);
-            if (last >= 0) pp.items[static_cast<int64_t>(last) * 8 + 6] = idx;
-            if (taken == 0) first3[0] = idx;
-            if (taken == 1) first3[1] = idx;
-            if (taken == 2) first3[2] = idx;
-            last = idx;
+        for (int dealt = 0; dealt < n_units; dealt += n_wg) {
+          int load_rank = 0;
+#pragma unroll 8
+          for (int j = 0; j < 64; ++j) {
+            const int wj = __builtin_amdgcn_readlane(load, j);
+            load_rank += (wj < load || (wj == load && j < lane)) ? 1 : 0;
           }
-          load += 2 * (got >> 8) + kItemFixedCostHalves;
+          if (load_rank < min(n_wg, n_units - dealt)) {
+            const int4 u = unit_at[by_len[dealt + load_rank]];
+            take(u.x, u.y, u.z);
+          }
         }
-        __builtin_amdgcn_wave_barrier();
-        base = stop ? base + __ffsll(stop) - 1 : min(base + 64, end);
+      } else {
+        // (a pair-ordered list that is not a whole number of batches starts with the short batch:
+        // the full batches that follow even the loads out again, which a short batch at the end
+        // cannot.  A list ordered by length keeps its batches aligned instead: workgroups that start
+        // equal-length items together sweep the same key ranges together and share them in L2,
+        // which is worth more there: 6 % on the dense long-window case.)
+        int n_batch = grouped && s_units[w] % n_wg ? s_units[w] % n_wg : n_wg;
+        for (int base = begin; base < end; n_batch = n_wg) {
+          // of whole pairs the next n_batch units lie within the next 64 items
+          const int unit = base + lane < end ? field(base + lane, 6) : -1, keys = base + lane < end ? field(base + lane, 5) : 0;
+          const bool first = unit < -1;
+          const int second = unit < -2 ? -3 - unit : -1;
+          const unsigned long long firsts = __ballot(first);
+          const int rank = __popcll(firsts & ((1ull << lane) - 1)), n_seen = __popcll(firsts), n_here = min(n_seen, n_batch);
+          const unsigned long long stop = __ballot(first && rank == n_batch);
+          int len = -1;                                     // lanes without a unit rank last
+          if (first && rank < n_batch) len = keys >> 16;
+          int item_rank = 0, load_rank = 0;                 // by decreasing length / increasing load, ties by lane
+#pragma unroll 8
+          for (int j = 0; j < 64; ++j) {
+            const int lj = __builtin_amdgcn_readlane(len, j), wj = __builtin_amdgcn_readlane(load, j);
+            item_rank += (lj > len || (lj == len && j < lane)) ? 1 : 0;
+            load_rank += (wj < load || (wj == load && j < lane)) ? 1 : 0;
+          }
+          s_by_rank[w][item_rank] = lane | (len << 8);
+          __builtin_amdgcn_wave_barrier();
+          const int got = load_rank < n_here ? s_by_rank[w][load_rank] : 0;
+          const int got_second = __shfl(second, got & 63);
+          if (load_rank < n_here) take(base + (got & 63), got_second, got >> 8);
+          __builtin_amdgcn_wave_barrier();
+          base = stop ? base + __ffsll(stop) - 1 : min(base + 64, end);
+        }
       }
       if (last >= 0) pp.items[static_cast<int64_t>(last) * 8 + 6] = -1;
       if (lane < kSlotsPerXcd) {

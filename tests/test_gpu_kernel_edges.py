@@ -99,6 +99,24 @@ def test_planned_attention_job_edges(cs, case):
         say(f"  -> {_attn_case(cs, np.random.default_rng(9350 + case), 'bf16', hq, hkv, 128, kv_lens, n_qs, scale_mult=mult)}")
 
 
+# Lists of up to 72 units an XCD are dealt by length over the whole list, longer ones batch by batch.
+DEALT = [
+    # Hq, Hkv, kv_lens, n_qs
+    (8, 8, [180 + 7 * (i % 40) for i in range(72)], [130 + i % 20 for i in range(72)]),                 # 72 units, ties
+    (8, 8, [180 + 7 * (i % 40) for i in range(73)], [130 + i % 20 for i in range(73)]),                 # 73
+    (28, 4, [900 + 31 * i for i in range(11)], [390 + 40 * (i % 4) for i in range(11)]),                 # pairs left over, odd row tiles
+    (16, 1, [700 + 60 * i for i in range(17)], [520 + 20 * (i % 3) if i != 5 else 0 for i in range(17)]),  # one pair left over, a stream without rows
+]
+
+
+@pytest.mark.parametrize("case", range(len(DEALT)))
+def test_planned_attention_dealt_by_length(cs, case):
+    hq, hkv, kv_lens, n_qs = DEALT[case]
+    n_qs = [min(n, k) for n, k in zip(n_qs, kv_lens)]
+    _plan_is_valid(cs, hq, hkv, kv_lens, n_qs)
+    say(f"  -> {_attn_case(cs, np.random.default_rng(9390 + case), 'bf16', hq, hkv, 128, kv_lens, n_qs)}")
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,d,kv_lens,n_qs", [
     ("bf16", 14, 2, 128, [300, 77], [40, 77]), ("bf16", 28, 4, 128, [1100], [300]), ("bf16", 8, 2, 64, [300, 77], [40, 77]),
     ("bf16", 28, 4, 128, [900, 700, 800, 640], [380, 500, 250, 400]), ("f32", 8, 2, 128, [300, 77], [40, 77])])
