@@ -406,9 +406,12 @@ int cs_kv_refresh_scatter(const void* k_new, const void* v_new, const int32_t* s
  *                (q, the caches and out are not touched and may be NULL), for callers that
  *                prefer every layer to run in REUSE mode.  Ignored where no plan is used (CS_F32, head_dim 64: an
  *                ONLY call then computes like any other).  Launches of few row tiles run without a plan as
- *                well (head_dim 128, fewer than 1,024 tiles of 128 rows by n_q, and not too long a window): a BUILD call
- *                of such a shape makes none and a REUSE call of it reads none; an ONLY call still writes the plan, so
- *                a caller of many such shapes has no use for it (BUILD at the first layer costs nothing there).
+ *                well (head_dim 128; by n_q and max_blocks, fewer than 512 tiles of 128 rows times kv heads, 768 with
+ *                more than four kv heads, 1,024 where the window is at most 512 or more than 2,048 entries, and not too
+ *                long a window): a BUILD call of such a shape makes none and a REUSE call of it reads none; an ONLY call
+ *                still writes the plan, so a caller of many such shapes has no use for it (BUILD at the first layer
+ *                costs nothing there).  These lines are measured and may move: a REUSE call always follows a BUILD or
+ *                ONLY call of its shape, whatever the shape.
  * Errors: CS_EINVAL (null pointer, negative size, n_q_heads not a multiple of n_kv_heads, unknown
  *         plan_mode, softmax_scale not a positive finite number), CS_EUNSUPPORTED (head_dim not in {64,128}, block_size != 16,
  *         n_q_heads/n_kv_heads > 16, strides not multiples of 16 bytes, unknown dtype; CS_BF16:

@@ -2249,6 +2249,13 @@ struct AttnPlan {
       off_un_head, off_st_uoff, off_hist, off_ml, off_o, total;
 };
 
+// Launches that run whole sweeps from a plan, by 128-row tiles x kv heads and key tiles of the longest window (see
+// tile_route_128).
+bool whole_sweeps(int64_t row_tiles, int key_tiles, int n_kv_heads) {
+  if (row_tiles >= 1024) return true;
+  return row_tiles >= (n_kv_heads > 4 ? 768 : 512) && key_tiles > 8 && key_tiles <= 32;
+}
+
 AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int32_t max_blocks) {
   AttnPlan a;
   a.bm = kBM;
@@ -2256,7 +2263,8 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
   a.rt_cap = a.r_cap * n_kv_heads;
   a.max_tiles = static_cast<int>((static_cast<int64_t>(max_blocks) * CS_KV_BLOCK + kBN - 1) / kBN);
   // split long key sweeps when the row tiles alone cannot fill the chip a couple of times over
-  a.span = a.rt_cap < kSpanUnits && a.max_tiles > 4 ? 1 : 0;
+  a.span = !whole_sweeps(a.rt_cap, a.max_tiles, n_kv_heads) && a.max_tiles > 4 ? 1 : 0;
+  static_assert(kSpanUnits >= 1024, "a split launch has fewer than 1,024 row tiles");
   // span plan: every cut adds an item to each row tile of a unit, and an item's list position names its partial-result slot
   a.items_cap = a.span ? a.rt_cap + 2 * 8 * kWorkgroupsPerXcd : a.rt_cap;
   a.pref_pitch = static_cast<int>(a.rt_cap / 8 + 2);
@@ -2291,12 +2299,18 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 // heads and key tiles of the longest window.  Both are the caller's upper bounds (n_q, max_blocks): the host knows no
 // other sizes, and the route has to be the same for all calls of a shape.  The row tiles that a launch then has are
 // fewer (in the runs below, with budgets 12-40 % above the rows, 0.6-0.85 of T), so a caller that budgets closer stays
-// on a route up to more work.  Below 1,024 row tiles the persistent kernel splits its sweeps and needs the merge
-// launch, and its plan costs 15-50 us a step.
-// us a layer in a step, plan not counted, persistent + merge / tile kernel (28/4 heads unless noted; T: row tiles):
-//   1,024 tiles and more       whole sweeps, no merge: T 1,044 48 / 51 (with the merge 53), T 1,076 with 50 key tiles 89 / 98
-//   kRows128 (to 1,023)        T 520 43.4 / 36.2, T 752 49.3 / 39.2, T 928 66.0 / 53.6, T 632 with 22 key tiles 50.0 / 43.5;
-//                              past 64 key tiles the split wins: T 508 with 89 91 / 112, T 564 with 121 (32 rows a wave) 137 / 167
+// on a route up to more work.  Below the lines of whole_sweeps the persistent kernel splits its sweeps and needs the merge
+// launch; its plan costs 15-50 us a step.
+// us a layer in a step, plan not counted, persistent / tile kernel (28/4 heads unless noted; T: row tiles):
+//   whole sweeps from T 1,024  T 1,044 48 / 51, T 1,076 with 50 key tiles 89 / 98
+//   ... from T 512 (768 with   no merge, and short lists are dealt by length.  us a step, plan included: T 928 1,477 / 1,751,
+//   more than four kv heads),  T 752 1,223 / 1,277, T 520 1,069 / 1,130, T 632 with 22 key tiles 1,312 / 1,398, 16/4 heads T 544
+//   9 to 32 key tiles          1,154 / 1,283, one kv head T 811 (16 layers) 856 / 1,012, 32/8 heads T 1,016 (16 layers) 960 / 1,064, T 880
+//                              912 / 948, but T 744 1,473 / 1,462 (32 layers), T 608 1,331 / 1,334.  Longer sweeps on few workgroups:
+//                              T 564 with 48 key tiles 2,158 / 2,059, T 624 with 59 2,695 / 2,682.  Below: T 472 1,250 / 1,199, T 404
+//                              1,050 / 1,000, T 460 with 40 1,935 / 1,822 (T 496 one kv head 1,100 / 1,183)
+//   kRows128 (what is left     past 64 key tiles the split wins: T 508 with 89 91 / 112, T 564 with 121 (32 rows a wave) 137 / 167
+//   to 1,023)
 //   kRows64Keys2 (to 440)      T 288 31.3 / 22.4; at T 520 its twice as many workgroups (two fit a CU) no longer all run
 //                              at once: 37.1 (kRows128 35.0); past 48 key tiles level
 //   kRows64Keys4 (to 128)      T 116 20.2 / 17.4, with 28 key tiles 28.3 / 24.9 (two groups 18.1, 28.7): one workgroup
@@ -2305,8 +2319,8 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 //   a few row tiles with long sweeps (2 key tiles > row tiles) keep the split over the whole chip (T 27 14.8 / 16.4)
 enum class TileRoute { kNone, kRows128, kRows64Keys2, kRows64Keys4 };
 
-TileRoute tile_route_128(int64_t row_tiles, int key_tiles) {
-  if (row_tiles >= 1024 || key_tiles > 64) return TileRoute::kNone;
+TileRoute tile_route_128(int64_t row_tiles, int key_tiles, int n_kv_heads) {
+  if (whole_sweeps(row_tiles, key_tiles, n_kv_heads) || key_tiles > 64) return TileRoute::kNone;
   if (row_tiles <= 128) {
     if (2 * key_tiles > (row_tiles > 16 ? row_tiles : 16)) return TileRoute::kNone;
     return key_tiles > 8 ? TileRoute::kRows64Keys4 : TileRoute::kRows64Keys2;
@@ -2425,7 +2439,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       if (plan_mode != CS_ATTN_PLAN_BUILD && plan_mode != CS_ATTN_PLAN_REUSE && plan_mode != CS_ATTN_PLAN_ONLY)
         return CS_EINVAL;
       const AttnPlan a = plan_attn(n_q, n_streams, group, n_kv_heads, max_blocks);
-      const TileRoute route = tile_route_128(a.rt_cap, a.max_tiles);
+      const TileRoute route = tile_route_128(a.rt_cap, a.max_tiles, n_kv_heads);
       if (a.items_cap * a.bm >= (1ll << 31)) return CS_EUNSUPPORTED;
       if (stride_slot >= (1ll << 26) || a.max_tiles >= (1 << 15)) return CS_EUNSUPPORTED;      // 32-bit byte offsets inside a cache block
       if (!workspace || workspace_bytes < a.total || !cs::aligned16(workspace)) return CS_EWORKSPACE;

@@ -117,6 +117,23 @@ def test_planned_attention_dealt_by_length(cs, case):
     say(f"  -> {_attn_case(cs, np.random.default_rng(9390 + case), 'bf16', hq, hkv, 128, kv_lens, n_qs)}")
 
 
+# Both sides of the lines from which whole sweeps run from a plan: row tiles x kv heads, key tiles of the longest window.
+WHOLE_SWEEPS = [
+    # Hq, Hkv, streams, rows of all streams, longest window, row tiles
+    (16, 4, 8, 3840, 700, 512), (16, 4, 8, 3839, 700, 508), (16, 4, 8, 3840, 512, 512), (16, 4, 8, 3840, 513, 512),
+    (16, 4, 8, 3840, 2048, 512), (16, 4, 8, 3840, 2049, 512), (32, 8, 6, 2880, 700, 768), (32, 8, 6, 2879, 700, 760),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,n_streams,rows,window,row_tiles", WHOLE_SWEEPS)
+def test_attention_at_the_lines_of_whole_sweeps(cs, hq, hkv, n_streams, rows, window, row_tiles):
+    n_qs = [rows // n_streams + (1 if i < rows % n_streams else 0) for i in range(n_streams)]
+    kv_lens = [max(n, window - 3 * i) for i, n in enumerate(n_qs)]
+    assert (rows * (hq // hkv) // 128 + n_streams) * hkv == row_tiles
+    _plan_is_valid(cs, hq, hkv, kv_lens, n_qs)
+    say(f"  -> {_attn_case(cs, np.random.default_rng(9400 + window + rows), 'bf16', hq, hkv, 128, kv_lens, n_qs)}")
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,d,kv_lens,n_qs", [
     ("bf16", 14, 2, 128, [300, 77], [40, 77]), ("bf16", 28, 4, 128, [1100], [300]), ("bf16", 8, 2, 64, [300, 77], [40, 77]),
     ("bf16", 28, 4, 128, [900, 700, 800, 640], [380, 500, 250, 400]), ("f32", 8, 2, 128, [300, 77], [40, 77])])
