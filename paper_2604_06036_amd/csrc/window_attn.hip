@@ -1613,12 +1613,13 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
   auto k_frag = [&](int st, int half) {
     ka[st & 3] = __builtin_bit_cast(bf16x8, reinterpret_cast<lds_u32x4*>(static_cast<uintptr_t>(k_addr[st]))[half * kHalfBytes / 16]);
   };
+  // (a row with a score that is no number has no maximum either: see past_frontier)
   auto row_max = [&](const f32x16 (&s)[RB], int rb) __attribute__((always_inline)) {
     float t = kNegInf;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) t = fmaxf(t, s[rb][r]);
+    for (int r = 0; r < 16; ++r) t = __builtin_elementwise_maximum(t, s[rb][r]);
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
-    t_max[rb] = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    t_max[rb] = __builtin_elementwise_maximum(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
   };
   auto mask = [&](f32x16 (&s)[RB], int half_tile) __attribute__((always_inline)) {
 #pragma unroll
@@ -1630,18 +1631,20 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
       }
   };
   // The scores of a half tile past some row's frontier.  Rows that see none of its keys (nor any later one) are out of
-  // the sweep: their reference maximum becomes infinite for the weights, which are 0 from here on.  Only where a
-  // frontier lies inside the half tile are scores masked one by one.  (A wave whose rows belong to two frames has
-  // frontiers thousands of keys apart, and all half tiles between them pass through here.)
+  // the sweep: their reference maximum becomes infinite for the weights, which are 0 from here on as long as the scores
+  // are finite.  Scores are masked one by one only where a frontier lies inside the half tile, or a score is infinite or
+  // no number (the row maxima keep both).  One branch for the two: a second one, or masking every half tile past a
+  // frontier, took 3-5 % of a long window's layer.  (A wave whose rows belong to two frames has frontiers thousands of
+  // keys apart, and all half tiles between them pass through here.)
   auto past_frontier = [&](f32x16 (&s)[RB], int half_tile) __attribute__((always_inline)) {
     const int j0 = 32 * half_tile;
-    bool straddles = false;
+    bool one_by_one = false;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       if (lim[rb] < j0) m_scaled[rb] = m_top[rb] = INFINITY;
-      straddles |= lim[rb] >= j0 && lim[rb] < j0 + 31;
+      one_by_one |= (lim[rb] >= j0 && lim[rb] < j0 + 31) || !(t_max[rb] < INFINITY);
     }
-    if (__ballot(straddles)) {
+    if (__ballot(one_by_one)) {
       mask(s, half_tile);
       row_max(s, 0);
       row_max(s, 1);
@@ -1704,12 +1707,12 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
     auto part_max = [&](int rb, int part) {
       float t = part ? t_max[rb] : kNegInf;
 #pragma unroll
-      for (int r = 0; r < 8; ++r) t = fmaxf(t, sn[rb][8 * part + r]);
+      for (int r = 0; r < 8; ++r) t = __builtin_elementwise_maximum(t, sn[rb][8 * part + r]);
       t_max[rb] = t;
     };
     auto swap_max = [&](int rb) {
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t_max[rb]), __float_as_uint(t_max[rb]), false, false);
-      asm("v_max_f32 %0, %1, %2" : "=v"(t_max[rb]) : "v"(sw[0]), "v"(sw[1]));      // (fmaxf would quiet each operand first)
+      t_max[rb] = __builtin_elementwise_maximum(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     };
     FENCE();
     form(0, 0);

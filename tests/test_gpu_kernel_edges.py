@@ -134,6 +134,49 @@ def test_attention_at_the_lines_of_whole_sweeps(cs, hq, hkv, n_streams, rows, wi
     say(f"  -> {_attn_case(cs, np.random.default_rng(9400 + window + rows), 'bf16', hq, hkv, 128, kv_lens, n_qs)}")
 
 
+# A key that is not finite, with finite values: on the routes of bf16 attention.  The early queries end in the half tile of
+# keys 96-127, the late ones in the window's last 80 keys; 64 rows of a wave hold some of both.
+NOT_FINITE = [
+    # Hq, Hkv, d, streams, window
+    (16, 8, 128, 64, 400),       # from a plan, whole sweeps
+    (16, 8, 128, 2, 4300),       # from a plan, split sweeps
+    (16, 8, 128, 8, 400),        # no plan
+    (8, 4, 64, 3, 400),
+]
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("case", range(len(NOT_FINITE)))
+def test_bf16_attention_key_that_is_not_finite(cs, case, bad):
+    """A key that is not finite reaches the queries that see it and no other: not those of an earlier frame in the same
+    wave (keys 127, 200 and 250), nor those just before it (the window's end)."""
+    hq, hkv, d, n_streams, window = NOT_FINITE[case]
+    rng = np.random.default_rng(9450 + case)
+    q_pos1 = np.concatenate([np.arange(100, 120), np.arange(window - 80, window)]).astype(np.int32)
+    n_tok, nb = q_pos1.size, -(-window // 16)
+    bt = rng.permutation(n_streams * nb).astype(np.int32).reshape(n_streams, nb)
+    cu = (np.arange(n_streams + 1) * n_tok).astype(np.int32)
+    q_pos = np.tile(q_pos1, n_streams)
+    kc, vc = (_pool(rng, (n_streams * nb * 16, hkv, d), "bf16") for _ in range(2))
+    q = _pool(rng, (cu[-1], hq, d), "bf16")
+    ref = oc.window_attn(hp.f64(q), hp.f64(kc), hp.f64(vc), cu, q_pos, bt, hq, 1 / math.sqrt(d))
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    wsb = cs.cs_window_prefill_attn_workspace(int(cu[-1]), n_streams, hq, hkv, d, nb, cs.CS_BF16)
+    for at in (127, 200, 250, window - 41):
+        say(f"bf16 attention, key {at} of {window} is {bad}: heads={hq}/{hkv} d={d} streams={n_streams}")
+        k_bad = kc.clone()
+        k_bad[bt[:, at // 16].astype(np.int64) * 16 + at % 16, :, 0] = bad
+        out = torch.zeros_like(q, device=DEV)
+        ws = torch.zeros((max(16, wsb),), dtype=torch.uint8, device=DEV)
+        cs.cs_window_prefill_attn(q.to(DEV), k_bad.to(DEV), vc.to(DEV), to(cu), to(q_pos), to(np.full(n_streams, window, np.int32)),
+                                  to(bt), nb, 16, out, int(cu[-1]), n_streams, hq, hkv, d, hkv * d, d, 1 / math.sqrt(d),
+                                  cs.CS_BF16, ws, wsb)
+        got, before = out.cpu(), q_pos < at
+        hp.check_attention(got[before], ref[before], "bf16")
+        if math.isnan(bad):
+            assert not torch.isfinite(got[~before].float()).any()
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,d,kv_lens,n_qs", [
     ("bf16", 14, 2, 128, [300, 77], [40, 77]), ("bf16", 28, 4, 128, [1100], [300]), ("bf16", 8, 2, 64, [300, 77], [40, 77]),
     ("bf16", 28, 4, 128, [900, 700, 800, 640], [380, 500, 250, 400]), ("f32", 8, 2, 128, [300, 77], [40, 77])])
