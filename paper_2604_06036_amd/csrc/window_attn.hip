@@ -1342,8 +1342,10 @@ __device__ __forceinline__ void unrolled(F&& f) {
   }
 }
 
-// One matrix instruction that accumulates in the accumulation registers, spelled out so that they stay there: the
-// compiler does not know it for one, so whoever reads the accumulators waits first (mfma_settle).
+// One matrix instruction that accumulates in the accumulation registers, spelled out so that they stay there.  The
+// compiler does not know it for one and keeps no distances for it: whoever reads the accumulators waits first
+// (mfma_settle), and a vector instruction that writes an operand stands two wait states or more before it by the order of
+// the slots (tests/test_matrix_waits.py checks both in the built code).
 __device__ __forceinline__ void mfma_acc(f32x16& acc, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
