@@ -169,41 +169,68 @@ struct RowTile {
   int s, kvh, q0, rows_total, r_tile;
 };
 
-// Which (stream, kv head, tile of BM rows) is workgroup b?  False: none (n_q may be an upper bound).  The streams'
-// tile counts are added up 64 streams per turn, one lane each; all lanes take the same values.  Longest sweeps of a
-// stream come first, the kv heads of a tile are neighbours, so each XCD (workgroups go round robin) serves a share
+// Which (stream, kv head, tile of BM rows) is workgroup b?  False: none (n_q may be an upper bound).  Of more than 64
+// streams each thread adds up the tiles of a few neighbours, and a scan over the workgroup finds whose streams hold the
+// tile (s_tiles: an int a thread, free again on return); a scan over 64 streams, a lane each, then finds the stream.  All
+// waves take the same values.  Longest sweeps of
+// a stream come first, the kv heads of a tile are neighbours, so each XCD (workgroups go round robin) serves a share
 // of every stream.  A list cut into one run per XCD, so that the tiles of a (stream, kv head) pair share its K and V
 // in one L2, was level when all streams are alike and 5-13 % slower when they differ: the runs then carry unequal
 // work (12 streams of 900 keys, head_dim 64: 33.4 against 30.5 us).
-template <int BM>
-__device__ __forceinline__ bool find_row_tile(const AttnParams& p, int b, RowTile& t) {
+template <int BM, int WAVES>
+__device__ __forceinline__ bool find_row_tile(const AttnParams& p, int b, int* s_tiles, RowTile& t) {
   const int lane = threadIdx.x & 63;
   const int x = b / p.n_kv_heads;
-  int64_t before = 0;
-  for (int s0 = 0; s0 < p.n_streams; s0 += 64) {
-    const int s = s0 + lane;
-    const int lo = s < p.n_streams ? p.cu_q[s] : 0;
-    const int rows = s < p.n_streams ? (p.cu_q[s + 1] - lo) * p.group : 0;
-    const int tiles = (rows + BM - 1) / BM;
-    int incl = tiles;
+  // tiles of the lanes up to and with this one
+  auto scan = [](int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8: inside each 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // row_bcast:15: lane 15 to the second 16, 47 to the fourth
+    return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // row_bcast:31: lane 31 to the upper half
+  };
+  int s0 = 0, end = p.n_streams, before = 0;
+  while (end - s0 > 64) {                  // (a second time only beyond 4,096 streams a wave)
+    const int share = (end - s0 - 1) / (64 * WAVES) + 1;
+    const int first = static_cast<int>(min(threadIdx.x * static_cast<unsigned>(share), static_cast<unsigned>(end - s0))) + s0;
+    const int mine_end = min(share, end - first);
+    int mine = 0, from = p.cu_q[first];
+    for (int k = 0; k < share; k += 4) {   // (past the thread's share: its end again, no rows)
+      int to[4];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl, off);
-      if (lane >= off) incl += v;
+      for (int i = 0; i < 4; ++i) to[i] = p.cu_q[first + min(k + i + 1, mine_end)];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        mine += ((to[i] - from) * p.group + BM - 1) / BM;
+        from = to[i];
+      }
     }
-    const unsigned long long found = __ballot(x < before + incl);
-    if (found) {
-      const int at = __ffsll(found) - 1;
-      t.s = s0 + at;
-      t.kvh = b % p.n_kv_heads;
-      t.q0 = __builtin_amdgcn_readlane(lo, at);
-      t.rows_total = __builtin_amdgcn_readlane(rows, at);
-      t.r_tile = static_cast<int>(before + __builtin_amdgcn_readlane(incl, at) - 1 - x) * BM;
-      return true;
-    }
-    before += __builtin_amdgcn_readlane(incl, 63);
+    s_tiles[threadIdx.x] = scan(mine);
+    __syncthreads();
+    int w = 0;
+    while (w < WAVES && x >= before + s_tiles[64 * w + 63]) before += s_tiles[64 * w++ + 63];
+    if (w == WAVES) return false;
+    const int incl = s_tiles[64 * w + lane];
+    const int at = __ffsll(__ballot(x < before + incl)) - 1;
+    if (at > 0) before += __builtin_amdgcn_readlane(incl, at - 1);
+    s0 += (64 * w + at) * share;
+    end = min(share, end - s0) + s0;
+    __syncthreads();                       // (s_tiles may be written again)
   }
-  return false;
+  const int s = s0 + lane;
+  const int lo = s < end ? p.cu_q[s] : 0;
+  const int rows = s < end ? (p.cu_q[s + 1] - lo) * p.group : 0;
+  const int incl = scan((rows + BM - 1) / BM);
+  const unsigned long long found = __ballot(x < before + incl);
+  if (!found) return false;
+  const int at = __ffsll(found) - 1;
+  t.s = s0 + at;
+  t.kvh = b % p.n_kv_heads;
+  t.q0 = __builtin_amdgcn_readlane(lo, at);
+  t.rows_total = __builtin_amdgcn_readlane(rows, at);
+  t.r_tile = (before + __builtin_amdgcn_readlane(incl, at) - 1 - x) * BM;
+  return true;
 }
 
 // bf16, one launch and no plan: a workgroup = one tile of 32 ROWW rows of one (stream, kv head), its waves
@@ -251,7 +278,7 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 
   if (p.clear_status && blockIdx.x == 0 && threadIdx.x == 0) *p.ws_status = 0;
   RowTile t;
-  if (!find_row_tile<BM>(p, blockIdx.x, t)) return;
+  if (!find_row_tile<BM, ROWW * KG>(p, blockIdx.x, reinterpret_cast<int*>(&s_kv[0][0][0][0]), t)) return;
   const int s = __builtin_amdgcn_readfirstlane(t.s), kvh = __builtin_amdgcn_readfirstlane(t.kvh);
   const int q0 = __builtin_amdgcn_readfirstlane(t.q0), rows_total = __builtin_amdgcn_readfirstlane(t.rows_total);
   const int r_tile = __builtin_amdgcn_readfirstlane(t.r_tile);
@@ -2083,7 +2110,7 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void window_attn_f32_kernel(Attn
   const int n = lane & 31, h = lane >> 5;
 
   RowTile rt;
-  if (!find_row_tile<kF32Rows>(p, blockIdx.x, rt)) return;
+  if (!find_row_tile<kF32Rows, kF32Waves>(p, blockIdx.x, reinterpret_cast<int*>(&s_o[0][0][0]), rt)) return;
   const int s = __builtin_amdgcn_readfirstlane(rt.s), kvh = __builtin_amdgcn_readfirstlane(rt.kvh);
   const int q0 = __builtin_amdgcn_readfirstlane(rt.q0), rows_total = __builtin_amdgcn_readfirstlane(rt.rows_total);
   const int r_tile = __builtin_amdgcn_readfirstlane(rt.r_tile);
@@ -2322,10 +2349,18 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 //                              per CU, all of them run at once and the longest sweep is the time; up to 8 key tiles two
 //                              groups are enough (300 keys 11.0 / 12.2, persistent 16.3)
 //   a few row tiles with long sweeps (2 key tiles > row tiles) keep the split over the whole chip (T 27 14.8 / 16.4)
+//   single_tiles: whole        Up to 128 rows a stream and kv head on average.  The persistent kernel's jobs of 256 rows then hold one row tile,
+//   sweeps, but one row tile   two of its four waves, and a plan orders nothing.  us a layer, persistent of 32 rows a wave, two workgroups a CU
+//   a stream (kRows128)        (no longer here) / of 64 / tile: 18 tokens of 28/4 heads, 263 streams of 290 keys 45 / 63 / 51, of 550 88.5 / 99 / 95,
+//                              of 1,000 144 / 153 / 145, 65 of 900 37 / 52 / 37, 1,025 of 550 309 / 314 / 316; 32 tokens of 32/8, 64 of 900 49 / 56 / 46;
+//                              5 tokens of 28/4, 263 of 550 65 / 89 / 68; 4,000 to 8,300 keys 1 to 8 % below either.  Plans of 27-38 us (1,025 streams 97
+//                              and 129) are not counted.  160 streams, every eighth of 118 tokens, the others of 2: 900 keys 92 / 104 / 91.  From two row
+//                              tiles a stream on the persistent kernel wins: 27 tokens, 129 streams of 550 keys 53 / 58 / 72
 enum class TileRoute { kNone, kRows128, kRows64Keys2, kRows64Keys4 };
 
-TileRoute tile_route_128(int64_t row_tiles, int key_tiles, int n_kv_heads) {
-  if (whole_sweeps(row_tiles, key_tiles, n_kv_heads) || key_tiles > 64) return TileRoute::kNone;
+TileRoute tile_route_128(int64_t row_tiles, int key_tiles, int n_kv_heads, bool single_tiles) {
+  if (whole_sweeps(row_tiles, key_tiles, n_kv_heads)) return single_tiles ? TileRoute::kRows128 : TileRoute::kNone;
+  if (key_tiles > 64) return TileRoute::kNone;
   if (row_tiles <= 128) {
     if (2 * key_tiles > (row_tiles > 16 ? row_tiles : 16)) return TileRoute::kNone;
     return key_tiles > 8 ? TileRoute::kRows64Keys4 : TileRoute::kRows64Keys2;
@@ -2444,7 +2479,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       if (plan_mode != CS_ATTN_PLAN_BUILD && plan_mode != CS_ATTN_PLAN_REUSE && plan_mode != CS_ATTN_PLAN_ONLY)
         return CS_EINVAL;
       const AttnPlan a = plan_attn(n_q, n_streams, group, n_kv_heads, max_blocks);
-      const TileRoute route = tile_route_128(a.rt_cap, a.max_tiles, n_kv_heads);
+      const TileRoute route = tile_route_128(a.rt_cap, a.max_tiles, n_kv_heads, n_q * group <= static_cast<int64_t>(a.bm) * n_streams);
       if (a.items_cap * a.bm >= (1ll << 31)) return CS_EUNSUPPORTED;
       if (stride_slot >= (1ll << 26) || a.max_tiles >= (1 << 15)) return CS_EUNSUPPORTED;      // 32-bit byte offsets inside a cache block
       if (!workspace || workspace_bytes < a.total || !cs::aligned16(workspace)) return CS_EWORKSPACE;

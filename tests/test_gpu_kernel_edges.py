@@ -134,6 +134,25 @@ def test_attention_at_the_lines_of_whole_sweeps(cs, hq, hkv, n_streams, rows, wi
     say(f"  -> {_attn_case(cs, np.random.default_rng(9400 + window + rows), 'bf16', hq, hkv, 128, kv_lens, n_qs)}")
 
 
+# Many streams of at most one row tile: the search for a workgroup's row tile in one, two and three steps (64 streams; 64 for
+# each thread of the workgroup), streams without rows at either end, and both sides of 128 rows a stream.
+MANY_STREAMS = [
+    # dtype, Hq, Hkv, d, streams, n_qs (repeated), window
+    ("bf16", 32, 16, 128, 64, [64], 130), ("bf16", 32, 16, 128, 65, [0, 64, 128, 64], 130), ("bf16", 32, 16, 128, 65, [65, 64], 130),
+    ("bf16", 20, 4, 128, 257, [0, 3, 25, 1], 90), ("bf16", 8, 1, 128, 1100, [16, 1, 0, 5], 40), ("bf16", 1, 1, 128, 16385, [0, 1, 2], 20),
+    ("bf16", 2, 1, 64, 257, [0, 3, 90, 1], 90), ("bf16", 1, 1, 64, 32770, [0, 1], 17), ("f32", 2, 1, 64, 513, [0, 3, 20, 1], 40),
+]
+
+
+@pytest.mark.parametrize("case", range(len(MANY_STREAMS)))
+def test_attention_of_many_streams(cs, case):
+    dtype, hq, hkv, d, n_streams, n_qs, window = MANY_STREAMS[case]
+    say(f"attention of many streams {case}: {dtype} heads={hq}/{hkv} d={d} streams={n_streams}")
+    n_qs = [n_qs[i % len(n_qs)] for i in range(n_streams)]
+    kv_lens = [max(n_qs[s], window - s % 13) for s in range(n_streams)]
+    say(f"  -> {_attn_case(cs, np.random.default_rng(9470 + case), dtype, hq, hkv, d, kv_lens, n_qs)}")
+
+
 # A key that is not finite, with finite values: on the routes of bf16 attention.  The early queries end in the half tile of
 # keys 96-127, the late ones in the window's last 80 keys; 64 rows of a wave hold some of both.
 NOT_FINITE = [
