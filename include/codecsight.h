@@ -395,7 +395,7 @@ int cs_kv_refresh_scatter(const void* k_new, const void* v_new, const int32_t* s
  *  workspace     cs_window_prefill_attn_workspace() bytes for the same shape arguments, 16-byte
  *                aligned (may be 0, then NULL is accepted).  Holds the work plan of the launch
  *                (the list of (stream, kv head, row tile, key range) items each XCD serves, a
- *                function of cu_q, q_pos and block_table only) and the partial results of row
+ *                function of cu_q, q_pos, kv_len and max_blocks only) and the partial results of row
  *                tiles whose key sweep is shared by several items.  Two calls that overlap in
  *                time must not share a workspace.
  *  plan_mode     CS_ATTN_PLAN_BUILD: workspace contents need not be initialised; the call plans

@@ -646,9 +646,8 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 // the item the same workgroup takes next (-1: none), [7] first row of the item's partial result in
 // the workspace, or -1 when the item covers the whole sweep and writes `out`.
 // Plan header (ints): [0..8] list offsets per XCD, [9] row tiles, [16..23] end item,
-// then one 32-int entry per workgroup j of XCD x at [32 + 32 (64 x + j)]: [0..2] its first three
-// items (-1: none), [3] cache block of its first item's frontier, [4..7] cache blocks of its first
-// tile request (one per wave), [8..15] a copy of its first item's descriptor, [16] its item count.
+// then one 32-int entry per workgroup j of XCD x at [32 + 32 (64 x + j)]: [0] its first item (-1: none),
+// [8..15] a copy of that item's descriptor (all that the workgroup reads of its entry).
 // Entries from kWorkgroupsPerXcd on name no item.
 constexpr int kSlotsPerXcd = 64;      // header entries per XCD
 constexpr int kWorkgroupsPerXcd = 32; // persistent workgroups per XCD: one per CU
@@ -672,7 +671,6 @@ constexpr int kSortMax = 2048;        // streams sorted by work in LDS; beyond, 
 struct PlanParams {
   const int32_t* __restrict__ cu_q;
   const int32_t* __restrict__ q_pos;
-  const int32_t* __restrict__ block_table;
   const int32_t* __restrict__ kv_len;
   int32_t max_blocks;
   int32_t n_streams, group, n_kv_heads, max_tiles, r_cap, bm, n_slots, hist_pitch;   // n_slots: workgroups per XCD
@@ -911,17 +909,8 @@ __device__ void plan_spans(const PlanParams& pp, int n_rt, int n_un, int* s_wave
     }
   }
   int32_t* hd = pp.header + kHdrHeads + kHdrEntryInts * (x * kSlotsPerXcd + j);
-  int32_t ids[4] = {0, 0, 0, 0}, last_id = 0;
-  if (count > 0) {
-    const int32_t* row = pp.block_table + static_cast<int64_t>(d_first[3] >> 8) * pp.max_blocks;
-    const int last_blk = max(d_first[4], 0) >> 4;
-    for (int i = 0; i < 4; ++i) ids[i] = row[min((d_first[5] & 0xffff) * 4 + i, last_blk)];
-    last_id = row[last_blk];
-  }
-  hd[0] = count > 0 ? first : -1; hd[1] = count > 1 ? first + 1 : -1; hd[2] = count > 2 ? first + 2 : -1; hd[3] = last_id;
-  for (int i = 0; i < 4; ++i) hd[4 + i] = ids[i];
+  hd[0] = count > 0 ? first : -1;
   for (int i = 0; i < 8; ++i) hd[8 + i] = d_first[i];
-  hd[16] = count;
 }
 
 __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanParams pp) {
@@ -1171,17 +1160,15 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
       const int begin = s_list_off[w], end = s_list_off[w + 1];
       const int n_wg = pp.n_slots;
       int load = lane < n_wg ? 0 : 0x7fffffff;          // half key tiles; lanes beyond the grid rank last
-      int last = -1, first3[3] = {-1, -1, -1}, taken = 0;
+      int first_item = -1, last = -1;
       auto field = [&](int i, int k) {
         return __hip_atomic_load(&pp.items[static_cast<int64_t>(i) * 8 + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       };
-      auto take = [&](int first_item, int second_item, int tiles) {
-        for (int k = 0; k < (second_item >= 0 ? 2 : 1); ++k, ++taken) {
-          const int idx = k ? second_item : first_item;
+      auto take = [&](int item, int second_item, int tiles) {
+        for (int k = 0; k < (second_item >= 0 ? 2 : 1); ++k) {
+          const int idx = k ? second_item : item;
           if (last >= 0) pp.items[static_cast<int64_t>(last) * 8 + 6] = idx;
-          if (taken == 0) first3[0] = idx;
-          if (taken == 1) first3[1] = idx;
-          if (taken == 2) first3[2] = idx;
+          else first_item = idx;
           last = idx;
         }
         load += 2 * tiles + kItemFixedCostHalves;
@@ -1266,20 +1253,10 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
       if (lane < kSlotsPerXcd) {
         int32_t* hd = pp.header + kHdrHeads + kHdrEntryInts * (w * kSlotsPerXcd + lane);
         int32_t d[8] = {0, 0, 0, 0, -1, 0, -1, -1};       // the end item
-        int32_t ids[4] = {0, 0, 0, 0}, last_id = 0;
-        if (taken > 0) {
-          for (int i = 0; i < 8; ++i)
-            d[i] = __hip_atomic_load(&pp.items[static_cast<int64_t>(first3[0]) * 8 + i], __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
-          const int32_t* row = pp.block_table + static_cast<int64_t>(d[3] >> 8) * pp.max_blocks;
-          const int last_blk = d[4] >> 4;
-          for (int i = 0; i < 4; ++i) ids[i] = row[min((d[5] & 0xffff) * 4 + i, last_blk)];
-          last_id = row[last_blk];
-        }
-        hd[0] = first3[0]; hd[1] = first3[1]; hd[2] = first3[2]; hd[3] = last_id;
-        for (int i = 0; i < 4; ++i) hd[4 + i] = ids[i];
+        if (first_item >= 0)
+          for (int i = 0; i < 8; ++i) d[i] = field(first_item, i);
+        hd[0] = first_item;
         for (int i = 0; i < 8; ++i) hd[8 + i] = d[i];
-        hd[16] = taken;
       }
     }
   }
@@ -1459,7 +1436,6 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
     return idx >= 0 ? p.ws_items + static_cast<int64_t>(idx) * 8 : p.ws_plan + kHdrEndItem;
   };
   const int32_t* entry = p.ws_plan + kHdrHeads + kHdrEntryInts * (xcd * kSlotsPerXcd + slot_j);
-  const i32x8 e0 = const_load8(entry);
   i32x8 d = const_load8(entry + 8);
   if ((d[5] >> 16) == 0) return;        // nothing for this workgroup
 
@@ -1478,12 +1454,6 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
   // tile requests: instruction i of a tensor moves rows 4 i + l_row of this wave's cache block; which 16-byte chunk
   auto k_chunk = [&](int i) __attribute__((always_inline)) { return static_cast<uint32_t>((l_pos ^ (4 * i + l_row)) * 16); };
   auto v_chunk = [&](int i) __attribute__((always_inline)) { return static_cast<uint32_t>((l_pos ^ (4 * l_row + 2 * (i & 1))) * 16); };
-  uint32_t kv_off[2 * IPW];
-#pragma unroll
-  for (int i = 0; i < IPW; ++i) {
-    kv_off[i] = (4 * i + l_row) * row_bytes + k_chunk(i);
-    kv_off[IPW + i] = (4 * i + l_row) * row_bytes + v_chunk(i);
-  }
   uint32_t k_addr[STEPS], v_addr[DB];   // LDS byte addresses of this lane's fragments in the current stage
 #pragma unroll
   for (int st = 0; st < STEPS; ++st)
@@ -2509,7 +2479,6 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
         PlanParams pp;
         pp.cu_q = cu_q;
         pp.q_pos = q_pos;
-        pp.block_table = block_table;
         pp.kv_len = kv_len;
         pp.max_blocks = max_blocks;
         pp.n_streams = n_streams;
