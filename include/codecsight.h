@@ -408,10 +408,13 @@ int cs_kv_refresh_scatter(const void* k_new, const void* v_new, const int32_t* s
  *                ONLY call then computes like any other).  Launches of few row tiles run without a plan as
  *                well (head_dim 128; by n_q and max_blocks, fewer than 512 tiles of 128 rows times kv heads, 768 with
  *                more than four kv heads, 1,024 where the window is at most 512 or more than 2,048 entries, and not too
- *                long a window): a BUILD call of such a shape makes none and a REUSE call of it reads none; an ONLY call
- *                still writes the plan, so a caller of many such shapes has no use for it (BUILD at the first layer
- *                costs nothing there).  These lines are measured and may move: a REUSE call always follows a BUILD or
- *                ONLY call of its shape, whatever the shape.
+ *                long a window), and so do larger ones with at most 128 rows (n_q times query heads of a kv group) a
+ *                stream on average and windows that would not be split: a BUILD call of such a shape makes no plan and
+ *                a REUSE call of it reads none; an ONLY call still writes the plan, so a caller of many such shapes has
+ *                no use for it (BUILD at the first layer costs nothing there).  Of shapes with a plan below 1,024 row
+ *                tiles a BUILD call makes it beside its own work, which does not use it: its results and those of a
+ *                REUSE call are those of two kernels (the same precision, not the same bits).  These lines are measured
+ *                and may move: a REUSE call always follows a BUILD or ONLY call of its shape, whatever the shape.
  * Errors: CS_EINVAL (null pointer, negative size, n_q_heads not a multiple of n_kv_heads, unknown
  *         plan_mode, softmax_scale not a positive finite number), CS_EUNSUPPORTED (head_dim not in {64,128}, block_size != 16,
  *         n_q_heads/n_kv_heads > 16, strides not multiples of 16 bytes, unknown dtype; CS_BF16:
@@ -441,8 +444,8 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  *
  * Exactly cs_kv_refresh_scatter(k_new, v_new, slot, ..., n_tok, ...) followed by
  * cs_window_prefill_attn(q, ..., plan_mode, ...) on the same layer, same arguments, same results
- * bit for bit.  CS_BF16 with head_dim 128, where attention runs from a plan (below 1,024 row tiles it
- * may not, see cs_window_prefill_attn): ONE launch: every workgroup of the persistent attention
+ * bit for bit.  CS_BF16 with head_dim 128, where attention runs from a plan and has at least 1,024 row tiles or
+ * splits its sweeps (see cs_window_prefill_attn): ONE launch: every workgroup of the persistent attention
  * grid first moves its share of the new rows (stores written through to memory at device scope),
  * the grid meets at a launch-wide barrier, then attention proceeds as in cs_window_prefill_attn; a
  * CS_ATTN_PLAN_BUILD call is preceded by the planning launch, a CS_ATTN_PLAN_ONLY call plans and

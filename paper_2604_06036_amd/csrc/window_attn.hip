@@ -253,8 +253,13 @@ __device__ __forceinline__ int v_swizzle(int r) {
   return D == 128 ? 4 * (r & 3) + 2 * ((r >> 2) & 1) : 4 * ((r >> 1) & 1) + 2 * ((r >> 2) & 1);
 }
 
+template <int D, int KG, int STAGES>
+struct TileStages {
+  __attribute__((aligned(1024))) uint16_t kv[KG][STAGES][2][kBN * D];
+};
+
 template <int D, int ROWW, int KG, int STAGES>
-__global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_bf16_tile_kernel(AttnParams p) {
+__device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, TileStages<D, KG, STAGES>& stages) {
   constexpr int BM = 32 * ROWW;
   constexpr int STEPS = D / 16, DB = D / 32;
   constexpr int TILE = kBN * D;        // elements of one K (or V) tile, unpadded
@@ -265,7 +270,7 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
   constexpr int IPB = IPW / BPW;       // its DMA instructions per block
   static_assert(BPW >= 1 && IPB * RPD == CS_KV_BLOCK, "a DMA instruction stays inside a cache block");
 
-  __shared__ __attribute__((aligned(1024))) uint16_t s_kv[KG][STAGES][2][TILE];
+  auto& s_kv = stages.kv;
   constexpr bool SPREAD = KG > 2;      // the merge of the groups is shared by all waves (see there)
   __shared__ float s_ml[SPREAD ? KG : 1][ROWW][2][64];
   static_assert(KG == 1 || KG == 2 || KG == DB, "of four groups each finishes one block of columns");
@@ -276,9 +281,9 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
   const int rw = wave % ROWW, kg = wave / ROWW;
   const int n = lane & 31, h = lane >> 5;
 
-  if (p.clear_status && blockIdx.x == 0 && threadIdx.x == 0) *p.ws_status = 0;
+  if (p.clear_status && block == 0 && threadIdx.x == 0) *p.ws_status = 0;
   RowTile t;
-  if (!find_row_tile<BM, ROWW * KG>(p, blockIdx.x, reinterpret_cast<int*>(&s_kv[0][0][0][0]), t)) return;
+  if (!find_row_tile<BM, ROWW * KG>(p, block, reinterpret_cast<int*>(&s_kv[0][0][0][0]), t)) return;
   const int s = __builtin_amdgcn_readfirstlane(t.s), kvh = __builtin_amdgcn_readfirstlane(t.kvh);
   const int q0 = __builtin_amdgcn_readfirstlane(t.q0), rows_total = __builtin_amdgcn_readfirstlane(t.rows_total);
   const int r_tile = __builtin_amdgcn_readfirstlane(t.r_tile);
@@ -407,6 +412,9 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
   // keys 883 / 865, 3 streams, 8/1 heads 617 / 608; one stream, 32/8 heads level.
   if (SPREAD && kg >= KG / 2) __syncthreads();
   const int n_trips = (n_key_tiles + KG - 1) / KG;
+  // The loop stands in a fixed place relative to the 64-byte lines that instructions are fetched by: the same instructions
+  // 4 bytes off those of 8 bytes took 4-5 % longer (2 streams of 3,700 keys, 28/4 heads 90.8 us a layer instead of 86.6).
+  asm volatile(".p2align 6");
   for (int trip = 0; trip < n_trips; ++trip, kt += KG) {
     wait_vmcnt<0>();
     __syncthreads();       // one stage: K has landed, every wave is done with the previous V; two: the tile, the other stage
@@ -623,6 +631,12 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
   }
 }
 
+template <int D, int ROWW, int KG, int STAGES>
+__global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_bf16_tile_kernel(AttnParams p) {
+  __shared__ TileStages<D, KG, STAGES> stages;
+  attend_row_tile<D, ROWW, KG, STAGES>(p, blockIdx.x, stages);
+}
+
 // =============================================================================================
 // bf16 / head_dim 128: planned, persistent kernel
 //
@@ -690,7 +704,8 @@ struct PlanParams {
   int32_t* sw_pref;     // [8][pref_pitch] span plan: cost prefix of each XCD's sweeps
 };
 
-// Exclusive prefix sum over the kPlanThreads threads of the planning workgroup.
+// Exclusive prefix sum over the THREADS threads of the planning workgroup.
+template <int THREADS>
 __device__ __forceinline__ int plan_block_scan(int v, int* s_wave, int& total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int incl = v;
@@ -703,7 +718,7 @@ __device__ __forceinline__ int plan_block_scan(int v, int* s_wave, int& total) {
   if (lane == 63) s_wave[w] = incl;
   __syncthreads();
   int base = 0, sum = 0;
-  for (int i = 0; i < kPlanThreads / 64; ++i) {
+  for (int i = 0; i < THREADS / 64; ++i) {
     const int t = s_wave[i];
     if (i < w) base += t;
     sum += t;
@@ -850,7 +865,7 @@ __device__ void plan_spans(const PlanParams& pp, int n_rt, int n_un, int* s_wave
     count += kb < n_kt2 ? 2 : 1;
   }
   int total_items;
-  const int first = plan_block_scan(tid < 512 ? count : 0, s_wave, total_items);
+  const int first = plan_block_scan<kPlanThreads>(tid < 512 ? count : 0, s_wave, total_items);
   if (tid < 512 && j == 0) pp.header[x] = first;
   if (tid == 0) {
     pp.header[8] = total_items;
@@ -913,46 +928,68 @@ __device__ void plan_spans(const PlanParams& pp, int n_rt, int n_un, int* s_wave
   for (int i = 0; i < 8; ++i) hd[8 + i] = d_first[i];
 }
 
-__global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanParams pp) {
-  __shared__ int s_wave[kPlanThreads / 64];
-  __shared__ __attribute__((aligned(16))) unsigned long long s_key[kSortMax];
-  static_assert(kDealAtOnce <= 128 && sizeof(int4) * 8 * 128 <= sizeof(s_key), "the deal keeps its units there");
-  __shared__ int s_list_off[9];
-  __shared__ int s_left_tiles[8], s_left_end[8];   // pairs left over by whole rounds: row tiles; last row tile + pair
-  __shared__ int s_by_rank[8][64];      // deal: lane (and length) of the item of each rank, per XCD
-  __shared__ PlanUnit s_unit[kSpanUnits];
-  __shared__ int s_units[8];            // units in each XCD's list
-  __shared__ int s_deal[8][128];       // deal at once: units by length
-  __shared__ int s_cut[8][kSlotsPerXcd + 1];   // span plan: first tile position of every workgroup's span
+// What planning keeps in LDS.
+struct PlanLds {
+  unsigned long long key[kSortMax];
+  int wave[kPlanThreads / 64];
+  int list_off[9];
+  int left_tiles[8], left_end[8];   // pairs left over by whole rounds: row tiles; last row tile + pair
+  int by_rank[8][64];      // deal: lane (and length) of the item of each rank, per XCD
+  int units[8];            // units in each XCD's list
+  int deal[8][128];        // deal at once: units by length
+};
+static_assert(kDealAtOnce <= 128 && sizeof(int4) * 8 * 128 <= sizeof(PlanLds::key), "the deal keeps its units there");
+// ... and the span plan besides
+struct SpanLds {
+  PlanUnit unit[kSpanUnits];
+  int cut[8][kSlotsPerXcd + 1];     // first tile position of every workgroup's span
+};
+
+template <int THREADS, bool SPAN>
+__device__ __forceinline__ void plan_work(const PlanParams& pp, PlanLds& lds, SpanLds* span_lds) {
+  auto& s_key = lds.key;
+  auto& s_wave = lds.wave;
+  auto& s_list_off = lds.list_off;
+  auto& s_left_tiles = lds.left_tiles;
+  auto& s_left_end = lds.left_end;
+  auto& s_by_rank = lds.by_rank;
+  auto& s_units = lds.units;
+  auto& s_deal = lds.deal;
   const int tid = threadIdx.x;
   const int hist_pitch = pp.hist_pitch;
 
   // ---- clear counters; row tiles per stream
   if (tid < 8) s_units[tid] = 0;
-  for (int i = tid; i < 8 * hist_pitch; i += kPlanThreads) pp.hist[i] = 0;
+  for (int i = tid; i < 8 * hist_pitch; i += THREADS) pp.hist[i] = 0;
+  int* s_toff = reinterpret_cast<int*>(s_key);           // the streams' first row tiles are searched in LDS if they fit
+  const bool in_lds = pp.n_streams <= 2 * kSortMax;
+  int* s_work = &s_deal[0][0];                           // ... and their work is summed up there
+  const bool work_in_lds = pp.n_streams <= 8 * 128;
   int carry = 0;
-  for (int s0 = 0; s0 < pp.n_streams; s0 += kPlanThreads) {
+  for (int s0 = 0; s0 < pp.n_streams; s0 += THREADS) {
     const int s = s0 + tid;
     int tiles = 0;
     if (s < pp.n_streams) {
       const int rows = plan_stream_rows(pp, s);
       tiles = (rows + pp.bm - 1) / pp.bm;
-      pp.st_work[s] = 0;
+      if (work_in_lds) s_work[s] = 0;
+      else pp.st_work[s] = 0;
     }
     int total;
-    const int excl = plan_block_scan(tiles, s_wave, total);
+    const int excl = plan_block_scan<THREADS>(tiles, s_wave, total);
     if (s < pp.n_streams) pp.st_toff[s] = carry + excl;
+    if (s < pp.n_streams && in_lds) s_toff[s] = carry + excl;
     carry += total;
   }
   const int n_rt = carry;                // row tiles per kv head
   if (tid == 0) pp.st_toff[pp.n_streams] = n_rt;
   // units: two neighbouring row tiles of a stream, counted from its end (an odd one out is the stream's first)
   int n_un = 0;
-  for (int s0 = 0; s0 < pp.n_streams; s0 += kPlanThreads) {
+  for (int s0 = 0; s0 < pp.n_streams; s0 += THREADS) {
     const int s = s0 + tid;
     const int tiles = s < pp.n_streams ? (plan_stream_rows(pp, s) + pp.bm - 1) / pp.bm : 0;
     int total;
-    const int excl = plan_block_scan((tiles + 1) >> 1, s_wave, total);
+    const int excl = plan_block_scan<THREADS>((tiles + 1) >> 1, s_wave, total);
     if (s < pp.n_streams) pp.st_uoff[s] = n_un + excl;
     n_un += total;
   }
@@ -960,11 +997,11 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
   __syncthreads();
 
   // ---- per row tile: its stream, its causal frontier; work per stream
-  for (int r = tid; r < n_rt; r += kPlanThreads) {
+  for (int r = tid; r < n_rt; r += THREADS) {
     int lo = 0, hi = pp.n_streams;       // last stream whose first row tile is <= r
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
-      if (pp.st_toff[mid] <= r) lo = mid; else hi = mid;
+      if ((in_lds ? s_toff[mid] : pp.st_toff[mid]) <= r) lo = mid; else hi = mid;
     }
     const int s = lo;
     const int t = r - pp.st_toff[s];
@@ -977,28 +1014,31 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
     pp.rt_wgmax[r] = wg_max;
     const int tiles_s = pp.st_toff[s + 1] - pp.st_toff[s];
     if (((tiles_s - 1 - t) & 1) == 0) pp.un_head[pp.st_uoff[s] + (t >> 1)] = r;
-    atomicAdd(&pp.st_work[s], max(wg_max, 0) / kBN + 1);
+    if (work_in_lds) atomicAdd(&s_work[s], max(wg_max, 0) / kBN + 1);
+    else atomicAdd(&pp.st_work[s], max(wg_max, 0) / kBN + 1);
   }
   __threadfence_block();
   __syncthreads();
 
-  if (pp.span) {
-    plan_spans(pp, n_rt, n_un, s_wave, s_cut, reinterpret_cast<int*>(s_key), s_unit);    // s_key is unused on this route
-    return;
+  if constexpr (SPAN) {
+    if (pp.span) {
+      plan_spans(pp, n_rt, n_un, s_wave, span_lds->cut, reinterpret_cast<int*>(s_key), span_lds->unit);    // s_key is unused on this route
+      return;
+    }
   }
 
   // ---- rank streams by decreasing work (ties: stream order)
   if (pp.n_streams <= kSortMax) {
     int n_sort = 1;
     while (n_sort < pp.n_streams) n_sort <<= 1;
-    for (int i = tid; i < n_sort; i += kPlanThreads)
+    for (int i = tid; i < n_sort; i += THREADS)
       s_key[i] = i < pp.n_streams
-                     ? (static_cast<unsigned long long>(0x7fffffff - __hip_atomic_load(&pp.st_work[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) << 32) | static_cast<unsigned>(i)
+                     ? (static_cast<unsigned long long>(0x7fffffff - (work_in_lds ? s_work[i] : __hip_atomic_load(&pp.st_work[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) << 32) | static_cast<unsigned>(i)
                      : ~0ull;
     __syncthreads();
     for (int k = 2; k <= n_sort; k <<= 1)
       for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int i = tid; i < n_sort; i += kPlanThreads) {
+        for (int i = tid; i < n_sort; i += THREADS) {
           const int partner = i ^ j;
           if (partner > i) {
             const unsigned long long a = s_key[i], b = s_key[partner];
@@ -1008,10 +1048,10 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
         }
         __syncthreads();
       }
-    for (int i = tid; i < pp.n_streams; i += kPlanThreads)
+    for (int i = tid; i < pp.n_streams; i += THREADS)
       pp.st_rank[static_cast<unsigned>(s_key[i] & 0xffffffffu)] = i;
   } else {
-    for (int i = tid; i < pp.n_streams; i += kPlanThreads) pp.st_rank[i] = i;
+    for (int i = tid; i < pp.n_streams; i += THREADS) pp.st_rank[i] = i;
   }
   __threadfence_block();
   __syncthreads();
@@ -1058,7 +1098,7 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
     bucket = pp.max_tiles + 1 - min(max(pp.rt_wgmax[head], 0) / kBN + 1, pp.max_tiles + 1);
     return ((pp.st_uoff[s] + ((head - pp.st_toff[s]) >> 1)) * pp.n_kv_heads + kvh) & 7;
   };
-  for (int r = tid; r < n_rt; r += kPlanThreads)
+  for (int r = tid; r < n_rt; r += THREADS)
     for (int kvh = 0; kvh < pp.n_kv_heads; ++kvh) {
       int bucket;
       const int x = place(r, pp.rt_stream[r], kvh, bucket);
@@ -1069,8 +1109,8 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
 
   // ---- per XCD (one wave each): first list position of every bucket
   {
-    const int w = tid >> 6, lane = tid & 63;
-    if (w < 8) {
+    const int lane = tid & 63;
+    for (int w = tid >> 6; w < 8; w += THREADS / 64) {
       int* hx = pp.hist + w * hist_pitch;
       int run = 0;
       for (int k0 = 0; k0 < hist_pitch; k0 += 64) {
@@ -1099,15 +1139,15 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
     pp.header[kHdrEndItem + 6] = -1;
     pp.header[kHdrEndItem + 7] = -1;
   }
-  for (int i = tid; i < kSyncInts; i += kPlanThreads) pp.header[kHdrSyncBase + i] = 0;
+  for (int i = tid; i < kSyncInts; i += THREADS) pp.header[kHdrSyncBase + i] = 0;
   __threadfence_block();
   __syncthreads();
 
   // ---- write the items (row-tile slots beyond the planned ones are marked unsplit, so that the
   //      merge kernel needs no other bound than the size of its grid)
-  for (int i = n_rt * pp.n_kv_heads + tid; i < pp.r_cap * pp.n_kv_heads; i += kPlanThreads)
+  for (int i = n_rt * pp.n_kv_heads + tid; i < pp.r_cap * pp.n_kv_heads; i += THREADS)
     pp.rt_desc[static_cast<int64_t>(i) * 8 + 4] = 0;
-  for (int r = tid; r < n_rt; r += kPlanThreads) {
+  for (int r = tid; r < n_rt; r += THREADS) {
     const int s = pp.rt_stream[r];
     const int t = r - pp.st_toff[s];
     const int q0 = pp.cu_q[s];
@@ -1155,8 +1195,8 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
   //      would produce, fixed here so that the attention kernel needs no atomics.  Items of one
   //      workgroup are chained through their `next` field.
   {
-    const int w = tid >> 6, lane = tid & 63;
-    if (w < 8) {
+    const int lane = tid & 63;
+    for (int w = tid >> 6; w < 8; w += THREADS / 64) {
       const int begin = s_list_off[w], end = s_list_off[w + 1];
       const int n_wg = pp.n_slots;
       int load = lane < n_wg ? 0 : 0x7fffffff;          // half key tiles; lanes beyond the grid rank last
@@ -1197,17 +1237,22 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
         int rank0 = 0, rank1 = 0;                         // by decreasing length, ties in list order
 #pragma unroll 8
         for (int j = 0; j < 64; ++j) {
-          const int l0 = __builtin_amdgcn_readlane(len0, j), l1 = __builtin_amdgcn_readlane(len1, j);
-          rank0 += (l0 > len0 || (l0 == len0 && j < lane) ? 1 : 0) + (l1 > len0 ? 1 : 0);
-          rank1 += (l0 >= len1 ? 1 : 0) + (l1 > len1 || (l1 == len1 && j < lane) ? 1 : 0);
+          const int l0 = __builtin_amdgcn_readlane(len0, j);
+          rank0 += l0 > len0 || (l0 == len0 && j < lane) ? 1 : 0;
+          rank1 += l0 >= len1 ? 1 : 0;
         }
-        by_len[rank0] = lane;
-        by_len[rank1] = lane + 64;
+        for (int j = 0; j < n_units - 64; ++j) {
+          const int l1 = __builtin_amdgcn_readlane(len1, j);
+          rank0 += l1 > len0 ? 1 : 0;
+          rank1 += l1 > len1 || (l1 == len1 && j < lane) ? 1 : 0;
+        }
+        if (lane < n_units) by_len[rank0] = lane;
+        if (lane + 64 < n_units) by_len[rank1] = lane + 64;
         __builtin_amdgcn_wave_barrier();
         for (int dealt = 0; dealt < n_units; dealt += n_wg) {
           int load_rank = 0;
 #pragma unroll 8
-          for (int j = 0; j < 64; ++j) {
+          for (int j = 0; j < kWorkgroupsPerXcd; ++j) {
             const int wj = __builtin_amdgcn_readlane(load, j);
             load_rank += (wj < load || (wj == load && j < lane)) ? 1 : 0;
           }
@@ -1236,8 +1281,12 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
           int item_rank = 0, load_rank = 0;                 // by decreasing length / increasing load, ties by lane
 #pragma unroll 8
           for (int j = 0; j < 64; ++j) {
-            const int lj = __builtin_amdgcn_readlane(len, j), wj = __builtin_amdgcn_readlane(load, j);
+            const int lj = __builtin_amdgcn_readlane(len, j);
             item_rank += (lj > len || (lj == len && j < lane)) ? 1 : 0;
+          }
+#pragma unroll 8
+          for (int j = 0; j < kWorkgroupsPerXcd; ++j) {
+            const int wj = __builtin_amdgcn_readlane(load, j);
             load_rank += (wj < load || (wj == load && j < lane)) ? 1 : 0;
           }
           s_by_rank[w][item_rank] = lane | (len << 8);
@@ -1260,6 +1309,29 @@ __global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanPara
       }
     }
   }
+}
+
+__global__ __launch_bounds__(kPlanThreads) void window_attn_plan_kernel(PlanParams pp) {
+  __shared__ __attribute__((aligned(16))) PlanLds lds;
+  __shared__ SpanLds span_lds;
+  plan_work<kPlanThreads, true>(pp, lds, &span_lds);
+}
+
+// A row tile to each workgroup but the first, which makes the plan of the calls that follow: a BUILD call of whole sweeps
+// below 1,024 row tiles.  The planning launch ahead of the persistent kernel cost such a call 27-32 us, which the layers
+// that reuse the plan repay after three to ten of them and a caller that plans in every call never.  us a BUILD call, with the
+// planning launch / tile kernel alone, no plan / this one: 10 streams of 420 tokens, 900 keys 83.2 / 62.5 / 62.1, of 610 70.5 / 44.6 /
+// 44.3; 20 of 200 tokens, 1,760 keys 124.7 / 112.3 / 114.6; 5 of 500 tokens, 610 keys 58.0 / 28.7 / 32.8 (planning takes 32 there, of
+// 150 streams 45).  One workgroup more is one round more where the others fill the chip to the last slot: 64 streams of two
+// row tiles and four kv heads, 930 keys 62.6 / 47.6 / 57.3.
+template <int ROWW, int KG, int STAGES>
+__global__ __launch_bounds__(64 * ROWW * KG, 2) void window_attn_bf16_tile_and_plan_kernel(AttnParams p, PlanParams pp) {
+  __shared__ TileStages<128, KG, STAGES> stages;
+  static_assert(sizeof(PlanLds) <= sizeof(stages), "the plan is made in the tile buffers");
+  if (blockIdx.x == 0)
+    plan_work<64 * ROWW * KG, false>(pp, *reinterpret_cast<PlanLds*>(&stages), nullptr);
+  else
+    attend_row_tile<128, ROWW, KG, STAGES>(p, blockIdx.x - 1, stages);
 }
 
 
@@ -2304,7 +2376,8 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 // on a route up to more work.  Below the lines of whole_sweeps the persistent kernel splits its sweeps and needs the merge
 // launch; its plan costs 15-50 us a step.
 // us a layer in a step, plan not counted, persistent / tile kernel (28/4 heads unless noted; T: row tiles):
-//   whole sweeps from T 1,024  T 1,044 48 / 51, T 1,076 with 50 key tiles 89 / 98
+//   whole sweeps from T 1,024  T 1,044 48 / 51, T 1,076 with 50 key tiles 89 / 98.  A BUILD call below runs in the tile kernel all the same,
+//                              with the planning as one workgroup more (see window_attn_bf16_tile_and_plan_kernel)
 //   ... from T 512 (768 with   no merge, and short lists are dealt by length.  us a step, plan included: T 928 1,477 / 1,751,
 //   more than four kv heads),  T 752 1,223 / 1,277, T 520 1,069 / 1,130, T 632 with 22 key tiles 1,312 / 1,398, 16/4 heads T 544
 //   9 to 32 key tiles          1,154 / 1,283, one kv head T 811 (16 layers) 856 / 1,012, 32/8 heads T 1,016 (16 layers) 960 / 1,064, T 880
@@ -2462,53 +2535,62 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       p.ws_desc = reinterpret_cast<int32_t*>(w + a.off_rt_desc);
       p.ws_ml = reinterpret_cast<float*>(w + a.off_ml);
       p.ws_o = reinterpret_cast<float*>(w + a.off_o);
+      // Without a plan the refresh write is a launch of its own, and so it is for whole sweeps of few row tiles: the launch-wide
+      // barrier takes 4-9 us more than that launch (10 streams of 420 tokens, 610 keys, us a layer of a graph 47.9 / 42.0).
+      const bool few = a.rt_cap < 1024;
+      const bool one_launch = fuse && route == TileRoute::kNone && (a.span || !few);
+      if (fuse && !one_launch && plan_mode != CS_ATTN_PLAN_ONLY) {
+        const int e = cs_kv_refresh_scatter(k_new, v_new, new_slot, const_cast<void*>(k_cache_layer),
+                                            const_cast<void*>(v_cache_layer), n_new, n_kv_heads, head_dim, stride_slot,
+                                            stride_head, dtype, stream);
+        if (e != CS_OK) return e;
+      }
       if (route != TileRoute::kNone && plan_mode != CS_ATTN_PLAN_ONLY) {
         // (the plan is neither needed nor made; the status word of a BUILD call still starts at zero)
         p.clear_status = plan_mode == CS_ATTN_PLAN_BUILD ? 1 : 0;
-        if (fuse) {
-          const int e = cs_kv_refresh_scatter(k_new, v_new, new_slot, const_cast<void*>(k_cache_layer),
-                                              const_cast<void*>(v_cache_layer), n_new, n_kv_heads, head_dim, stride_slot,
-                                              stride_head, dtype, stream);
-          if (e != CS_OK) return e;
-        }
         if (route == TileRoute::kRows128) return launch_tiles<128, 4, 1, 2>(p, st);
         if (route == TileRoute::kRows64Keys2) return launch_tiles<128, 2, 2, 1>(p, st);
         return launch_tiles<128, 2, 4, 1>(p, st);
       }
+      PlanParams pp;
+      pp.cu_q = cu_q;
+      pp.q_pos = q_pos;
+      pp.kv_len = kv_len;
+      pp.max_blocks = max_blocks;
+      pp.n_streams = n_streams;
+      pp.group = group;
+      pp.n_kv_heads = n_kv_heads;
+      pp.max_tiles = a.max_tiles;
+      pp.r_cap = static_cast<int32_t>(a.r_cap);
+      pp.bm = a.bm;
+      pp.n_slots = a.grid / 8;
+      pp.hist_pitch = a.hist_pitch;
+      pp.header = reinterpret_cast<int32_t*>(w);
+      pp.items = reinterpret_cast<int32_t*>(w + a.off_items);
+      pp.rt_desc = reinterpret_cast<int32_t*>(w + a.off_rt_desc);
+      pp.st_toff = reinterpret_cast<int32_t*>(w + a.off_st_toff);
+      pp.st_work = reinterpret_cast<int32_t*>(w + a.off_st_work);
+      pp.st_rank = reinterpret_cast<int32_t*>(w + a.off_st_rank);
+      pp.rt_stream = reinterpret_cast<int32_t*>(w + a.off_rt_stream);
+      pp.rt_wgmax = reinterpret_cast<int32_t*>(w + a.off_rt_wgmax);
+      pp.un_head = reinterpret_cast<int32_t*>(w + a.off_un_head);
+      pp.st_uoff = reinterpret_cast<int32_t*>(w + a.off_st_uoff);
+      pp.hist = reinterpret_cast<int32_t*>(w + a.off_hist);
+      pp.span = a.span;
+      pp.pref_pitch = a.pref_pitch;
+      pp.sw_pref = reinterpret_cast<int32_t*>(w + a.off_pref);
+      if (plan_mode == CS_ATTN_PLAN_BUILD && few && !a.span) {
+        const int64_t tiles = ((n_q * group) / kBM + n_streams) * n_kv_heads;
+        hipLaunchKernelGGL((window_attn_bf16_tile_and_plan_kernel<4, 1, 2>), dim3(static_cast<unsigned>(tiles) + 1), dim3(256), 0, st, p, pp);
+        return cs::note_hip(hipGetLastError());
+      }
       if (plan_mode != CS_ATTN_PLAN_REUSE) {
-        PlanParams pp;
-        pp.cu_q = cu_q;
-        pp.q_pos = q_pos;
-        pp.kv_len = kv_len;
-        pp.max_blocks = max_blocks;
-        pp.n_streams = n_streams;
-        pp.group = group;
-        pp.n_kv_heads = n_kv_heads;
-        pp.max_tiles = a.max_tiles;
-        pp.r_cap = static_cast<int32_t>(a.r_cap);
-        pp.bm = a.bm;
-        pp.n_slots = a.grid / 8;
-        pp.hist_pitch = a.hist_pitch;
-        pp.header = reinterpret_cast<int32_t*>(w);
-        pp.items = reinterpret_cast<int32_t*>(w + a.off_items);
-        pp.rt_desc = reinterpret_cast<int32_t*>(w + a.off_rt_desc);
-        pp.st_toff = reinterpret_cast<int32_t*>(w + a.off_st_toff);
-        pp.st_work = reinterpret_cast<int32_t*>(w + a.off_st_work);
-        pp.st_rank = reinterpret_cast<int32_t*>(w + a.off_st_rank);
-        pp.rt_stream = reinterpret_cast<int32_t*>(w + a.off_rt_stream);
-        pp.rt_wgmax = reinterpret_cast<int32_t*>(w + a.off_rt_wgmax);
-        pp.un_head = reinterpret_cast<int32_t*>(w + a.off_un_head);
-        pp.st_uoff = reinterpret_cast<int32_t*>(w + a.off_st_uoff);
-        pp.hist = reinterpret_cast<int32_t*>(w + a.off_hist);
-        pp.span = a.span;
-        pp.pref_pitch = a.pref_pitch;
-        pp.sw_pref = reinterpret_cast<int32_t*>(w + a.off_pref);
         hipLaunchKernelGGL(window_attn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, pp);
         const int e = cs::note_hip(hipGetLastError());
         if (e != CS_OK) return e;
         if (plan_mode == CS_ATTN_PLAN_ONLY) return CS_OK;
       }
-      if (fuse)
+      if (one_launch)
         hipLaunchKernelGGL((window_attn_bf16_stream_kernel<true>), dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);
       else
         hipLaunchKernelGGL((window_attn_bf16_stream_kernel<false>), dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);

@@ -8,7 +8,7 @@ import torch
 
 from oracle import codecsight_oracle as oc
 from tests import helpers as hp
-from tests.test_gpu_parity import DEV, _attention_plan, _attn_case, _pool, _project_gpu, _random_block_frames, _residual_gpu, cs, say   # noqa: F401  (cs is a fixture)
+from tests.test_gpu_parity import DEV, PLAN_HDR_INTS, _attention_plan, _attn_case, _pool, _project_gpu, _random_block_frames, _residual_gpu, cs, say   # noqa: F401  (cs is a fixture)
 from tests.test_gpu_parity import test_attention_plan_is_a_valid_schedule as _plan_is_valid
 
 pytestmark = pytest.mark.gpu
@@ -132,6 +132,61 @@ def test_attention_at_the_lines_of_whole_sweeps(cs, hq, hkv, n_streams, rows, wi
     assert (rows * (hq // hkv) // 128 + n_streams) * hkv == row_tiles
     _plan_is_valid(cs, hq, hkv, kv_lens, n_qs)
     say(f"  -> {_attn_case(cs, np.random.default_rng(9400 + window + rows), 'bf16', hq, hkv, 128, kv_lens, n_qs)}")
+
+
+# A BUILD call of whole sweeps below 1,024 row tiles makes the plan in a workgroup of the tile launch.
+BUILD_BESIDE = [
+    # Hq, Hkv, kv_lens, n_qs
+    (16, 4, [700 - 3 * i for i in range(8)], [480] * 8),                                                # 512 row tiles, 32 pairs
+    (28, 4, [1100, 900, 1201], [1090, 0, 1200]),                                                        # 12 pairs: ordered by length; a stream without rows
+    (16, 1, [700 + 9 * i for i in range(23)], [250 + 3 * i for i in range(23)]),                         # pairs left over by whole rounds
+    (8, 1, [520 + i % 40 for i in range(250)], [20 + i % 30 for i in range(250)]),                       # more streams than one turn of the workgroup's scan
+    (32, 8, [1040, 1007, 1000], [1000] * 3),
+]
+
+
+@pytest.mark.parametrize("case", range(len(BUILD_BESIDE)))
+def test_attention_plan_made_beside_the_first_layer(cs, case):
+    """The BUILD call's results, the plan it leaves (that of an ONLY call), and a REUSE call that runs from it."""
+    hq, hkv, kv_lens, n_qs = BUILD_BESIDE[case]
+    say(f"attention, plan beside the first layer: heads={hq}/{hkv} kv={kv_lens[:4]} n_q={n_qs[:4]} streams={len(kv_lens)}")
+    rng, d, n_streams = np.random.default_rng(9480 + case), 128, len(kv_lens)
+    nb = [-(-k // 16) for k in kv_lens]
+    bt, ids, at = np.zeros((n_streams, max(nb)), np.int32), rng.permutation(sum(nb)), 0
+    for s in range(n_streams):
+        bt[s, : nb[s]] = ids[at: at + nb[s]]
+        at += nb[s]
+    cu = np.concatenate([[0], np.cumsum(n_qs)]).astype(np.int32)
+    q_pos = np.concatenate([np.sort(rng.choice(kv_lens[s], n_qs[s], replace=False)) for s in range(n_streams)]).astype(np.int32)
+    n_q = int(cu[-1])
+    assert 512 <= (n_q * (hq // hkv) // 128 + n_streams) * hkv < 1024 and n_q * (hq // hkv) > 128 * n_streams
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    wsb = cs.cs_window_prefill_attn_workspace(n_q, n_streams, hq, hkv, d, max(nb), cs.CS_BF16)
+    ws = torch.randint(0, 255, (wsb,), dtype=torch.uint8, device=DEV)
+    lists = [to(cu), to(q_pos), to(np.asarray(kv_lens, np.int32)), to(bt)]
+    for mode in (cs.CS_ATTN_PLAN_BUILD, cs.CS_ATTN_PLAN_REUSE):
+        kc, vc = (_pool(rng, (sum(nb) * 16, hkv, d), "bf16") for _ in range(2))
+        q = _pool(rng, (n_q, hq, d), "bf16")
+        out = torch.full_like(q, 7.0, device=DEV)
+        cs.cs_window_prefill_attn(q.to(DEV), kc.to(DEV), vc.to(DEV), *lists, max(nb), 16, out, n_q, n_streams, hq, hkv, d, hkv * d, d,
+                                  1 / math.sqrt(d), cs.CS_BF16, ws, wsb, mode)
+        ref = oc.window_attn(hp.f64(q), hp.f64(kc), hp.f64(vc), cu, q_pos, bt, hq, 1 / math.sqrt(d))
+        say(f"  -> {hp.check_attention(out.cpu(), ref, 'bf16')}")
+        assert cs.cs_attn_status(ws) == 0
+    left = ws.clone()
+    hdr, items = _attention_plan(cs, cu, q_pos, np.asarray(kv_lens), bt, hq, hkv)
+    off = (((PLAN_HDR_INTS + 63) // 64 * 64 + 18 * 64) * 4 + 255) // 256 * 256
+    got = left[off: off + items.nbytes].view(torch.int32).cpu().numpy().reshape(items.shape)
+    assert np.array_equal(left[:36].view(torch.int32).cpu().numpy(), hdr[:9])
+    if n_streams * hkv >= 16:
+        assert np.array_equal(got, items)
+    else:                                                                 # (equally long items in the order of arrival)
+        part = lambda a: sorted(tuple(int(v) for v in (*i[:6], i[7])) for i in a)
+        assert part(got) == part(items)
+
+
+def test_attention_plan_of_more_streams_than_are_searched_in_lds(cs):
+    _plan_is_valid(cs, 2, 1, [20] * 4100, [2 + i % 3 for i in range(4100)])
 
 
 # Many streams of at most one row tile: the search for a workgroup's row tile in one, two and three steps (64 streams; 64 for
