@@ -2410,7 +2410,11 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 //   kRows64Keys4 (to 128)      T 116 20.2 / 17.4, with 28 key tiles 28.3 / 24.9 (two groups 18.1, 28.7): one workgroup
 //                              per CU, all of them run at once and the longest sweep is the time; up to 8 key tiles two
 //                              groups are enough (300 keys 11.0 / 12.2, persistent 16.3)
-//   a few row tiles with long sweeps (2 key tiles > row tiles) keep the split over the whole chip (T 27 14.8 / 16.4)
+//   a few row tiles with       split over the whole chip, whose time goes by all tiles together; the tile kernel's by the longest sweep.  F:
+//   long sweeps (2 key tiles   row tiles without the streams' part-filled ones.  us a layer (persistent of 32 rows a wave, no longer here,) of 64 / tile:
+//   > T and > 20 + 3/8 F)      F 0, 18 tokens of 28/4 heads, 9 key tiles 12.7, 16.1 / 11.9, 16 13.6, 16.4 / 15.1, 24 14.3, 16.5 / 18.9, 48 17.2, 19.1 / 30.4;
+//                              F 12 24 key tiles 17.3, 19.9 / 19.1, 32 19.4, 21.4 / 22.9; F 40 32 27.3, 29.3 / 23.0, 40 28.4, 29.8 / 26.8; F 28, 8 streams, 32 24.1,
+//                              23.5 / 26.2; F 88 48 36.8, 36.5 / 31.0.  A BUILD call saves the plan besides (24 key tiles, F 40 38 / 19)
 //   single_tiles: whole        Up to 128 rows a stream and kv head on average.  The persistent kernel's jobs of 256 rows then hold one row tile,
 //   sweeps, but one row tile   two of its four waves, and a plan orders nothing.  us a layer, persistent of 32 rows a wave, two workgroups a CU
 //   a stream (kRows128)        (no longer here) / of 64 / tile: 18 tokens of 28/4 heads, 263 streams of 290 keys 45 / 63 / 51, of 550 88.5 / 99 / 95,
@@ -2420,11 +2424,11 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 //                              tiles a stream on the persistent kernel wins: 27 tokens, 129 streams of 550 keys 53 / 58 / 72
 enum class TileRoute { kNone, kRows128, kRows64Keys2, kRows64Keys4 };
 
-TileRoute tile_route_128(int64_t row_tiles, int key_tiles, int n_kv_heads, bool single_tiles) {
+TileRoute tile_route_128(int64_t row_tiles, int64_t full_tiles, int key_tiles, int n_kv_heads, bool single_tiles) {
   if (whole_sweeps(row_tiles, key_tiles, n_kv_heads)) return single_tiles ? TileRoute::kRows128 : TileRoute::kNone;
   if (key_tiles > 64) return TileRoute::kNone;
   if (row_tiles <= 128) {
-    if (2 * key_tiles > (row_tiles > 16 ? row_tiles : 16)) return TileRoute::kNone;
+    if (2 * key_tiles > row_tiles && key_tiles > 20 + 3 * full_tiles / 8) return TileRoute::kNone;
     return key_tiles > 8 ? TileRoute::kRows64Keys4 : TileRoute::kRows64Keys2;
   }
   if (row_tiles <= 440) return key_tiles <= 48 ? TileRoute::kRows64Keys2 : TileRoute::kNone;
@@ -2541,7 +2545,8 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       if (plan_mode != CS_ATTN_PLAN_BUILD && plan_mode != CS_ATTN_PLAN_REUSE && plan_mode != CS_ATTN_PLAN_ONLY)
         return CS_EINVAL;
       const AttnPlan a = plan_attn(n_q, n_streams, group, n_kv_heads, max_blocks);
-      const TileRoute route = tile_route_128(a.rt_cap, a.max_tiles, n_kv_heads, n_q * group <= static_cast<int64_t>(a.bm) * n_streams);
+      const TileRoute route = tile_route_128(a.rt_cap, (n_q * group) / a.bm * n_kv_heads, a.max_tiles, n_kv_heads,
+                                              n_q * group <= static_cast<int64_t>(a.bm) * n_streams);
       if (a.items_cap * a.bm >= (1ll << 31)) return CS_EUNSUPPORTED;
       if (stride_slot >= (1ll << 26) || a.max_tiles >= (1 << 15)) return CS_EUNSUPPORTED;      // 32-bit byte offsets inside a cache block
       if (!workspace || workspace_bytes < a.total || !cs::aligned16(workspace)) return CS_EWORKSPACE;

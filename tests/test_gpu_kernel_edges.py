@@ -199,6 +199,15 @@ MANY_STREAMS = [
 ]
 
 
+# Few row tiles, 20 + 3/8 of the full ones key tiles and one more: the tile kernel, and sweeps split over the chip.
+FEW_ROW_TILES = [(28, 4, 1280, 18), (28, 4, 1281, 18), (28, 4, 1535, 70), (28, 4, 1545, 70), (16, 1, 1472, 70), (16, 1, 1473, 70)]
+
+
+@pytest.mark.parametrize("hq,hkv,window,rows", FEW_ROW_TILES)
+def test_attention_of_few_row_tiles(cs, hq, hkv, window, rows):
+    say(f"  -> {_attn_case(cs, np.random.default_rng(9490 + window), 'bf16', hq, hkv, 128, [window - 16, 50], [rows - 1, 1])}")
+
+
 @pytest.mark.parametrize("case", range(len(MANY_STREAMS)))
 def test_attention_of_many_streams(cs, case):
     dtype, hq, hkv, d, n_streams, n_qs, window = MANY_STREAMS[case]
