@@ -1213,13 +1213,14 @@ __device__ __forceinline__ void plan_work(const PlanParams& pp, PlanLds& lds, Sp
         }
         load += 2 * tiles + kItemFixedCostHalves;
       };
-      // A pair-ordered list of up to two and a quarter rounds is dealt by length over the whole list: its pairs are under
-      // way together in any case, and batches in list order let long units meet.  us a step in list order / by length: 12
-      // streams of 1,000 keys (71 units an XCD) 1,157 / 1,069, 11 (67) 1,847 / 1,713, 5 of 3,200 (71) 2,564 / 2,504, 5 ragged
-      // (54) 3,415 / 3,337, 9 and 10 of 1,000 (53, 57) 1,597 / 1,566, 963 / 947.  Longer lists keep their order, so that few
-      // pairs at a time share an L2: 12 of 1,000, eight kv heads (81) 1,337 / 1,386, 15 of 1,000 (88) 2,177 / 2,182, 16 of 900
-      // (90) 2,035 / 2,069, 9 of 2,000 (107) 2,595 / 2,681.  Some of them would gain (16 of 1,000 (92) 1,372 / 1,328, 25 of
-      // 2,900, one kv head (100) 2,519 / 2,400) and working both deals out tells which, but that costs 15-30 us a plan.
+      // A short pair-ordered list is dealt by length over the whole list: its pairs are under way together in any case, and
+      // batches in list order let long units meet.  us a step in list order / by length: 12 streams of 1,000 keys (71 units an
+      // XCD) 1,157 / 1,069, 11 (67) 1,847 / 1,713, 5 of 3,200 (71) 2,564 / 2,504, 5 ragged (54) 3,415 / 3,337, 9 and 10 of 1,000
+      // (53, 57) 1,597 / 1,566, 963 / 947.  Longer lists keep their order, so that few pairs at a time share an L2: 12 of 1,000,
+      // eight kv heads (81) 1,337 / 1,386, 15 of 1,000 (88) 2,177 / 2,182, 16 of 900 (90) 2,035 / 2,069, 9 of 2,000 (107) 2,595 /
+      // 2,681.  The line at 72 lies above all that gained and below all that lost, but the number of units is not what decides:
+      // the spread of their lengths against a round does, and lists of 92 and 100 would gain too (16 of 1,000 1,372 / 1,328, 25
+      // of 2,900, one kv head 2,519 / 2,400).  Working both deals out tells which, but cost 15-30 us a plan.
       if (grouped && s_units[w] <= kDealAtOnce) {
         int4* unit_at = reinterpret_cast<int4*>(s_key) + w * 128;     // first item, second (or -1), key tiles
         int* by_len = s_deal[w];

@@ -80,6 +80,7 @@ def test_unplanned_attention_tile_edges(cs, case):
 
 
 # bf16 attention from a plan, head_dim 128: jobs of one or two 128-row tiles, four waves of 64 rows, 32 keys at a time
+# (the first two have at most 128 rows a stream on average and run without a plan)
 PLANNED_ATTN = [
     # Hq, Hkv, kv_lens, n_qs
     (8, 8, [1 + 9 * i % 71 for i in range(132)], [1 + 5 * i % (1 + 9 * i % 71) for i in range(132)]),   # one head a group, jobs of one or two key tiles
@@ -88,6 +89,8 @@ PLANNED_ATTN = [
     (7, 1, [6100], [42]),                                                                                # split sweeps, three row tiles
     (8, 2, [7000, 64, 4200], [150, 64, 31]),                                                             # split and whole, frontiers far apart
     (28, 4, [4300], [19]),                                                                               # two row tiles, 5 rows in the second
+    (8, 8, [400 if i % 2 else 1 + 9 * i % 71 for i in range(132)], [320 if i % 2 else 1 + 5 * i % (1 + 9 * i % 71) for i in range(132)]),   # one head a group, jobs of one key tile and more
+    (32, 2, [40 + i % 90 for i in range(516)], [1 + i % 11 if i % 4 else 21 for i in range(516)]),        # 16 heads a group, one to three row tiles
 ]
 
 
