@@ -188,6 +188,34 @@ def test_attention_plan_made_beside_the_first_layer(cs, case):
         assert part(got) == part(items)
 
 
+def test_fused_call_of_a_shape_whose_plan_is_made_beside(cs):
+    """BUILD, then REUSE: the fused call against the two calls of the same mode, bit for bit, cache contents included."""
+    rng, hq, hkv, d, n_streams, n_tok, window = np.random.default_rng(9485), 16, 4, 128, 8, 480, 700
+    nb, n_q = -(-window // 16), n_streams * n_tok
+    say(f"fused call, plan beside the first layer: heads={hq}/{hkv} streams={n_streams} rows={n_q * (hq // hkv)}")
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    bt = rng.permutation(n_streams * nb).astype(np.int32).reshape(n_streams, nb)
+    pos = np.stack([np.sort(rng.choice(window, n_tok, replace=False)) for _ in range(n_streams)])
+    slot = to((np.take_along_axis(bt, pos // 16, 1) * 16 + pos % 16).astype(np.int32).reshape(-1))
+    lists = [to((np.arange(n_streams + 1) * n_tok).astype(np.int32)), to(pos.astype(np.int32).reshape(-1)),
+             to(np.full(n_streams, window, np.int32)), to(bt)]
+    wsb = cs.cs_window_prefill_attn_workspace(n_q, n_streams, hq, hkv, d, nb, cs.CS_BF16)
+    ws = [torch.randint(0, 255, (wsb,), dtype=torch.uint8, device=DEV) for _ in range(2)]
+    for mode in (cs.CS_ATTN_PLAN_BUILD, cs.CS_ATTN_PLAN_REUSE):
+        pool = [_pool(rng, (n_streams * nb * 16, hkv, d), "bf16").to(DEV) for _ in range(2)]
+        new = [_pool(rng, (n_q, hkv, d), "bf16").to(DEV) for _ in range(2)]
+        q = _pool(rng, (n_q, hq, d), "bf16").to(DEV)
+        tail = lambda out, w: (*lists, nb, 16, out, n_q, n_streams, hq, hkv, d, hkv * d, d, 1 / math.sqrt(d), cs.CS_BF16, w, wsb, mode)
+        k1, v1, k2, v2 = (t.clone() for t in pool + pool)
+        out1, out2 = torch.zeros_like(q), torch.ones_like(q)
+        cs.cs_refresh_prefill_attn(*new, slot, n_q, q, k1, v1, *tail(out1, ws[0]))
+        cs.cs_kv_refresh_scatter(*new, slot, k2, v2, n_q, hkv, d, hkv * d, d, cs.CS_BF16)
+        cs.cs_window_prefill_attn(q, k2, v2, *tail(out2, ws[1]))
+        for a, b in ((k1, k2), (v1, v2), (out1, out2)):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+        assert cs.cs_attn_status(ws[0]) == 0
+
+
 def test_attention_plan_of_more_streams_than_are_searched_in_lds(cs):
     _plan_is_valid(cs, 2, 1, [20] * 4100, [2 + i % 3 for i in range(4100)])
 

@@ -869,7 +869,6 @@ FUSED_CASES = [
     ("bf16", 8, 2, 128, [3000, 700, 40], [257, 64, 40]),
     ("bf16", 4, 4, 64, [200, 129], [64, 129]),                 # head_dim 64: two launches behind the one call
     ("f32", 2, 1, 64, [452], [332]),                           # fp32: two launches behind the one call
-    ("bf16", 16, 4, 128, [700 - 5 * i for i in range(8)], [490] * 8),   # plan made beside the first call; two launches
     ("bf16", 32, 8, 128, [200 + i for i in range(66)], [31] * 66),      # one row tile a stream: no plan, two launches
 ]
 
