@@ -648,17 +648,17 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 // every decoder layer of a step.
 //
 // The attention kernel is persistent: workgroup b serves XCD b % 8 (workgroups are dealt to XCDs round robin by the
-// hardware) and follows its chain of items.  Where two items that follow each other are row tiles of one sweep and
-// begin at the same key tile, it takes them as ONE job of 256 rows: every K/V tile that it fetches, and every fragment
+// hardware) and follows its chain of items.  It takes the two row tiles of a unit, which follow each other there and begin at
+// the same key tile, as ONE job of 256 rows: every K/V tile that it fetches, and every fragment
 // that a wave reads from LDS, then serves twice the rows (see window_attn_bf16_stream_kernel).  The plan makes
-// chains of such units: two neighbouring row tiles of a stream counted from its end, or, of a pair whose row tiles go
+// chains of units: two neighbouring row tiles of a stream counted from its end, or, of a pair whose row tiles go
 // to all XCDs, two that the same XCD takes.
 
 // Item descriptor: 8 ints.  [0] first query token of the stream, [1] rows of the stream (tokens x
 // heads per kv group), [2] first row of the tile, [3] kv head | stream << 8, [4] highest visible
 // cache index among the tile's rows, [5] key tiles [begin, end) as begin | end << 16, [6] index of
-// the item the same workgroup takes next (-1: none), [7] first row of the item's partial result in
-// the workspace, or -1 when the item covers the whole sweep and writes `out`.
+// the item the same workgroup takes next (-1: none), [7] first row of the item's partial result in the workspace (an even
+// number), or -2 when the item covers the whole sweep and writes `out`; plus 1, unless it is the second of its unit.
 // Plan header (ints): [0..8] list offsets per XCD, [9] row tiles, [16..23] end item,
 // then one 32-int entry per workgroup j of XCD x at [32 + 32 (64 x + j)]: [0] its first item (-1: none),
 // [8..15] a copy of that item's descriptor (all that the workgroup reads of its entry).
@@ -905,7 +905,7 @@ __device__ void plan_spans(const PlanParams& pp, int n_rt, int n_un, int* s_wave
       const int n_mine = second ? n_kt2 : n_kt, ke_mine = min(ke, n_mine);
       const bool split = kb > 0 || ke_mine < n_mine;
       int32_t d[8] = {un.q0, un.rows, un.r_tile - second * pp.bm, kvh | (s << 8), second ? un.wg_max2 : un.wg_max, kb | (ke_mine << 16),
-                      i < i_hi || second < (two ? 1 : 0) ? pos + 1 : -1, split ? pos * pp.bm : -1};
+                      i < i_hi || second < (two ? 1 : 0) ? pos + 1 : -1, (split ? pos * pp.bm : -2) | (second ? 0 : 1)};
       int32_t* it = pp.items + static_cast<int64_t>(pos) * 8;
 #pragma unroll
       for (int k = 0; k < 8; ++k) it[k] = d[k];
@@ -1181,7 +1181,7 @@ __device__ __forceinline__ void plan_work(const PlanParams& pp, PlanLds& lds, Sp
         const int wg_max = pp.rt_wgmax[r - second];
         int32_t* it = pp.items + static_cast<int64_t>(pos + second) * 8;
         it[0] = q0; it[1] = rows; it[2] = (t - second) * pp.bm; it[3] = kvh | (s << 8); it[4] = wg_max;
-        it[5] = (max(wg_max, 0) / kBN + 1) << 16; it[6] = second ? -1 : unit; it[7] = -1;
+        it[5] = (max(wg_max, 0) / kBN + 1) << 16; it[6] = second ? -1 : unit; it[7] = second || unit == -1 ? -2 : -1;
       }
     }
   }
@@ -1531,11 +1531,10 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
   i32x8 d = const_load8(entry + 8);
   if ((d[5] >> 16) == 0) return;        // nothing for this workgroup
 
-  // Two items that follow each other in the chain, are row tiles of one sweep and start at the same key tile (the second
-  // no longer than the first) are taken as one job of 256 rows: waves 0-1 the second, waves 2-3 the first.
-  auto couple = [&](const i32x8& a, const i32x8& b) {
-    return a[3] == b[3] && a[0] == b[0] && (a[5] & 0xffff) == (b[5] & 0xffff) && (b[5] >> 16) > 0 && (b[5] >> 16) <= (a[5] >> 16);
-  };
+  // The two items of a unit follow each other in the chain and are taken as one job of 256 rows: waves 0-1 the second, waves
+  // 2-3 the first.  The plan marks the second; what the items hold does not tell (a stream's odd first row tile, a unit of its
+  // own, may stand before a later unit that ends in the same key tile), and comparing it took 0.8 % of a step.
+  auto joins = [](const i32x8& b) { return (b[7] & 1) == 0; };
   auto mine = [&](const i32x8& a, const i32x8& b, bool both) { return wave < 2 && both ? b : a; };
   auto takes_part = [&](bool both) { return both || wave >= 2; };
 
@@ -1601,7 +1600,7 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
     r_parity ^= 1;
   };
   auto enter_queries = [&]() __attribute__((always_inline)) {
-    const i32x8 it = mine(r_cur, r_x1, couple(r_cur, r_x1));
+    const i32x8 it = mine(r_cur, r_x1, joins(r_x1));
     const Rows r = rows_of(it);
     src_k = src_v = static_cast<const char*>(p.q) + (static_cast<int64_t>(r.tok0) * p.n_q_heads + (it[3] & 255) * p.group) * (D * 2);
     src_id = 0;
@@ -1653,7 +1652,7 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
         ++r_kt;
       } else if (r_live) {
         i32x8 to = r_x1;
-        if (couple(r_cur, r_x1)) {
+        if (joins(r_x1)) {
           to = const_load8(item_at(r_x1[6]));
           wait_scalar();
         }
@@ -1964,7 +1963,7 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
     mfma_settle(o);
     results(0);
     const bool stored = out && out_part < 0;            // 8 + 8 stores, then
-    const bool paired = couple(d, x1);
+    const bool paired = joins(x1);
     const i32x8 my = mine(d, x1, paired);
     const int kb = d[5] & 0xffff, ke = d[5] >> 16;
     const bool works = takes_part(paired) && my[2] + (wave & 1) * WROWS < my[1];
@@ -2076,7 +2075,7 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
     out = works;
     out_rows = rows_of(my);
     out_kvh = my[3] & 255;
-    out_part = my[7];
+    out_part = my[7] & ~1;
     d = nd;
     if ((d[5] >> 16) <= 0) break;
     x1 = const_load8(item_at(d[6]));

@@ -120,6 +120,22 @@ def test_planned_attention_dealt_by_length(cs, case):
     say(f"  -> {_attn_case(cs, np.random.default_rng(9390 + case), 'bf16', hq, hkv, 128, kv_lens, n_qs)}")
 
 
+# A stream's odd first row tile, a unit of its own, stands in a chain before a later unit of the same sweep that ends in the
+# same key tile: the two are no job, since the keys of a job end with its first row tile's.
+FIRST_TILE_ALONE = [
+    # Hq, Hkv, kv_lens, n_qs
+    (32, 8, [128, 5000], [70, 512]), (64, 8, [60, 4300], [40, 40]), (56, 8, [64, 4300], [41, 90]), (64, 4, [60, 4300], [40, 150]),
+    (64, 8, [2072], [2064]),                                                                             # whole sweeps, ordered by length
+]
+
+
+@pytest.mark.parametrize("case", range(len(FIRST_TILE_ALONE)))
+def test_planned_attention_first_row_tile_alone(cs, case):
+    hq, hkv, kv_lens, n_qs = FIRST_TILE_ALONE[case]
+    say(f"planned attention, first row tile alone {case}: heads={hq}/{hkv} kv={kv_lens} n_q={n_qs}")
+    say(f"  -> {_attn_case(cs, np.random.default_rng(9420 + case), 'bf16', hq, hkv, 128, kv_lens, n_qs, last_queries=True)}")
+
+
 # Both sides of the lines from which whole sweeps run from a plan: row tiles x kv heads, key tiles of the longest window.
 WHOLE_SWEEPS = [
     # Hq, Hkv, streams, rows of all streams, longest window, row tiles

@@ -554,11 +554,11 @@ def test_kv_refresh_scatter(cs, dtype, n_tok, n_heads, d, layout):
 
 # =============================================================================== (d) attention
 def _attn_case(cs, rng, dtype, n_q_heads, n_kv_heads, d, kv_lens, n_qs, shuffle=True, poison=True,
-               all_queries=False, scale_mult=1.0, late_outlier=0.0):
+               all_queries=False, scale_mult=1.0, late_outlier=0.0, last_queries=False):
     """`scale_mult` multiplies the softmax scale (peaked rows: the running maximum keeps rising along
     the sweep); `late_outlier` > 0 multiplies one key row near the end of every stream by that
     factor (a maximum that jumps late, past the first tile and past the first key range of a split
-    sweep)."""
+    sweep); `last_queries`: a stream's queries are its last positions instead of random ones."""
     n_streams = len(kv_lens)
     nb = [(-(-L // 16)) for L in kv_lens]
     max_blocks = max(nb) + 1
@@ -575,6 +575,8 @@ def _attn_case(cs, rng, dtype, n_q_heads, n_kv_heads, d, kv_lens, n_qs, shuffle=
     for s in range(n_streams):
         if all_queries:
             pos = np.arange(kv_lens[s])
+        elif last_queries:
+            pos = np.arange(kv_lens[s] - n_qs[s], kv_lens[s])
         else:
             pos = np.sort(rng.choice(kv_lens[s], size=n_qs[s], replace=False)) if n_qs[s] else np.zeros(0, int)
         q_pos.append(pos)
