@@ -136,21 +136,27 @@ def test_planned_attention_first_row_tile_alone(cs, case):
     say(f"  -> {_attn_case(cs, np.random.default_rng(9420 + case), 'bf16', hq, hkv, 128, kv_lens, n_qs, last_queries=True)}")
 
 
-# Both sides of the lines from which whole sweeps run from a plan: row tiles x kv heads, key tiles of the longest window.
+# Both sides of the lines from which whole sweeps run from a plan: row tiles x kv heads, key tiles of the table's rows (a block
+# more than the window has), and more than 128 rows a stream on average.
 WHOLE_SWEEPS = [
-    # Hq, Hkv, streams, rows of all streams, longest window, row tiles
-    (16, 4, 8, 3840, 700, 512), (16, 4, 8, 3839, 700, 508), (16, 4, 8, 3840, 512, 512), (16, 4, 8, 3840, 513, 512),
-    (16, 4, 8, 3840, 2048, 512), (16, 4, 8, 3840, 2049, 512), (32, 8, 6, 2880, 700, 768), (32, 8, 6, 2879, 700, 760),
+    # Hq, Hkv, streams, rows of all streams, longest window, row tiles, key tiles, a BUILD call makes a plan
+    (16, 4, 8, 3840, 700, 512, 12, True), (16, 4, 8, 3839, 700, 508, 12, False), (16, 4, 8, 3840, 496, 512, 8, False),
+    (16, 4, 8, 3840, 497, 512, 9, True), (16, 4, 8, 3840, 2032, 512, 32, True), (16, 4, 8, 3840, 2033, 512, 33, False),
+    (32, 8, 6, 2880, 700, 768, 12, True), (32, 8, 6, 2879, 700, 760, 12, False),
+    (16, 4, 64, 6144, 400, 1024, 7, True), (16, 4, 64, 6143, 400, 1020, 7, False),
+    (8, 4, 128, 8192, 300, 1024, 5, False), (8, 4, 128, 8193, 300, 1024, 5, True),
 ]
 
 
-@pytest.mark.parametrize("hq,hkv,n_streams,rows,window,row_tiles", WHOLE_SWEEPS)
-def test_attention_at_the_lines_of_whole_sweeps(cs, hq, hkv, n_streams, rows, window, row_tiles):
+@pytest.mark.parametrize("hq,hkv,n_streams,rows,window,row_tiles,key_tiles,plans", WHOLE_SWEEPS)
+def test_attention_at_the_lines_of_whole_sweeps(cs, hq, hkv, n_streams, rows, window, row_tiles, key_tiles, plans):
     n_qs = [rows // n_streams + (1 if i < rows % n_streams else 0) for i in range(n_streams)]
-    kv_lens = [max(n, window - 3 * i) for i, n in enumerate(n_qs)]
+    kv_lens = [max(n, window - 3 * i % 200) for i, n in enumerate(n_qs)]
     assert (rows * (hq // hkv) // 128 + n_streams) * hkv == row_tiles
+    assert -(-(-(-max(kv_lens) // 16) + 1) * 16 // 64) == key_tiles
     _plan_is_valid(cs, hq, hkv, kv_lens, n_qs)
-    say(f"  -> {_attn_case(cs, np.random.default_rng(9400 + window + rows), 'bf16', hq, hkv, 128, kv_lens, n_qs)}")
+    say(f"  -> {_attn_case(cs, np.random.default_rng(9400 + window + rows), 'bf16', hq, hkv, 128, kv_lens, n_qs, left=(left := []))}")
+    assert (left[0] != left[1]) == plans                                  # the plan header's first bytes, before and after
 
 
 # A BUILD call of whole sweeps below 1,024 row tiles makes the plan in a workgroup of the tile launch.

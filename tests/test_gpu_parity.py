@@ -554,11 +554,12 @@ def test_kv_refresh_scatter(cs, dtype, n_tok, n_heads, d, layout):
 
 # =============================================================================== (d) attention
 def _attn_case(cs, rng, dtype, n_q_heads, n_kv_heads, d, kv_lens, n_qs, shuffle=True, poison=True,
-               all_queries=False, scale_mult=1.0, late_outlier=0.0, last_queries=False):
+               all_queries=False, scale_mult=1.0, late_outlier=0.0, last_queries=False, left=None):
     """`scale_mult` multiplies the softmax scale (peaked rows: the running maximum keeps rising along
     the sweep); `late_outlier` > 0 multiplies one key row near the end of every stream by that
     factor (a maximum that jumps late, past the first tile and past the first key range of a split
-    sweep); `last_queries`: a stream's queries are its last positions instead of random ones."""
+    sweep); `last_queries`: a stream's queries are its last positions instead of random ones; `left` takes
+    the workspace's first 36 bytes (the list offsets of a plan) before and after the call."""
     n_streams = len(kv_lens)
     nb = [(-(-L // 16)) for L in kv_lens]
     max_blocks = max(nb) + 1
@@ -607,11 +608,15 @@ def _attn_case(cs, rng, dtype, n_q_heads, n_kv_heads, d, kv_lens, n_qs, shuffle=
     code = cs.CS_BF16 if dtype == "bf16" else cs.CS_F32
     wsb = cs.cs_window_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, d, max_blocks, code)
     ws = torch.randint(0, 255, (max(16, wsb),), dtype=torch.uint8, device=DEV)     # dirty workspace
+    if left is not None:
+        left.append(bytes(ws[:36].cpu().numpy()))
     cs.cs_window_prefill_attn(q.to(DEV), kd, vd, torch.from_numpy(cu).to(DEV), torch.from_numpy(q_pos).to(DEV),
                               torch.tensor(kv_lens, dtype=torch.int32, device=DEV),
                               torch.from_numpy(bt).to(DEV), max_blocks, 16, out, n_q, n_streams, n_q_heads,
                               n_kv_heads, d, kd.stride(0), kd.stride(1), scale, code, ws, wsb)
     torch.cuda.synchronize()
+    if left is not None:
+        left.append(bytes(ws[:36].cpu().numpy()))
     return hp.check_attention(out[:n_q].cpu(), ref, dtype)
 
 
