@@ -408,8 +408,9 @@ int cs_kv_refresh_scatter(const void* k_new, const void* v_new, const int32_t* s
  *                ONLY call then computes like any other).  Launches of few row tiles run without a plan as
  *                well (head_dim 128; by n_q and max_blocks, fewer than 512 tiles of 128 rows times kv heads, 768 with
  *                more than four kv heads, 1,024 where the window is at most 512 or more than 2,048 entries, and not too
- *                long a window), and so do larger ones with at most 128 rows (n_q times query heads of a kv group) a
- *                stream on average and windows that would not be split: a BUILD call of such a shape makes no plan and
+ *                long a window; with at most 128 row tiles of 64 rows also the longest windows, whose sweeps are then cut into pieces
+ *                with partial results in the workspace), and so do larger ones with at most 128 rows (n_q times query heads
+ *                of a kv group) a stream on average and windows that would not be split: a BUILD call of such a shape makes no plan and
  *                a REUSE call of it reads none; an ONLY call still writes the plan, so a caller of many such shapes has
  *                no use for it (BUILD at the first layer costs nothing there).  Of shapes with a plan below 1,024 row
  *                tiles a BUILD call makes it beside its own work, which does not use it: its results and those of a
@@ -445,7 +446,7 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  * Exactly cs_kv_refresh_scatter(k_new, v_new, slot, ..., n_tok, ...) followed by
  * cs_window_prefill_attn(q, ..., plan_mode, ...) on the same layer, same arguments, same results
  * bit for bit.  CS_BF16 with head_dim 128, where attention runs from a plan and has at least 1,024 row tiles or
- * splits its sweeps (see cs_window_prefill_attn): ONE launch: every workgroup of the persistent attention
+ * splits its sweeps by it (see cs_window_prefill_attn): ONE launch: every workgroup of the persistent attention
  * grid first moves its share of the new rows (stores written through to memory at device scope),
  * the grid meets at a launch-wide barrier, then attention proceeds as in cs_window_prefill_attn; a
  * CS_ATTN_PLAN_BUILD call is preceded by the planning launch, a CS_ATTN_PLAN_ONLY call plans and

@@ -57,6 +57,7 @@ struct AttnParams {
   // twice and is far slower here, also with write-through stores in place of an L2 write-back: single stream, 919 keys,
   // 42 against 23 us per call; 6,033 keys 133 against 117; 17,630 keys 310 against 290.)
   int32_t bm;
+  int32_t pieces;          // workgroups that share a sweep without a plan (window_attn_bf16_tile_kernel<.., SPLIT>)
   const int32_t* ws_plan;   // plan header (list offsets per XCD, row-tile count, end item, first items)
   const int32_t* ws_items;  // item descriptors, 8 ints each, the 8 XCD lists back to back
   // refresh write fused into the launch (cs_refresh_prefill_attn): rows to write before attention
@@ -237,6 +238,8 @@ __device__ __forceinline__ bool find_row_tile(const AttnParams& p, int b, int* s
 // arranged as KG key groups of ROWW row waves.  Group g sweeps key tiles g, g + KG, ...; the groups' partial
 // results meet in LDS at the end, so a sweep is shared by KG times as many waves without a trip through memory
 // and without a merge launch.  head_dim 64 always runs here, head_dim 128 where tile_route_128 says so.
+// SPLIT: a sweep is cut into up to p.pieces runs of whole trips (KG key tiles each), a workgroup to a run; where there
+// are several, their partial rows go to the workspace and window_attn_merge_kernel, told by `describe`, combines them.
 // Tiles go to LDS by DMA with the persistent kernel's layout and swizzle idea.  STAGES 2: the next tile is requested
 // at the top of a tile, one workgroup barrier per tile.  STAGES 1 (half the LDS: more workgroups per CU, or more key
 // groups): K of the next tile is requested when S is done and lands behind P V, V when P V is done and lands behind
@@ -258,7 +261,7 @@ struct TileStages {
   __attribute__((aligned(1024))) uint16_t kv[KG][STAGES][2][kBN * D];
 };
 
-template <int D, int ROWW, int KG, int STAGES>
+template <int D, int ROWW, int KG, int STAGES, bool SPLIT = false>
 __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, TileStages<D, KG, STAGES>& stages) {
   constexpr int BM = 32 * ROWW;
   constexpr int STEPS = D / 16, DB = D / 32;
@@ -282,8 +285,27 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   const int n = lane & 31, h = lane >> 5;
 
   if (p.clear_status && block == 0 && threadIdx.x == 0) *p.ws_status = 0;
-  RowTile t;
-  if (!find_row_tile<BM, ROWW * KG>(p, block, reinterpret_cast<int*>(&s_kv[0][0][0][0]), t)) return;
+  int piece = 0;
+  if constexpr (SPLIT) {                                // the pieces of a row tile are neighbours, like the kv heads of one
+    const int x = block / p.n_kv_heads;
+    piece = x % p.pieces;
+    block = x / p.pieces * p.n_kv_heads + block % p.n_kv_heads;
+  }
+  auto describe = [&](const RowTile& t, int n_pieces) {  // to the merge kernel: once a row tile, also where there is none
+    if (SPLIT && piece == 0 && threadIdx.x == 0) {
+      int32_t* rd = p.ws_desc + static_cast<int64_t>(block) * 8;
+      rd[0] = t.q0; rd[1] = t.rows_total; rd[2] = t.r_tile; rd[3] = t.kvh; rd[4] = n_pieces; rd[5] = block * p.pieces; rd[6] = 0;
+    }
+  };
+  RowTile t = {};
+  const bool found = find_row_tile<BM, ROWW * KG>(p, block, reinterpret_cast<int*>(&s_kv[0][0][0][0]), t);
+  auto settle = [] { if (SPLIT) __builtin_amdgcn_s_waitcnt(0xc07f); };      // (before the workgroup may end: no scalar load is left in flight)
+  settle();
+  if (!found) {
+    describe(t, 0);
+    settle();
+    return;
+  }
   const int s = __builtin_amdgcn_readfirstlane(t.s), kvh = __builtin_amdgcn_readfirstlane(t.kvh);
   const int q0 = __builtin_amdgcn_readfirstlane(t.q0), rows_total = __builtin_amdgcn_readfirstlane(t.rows_total);
   const int r_tile = __builtin_amdgcn_readfirstlane(t.r_tile);
@@ -299,13 +321,24 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   const int cap = min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1;
   const int lim = valid ? min(p.q_pos[tok], cap) : -1;
   const int wg_max = min(p.q_pos[q0 + (min(r_tile + BM, rows_total) - 1) / p.group], cap);
-  if (wg_max < 0) return;                               // the stream defines no cache entry: rows left untouched
+  if (!SPLIT && wg_max < 0) return;                     // the stream defines no cache entry: rows left untouched
   // positions do not decrease along the rows
   const int rows_here = min(32, rows_total - w_first);
   const int wave_min = rows_here > 0 ? __builtin_amdgcn_readlane(lim, 0) : -1;
   const int wave_max = rows_here > 0 ? __builtin_amdgcn_readlane(lim, max(rows_here, 1) - 1) : -1;
   const int n_key_tiles = wg_max / kBN + 1;
   const int last_blk = wg_max / CS_KV_BLOCK;
+  // ---- this workgroup's key tiles [kt_begin, kt_end): pieces are whole trips of the groups
+  int kt_begin = 0, kt_end = n_key_tiles, n_pieces = 1;
+  if constexpr (SPLIT) {
+    const int len = ((n_key_tiles + p.pieces - 1) / p.pieces + KG - 1) / KG * KG;
+    n_pieces = wg_max < 0 ? 0 : (n_key_tiles + len - 1) / len;
+    describe(t, n_pieces);
+    settle();
+    if (piece >= n_pieces) return;
+    kt_begin = piece * len;
+    kt_end = min(kt_begin + len, n_key_tiles);
+  }
 
   // ---- tile requests.  This wave fetches rows [16 BPW rw, + 16 BPW) of its group's tiles; inside a cache block
   //      a lane's source offset is constant.  The tile that holds the frontier takes per-lane addresses: rows past
@@ -367,11 +400,11 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
     }
   };
 
-  int kt = kg;
+  int kt = kt_begin + kg;
   load_ids(kt);
   asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(last_id));
   wait_ids();
-  if (kt < n_key_tiles) {
+  if (kt < kt_end) {
     request(kt, 0, 0);
     if (STAGES == 2) request(kt, 0, 1);
   }
@@ -411,18 +444,18 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   // the others: all waves meet the same number).  us a step in step / behind: one stream of 900 keys 642 / 635, of 1,800
   // keys 883 / 865, 3 streams, 8/1 heads 617 / 608; one stream, 32/8 heads level.
   if (SPREAD && kg >= KG / 2) __syncthreads();
-  const int n_trips = (n_key_tiles + KG - 1) / KG;
+  const int n_trips = (kt_end - kt_begin + KG - 1) / KG;
   // The loop stands in a fixed place relative to the 64-byte lines that instructions are fetched by: the same instructions
   // 4 bytes off those of 8 bytes took 4-5 % longer (2 streams of 3,700 keys, 28/4 heads 90.8 us a layer instead of 86.6).
   asm volatile(".p2align 6");
   for (int trip = 0; trip < n_trips; ++trip, kt += KG) {
     wait_vmcnt<0>();
     __syncthreads();       // one stage: K has landed, every wave is done with the previous V; two: the tile, the other stage
-    const bool here = kt < n_key_tiles, computes = here && kt * kBN <= wave_max;
+    const bool here = kt < kt_end, computes = here && kt * kBN <= wave_max;
     const int stage = STAGES == 2 ? trip & 1 : 0;
     const uint32_t stage_off = stage * (2 * TILE * 2);
     if (STAGES == 2) {
-      if (kt + KG < n_key_tiles) {
+      if (kt + KG < kt_end) {
         request(kt + KG, stage ^ 1, 0);
         request(kt + KG, stage ^ 1, 1);
       }
@@ -519,7 +552,7 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
       wait_ids();
       wait_vmcnt<0>();
       __syncthreads();                     // V has landed; every wave is done with this K tile
-      if (kt + KG < n_key_tiles) request(kt + KG, 0, 0);
+      if (kt + KG < kt_end) request(kt + KG, 0, 0);
     }
     if (computes) {
 #pragma unroll
@@ -569,6 +602,9 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
     }
     const float inv = 1.f / l_all;
     uint16_t* orow = static_cast<uint16_t*>(p.out) + q_at + 32 * kg + 4 * h;
+    const bool partial = SPLIT && n_pieces > 1;
+    const int64_t prow = SPLIT ? (static_cast<int64_t>(block) * p.pieces + piece) * BM + rw * 32 + n : 0;
+    if (partial && valid && kg == 0 && h == 0) *reinterpret_cast<float2*>(p.ws_ml + prow * 2) = make_float2(m_all, l_all);
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) {
       float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -577,7 +613,9 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
         const float4 x = s_o4[((g * ROWW + rw) * DB * 4 + kg * 4 + rq) * 64 + lane];
         t.x = fmaf(w[g], x.x, t.x); t.y = fmaf(w[g], x.y, t.y); t.z = fmaf(w[g], x.z, t.z); t.w = fmaf(w[g], x.w, t.w);
       }
-      if (valid) {                         // register r of a block is d = 32 db + 8 (r / 4) + 4 h + r % 4
+      if (partial) {
+        if (valid) *reinterpret_cast<float4*>(p.ws_o + prow * D + 32 * kg + 4 * h + 8 * rq) = t;
+      } else if (valid) {                  // register r of a block is d = 32 db + 8 (r / 4) + 4 h + r % 4
         cs::u32x2 pk;
         pk.x = pack_bf16x2(t.x * inv, t.y * inv);
         pk.y = pack_bf16x2(t.z * inv, t.w * inv);
@@ -631,10 +669,10 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   }
 }
 
-template <int D, int ROWW, int KG, int STAGES>
+template <int D, int ROWW, int KG, int STAGES, bool SPLIT = false>
 __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_bf16_tile_kernel(AttnParams p) {
   __shared__ TileStages<D, KG, STAGES> stages;
-  attend_row_tile<D, ROWW, KG, STAGES>(p, blockIdx.x, stages);
+  attend_row_tile<D, ROWW, KG, STAGES, SPLIT>(p, blockIdx.x, stages);
 }
 
 // =============================================================================================
@@ -2410,11 +2448,21 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 //   kRows64Keys4 (to 128)      T 116 20.2 / 17.4, with 28 key tiles 28.3 / 24.9 (two groups 18.1, 28.7): one workgroup
 //                              per CU, all of them run at once and the longest sweep is the time; up to 8 key tiles two
 //                              groups are enough (300 keys 11.0 / 12.2, persistent 16.3)
-//   a few row tiles with       split over the whole chip, whose time goes by all tiles together; the tile kernel's by the longest sweep.  F:
-//   long sweeps (2 key tiles   row tiles without the streams' part-filled ones.  us a layer (persistent of 32 rows a wave, no longer here,) of 64 / tile:
-//   > T and > 20 + 3/8 F)      F 0, 18 tokens of 28/4 heads, 9 key tiles 12.7, 16.1 / 11.9, 16 13.6, 16.4 / 15.1, 24 14.3, 16.5 / 18.9, 48 17.2, 19.1 / 30.4;
-//                              F 12 24 key tiles 17.3, 19.9 / 19.1, 32 19.4, 21.4 / 22.9; F 40 32 27.3, 29.3 / 23.0, 40 28.4, 29.8 / 26.8; F 28, 8 streams, 32 24.1,
-//                              23.5 / 26.2; F 88 48 36.8, 36.5 / 31.0.  A BUILD call saves the plan besides (24 key tiles, F 40 38 / 19)
+//   kSplit64Keys4: few row     each in pieces of its keys, a workgroup of four key groups to a piece, and a merge launch.  As many pieces as
+//   tiles with long sweeps     let all workgroups run at once (one a CU), by the 64-row tiles U of streams that are alike, and no more than
+//                              one trip of the groups has tiles for.  us a layer, persistent of 32 rows a wave (no longer here) / of 64 / this:
+//                              18 tokens of 28/4 heads, 215 key tiles 36.0 / 32.5 / 26.4; 2 of 16/4, 21 key tiles 13.5 / 16.5 / 11.4; U 16 18 key
+//                              tiles 14.5 / 16.1 / 13.4, 72 23.6 / 23.5 / 18.2; U 48 24 21.5 / 20.3 / 15.3, 237 86 / 85 / 70; U 60 118 48.8 / 58.9 / 43.7
+//                              (without a plan either: 16 key tiles, U 64 16.9 / 15.8 / 15.2, 13 level, below a whole sweep is as fast).
+//                              Three pieces: U 78 20 21.2 / 19.9 / 18.3, 33 25.6 / 25.3 / 21.5, but 13 17.0 / 16.0 / 17.4; U 80 101 36 / 41 / 33,
+//                              113 38 / 43 / 50.  Two: U 104 72 52 / 58 / 43, U 128 48 33 / 32 / 28, 20 23.9 / 23.3 / 22.0, but U 112 17 17.1 / 15.8 /
+//                              17.5; U 128 98 45 / 55 / 46, U 93 127 37 / 40 / 47; of up to 64 rows a stream, U 72 239 122 / 115 / 109, U 80 148
+//                              91 / 89 / 75, U 116 122 107 / 98 / 92.  A piece more than fit at once costs 10-50 %, one fewer 0-20 %, hence the
+//                              mean of U and the most that n_q rows can make
+//   what is left of them (2    split from a plan: F row tiles without the streams' part-filled ones, persistent of 64 / tile: F 88 48 key tiles
+//   key tiles > T, > 20 + 3/8 F)  36.5 / 31.0, F 64 55 35.4 / (pieces 30.8)
+//   long sweeps of streams     whole in one launch: 39 streams of 11 tokens, 16/4 heads, 53 key tiles 60 / 65 / 49, 50 of 5, 73 key tiles 112 / 109 /
+//   of up to 64 rows           93 (of 96 rows 24 streams, 50 key tiles 41 / 46 / 50)
 //   single_tiles: whole        Up to 128 rows a stream and kv head on average.  The persistent kernel's jobs of 256 rows then hold one row tile,
 //   sweeps, but one row tile   two of its four waves, and a plan orders nothing.  us a layer, persistent of 32 rows a wave, two workgroups a CU
 //   a stream (kRows128)        (no longer here) / of 64 / tile: 18 tokens of 28/4 heads, 263 streams of 290 keys 45 / 63 / 51, of 550 88.5 / 99 / 95,
@@ -2422,17 +2470,32 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 //                              5 tokens of 28/4, 263 of 550 65 / 89 / 68; 4,000 to 8,300 keys 1 to 8 % below either.  Plans of 27-38 us (1,025 streams 97
 //                              and 129) are not counted.  160 streams, every eighth of 118 tokens, the others of 2: 900 keys 92 / 104 / 91.  From two row
 //                              tiles a stream on the persistent kernel wins: 27 tokens, 129 streams of 550 keys 53 / 58 / 72
-enum class TileRoute { kNone, kRows128, kRows64Keys2, kRows64Keys4 };
+enum class TileRoute { kNone, kRows128, kRows64Keys2, kRows64Keys4, kSplit64Keys4 };
 
-TileRoute tile_route_128(int64_t row_tiles, int64_t full_tiles, int key_tiles, int n_kv_heads, bool single_tiles) {
-  if (whole_sweeps(row_tiles, key_tiles, n_kv_heads)) return single_tiles ? TileRoute::kRows128 : TileRoute::kNone;
-  if (key_tiles > 64) return TileRoute::kNone;
+struct TileChoice {
+  TileRoute route;
+  int pieces;          // kSplit64Keys4: of a sweep
+};
+
+TileChoice tile_route_128(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int64_t row_tiles, int key_tiles) {
+  const int64_t rows = (n_q + n_streams - 1) / n_streams * group;                  // of a stream and kv head, if all are alike
+  // 64-row tiles: as many as alike streams have, at most n_q * group / 64 + n_streams a kv head; the mean of the two
+  const int64_t tiles64 = (((rows + 63) / 64 * n_streams + n_q * group / 64 + n_streams) * n_kv_heads + 1) / 2;
+  if (whole_sweeps(row_tiles, key_tiles, n_kv_heads))
+    return {n_q * group <= static_cast<int64_t>(kBM) * n_streams ? TileRoute::kRows128 : TileRoute::kNone, 1};
+  const int64_t trips = (key_tiles + 3) / 4;
+  const int pieces = static_cast<int>(256 / tiles64 < trips ? 256 / tiles64 : trips);
+  if (pieces >= 4 || (pieces > 1 && key_tiles > (pieces == 3 ? 15 : 20) && (key_tiles <= 112 || rows <= 64)))
+    return {TileRoute::kSplit64Keys4, pieces};
+  if (rows <= 64 && tiles64 <= 256 && key_tiles > 48) return {TileRoute::kRows64Keys4, 1};
+  if (key_tiles > 64) return {TileRoute::kNone, 1};
   if (row_tiles <= 128) {
-    if (2 * key_tiles > row_tiles && key_tiles > 20 + 3 * full_tiles / 8) return TileRoute::kNone;
-    return key_tiles > 8 ? TileRoute::kRows64Keys4 : TileRoute::kRows64Keys2;
+    const int64_t full_tiles = n_q * group / kBM * n_kv_heads;
+    if (2 * key_tiles > row_tiles && key_tiles > 20 + 3 * full_tiles / 8) return {TileRoute::kNone, 1};
+    return {key_tiles > 8 ? TileRoute::kRows64Keys4 : TileRoute::kRows64Keys2, 1};
   }
-  if (row_tiles <= 440) return key_tiles <= 48 ? TileRoute::kRows64Keys2 : TileRoute::kNone;
-  return TileRoute::kRows128;
+  if (row_tiles <= 440) return {key_tiles <= 48 ? TileRoute::kRows64Keys2 : TileRoute::kNone, 1};
+  return {TileRoute::kRows128, 1};
 }
 
 template <int D, int ROWW, int KG, int STAGES>
@@ -2441,6 +2504,15 @@ int launch_tiles(const AttnParams& p, hipStream_t st) {
   if (tiles > 0x7fffffffll) return CS_EUNSUPPORTED;
   hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES>), dim3(static_cast<unsigned>(tiles)),
                      dim3(64 * ROWW * KG), 0, st, p);
+  return cs::note_hip(hipGetLastError());
+}
+
+int launch_split_tiles(const AttnParams& p, hipStream_t st) {
+  const int64_t tiles = ((p.n_q * p.group) / p.bm + p.n_streams) * p.n_kv_heads;
+  hipLaunchKernelGGL((window_attn_bf16_tile_kernel<128, 2, 4, 1, true>), dim3(static_cast<unsigned>(tiles * p.pieces)), dim3(512), 0, st, p);
+  const int e = cs::note_hip(hipGetLastError());
+  if (e != CS_OK) return e;
+  hipLaunchKernelGGL(window_attn_merge_kernel, dim3(static_cast<unsigned>(tiles * (p.bm / 8))), dim3(256), 0, st, p);
   return cs::note_hip(hipGetLastError());
 }
 
@@ -2545,8 +2617,8 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       if (plan_mode != CS_ATTN_PLAN_BUILD && plan_mode != CS_ATTN_PLAN_REUSE && plan_mode != CS_ATTN_PLAN_ONLY)
         return CS_EINVAL;
       const AttnPlan a = plan_attn(n_q, n_streams, group, n_kv_heads, max_blocks);
-      const TileRoute route = tile_route_128(a.rt_cap, (n_q * group) / a.bm * n_kv_heads, a.max_tiles, n_kv_heads,
-                                              n_q * group <= static_cast<int64_t>(a.bm) * n_streams);
+      const TileChoice choice = tile_route_128(n_q, n_streams, group, n_kv_heads, a.rt_cap, a.max_tiles);
+      const TileRoute route = choice.route;
       if (a.items_cap * a.bm >= (1ll << 31)) return CS_EUNSUPPORTED;
       if (stride_slot >= (1ll << 26) || a.max_tiles >= (1 << 15)) return CS_EUNSUPPORTED;      // 32-bit byte offsets inside a cache block
       if (!workspace || workspace_bytes < a.total || !cs::aligned16(workspace)) return CS_EWORKSPACE;
@@ -2574,6 +2646,14 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
         p.clear_status = plan_mode == CS_ATTN_PLAN_BUILD ? 1 : 0;
         if (route == TileRoute::kRows128) return launch_tiles<128, 4, 1, 2>(p, st);
         if (route == TileRoute::kRows64Keys2) return launch_tiles<128, 2, 2, 1>(p, st);
+        if (route == TileRoute::kSplit64Keys4) {
+          // (row tiles and pieces of them: at most twice those of alike streams, so 256 and 512; the workspace has place for
+          // the items of a plan, 512 and more, and for the partial results of as many 128-row tiles)
+          p.bm = 64;
+          p.pieces = choice.pieces;
+          p.ws_desc = reinterpret_cast<int32_t*>(w + a.off_items);      // (no plan: its items' place is free)
+          return launch_split_tiles(p, st);
+        }
         return launch_tiles<128, 2, 4, 1>(p, st);
       }
       PlanParams pp;

@@ -80,7 +80,7 @@ def test_unplanned_attention_tile_edges(cs, case):
 
 
 # bf16 attention from a plan, head_dim 128: jobs of one or two 128-row tiles, four waves of 64 rows, 32 keys at a time
-# (the first two have at most 128 rows a stream on average and run without a plan)
+# (0 and 1 have at most 128 rows a stream on average, 3 to 5 few row tiles: these run without a plan)
 PLANNED_ATTN = [
     # Hq, Hkv, kv_lens, n_qs
     (8, 8, [1 + 9 * i % 71 for i in range(132)], [1 + 5 * i % (1 + 9 * i % 71) for i in range(132)]),   # one head a group, jobs of one or two key tiles
@@ -91,6 +91,9 @@ PLANNED_ATTN = [
     (28, 4, [4300], [19]),                                                                               # two row tiles, 5 rows in the second
     (8, 8, [400 if i % 2 else 1 + 9 * i % 71 for i in range(132)], [320 if i % 2 else 1 + 5 * i % (1 + 9 * i % 71) for i in range(132)]),   # one head a group, jobs of one key tile and more
     (32, 2, [40 + i % 90 for i in range(516)], [1 + i % 11 if i % 4 else 21 for i in range(516)]),        # 16 heads a group, one to three row tiles
+    (14, 2, [8100], [640]),                                                                              # split sweeps, 35 row tiles a kv head
+    (8, 2, [9000, 64, 7200], [750, 64, 431]),                                                            # split and whole, frontiers far apart
+    (56, 4, [4300, 4250], [150, 10]),                                                                    # 140 rows: 12 in the second row tile
 ]
 
 
@@ -124,7 +127,7 @@ def test_planned_attention_dealt_by_length(cs, case):
 # same key tile: the two are no job, since the keys of a job end with its first row tile's.
 FIRST_TILE_ALONE = [
     # Hq, Hkv, kv_lens, n_qs
-    (32, 8, [128, 5000], [70, 512]), (64, 8, [60, 4300], [40, 40]), (56, 8, [64, 4300], [41, 90]), (64, 4, [60, 4300], [40, 150]),
+    (32, 8, [128, 5000], [70, 512]), (64, 8, [60, 8000], [40, 40]), (56, 8, [64, 8000], [41, 90]), (64, 4, [60, 4300], [40, 150]),
     (64, 8, [2072], [2064]),                                                                             # whole sweeps, ordered by length
 ]
 
@@ -252,13 +255,31 @@ MANY_STREAMS = [
 ]
 
 
-# Few row tiles, 20 + 3/8 of the full ones key tiles and one more: the tile kernel, and sweeps split over the chip.
-FEW_ROW_TILES = [(28, 4, 1280, 18), (28, 4, 1281, 18), (28, 4, 1535, 70), (28, 4, 1545, 70), (16, 1, 1472, 70), (16, 1, 1473, 70)]
+# Few row tiles with long sweeps: in pieces, each a workgroup.  Both sides of every line (pieces of a sweep, by the 64-row tiles;
+# key tiles), rows at the edges of row tiles, streams that are shorter than others or have no rows.
+FEW_ROW_TILES = [
+    # Hq, Hkv, kv_lens, n_qs
+    (28, 4, [750, 40], [17, 1]), (28, 4, [752, 40], [17, 1]), (28, 4, [753, 40], [17, 1]),               # 12 and 13 key tiles
+    (28, 4, [5300, 1], [69, 1]), (16, 1, [1472, 64], [69, 1]), (8, 1, [17000], [8]), (8, 1, [17000], [9]),       # 64 and 72 rows
+    (32, 4, [1900 - 60 * i for i in range(6)], [16, 0, 8, 17, 9, 0]),                                    # streams without rows, one to three row tiles
+    (16, 16, [3000, 2990, 100, 3010], [64, 65, 64, 33]),                                                 # one head a group, two pieces
+    (16, 16, [1230], [1]), (16, 1, [1100], [1]), (16, 1, [65, 15000], [3, 4]),
+    (4, 1, [900 + 7 * i for i in range(66)], [1 + i % 16 for i in range(66)]),                           # more streams than a wave has lanes, three pieces
+    (4, 1, [1300 + 7 * i for i in range(100)], [1 + i % 16 for i in range(100)]),                        # two
+    (4, 1, [1300 + 7 * i for i in range(103)], [1 + i % 16 for i in range(103)]),                        # one
+    (4, 1, [3100 + 9 * i for i in range(150)], [1 + i % 16 for i in range(150)]),                        # whole sweeps of up to 64 rows
+    (2, 1, [1700] * 100, [3] * 99 + [700]),                                                              # unlike streams: more row tiles than the rule counts
+]
 
 
-@pytest.mark.parametrize("hq,hkv,window,rows", FEW_ROW_TILES)
-def test_attention_of_few_row_tiles(cs, hq, hkv, window, rows):
-    say(f"  -> {_attn_case(cs, np.random.default_rng(9490 + window), 'bf16', hq, hkv, 128, [window - 16, 50], [rows - 1, 1])}")
+@pytest.mark.parametrize("case", range(len(FEW_ROW_TILES)))
+def test_attention_of_few_row_tiles(cs, case):
+    hq, hkv, kv_lens, n_qs = FEW_ROW_TILES[case]
+    say(f"attention of few row tiles {case}: heads={hq}/{hkv} kv={kv_lens[:6]} n_q={n_qs[:6]} streams={len(kv_lens)}")
+    for mult, last in ((1.0, False), (6.0, True)):
+        r = _attn_case(cs, np.random.default_rng(9490 + case), "bf16", hq, hkv, 128, kv_lens, n_qs, scale_mult=mult, last_queries=last, left=(left := []))
+        say(f"  -> {r}")
+        assert left[0] == left[1]                                         # no plan
 
 
 @pytest.mark.parametrize("case", range(len(MANY_STREAMS)))
@@ -275,7 +296,8 @@ def test_attention_of_many_streams(cs, case):
 NOT_FINITE = [
     # Hq, Hkv, d, streams, window
     (16, 8, 128, 64, 400),       # from a plan, whole sweeps
-    (16, 8, 128, 2, 4300),       # from a plan, split sweeps
+    (16, 8, 128, 2, 4300),       # no plan, sweeps in pieces
+    (16, 8, 128, 6, 7300),       # from a plan, split sweeps
     (16, 8, 128, 8, 400),        # no plan
     (8, 4, 64, 3, 400),
 ]

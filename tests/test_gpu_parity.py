@@ -870,10 +870,11 @@ def test_attention_plan_modes(cs):
 
 FUSED_CASES = [
     # dtype, Hq, Hkv, d, kv_lens, n_qs
-    ("bf16", 28, 4, 128, [915], [425]),                        # split sweeps (merge kernel after the fused launch)
+    ("bf16", 28, 4, 128, [915], [425]),                        # no plan, two launches
+    ("bf16", 28, 4, 128, [6033], [300]),                       # split sweeps (merge kernel after the fused launch)
     ("bf16", 32, 8, 128, [300, 1, 640, 77], [100, 1, 333, 0]),
     ("bf16", 28, 4, 128, [1100 + 13 * i for i in range(32)], [380 + 5 * i for i in range(32)]),   # all 256 workgroups busy
-    ("bf16", 8, 2, 128, [3000, 700, 40], [257, 64, 40]),
+    ("bf16", 8, 2, 128, [3000, 700, 40], [257, 64, 40]),       # sweeps in pieces, three launches
     ("bf16", 4, 4, 64, [200, 129], [64, 129]),                 # head_dim 64: two launches behind the one call
     ("f32", 2, 1, 64, [452], [332]),                           # fp32: two launches behind the one call
     ("bf16", 32, 8, 128, [200 + i for i in range(66)], [31] * 66),      # one row tile a stream: no plan, two launches
