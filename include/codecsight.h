@@ -445,8 +445,8 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  *
  * Exactly cs_kv_refresh_scatter(k_new, v_new, slot, ..., n_tok, ...) followed by
  * cs_window_prefill_attn(q, ..., plan_mode, ...) on the same layer, same arguments, same results
- * bit for bit.  CS_BF16 with head_dim 128, where attention runs from a plan and has at least 1,024 row tiles or
- * splits its sweeps by it (see cs_window_prefill_attn): ONE launch: every workgroup of the persistent attention
+ * bit for bit.  CS_BF16 with head_dim 128, where attention runs from a plan that splits its sweeps, or has at
+ * least 1,024 row tiles and is not of streams of few rows (those have two workgroups per CU): ONE launch: every workgroup of the persistent attention
  * grid first moves its share of the new rows (stores written through to memory at device scope),
  * the grid meets at a launch-wide barrier, then attention proceeds as in cs_window_prefill_attn; a
  * CS_ATTN_PLAN_BUILD call is preceded by the planning launch, a CS_ATTN_PLAN_ONLY call plans and

@@ -159,6 +159,11 @@ typedef __attribute__((ext_vector_type(8))) int32_t i32x8;
 
 // Scalar loads issued by hand: the results are uniform, travel outside the vector-memory queue
 // (so waiting for them never drains tile requests) and are only read after the explicit wait.
+__device__ __forceinline__ i32x8 sload8(const void* ptr) {
+  i32x8 v;
+  asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
+  return v;
+}
 __device__ __forceinline__ int32_t sload1(const void* ptr) {
   int32_t v;
   asm volatile("s_load_dword %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
@@ -690,7 +695,8 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 // the same key tile, as ONE job of 256 rows: every K/V tile that it fetches, and every fragment
 // that a wave reads from LDS, then serves twice the rows (see window_attn_bf16_stream_kernel).  The plan makes
 // chains of units: two neighbouring row tiles of a stream counted from its end, or, of a pair whose row tiles go
-// to all XCDs, two that the same XCD takes.
+// to all XCDs, two that the same XCD takes.  For streams of few rows a kernel with two workgroups per CU takes every row tile
+// as a job of its own (window_attn_bf16_rows32_kernel).
 
 // Item descriptor: 8 ints.  [0] first query token of the stream, [1] rows of the stream (tokens x
 // heads per kv group), [2] first row of the tile, [3] kv head | stream << 8, [4] highest visible
@@ -700,7 +706,7 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 // Plan header (ints): [0..8] list offsets per XCD, [9] row tiles, [16..23] end item,
 // then one 32-int entry per workgroup j of XCD x at [32 + 32 (64 x + j)]: [0] its first item (-1: none),
 // [8..15] a copy of that item's descriptor (all that the workgroup reads of its entry).
-// Entries from kWorkgroupsPerXcd on name no item.
+// Entries from kWorkgroupsPerXcd on name no item but where two workgroups share a CU (window_attn_bf16_rows32_kernel).
 constexpr int kSlotsPerXcd = 64;      // header entries per XCD
 constexpr int kWorkgroupsPerXcd = 32; // persistent workgroups per XCD: one per CU
 constexpr int kHdrEndItem = 16, kHdrHeads = 32;
@@ -717,6 +723,7 @@ constexpr int kPlanHeaderInts = kHdrSyncBase + kSyncInts;
 // 244 us a layer, over 6,000 keys 111 against 104.
 constexpr int kItemFixedCostHalves = 5;
 constexpr int kPlanThreads = 1024;
+constexpr int kSoloFixedCostHalves = 3;  // ... and an item of the kernel of 32 rows a wave
 constexpr int kDealAtOnce = 72;       // units of an XCD that are dealt by length over the whole list (at most two a lane)
 constexpr int kSortMax = 2048;        // streams sorted by work in LDS; beyond, stream order is kept
 
@@ -726,6 +733,7 @@ struct PlanParams {
   const int32_t* __restrict__ kv_len;
   int32_t max_blocks;
   int32_t n_streams, group, n_kv_heads, max_tiles, r_cap, bm, n_slots, hist_pitch;   // n_slots: workgroups per XCD
+  int32_t solo;         // 1: every row tile is a unit of its own (window_attn_bf16_rows32_kernel)
   int32_t* header;      // [kPlanHeaderInts]
   int32_t* items;       // [items_cap][8]
   int32_t* rt_desc;     // [r_cap * n_kv_heads][8]: q0, rows_total, r_tile, kvh, n_split
@@ -1209,7 +1217,9 @@ __device__ __forceinline__ void plan_work(const PlanParams& pp, PlanLds& lds, Sp
       // -3 - i with item i).  Of a whole pair two neighbours make a unit; of a pair left over the row tiles that this
       // XCD takes, two by two
       int unit = -1;
-      if (!grouped || pair < whole_pairs) {
+      if (grouped && pp.solo) {
+        unit = -2;
+      } else if (!grouped || pair < whole_pairs) {
         if ((level & 1) == 0) unit = t > 0 ? -4 - pos : -2;
       } else if ((level & 8) == 0) {
         unit = t >= 8 ? -3 - (s_list_off[x] + start + left_before(pair, level + 8, x)) : -2;
@@ -1249,7 +1259,8 @@ __device__ __forceinline__ void plan_work(const PlanParams& pp, PlanLds& lds, Sp
           else first_item = idx;
           last = idx;
         }
-        load += 2 * tiles + kItemFixedCostHalves;
+        // (the second of two workgroups of a CU, which the issue arbiter serves less often, gets 3/4 of the first one's work)
+        load += pp.solo ? (2 * tiles + kSoloFixedCostHalves) * (lane >= kWorkgroupsPerXcd ? 4 : 3) : 2 * tiles + kItemFixedCostHalves;
       };
       // A short pair-ordered list is dealt by length over the whole list: its pairs are under way together in any case, and
       // batches in list order let long units meet.  us a step in list order / by length: 12 streams of 1,000 keys (71 units an
@@ -1291,7 +1302,7 @@ __device__ __forceinline__ void plan_work(const PlanParams& pp, PlanLds& lds, Sp
         for (int dealt = 0; dealt < n_units; dealt += n_wg) {
           int load_rank = 0;
 #pragma unroll 8
-          for (int j = 0; j < kWorkgroupsPerXcd; ++j) {
+          for (int j = 0; j < n_wg; ++j) {
             const int wj = __builtin_amdgcn_readlane(load, j);
             load_rank += (wj < load || (wj == load && j < lane)) ? 1 : 0;
           }
@@ -1324,7 +1335,7 @@ __device__ __forceinline__ void plan_work(const PlanParams& pp, PlanLds& lds, Sp
             item_rank += (lj > len || (lj == len && j < lane)) ? 1 : 0;
           }
 #pragma unroll 8
-          for (int j = 0; j < kWorkgroupsPerXcd; ++j) {
+          for (int j = 0; j < n_wg; ++j) {
             const int wj = __builtin_amdgcn_readlane(load, j);
             load_rank += (wj < load || (wj == load && j < lane)) ? 1 : 0;
           }
@@ -2128,6 +2139,384 @@ __global__ __launch_bounds__(256, 1) void window_attn_bf16_stream_kernel(AttnPar
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
+// The persistent kernel for streams of few rows: 4 waves of 32 rows, a row tile a job, two workgroups per CU.  Jobs of 256
+// rows (below) are too coarse there: a stream's last row tile is alone in every other job and leaves two waves without work,
+// two units a workgroup and a few more take three rounds, and a job's own 8,900 cycles weigh on short sweeps.  Here the
+// second workgroup of a CU fills what the first leaves idle.  What bounds it: the vector pipe beside the matrix pipe, and on
+// the shortest sweeps K and V at memory rate.
+// us a layer of REUSE calls, jobs of 256 rows / this kernel: 68 streams of 200 rows a kv head, 32/8 heads, 700 keys 86 / 56, 137 of 252,
+// 28/4 heads 85 / 55, 34 of 448, 32/8 heads 97 / 69 (1,300 keys).  Where it runs and where not: solo_row_tiles.
+// Tile requests run one tile ahead of the computation ACROSS item boundaries; item descriptors and cache-block ids arrive by
+// scalar loads a tile ahead of their use, the queries of the next item are requested before the finished one is stored.
+__global__ __launch_bounds__(256, 2) void window_attn_bf16_rows32_kernel(AttnParams p) {
+  constexpr int D = 128;
+  constexpr int STEPS = D / 16, DB = D / 32;
+  constexpr int TILE = kBN * D;         // elements of one K (or V) tile: 16 KiB, unpadded
+  constexpr int IPW = 4;                // 1-KiB DMA instructions per wave, per tile, per tensor
+
+  __shared__ __attribute__((aligned(1024))) uint16_t sK[2][TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t sV[2][TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t s_sink[4][512];   // see request_part
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, h = lane >> 5;
+
+  // ---- this workgroup's items: a chain through the `next` field of the descriptors; three are kept loaded
+  const int xcd = blockIdx.x & 7, slot_j = blockIdx.x >> 3;
+  auto item_at = [&](int idx) -> const int32_t* {
+    return idx >= 0 ? p.ws_items + static_cast<int64_t>(idx) * 8 : p.ws_plan + kHdrEndItem;
+  };
+  i32x8 d0 = sload8(p.ws_plan + kHdrHeads + kHdrEntryInts * (xcd * kSlotsPerXcd + slot_j) + 8);
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(d0));
+  if ((d0[5] >> 16) == 0) return;       // nothing for this workgroup
+
+  // ---- constants of the lane: DMA sources inside a cache block, LDS addresses of its fragments in stage 0
+  const uint16_t* kall = static_cast<const uint16_t*>(p.k);
+  const uint16_t* vall = static_cast<const uint16_t*>(p.v);
+  const int64_t blk_stride = static_cast<int64_t>(CS_KV_BLOCK) * p.stride_slot;
+  const int l_row = lane >> 4, l_pos = lane & 15;
+  uint32_t k_off[IPW], v_off[IPW];      // byte offsets inside a cache block (the host checks the range)
+  int k_chunk[IPW], v_chunk[IPW];
+#pragma unroll
+  for (int i = 0; i < IPW; ++i) {
+    const int trow = 4 * i + l_row;                         // row of this wave's block
+    k_chunk[i] = l_pos ^ trow;
+    v_chunk[i] = l_pos ^ (4 * (trow & 3) + 2 * ((trow >> 2) & 1));
+    k_off[i] = static_cast<uint32_t>((trow * p.stride_slot + k_chunk[i] * 8) * 2);
+    v_off[i] = static_cast<uint32_t>((trow * p.stride_slot + v_chunk[i] * 8) * 2);
+  }
+  uint32_t k_addr[STEPS], v_addr[DB];
+#pragma unroll
+  for (int st = 0; st < STEPS; ++st)
+    k_addr[st] = lds_address(&sK[0][0]) + 2 * (n * D + (((2 * st + h) ^ (n & 15)) << 3));
+  const int i16 = lane & 15, gid = (lane >> 4) & 1;
+  const int v_row = 4 * h + (i16 >> 2);
+  const int v_swz = 4 * (v_row & 3) + 2 * (v_row >> 2);
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+    v_addr[db] = lds_address(&sV[0][0]) + 2 * (v_row * D + (((4 * db + 2 * gid + ((i16 & 3) >> 1)) ^ v_swz) << 3) + 4 * (i16 & 1));
+
+  // ---- a slot of the tile stream: one key tile of one item, with the cache-block ids its request needs (this wave's
+  //      quarter of the tile, and the block of the item's frontier)
+  struct Slot {
+    int kt, ke, wg_max, seq;
+    const int32_t* row;  // the stream's block-table row
+    int64_t head_off;    // element offset of the kv head inside a cache row
+    int id, last_id;
+    int live;            // an int: a bool would leave tail padding that struct copies drag through memory
+  };
+  i32x8 d1, d2;
+  int seq0 = 0;                         // d0 is the seq0-th item of this workgroup
+  auto first_slot = [&](const i32x8& d, int seq) {
+    Slot s;
+    s.kt = d[5] & 0xffff; s.ke = d[5] >> 16; s.wg_max = d[4]; s.seq = seq;
+    s.row = p.block_table + static_cast<int64_t>(d[3] >> 8) * p.max_blocks;
+    s.head_off = static_cast<int64_t>(d[3] & 255) * p.stride_head;
+    s.id = 0; s.last_id = 0;
+    s.live = (d[5] >> 16) > 0 ? 1 : 0;
+    return s;
+  };
+  auto successor = [&](const Slot& c) {
+    if (c.kt + 1 < c.ke) {
+      Slot s = c;
+      s.kt = c.kt + 1;
+      return s;
+    }
+    const int rel = c.seq + 1 - seq0;                       // 1 or 2
+    return first_slot(rel == 1 ? d1 : d2, c.seq + 1);
+  };
+  auto request_ids = [&](Slot& s) {
+    const int last_blk = max(s.wg_max, 0) >> 4;           // CS_KV_BLOCK = 16
+    s.id = sload1(s.row + min(s.kt * 4 + wave, last_blk));
+    s.last_id = sload1(s.row + last_blk);
+  };
+  // A tile request is 8 DMA instructions per wave (4 for K, 4 for V), each moving 1 KiB.  Issued back to back they hold the
+  // wave for hundreds of cycles: regular tiles are issued one instruction at a time between the matrix instructions of the S
+  // phase, with a wave-uniform base and the lane's constant offset.  The S phase always issues its eight parts, so that no
+  // branch splits it: when there is nothing to request (the next tile holds a frontier and went out at once, or there is
+  // none) they re-read the current tile's cache block into a 1-KiB sink.
+  const uint16_t *req_k = nullptr, *req_v = nullptr;
+  uint32_t req_dst_k = 0, req_dst_v = 0, req_step = 0;
+  const uint32_t lds_k0 = lds_address(&sK[0][wave * IPW * 512]), lds_v0 = lds_address(&sV[0][wave * IPW * 512]);
+  const uint32_t lds_sink = lds_address(&s_sink[wave][0]);
+  auto request_part = [&](int part) {
+    const int i = part & 3;
+    if (part < 4) dma16_sa(k_off[i], req_k, req_dst_k + i * req_step);
+    else dma16_sa(v_off[i], req_v, req_dst_v + i * req_step);
+  };
+  auto prepare = [&](const Slot& s, uint32_t dst_k, uint32_t dst_v, uint32_t step) {
+    // (a block spans fewer than 2^31 elements: the host checks the slot stride)
+    const int64_t at = s.head_off + static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(s.id)) *
+                                                         static_cast<uint32_t>(blk_stride));
+    req_k = kall + at;
+    req_v = vall + at;
+    req_dst_k = dst_k;
+    req_dst_v = dst_v;
+    req_step = step;
+  };
+  auto prepare_sink = [&](const Slot& s) { prepare(s, lds_sink, lds_sink, 0); };
+  auto prepare_regular = [&](const Slot& s, int stage) { prepare(s, lds_k0 + stage * (TILE * 2), lds_v0 + stage * (TILE * 2), 1024); };
+  auto issue = [&](const Slot& s, int stage) {     // the whole request at once
+    if (s.kt != s.wg_max / kBN) {
+      prepare_regular(s, stage);
+#pragma unroll
+      for (int part = 0; part < 2 * IPW; ++part) request_part(part);
+      return;
+    }
+    // the tile that holds the frontier of its item: rows past the frontier may be unallocated or hold anything, they
+    // fetch the frontier row instead (finite data, weight 0 after masking)
+    const uint16_t* kg = kall + s.head_off;
+    const uint16_t* vg = vall + s.head_off;
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      const int q = wave * IPW + i;
+      const int j_un = s.kt * kBN + 4 * q + l_row;
+      const bool over = j_un > s.wg_max;
+      const int j = over ? s.wg_max : j_un;
+      const int64_t slot = static_cast<int64_t>(over ? s.last_id : s.id) * CS_KV_BLOCK + j % CS_KV_BLOCK;
+      dma16(kg + slot * p.stride_slot + k_chunk[i] * 8, &sK[stage][q * 512]);
+      dma16(vg + slot * p.stride_slot + v_chunk[i] * 8, &sV[stage][q * 512]);
+    }
+  };
+
+  // ---- per-item state of the lane
+  bf16x8 qf[STEPS];
+  int lim_raw = 0, it_tok_head = 0;
+  bool it_valid = false;
+  int it_rows_left = 0;                 // rows of the stream at and after this wave's first row
+  auto load_item = [&](const i32x8& d) {
+    it_rows_left = d[1] - (d[2] + wave * 32);
+    const int row = d[2] + wave * 32 + n;
+    it_valid = row < d[1];
+    const int row_c = it_valid ? row : d[1] - 1;
+    const int tq = row_c / p.group;
+    const int tok = d[0] + tq;
+    it_tok_head = tok * p.n_q_heads + (d[3] & 255) * p.group + (row_c - tq * p.group);
+    const uint16_t* qrow = static_cast<const uint16_t*>(p.q) + static_cast<int64_t>(it_tok_head) * D;
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st)
+      qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const cs::u32x4*>(qrow + 16 * st + 8 * h));
+    lim_raw = min(p.q_pos[tok], d[4]);      // d[4]: the tile's frontier, already inside the stream's entries
+  };
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) o[db] = zero16;
+  float m_run = kNegInf, l_run = 0.f;
+  int lim = -1, wave_min = -1, wave_max = -1;
+  const float slack = kMaxSlack / p.scale_log2e;
+
+  auto compute = [&](int kt, int stage) {
+    const int j0 = kt * kBN;
+    f32x16 sacc[2];
+    constexpr int KPF = 2;        // K fragments are read two steps ahead of their matrix instructions
+    bf16x8 ka[KPF + 1][2];
+    typedef __attribute__((address_space(3))) const cs::u32x4 lds_u32x4;
+    // LDS addresses of this tile's fragments: one add per address and tile; pinned in registers, so that every read folds
+    // its row-group offset into the instruction's immediate field
+    const uint32_t stage_off = static_cast<uint32_t>(stage) * (TILE * 2);
+    uint32_t kad[STEPS], va[DB];
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+      kad[st] = k_addr[st] + stage_off;
+      asm volatile("" : "+v"(kad[st]));
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      va[db] = v_addr[db] + stage_off;
+      asm volatile("" : "+v"(va[db]));
+    }
+    auto k_frag = [&](int st, int kb) {
+      return __builtin_bit_cast(bf16x8, reinterpret_cast<lds_u32x4*>(static_cast<uintptr_t>(kad[st]))[kb * 32 * D * 2 / 16]);
+    };
+#pragma unroll
+    for (int st = 0; st < KPF; ++st) {
+      ka[st][0] = k_frag(st, 0);
+      ka[st][1] = k_frag(st, 1);
+    }
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+      if (st + KPF < STEPS) {
+        ka[(st + KPF) % (KPF + 1)][0] = k_frag(st + KPF, 0);
+        ka[(st + KPF) % (KPF + 1)][1] = k_frag(st + KPF, 1);
+      }
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+        sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[st % (KPF + 1)][kb], qf[st], st == 0 ? zero16 : sacc[kb], 0, 0, 0);
+      request_part(st);
+    }
+    // pin that order (the scheduler would otherwise pull each read back to just before its use)
+    __builtin_amdgcn_sched_group_barrier(0x100, 2 * KPF, 0);
+#pragma unroll
+    for (int st = 0; st < STEPS - KPF; ++st) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 2 * KPF, 0);
+    if (j0 + kBN - 1 > wave_min) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = j0 + 32 * kb + 8 * (r / 4) + 4 * h + (r % 4);
+          if (key > lim) sacc[kb][r] = kNegInf;
+        }
+    }
+    float t_max = kNegInf;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) t_max = fmaxf(t_max, sacc[kb][r]);
+    // the two half-waves hold the same queries
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t_max), __float_as_uint(t_max), false, false);
+    t_max = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    if (__any(t_max > m_run + slack)) {
+      const bool up = t_max > m_run + slack;
+      const float m_new = up ? t_max : m_run;
+      const float alpha = up ? __builtin_amdgcn_exp2f((m_run - m_new) * p.scale_log2e) : 1.f;
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    }
+    const float m_scaled = (m_run == kNegInf ? 0.f : m_run) * p.scale_log2e;
+    bf16x8 pb[2][2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int mm = 0; mm < 2; ++mm) {
+        cs::u32x4 w;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float e0 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * mm + 2 * c], p.scale_log2e, -m_scaled));
+          const float e1 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * mm + 2 * c + 1], p.scale_log2e, -m_scaled));
+          const uint32_t pk = pack_bf16x2(e0, e1);
+          l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), __builtin_bit_cast(bf16x2, 0x3f803f80u), l_run, false);
+          w[c] = pk;
+        }
+        pb[kb][mm] = __builtin_bit_cast(bf16x8, w);
+      }
+    // 16 matrix instructions, m = (key block, key half, d block); V^T fragments are read VPF of them ahead
+    constexpr int VPF = 3;
+    s16x4 vlo[VPF + 1], vhi[VPF + 1];
+    auto v_frag = [&](int m) {
+      const int g0 = (32 * (m >> 3) + 16 * ((m >> 2) & 1)) * D;
+      const uint32_t a = va[m & 3];
+      vlo[m % (VPF + 1)] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(((lds_s16x4*)(static_cast<uintptr_t>(a))) + g0 * 2 / 8);
+      vhi[m % (VPF + 1)] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(((lds_s16x4*)(static_cast<uintptr_t>(a))) + (g0 + 8 * D) * 2 / 8);
+    };
+#pragma unroll
+    for (int m = 0; m < VPF; ++m) v_frag(m);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      if (m + VPF < 16) v_frag(m + VPF);
+      const s16x8 a = __builtin_shufflevector(vlo[m % (VPF + 1)], vhi[m % (VPF + 1)], 0, 1, 2, 3, 4, 5, 6, 7);
+      o[m & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pb[m >> 3][(m >> 2) & 1], o[m & 3], 0, 0, 0);
+    }
+  };
+
+  // Normalises and stores the rows of the finished item, then clears the accumulators.
+  auto finish_item = [&](int tok_head, bool valid) {
+    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    if (valid) {
+      const float inv = __builtin_amdgcn_rcpf(l_tot);      // 1 ulp: far below the bf16 result's rounding
+      uint16_t* orow = static_cast<uint16_t*>(p.out) + static_cast<int64_t>(tok_head) * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          cs::u32x2 w;
+          w.x = pack_bf16x2(o[db][4 * rq + 0] * inv, o[db][4 * rq + 1] * inv);
+          w.y = pack_bf16x2(o[db][4 * rq + 2] * inv, o[db][4 * rq + 3] * inv);
+          *reinterpret_cast<cs::u32x2*>(orow + 32 * db + 8 * rq + 4 * h) = w;
+        }
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = zero16;
+    m_run = kNegInf;
+    l_run = 0.f;
+  };
+
+  // ---- prologue: first item, first tile request, the next two items, block ids of the second slot
+  Slot cur = first_slot(d0, 0);
+  request_ids(cur);
+  d1 = sload8(item_at(d0[6]));
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(cur.id), "+s"(cur.last_id), "+s"(d1));
+  issue(cur, 0);
+  d2 = sload8(item_at(d1[6]));
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(d2));
+  Slot nxt = successor(cur);
+  request_ids(nxt);
+  load_item(d0);
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(nxt.id), "+s"(nxt.last_id));
+  bool new_item = true, ep_pending = false, ep_valid = false;
+  int ep_tok_head = 0;
+  int stage = 0;
+
+  for (;;) {
+    // everything requested so far has landed: the tile of `cur`, and at an item boundary the queries and frontier of its
+    // item (telling the compiler so here keeps it from waiting for them later, when that wait would also cover the tile
+    // request issued below)
+    wait_vmcnt<0>();
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) asm volatile("" : "+v"(qf[st]));
+    asm volatile("" : "+v"(lim_raw));
+    __syncthreads();                     // every wave's share landed; every wave left the other stage
+    if (new_item) {
+      lim = it_valid ? lim_raw : -1;
+      const int rows_here = min(32, it_rows_left);        // rows of this wave that exist; positions do not decrease along them
+      wave_min = rows_here > 0 ? __builtin_amdgcn_readlane(lim, 0) : -1;
+      wave_max = rows_here > 0 ? __builtin_amdgcn_readlane(lim, max(rows_here, 1) - 1) : -1;
+      new_item = false;
+    }
+    // request the next tile: at once if it holds the frontier of its item or if this wave has nothing to compute in this
+    // step, else spread over the S phase of this step
+    const bool computes = cur.kt * kBN <= wave_max;
+    if (nxt.live && computes && nxt.kt != nxt.wg_max / kBN) {
+      prepare_regular(nxt, stage ^ 1);
+    } else {
+      if (nxt.live) issue(nxt, stage ^ 1);
+      prepare_sink(cur);
+    }
+    // scalar requests for later steps: block ids of the slot after next; at the last tile of an item also the descriptor
+    // three items ahead.  Always issued, towards harmless addresses when there is nothing to fetch: a conditional request
+    // would let the compiler merge the pending register with another value before the wait
+    const bool cur_last = cur.kt + 1 == cur.ke;
+    Slot nn = nxt.live ? successor(nxt) : nxt;
+    request_ids(nn);
+    i32x8 d3 = sload8(cur_last ? item_at(d2[6]) : p.ws_plan + kHdrEndItem);
+
+    if (ep_pending) {
+      finish_item(ep_tok_head, ep_valid);
+      ep_pending = false;
+    }
+    if (computes) compute(cur.kt, stage);
+
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(nn.id), "+s"(nn.last_id), "+s"(d3));
+    if (cur_last) {
+      ep_pending = true;
+      ep_tok_head = it_tok_head;
+      ep_valid = it_valid;
+      if ((d1[5] >> 16) > 0) {
+        load_item(d1);
+        new_item = true;
+      }
+      d0 = d1; d1 = d2; d2 = d3;
+      ++seq0;
+    }
+    if (!nxt.live) break;
+    cur = nxt;
+    nxt = nn;
+    stage ^= 1;
+  }
+  finish_item(ep_tok_head, ep_valid);
+  wait_vmcnt<0>();                       // no request may land after the workgroup's LDS has been given on
+}
+
 // Merges the partial results of split row tiles: out = sum_c w_c O_c / sum_c w_c l_c with
 // w_c = 2^((m_c - max_c m_c) * scale * log2 e).  One workgroup per 8 rows; 32 threads per row.
 __global__ __launch_bounds__(256) void window_attn_merge_kernel(AttnParams p) {
@@ -2371,7 +2760,8 @@ struct AttnPlan {
   int64_t rt_cap;        // ... times kv heads
   int64_t items_cap;     // upper bound on work items
   int max_tiles;         // key tiles of the longest sweep
-  int grid;              // persistent workgroups: 8 XCDs x up to kWorkgroupsPerXcd
+  int grid;              // persistent workgroups: 8 XCDs x up to kWorkgroupsPerXcd, or twice as many
+  int solo;              // whole sweeps in the kernel of 32 rows a wave
   int bm;                // rows per item
   int hist_pitch;        // buckets of the planner's counting sort, per XCD
   int span, pref_pitch;  // span plan (see plan_spans) and the ints per XCD of its prefix array
@@ -2387,6 +2777,24 @@ bool whole_sweeps(int64_t row_tiles, int key_tiles, int n_kv_heads) {
   return row_tiles >= (n_kv_heads > 4 ? 768 : 512) && key_tiles > 8 && key_tiles <= 32;
 }
 
+// Of those from 1,024 row tiles on, launches whose row tiles are jobs of their own (window_attn_bf16_rows32_kernel), by the
+// mean of the streams' rows, the row tiles T and the key tiles.  us a layer of REUSE calls, jobs of 256 rows / this kernel,
+// streams alike (five head layouts) and, in brackets, of 0.4 to 1.6 times the rows and keys:
+//   up to 260 rows, 300 keys  T 1,100 46.5 / 33 (41 / 33), T 2,600 72 / 60 (67 / 60); 700 keys T 1,100 78 / 56 (66 / 62),
+//                             T 2,600 1.16 times as long (1.03), T 5,000 1.11 (1.01); 1,300 keys 1.26 to 1.11 (1.03 to 1.00);
+//                             47 key tiles 1.08 to 0.98; 75 key tiles (1.00 to 0.95)
+//   up to 400                 300 and 700 keys 1.37 to 1.11 (1.17 to 0.99), 1,300 keys 1.31 to 1.11 (1.02 to 0.98), 47 key tiles
+//                             1.18 to 1.04, 75 (0.97 to 0.94)
+//   up to 1,400               T below 2,600: 640 rows 1.23 to 1.02 (1.18 to 1.01), 1,000 rows 1.13 to 1.00 (1.07 to 0.99), 1,300 rows
+//                             1.08 to 0.97 (1.04 to 0.97); 33 key tiles (0.96 to 0.92).  T above: 640 rows 1.04 to 1.01
+//                             (0.97), 1,000 rows 1.01 to 0.98 (0.97 to 0.94)
+//   beyond                    1,700 rows 1.01 to 0.94, 2,400 rows 1.03 to 0.92
+// (1,024 row tiles of at most 1,400 rows a stream are 86 pairs at least: the planner deals by pair.)
+bool solo_row_tiles(int64_t n_q, int32_t n_streams, int32_t group, int64_t row_tiles, int key_tiles) {
+  const int64_t rows = n_q * group;
+  return row_tiles >= 1024 && ((rows <= 400ll * n_streams && key_tiles <= 48) || (rows <= 1400ll * n_streams && key_tiles <= 24 && row_tiles < 2500));
+}
+
 AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int32_t max_blocks) {
   AttnPlan a;
   a.bm = kBM;
@@ -2400,7 +2808,9 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
   a.items_cap = a.span ? a.rt_cap + 2 * 8 * kWorkgroupsPerXcd : a.rt_cap;
   a.pref_pitch = static_cast<int>(a.rt_cap / 8 + 2);
   const int64_t per_xcd = (a.items_cap + 7) / 8;
-  a.grid = 8 * static_cast<int>(per_xcd < kWorkgroupsPerXcd ? per_xcd : kWorkgroupsPerXcd);
+  a.solo = solo_row_tiles(n_q, n_streams, group, a.rt_cap, a.max_tiles) ? 1 : 0;
+  const int64_t most = a.solo ? kSlotsPerXcd : kWorkgroupsPerXcd;
+  a.grid = 8 * static_cast<int>(per_xcd < most ? per_xcd : most);
   size_t at = kPlanHeaderInts * sizeof(int32_t);
   auto take = [&](size_t bytes) {
     const size_t here = (at + 255) & ~static_cast<size_t>(255);
@@ -2634,7 +3044,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       // Without a plan the refresh write is a launch of its own, and so it is for whole sweeps of few row tiles: the launch-wide
       // barrier takes 4-9 us more than that launch (10 streams of 420 tokens, 610 keys, us a layer of a graph 47.9 / 42.0).
       const bool few = a.rt_cap < 1024;
-      const bool one_launch = fuse && route == TileRoute::kNone && (a.span || !few);
+      const bool one_launch = fuse && route == TileRoute::kNone && (a.span || !few) && !a.solo;
       if (fuse && !one_launch && plan_mode != CS_ATTN_PLAN_ONLY) {
         const int e = cs_kv_refresh_scatter(k_new, v_new, new_slot, const_cast<void*>(k_cache_layer),
                                             const_cast<void*>(v_cache_layer), n_new, n_kv_heads, head_dim, stride_slot,
@@ -2668,6 +3078,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       pp.r_cap = static_cast<int32_t>(a.r_cap);
       pp.bm = a.bm;
       pp.n_slots = a.grid / 8;
+      pp.solo = a.solo;
       pp.hist_pitch = a.hist_pitch;
       pp.header = reinterpret_cast<int32_t*>(w);
       pp.items = reinterpret_cast<int32_t*>(w + a.off_items);
@@ -2694,7 +3105,9 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
         if (e != CS_OK) return e;
         if (plan_mode == CS_ATTN_PLAN_ONLY) return CS_OK;
       }
-      if (one_launch)
+      if (a.solo)
+        hipLaunchKernelGGL(window_attn_bf16_rows32_kernel, dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);
+      else if (one_launch)
         hipLaunchKernelGGL((window_attn_bf16_stream_kernel<true>), dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);
       else
         hipLaunchKernelGGL((window_attn_bf16_stream_kernel<false>), dim3(static_cast<unsigned>(a.grid)), dim3(256), 0, st, p);

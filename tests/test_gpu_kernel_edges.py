@@ -94,6 +94,9 @@ PLANNED_ATTN = [
     (14, 2, [8100], [640]),                                                                              # split sweeps, 35 row tiles a kv head
     (8, 2, [9000, 64, 7200], [750, 64, 431]),                                                            # split and whole, frontiers far apart
     (56, 4, [4300, 4250], [150, 10]),                                                                    # 140 rows: 12 in the second row tile
+    # (6 and 7 again, with a window that is too long for jobs of one row tile each)
+    (8, 8, [3100] + [400 if i % 2 else 1 + 9 * i % 71 for i in range(132)], [70] + [320 if i % 2 else 1 + 5 * i % (1 + 9 * i % 71) for i in range(132)]),
+    (32, 2, [3100] + [40 + i % 90 for i in range(516)], [9] + [1 + i % 11 if i % 4 else 21 for i in range(516)]),
 ]
 
 
@@ -105,11 +108,14 @@ def test_planned_attention_job_edges(cs, case):
         say(f"  -> {_attn_case(cs, np.random.default_rng(9350 + case), 'bf16', hq, hkv, 128, kv_lens, n_qs, scale_mult=mult)}")
 
 
-# Lists of up to 72 units an XCD are dealt by length over the whole list, longer ones batch by batch.
+# Lists of up to 72 units an XCD are dealt by length over the whole list, longer ones batch by batch.  (A unit is two row tiles
+# but in the first two cases, where it is one.)
 DEALT = [
     # Hq, Hkv, kv_lens, n_qs
     (8, 8, [180 + 7 * (i % 40) for i in range(72)], [130 + i % 20 for i in range(72)]),                 # 72 units, ties
     (8, 8, [180 + 7 * (i % 40) for i in range(73)], [130 + i % 20 for i in range(73)]),                 # 73
+    (8, 8, [3100] + [180 + 7 * (i % 40) for i in range(71)], [130 + i % 20 for i in range(72)]),         # 72 units, ties
+    (8, 8, [3100] + [180 + 7 * (i % 40) for i in range(72)], [130 + i % 20 for i in range(73)]),         # 73
     (28, 4, [900 + 31 * i for i in range(11)], [390 + 40 * (i % 4) for i in range(11)]),                 # pairs left over, odd row tiles
     (16, 1, [700 + 60 * i for i in range(17)], [520 + 20 * (i % 3) if i != 5 else 0 for i in range(17)]),  # one pair left over, a stream without rows
 ]
@@ -160,6 +166,34 @@ def test_attention_at_the_lines_of_whole_sweeps(cs, hq, hkv, n_streams, rows, wi
     _plan_is_valid(cs, hq, hkv, kv_lens, n_qs)
     say(f"  -> {_attn_case(cs, np.random.default_rng(9400 + window + rows), 'bf16', hq, hkv, 128, kv_lens, n_qs, left=(left := []))}")
     assert (left[0] != left[1]) == plans                                  # the plan header's first bytes, before and after
+
+
+# Whole sweeps whose row tiles are jobs of their own, two workgroups a CU: both sides of every line (row tiles, mean rows of a
+# stream, key tiles), row tiles of all fillings, streams without rows, frontiers on tile edges.
+ROW_TILE_JOBS = [
+    # Hq, Hkv, kv_lens, n_qs, row tiles, key tiles, row tiles are jobs
+    (32, 4, [300 - i for i in range(64)], [50] * 64, 1056, 5, True), (32, 4, [300 - i for i in range(62)], [50] * 62, 1020, 5, False),
+    (32, 4, [3056] + [90] * 63, [50] * 64, 1056, 48, True), (32, 4, [3057] + [90] * 63, [50] * 64, 1056, 49, False),
+    (32, 4, [1521] + [90] * 63, [50] * 64, 1056, 25, True), (32, 4, [1521] + [90] * 63, [51] + [50] * 63, 1056, 25, False),
+    (28, 4, [1520] + [260] * 23, [200] * 24, 1144, 24, True), (28, 4, [1521] + [260] * 23, [200] * 24, 1144, 25, False),
+    (28, 4, [1520] + [260] * 23, [201] + [200] * 23, 1144, 24, False),
+    (8, 1, [90] * 500, [64] * 499 + [63], 2499, 2, True), (8, 1, [90] * 500, [64] * 500, 2500, 2, False),
+    (8, 8, [321 + i % 70 for i in range(66)], [(0, 1, 31, 33, 127, 128, 129, 160, 255, 257, 321)[i % 11] for i in range(66)], 1064, 7, True),
+    (16, 1, [63 + i % 4 for i in range(1100)], [(0, 1, 2, 8, 9, 16, 60)[i % 7] for i in range(1100)], 2984, 2, True),
+]
+
+
+@pytest.mark.parametrize("case", range(len(ROW_TILE_JOBS)))
+def test_attention_whose_row_tiles_are_jobs(cs, case):
+    hq, hkv, kv_lens, n_qs, row_tiles, key_tiles, jobs = ROW_TILE_JOBS[case]
+    assert (sum(n_qs) * (hq // hkv) // 128 + len(n_qs)) * hkv == row_tiles
+    assert -(-(-(-max(kv_lens) // 16) + 1) * 16 // 64) == key_tiles
+    _plan_is_valid(cs, hq, hkv, kv_lens, n_qs, entries=(entries := []))
+    if row_tiles >= 1024:
+        assert entries[0][:, :32].all() and entries[0][:, 32:].any() == jobs      # the workgroups that have work
+    for mult, outlier in ((1.0, 12.0), (6.0, 0.0)):
+        r = _attn_case(cs, np.random.default_rng(9500 + case), "bf16", hq, hkv, 128, kv_lens, n_qs, scale_mult=mult, late_outlier=outlier, last_queries=mult > 1)
+        say(f"  -> {r}")
 
 
 # A BUILD call of whole sweeps below 1,024 row tiles makes the plan in a workgroup of the tile launch.
@@ -295,7 +329,8 @@ def test_attention_of_many_streams(cs, case):
 # keys 96-127, the late ones in the window's last 80 keys; 64 rows of a wave hold some of both.
 NOT_FINITE = [
     # Hq, Hkv, d, streams, window
-    (16, 8, 128, 64, 400),       # from a plan, whole sweeps
+    (16, 8, 128, 64, 400),       # from a plan, whole sweeps, a row tile a job
+    (64, 8, 128, 44, 400),       # from a plan, whole sweeps
     (16, 8, 128, 2, 4300),       # no plan, sweeps in pieces
     (16, 8, 128, 6, 7300),       # from a plan, split sweeps
     (16, 8, 128, 8, 400),        # no plan

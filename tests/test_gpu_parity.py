@@ -651,11 +651,12 @@ def _attention_plan(cs, cu, q_pos, kv_lens, bt, hq, hkv):
     (28, 4, [300 + 7 * i for i in range(40)], [60 + i for i in range(40)]),     # more items than workgroups
     (28, 4, [1100 + 13 * i for i in range(32)], [380 + 5 * i for i in range(32)]),
 ])
-def test_attention_plan_is_a_valid_schedule(cs, hq, hkv, kv_lens, n_qs):
+def test_attention_plan_is_a_valid_schedule(cs, hq, hkv, kv_lens, n_qs, entries=None):
     """The planning launch alone (nothing computed, nothing that could fault on a bad schedule): the
     items cover every (stream, kv head, row tile) and its key tiles exactly once, every item lies on
-    exactly one workgroup's chain inside its XCD's list, and each workgroup's header entry agrees
-    with its chain.  Runs before the attention tests, which trust the plan."""
+    exactly one workgroup's chain inside its XCD's list, each workgroup's header entry agrees
+    with its chain, and an item that joins the one before it is a lower row tile of the same sweep that
+    begins with it and ends no later.  `entries` takes which header entries name an item.  Runs before the attention tests, which trust the plan."""
     say(f"attention plan: heads={hq}/{hkv} streams={len(kv_lens)} rows={sum(n_qs) * (hq // hkv)}")
     rng = np.random.default_rng(4000 + len(kv_lens) + sum(n_qs))
     g = hq // hkv
@@ -709,7 +710,16 @@ def test_attention_plan_is_a_valid_schedule(cs, hq, hkv, kv_lens, n_qs):
                 assert np.array_equal(e[8:16], items[chain[0]])
             else:
                 assert list(e[8:16]) == [0, 0, 0, 0, -1, 0, -1, -1]
+            joins = [bool(items[k, 7] & 1 == 0) for k in chain]
+            assert not any(joins[:1]) and not any(a and b for a, b in zip(joins, joins[1:]))
+            for a, b, joined in zip(chain, chain[1:], joins[1:]):
+                if joined:
+                    a, b = items[a], items[b]
+                    assert a[0] == b[0] and a[1] == b[1] and a[3] == b[3] and b[2] < a[2] and b[4] <= a[4]
+                    assert a[5] & 0xffff == b[5] & 0xffff and b[5] >> 16 <= a[5] >> 16
     assert seen.all()
+    if entries is not None:
+        entries.append(np.array([[hdr[32 + 32 * (64 * x + j)] >= 0 for j in range(64)] for x in range(8)]))
 
 
 ATTN_CASES = [
@@ -878,6 +888,7 @@ FUSED_CASES = [
     ("bf16", 4, 4, 64, [200, 129], [64, 129]),                 # head_dim 64: two launches behind the one call
     ("f32", 2, 1, 64, [452], [332]),                           # fp32: two launches behind the one call
     ("bf16", 32, 8, 128, [200 + i for i in range(66)], [31] * 66),      # one row tile a stream: no plan, two launches
+    ("bf16", 32, 8, 128, [200 + i for i in range(66)], [64] * 66),      # row tiles are jobs: two launches
 ]
 
 
