@@ -2785,14 +2785,15 @@ bool whole_sweeps(int64_t row_tiles, int key_tiles, int n_kv_heads) {
 //                             47 key tiles 1.08 to 0.98; 75 key tiles (1.00 to 0.95)
 //   up to 400                 300 and 700 keys 1.37 to 1.11 (1.17 to 0.99), 1,300 keys 1.31 to 1.11 (1.02 to 0.98), 47 key tiles
 //                             1.18 to 1.04, 75 (0.97 to 0.94)
-//   up to 1,400               T below 2,600: 640 rows 1.23 to 1.02 (1.18 to 1.01), 1,000 rows 1.13 to 1.00 (1.07 to 0.99), 1,300 rows
-//                             1.08 to 0.97 (1.04 to 0.97); 33 key tiles (0.96 to 0.92).  T above: 640 rows 1.04 to 1.01
-//                             (0.97), 1,000 rows 1.01 to 0.98 (0.97 to 0.94)
+//   up to 1,400               T below 2,000: 640 rows 1.23 to 1.10 (1.18 to 0.97), 1,000 rows 1.18 to 1.04 (1.08 to 0.97), 1,300 rows
+//                             1.09 to 1.03 (1.03 to 0.92); 33 key tiles (1.00 to 0.92).  T above: 640 rows 1.13 to 1.03
+//                             (1.04 to 0.96), 1,000 rows 1.03 to 0.97 (1.02 to 0.94).  Whole steps of 10 to 31 layers with 1,070 to
+//                             1,400 rows, streams as they come: T 1,048 to 1,820 1.02 to 0.99, T 1,860 to 2,324 0.99 to 0.97
 //   beyond                    1,700 rows 1.01 to 0.94, 2,400 rows 1.03 to 0.92
 // (1,024 row tiles of at most 1,400 rows a stream are 86 pairs at least: the planner deals by pair.)
 bool solo_row_tiles(int64_t n_q, int32_t n_streams, int32_t group, int64_t row_tiles, int key_tiles) {
   const int64_t rows = n_q * group;
-  return row_tiles >= 1024 && ((rows <= 400ll * n_streams && key_tiles <= 48) || (rows <= 1400ll * n_streams && key_tiles <= 24 && row_tiles < 2500));
+  return row_tiles >= 1024 && ((rows <= 400ll * n_streams && key_tiles <= 48) || (rows <= 1400ll * n_streams && key_tiles <= 24 && row_tiles < 1800));
 }
 
 AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int32_t max_blocks) {

@@ -177,7 +177,7 @@ ROW_TILE_JOBS = [
     (32, 4, [1521] + [90] * 63, [50] * 64, 1056, 25, True), (32, 4, [1521] + [90] * 63, [51] + [50] * 63, 1056, 25, False),
     (28, 4, [1520] + [260] * 23, [200] * 24, 1144, 24, True), (28, 4, [1521] + [260] * 23, [200] * 24, 1144, 25, False),
     (28, 4, [1520] + [260] * 23, [201] + [200] * 23, 1144, 24, False),
-    (8, 1, [90] * 500, [64] * 499 + [63], 2499, 2, True), (8, 1, [90] * 500, [64] * 500, 2500, 2, False),
+    (8, 1, [90] * 360, [64] * 359 + [63], 1799, 2, True), (8, 1, [90] * 360, [64] * 360, 1800, 2, False),
     (8, 8, [321 + i % 70 for i in range(66)], [(0, 1, 31, 33, 127, 128, 129, 160, 255, 257, 321)[i % 11] for i in range(66)], 1064, 7, True),
     (16, 1, [63 + i % 4 for i in range(1100)], [(0, 1, 2, 8, 9, 16, 60)[i % 7] for i in range(1100)], 2984, 2, True),
 ]
