@@ -2866,8 +2866,9 @@ AttnPlan plan_attn(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_h
 //                              tiles 14.5 / 16.1 / 13.4, 72 23.6 / 23.5 / 18.2; U 48 24 21.5 / 20.3 / 15.3, 237 86 / 85 / 70; U 60 118 48.8 / 58.9 / 43.7
 //                              (without a plan either: 16 key tiles, U 64 16.9 / 15.8 / 15.2, 13 level, below a whole sweep is as fast).
 //                              Three pieces: U 78 20 21.2 / 19.9 / 18.3, 33 25.6 / 25.3 / 21.5, but 13 17.0 / 16.0 / 17.4; U 80 101 36 / 41 / 33,
-//                              113 38 / 43 / 50.  Two: U 104 72 52 / 58 / 43, U 128 48 33 / 32 / 28, 20 23.9 / 23.3 / 22.0, but U 112 17 17.1 / 15.8 /
-//                              17.5; U 128 98 45 / 55 / 46, U 93 127 37 / 40 / 47; of up to 64 rows a stream, U 72 239 122 / 115 / 109, U 80 148
+//                              113 38 / 43 / 50, and with 16 key tiles U 72 to 80 15.2 to 15.5 / 15.9 to 16.9 (of 64 / this).  Two: U 104 72 52 / 58 / 43, U 128 48 33 / 32 / 28, 20 23.9 / 23.3 / 22.0, but U 112 17 17.1 / 15.8 /
+//                              17.5; past 80 key tiles two pieces lose but for up to 64 rows a stream (persistent of 64 / this: U 104 65 30.3 / 28.4,
+//                              107 79 32.8 / 31.9, 118 84 35.0 / 35.8, 122 96 35.7 / 38.4, 98 94 32.4 / 38.8); of up to 64 rows a stream, U 72 239 122 / 115 / 109, U 80 148
 //                              91 / 89 / 75, U 116 122 107 / 98 / 92.  A piece more than fit at once costs 10-50 %, one fewer 0-20 %, hence the
 //                              mean of U and the most that n_q rows can make
 //   what is left of them (2    split from a plan: F row tiles without the streams' part-filled ones, persistent of 64 / tile: F 88 48 key tiles
@@ -2896,7 +2897,7 @@ TileChoice tile_route_128(int64_t n_q, int32_t n_streams, int32_t group, int32_t
     return {n_q * group <= static_cast<int64_t>(kBM) * n_streams ? TileRoute::kRows128 : TileRoute::kNone, 1};
   const int64_t trips = (key_tiles + 3) / 4;
   const int pieces = static_cast<int>(256 / tiles64 < trips ? 256 / tiles64 : trips);
-  if (pieces >= 4 || (pieces > 1 && key_tiles > (pieces == 3 ? 15 : 20) && (key_tiles <= 112 || rows <= 64)))
+  if (pieces >= 4 || (pieces > 1 && key_tiles > (pieces == 3 ? 16 : 20) && (key_tiles <= (pieces == 2 ? 80 : 112) || rows <= 64)))
     return {TileRoute::kSplit64Keys4, pieces};
   if (rows <= 64 && tiles64 <= 256 && key_tiles > 48) return {TileRoute::kRows64Keys4, 1};
   if (key_tiles > 64) return {TileRoute::kNone, 1};

@@ -94,6 +94,7 @@ PLANNED_ATTN = [
     (14, 2, [8100], [640]),                                                                              # split sweeps, 35 row tiles a kv head
     (8, 2, [9000, 64, 7200], [750, 64, 431]),                                                            # split and whole, frontiers far apart
     (56, 4, [4300, 4250], [150, 10]),                                                                    # 140 rows: 12 in the second row tile
+    (16, 16, [5105, 300, 110], [100, 100, 100]),                                                         # three streams of two row tiles, 81 key tiles
     # (6 and 7 again, with a window that is too long for jobs of one row tile each)
     (8, 8, [3100] + [400 if i % 2 else 1 + 9 * i % 71 for i in range(132)], [70] + [320 if i % 2 else 1 + 5 * i % (1 + 9 * i % 71) for i in range(132)]),
     (32, 2, [3100] + [40 + i % 90 for i in range(516)], [9] + [1 + i % 11 if i % 4 else 21 for i in range(516)]),
@@ -302,6 +303,7 @@ FEW_ROW_TILES = [
     (4, 1, [1300 + 7 * i for i in range(100)], [1 + i % 16 for i in range(100)]),                        # two
     (4, 1, [1300 + 7 * i for i in range(103)], [1 + i % 16 for i in range(103)]),                        # one
     (4, 1, [3100 + 9 * i for i in range(150)], [1 + i % 16 for i in range(150)]),                        # whole sweeps of up to 64 rows
+    (16, 16, [5104, 300, 110], [100, 100, 100]),                                                         # two pieces, 80 key tiles
     (2, 1, [1700] * 100, [3] * 99 + [700]),                                                              # unlike streams: more row tiles than the rule counts
 ]
 
