@@ -465,12 +465,26 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  * adds); replayed from a HIP graph, where a kernel boundary costs about 2 us, the step built on it
  * is 3-6 % longer than the step of separate calls.
  *
+ * CS_ATTN_OWN_ROWS, or-ed into plan_mode, is the caller's word that the new rows are the queries' own: n_tok == n_q; row t
+ * of k_new / v_new is query token t's, and slot[t] the slot that block_table gives position q_pos[t] of its stream; positions
+ * increase strictly inside a stream; rows from cu_q[n_streams] on have a negative slot.  The workspace then takes
+ * cs_refresh_prefill_attn_workspace() bytes, and a REUSE call follows a BUILD or ONLY call with the flag and the same cu_q,
+ * q_pos, kv_len, block_table and shape arguments.  Same results, bit for bit.  What it allows (CS_BF16, caches with
+ * stride_head == head_dim and stride_slot == n_kv_heads * head_dim, shapes that run without a plan): a REUSE call is one launch
+ * that reads the new keys and values where the caller has them and writes them to the cache beside its own work, so that
+ * nothing waits for the write.  Other calls with the flag write first and attend then, as two launches.
+ *
  *  k_new, v_new, slot, n_tok    as in cs_kv_refresh_scatter (slot < 0 skips the row)
  *  k_cache_layer, v_cache_layer i/o
  *  all other arguments          as in cs_window_prefill_attn
  * Errors: those of the two calls; the attention call's arguments are checked before anything is
  * queued, so a call that returns an argument error has moved no row.
  * ------------------------------------------------------------------------------------------ */
+#define CS_ATTN_OWN_ROWS (1 << 16)   /* plan_mode bit, see above */
+size_t cs_refresh_prefill_attn_workspace(int64_t n_q, int32_t n_streams, int32_t n_q_heads,
+                                         int32_t n_kv_heads, int32_t head_dim, int32_t max_blocks,
+                                         int32_t dtype);
+
 #define CS_ATTN_STATUS_OFFSET 56   /* byte offset of the barrier status word in the attention workspace */
 
 int cs_refresh_prefill_attn(const void* k_new, const void* v_new, const int32_t* slot, int64_t n_tok,

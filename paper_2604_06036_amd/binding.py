@@ -19,6 +19,7 @@ LIB_PATH = os.path.join(_HERE, "libcodecsight.so")
 CS_OK, CS_EINVAL, CS_EUNSUPPORTED, CS_EHIP, CS_EWORKSPACE = 0, -1, -2, -3, -4
 CS_F32, CS_BF16 = 0, 1
 CS_ATTN_PLAN_BUILD, CS_ATTN_PLAN_REUSE, CS_ATTN_PLAN_ONLY = 0, 1, 2
+CS_ATTN_OWN_ROWS = 1 << 16
 CS_FRAME_P, CS_FRAME_I = 0, 1
 CS_ROPE_HALF_SPLIT, CS_ROPE_INTERLEAVED = 0, 1
 CS_KV_BLOCK = 16
@@ -30,7 +31,7 @@ EXPORTS = ("cs_version", "cs_last_hip_error", "cs_mfma_rate_probe", "cs_project_
            "cs_score_compact_noalloc",
            "cs_plan_refresh_workspace", "cs_plan_refresh", "cs_kv_rerotate", "cs_kv_rerotate_axes", "cs_kv_refresh_scatter",
            "cs_window_prefill_attn_workspace",
-           "cs_window_prefill_attn", "cs_refresh_prefill_attn")
+           "cs_window_prefill_attn", "cs_refresh_prefill_attn_workspace", "cs_refresh_prefill_attn")
 
 
 class CodecSightError(RuntimeError):
@@ -86,6 +87,8 @@ def lib() -> ctypes.CDLL:
     L.cs_kv_refresh_scatter.argtypes = [vp, vp, vp, vp, vp, i64, i32, i32, i64, i64, i32, vp]
     L.cs_window_prefill_attn_workspace.restype = sz
     L.cs_window_prefill_attn_workspace.argtypes = [i64, i32, i32, i32, i32, i32, i32]
+    L.cs_refresh_prefill_attn_workspace.restype = sz
+    L.cs_refresh_prefill_attn_workspace.argtypes = L.cs_window_prefill_attn_workspace.argtypes
     L.cs_window_prefill_attn.restype = c.c_int
     L.cs_window_prefill_attn.argtypes = [vp, vp, vp, vp, vp, vp, vp, i32, i32, vp, i64, i32, i32, i32,
                                          i32, i64, i64, f32, i32, vp, sz, i32, vp]
@@ -301,6 +304,12 @@ def cs_window_prefill_attn(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len,
 
 
 CS_ATTN_STATUS_OFFSET = 56
+
+
+def cs_refresh_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype) -> int:
+    """Bytes for calls with CS_ATTN_OWN_ROWS; the others need those of cs_window_prefill_attn_workspace."""
+    return int(lib().cs_refresh_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim,
+                                                       max_blocks, dtype))
 
 
 def cs_refresh_prefill_attn(k_new, v_new, slot, n_tok, q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len,

@@ -66,6 +66,8 @@ struct AttnParams {
   const int32_t* __restrict__ new_slot;
   int64_t n_new;
   int32_t row_vecs, head_vecs;   // 16-byte vectors per new row / per head
+  cs::u32x2* ws_own;     // CS_ATTN_OWN_ROWS: where the rows of each cache block are (OwnEntry), [streams][max_blocks]
+  int32_t* ws_tiles;     // and the row tiles of a launch without a plan, [workgroups][8] (window_attn_own_rows_kernel)
   int32_t* ws_sync;      // counters of the fused launch's launch-wide barrier (see launch_barrier)
   int32_t* ws_status;    // its status word
   int32_t clear_status;  // the launch without a plan zeroes it
@@ -170,6 +172,49 @@ __device__ __forceinline__ int32_t sload1(const void* ptr) {
   return v;
 }
 
+typedef __attribute__((ext_vector_type(2))) int32_t i32x2;
+__device__ __forceinline__ i32x2 sload2(const void* ptr) {
+  i32x2 v;
+  asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
+  return v;
+}
+
+// A pointer that is the same in all lanes, for an instruction that takes it in scalar registers.
+template <typename T>
+__device__ __forceinline__ T* uniform(T* ptr) {
+  const uint64_t at = reinterpret_cast<uintptr_t>(ptr);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at)), hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at >> 32));
+  return reinterpret_cast<T*>(static_cast<uintptr_t>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+
+// Where a call that reads its queries' own rows (CS_ATTN_OWN_ROWS) finds those of a cache block, two words a block of every
+// stream: the block's id (27 bits), the index, among the stream's queries, of the first of its rows that the call brings (21
+// bits), and which of its 16 rows those are (16 bits; all of them where every row that the stream defines is one).  They are
+// consecutive among the call's rows, queries being in order.
+constexpr int kOwnIdBits = 27, kOwnRowBits = 21;      // (slots are 32-bit: ids below 2^27; windows of up to 2^21 entries)
+struct OwnEntry {
+  uint32_t id, row, mask;
+  __device__ __forceinline__ OwnEntry(const i32x2& e) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(e.x), hi = __builtin_amdgcn_readfirstlane(e.y);
+    id = lo & ((1u << kOwnIdBits) - 1);
+    row = lo >> kOwnIdBits | hi >> 16 << (32 - kOwnIdBits);
+    mask = hi & 0xffffu;
+  }
+  static __device__ __forceinline__ cs::u32x2 packed(uint32_t id, uint32_t row, uint32_t mask) {
+    return cs::u32x2{id | row << kOwnIdBits, row >> (32 - kOwnIdBits) << 16 | mask};
+  }
+  // of row r of the block: whether it is one of the call's own, and which of the stream's
+  __device__ __forceinline__ bool own(int r) const { return mask >> r & 1; }
+  __device__ __forceinline__ uint32_t row_of(int r) const { return row + __popc(mask & ((1u << r) - 1)); }
+};
+
+// ---- loads of data that does not change during the launch: through the constant address space they are scalar loads
+typedef const __attribute__((address_space(4))) i32x8 const_i32x8;
+__device__ __forceinline__ i32x8 const_load8(const int32_t* at) { return *(const_i32x8*)reinterpret_cast<uintptr_t>(at); }
+
+// A scalar load that the compiler knows of turns every wait for an LDS read into a wait for all: it is waited for on the spot.
+__device__ __forceinline__ void wait_scalar() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+
 // One row tile of a launch without a plan: stream, kv head, first row.
 struct RowTile {
   int s, kvh, q0, rows_total, r_tile;
@@ -239,6 +284,14 @@ __device__ __forceinline__ bool find_row_tile(const AttnParams& p, int b, int* s
   return true;
 }
 
+// The frontier of a row tile: the last cache entry that its last row sees, inside those that the stream's block-table row
+// defines (-1: none).
+template <int BM>
+__device__ __forceinline__ int tile_frontier(const AttnParams& p, const RowTile& t) {
+  const int cap = min(p.kv_len[t.s], p.max_blocks * CS_KV_BLOCK) - 1;
+  return min(p.q_pos[t.q0 + (min(t.r_tile + BM, t.rows_total) - 1) / p.group], cap);
+}
+
 // bf16, one launch and no plan: a workgroup = one tile of 32 ROWW rows of one (stream, kv head), its waves
 // arranged as KG key groups of ROWW row waves.  Group g sweeps key tiles g, g + KG, ...; the groups' partial
 // results meet in LDS at the end, so a sweep is shared by KG times as many waves without a trip through memory
@@ -261,12 +314,51 @@ __device__ __forceinline__ int v_swizzle(int r) {
   return D == 128 ? 4 * (r & 3) + 2 * ((r >> 2) & 1) : 4 * ((r >> 1) & 1) + 2 * ((r >> 2) & 1);
 }
 
+// A workgroup's share of the refresh write in a launch that reads its own rows where the caller has them
+// (CS_ATTN_OWN_ROWS): 16 bytes of K and of V a thread, more than once where the launch has fewer threads.  Asked for behind
+// everything that the sweep waits for (loads return in order) and stored behind the sweep.  A launch of its own took 3.9 us of a
+// layer of one stream (900 keys, 28/4 heads) and its 28 layers 586 us; this share 0.7, reading the new rows in place of the
+// cache 0.65 more, 516 us.  12 streams of head_dim 64, 24 layers 836 -> 784 us.  First workgroups of their own for the share:
+// the same for one stream, 827 us for the 12.
+template <int THREADS>
+struct OwnMove {
+  cs::u32x4 k, v;
+  int slot = -1;
+  uint32_t rem = 0;
+  __device__ __forceinline__ void load(const AttnParams& p) {
+    const uint32_t n_units = static_cast<uint32_t>(p.n_new) * p.row_vecs;      // (below 2^31: the host checks)
+    const uint64_t apart = static_cast<uint64_t>(gridDim.x) * THREADS;
+    if (static_cast<uint64_t>(blockIdx.x) * THREADS + threadIdx.x >= n_units) return;
+    uint32_t unit = blockIdx.x * THREADS + threadIdx.x;
+    for (;;) {
+      const uint32_t tok = unit / p.row_vecs;
+      rem = unit - tok * p.row_vecs;
+      slot = p.new_slot[tok];
+      k = __builtin_nontemporal_load(static_cast<const cs::u32x4*>(p.k_new) + unit);
+      v = __builtin_nontemporal_load(static_cast<const cs::u32x4*>(p.v_new) + unit);
+      if (n_units - unit <= apart) break;
+      unit += static_cast<uint32_t>(apart);
+      store(p);
+    }
+  }
+  __device__ __forceinline__ void store(const AttnParams& p) const {
+    if (slot < 0) return;
+    const int64_t to = static_cast<int64_t>(slot) * p.row_vecs + rem;
+    __builtin_nontemporal_store(k, static_cast<cs::u32x4*>(const_cast<void*>(p.k)) + to);
+    __builtin_nontemporal_store(v, static_cast<cs::u32x4*>(const_cast<void*>(p.v)) + to);
+  }
+  __device__ __forceinline__ void all(const AttnParams& p) {
+    load(p);
+    store(p);
+  }
+};
+
 template <int D, int KG, int STAGES>
 struct TileStages {
   __attribute__((aligned(1024))) uint16_t kv[KG][STAGES][2][kBN * D];
 };
 
-template <int D, int ROWW, int KG, int STAGES, bool SPLIT = false>
+template <int D, int ROWW, int KG, int STAGES, bool SPLIT = false, bool OWN = false>
 __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, TileStages<D, KG, STAGES>& stages) {
   constexpr int BM = 32 * ROWW;
   constexpr int STEPS = D / 16, DB = D / 32;
@@ -302,14 +394,30 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
       rd[0] = t.q0; rd[1] = t.rows_total; rd[2] = t.r_tile; rd[3] = t.kvh; rd[4] = n_pieces; rd[5] = block * p.pieces; rd[6] = 0;
     }
   };
+  // The row tile: found from cu_q and q_pos, or, in a call that follows the one that plans, read from what that one left:
+  // first query token and rows of the stream, first row, kv head, frontier, stream.
+  OwnMove<64 * ROWW * KG> move;
+  auto settle = [] { if (SPLIT || OWN) wait_scalar(); };      // (before the workgroup may end: no scalar load is left in flight)
   RowTile t = {};
-  const bool found = find_row_tile<BM, ROWW * KG>(p, block, reinterpret_cast<int*>(&s_kv[0][0][0][0]), t);
-  auto settle = [] { if (SPLIT) __builtin_amdgcn_s_waitcnt(0xc07f); };      // (before the workgroup may end: no scalar load is left in flight)
-  settle();
-  if (!found) {
-    describe(t, 0);
+  int wg_max, cap;
+  if constexpr (OWN) {
+    const i32x8 d = const_load8(p.ws_tiles + static_cast<int64_t>(block) * 8);
+    t.q0 = d[0]; t.rows_total = d[1]; t.r_tile = d[2]; t.kvh = d[3]; t.s = d[5];
+    cap = wg_max = d[4];
+    if (t.rows_total <= 0) {
+      describe(t, 0);
+      move.all(p);
+      settle();
+      return;
+    }
+  } else {
+    const bool found = find_row_tile<BM, ROWW * KG>(p, block, reinterpret_cast<int*>(&s_kv[0][0][0][0]), t);
     settle();
-    return;
+    if (!found) {
+      describe(t, 0);
+      settle();
+      return;
+    }
   }
   const int s = __builtin_amdgcn_readfirstlane(t.s), kvh = __builtin_amdgcn_readfirstlane(t.kvh);
   const int q0 = __builtin_amdgcn_readfirstlane(t.q0), rows_total = __builtin_amdgcn_readfirstlane(t.rows_total);
@@ -323,10 +431,16 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   const int row_c = valid ? row : rows_total - 1;
   const int tok = q0 + row_c / p.group;
   const int head = kvh * p.group + row_c % p.group;
-  const int cap = min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1;
+  if constexpr (!OWN) {
+    cap = min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1;
+    wg_max = min(p.q_pos[q0 + (min(r_tile + BM, rows_total) - 1) / p.group], cap);
+  }
   const int lim = valid ? min(p.q_pos[tok], cap) : -1;
-  const int wg_max = min(p.q_pos[q0 + (min(r_tile + BM, rows_total) - 1) / p.group], cap);
-  if (!SPLIT && wg_max < 0) return;                     // the stream defines no cache entry: rows left untouched
+  if (!SPLIT && wg_max < 0) {                           // the stream defines no cache entry: rows left untouched
+    if constexpr (OWN) move.all(p);
+    settle();
+    return;
+  }
   // positions do not decrease along the rows
   const int rows_here = min(32, rows_total - w_first);
   const int wave_min = rows_here > 0 ? __builtin_amdgcn_readlane(lim, 0) : -1;
@@ -340,7 +454,11 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
     n_pieces = wg_max < 0 ? 0 : (n_key_tiles + len - 1) / len;
     describe(t, n_pieces);
     settle();
-    if (piece >= n_pieces) return;
+    if (piece >= n_pieces) {
+      if constexpr (OWN) move.all(p);
+      settle();
+      return;
+    }
     kt_begin = piece * len;
     kt_end = min(kt_begin + len, n_key_tiles);
   }
@@ -367,11 +485,17 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   // requests; issued unconditionally (the last tile's blocks again when there is no next tile).  Every load is waited
   // for in the trip that issued it, also where nothing reads it: the compiler does not know that the register is
   // still to be written, and is free to reuse a dead one
-  int ids[BPW], ids_next[BPW];
+  typedef typename std::conditional<OWN, i32x2, int>::type BlockAt;      // an entry of the table of own rows, or an id
+  const i32x2* own_t = reinterpret_cast<const i32x2*>(p.ws_own) + static_cast<int64_t>(s) * p.max_blocks;
+  auto load_block = [&](int blk) -> BlockAt {
+    if constexpr (OWN) return sload2(own_t + blk);
+    else return sload1(bt + blk);
+  };
+  BlockAt ids[BPW], ids_next[BPW];
   auto load_ids = [&](int kt) {
 #pragma unroll
     for (int b = 0; b < BPW; ++b)
-      ids_next[b] = sload1(bt + min(min(kt, n_key_tiles - 1) * (kBN / CS_KV_BLOCK) + rw * BPW + b, last_blk));
+      ids_next[b] = load_block(min(min(kt, n_key_tiles - 1) * (kBN / CS_KV_BLOCK) + rw * BPW + b, last_blk));
   };
   auto wait_ids = [&]() {
 #pragma unroll
@@ -380,11 +504,39 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
       ids[b] = ids_next[b];
     }
   };
-  int last_id = sload1(bt + last_blk);
+  BlockAt last_id = load_block(last_blk);
+  // (own rows: this call's, in the cache's layout; the same offsets inside 16 rows in a row)
+  const int64_t own_at = static_cast<int64_t>(q0) * p.stride_slot + static_cast<int64_t>(kvh) * D;
+  const uint16_t* kn = OWN ? static_cast<const uint16_t*>(p.k_new) + own_at : nullptr;
+  const uint16_t* vn = OWN ? static_cast<const uint16_t*>(p.v_new) + own_at : nullptr;
   auto request = [&](int kt, int stage, int which) {
     const uint16_t* base = which ? vh : kh;
     uint16_t* dst = &s_kv[kg][stage][which][rw * IPW * 512];
-    if (kt != n_key_tiles - 1 && !wide) {
+    if constexpr (OWN) {
+      const uint16_t* base_new = which ? vn : kn;
+#pragma unroll
+      for (int b = 0; b < BPW; ++b) {
+        const OwnEntry e(ids[b]);
+        if (kt != n_key_tiles - 1 && !wide && (e.mask == 0 || e.mask == 0xffffu)) {
+          const uint16_t* src = uniform(e.mask ? base_new + e.row * p.stride_slot : base + e.id * blk_stride);
+#pragma unroll
+          for (int i = 0; i < IPB; ++i) dma16_s(which ? v_off[i] : k_off[i], src, dst + (b * IPB + i) * 512);
+        } else {
+          const OwnEntry last(last_id);
+#pragma unroll
+          for (int i = 0; i < IPB; ++i) {
+            const int j_un = kt * kBN + (rw * BPW + b) * CS_KV_BLOCK + RPD * i + l_row;
+            const bool over = j_un > wg_max;
+            const OwnEntry at = over ? last : e;
+            const int r = (over ? wg_max : j_un) % CS_KV_BLOCK;
+            const uint16_t* src = at.own(r) ? base_new + at.row_of(r) * p.stride_slot
+                                            : base + (static_cast<int64_t>(at.id) * CS_KV_BLOCK + r) * p.stride_slot;
+            dma16(src + chunk_of(i, which == 1) * 8, dst + (b * IPB + i) * 512);
+          }
+        }
+      }
+      return;
+    } else if (kt != n_key_tiles - 1 && !wide) {
 #pragma unroll
       for (int b = 0; b < BPW; ++b) {
         const uint16_t* src = base + ids[b] * blk_stride;
@@ -422,6 +574,9 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
 #pragma unroll
   for (int st = 0; st < STEPS; ++st)
     qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const cs::u32x4*>(qrow + 16 * st + 8 * h));
+
+
+  if constexpr (OWN) move.load(p);
 
   // ---- LDS byte addresses of this lane's fragments
   uint32_t k_addr[STEPS], v_addr[DB];
@@ -577,6 +732,7 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
     if (STAGES == 2) wait_ids();
   }
   if (SPREAD && kg < KG / 2) __syncthreads();
+  if constexpr (OWN) move.store(p);
 
   // ---- the groups' partial results (a group that met no visible key holds m = -inf, l = 0, O = 0).  Of two groups the
   //      second hands over to the first.  Of four, every wave leaves all of its columns in LDS and finishes one block of its
@@ -674,10 +830,56 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   }
 }
 
-template <int D, int ROWW, int KG, int STAGES, bool SPLIT = false>
+template <int D, int ROWW, int KG, int STAGES, bool SPLIT = false, bool OWN = false>
 __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_bf16_tile_kernel(AttnParams p) {
   __shared__ TileStages<D, KG, STAGES> stages;
-  attend_row_tile<D, ROWW, KG, STAGES, SPLIT>(p, blockIdx.x, stages);
+  attend_row_tile<D, ROWW, KG, STAGES, SPLIT, OWN>(p, blockIdx.x, stages);
+}
+
+// What the call that plans does for those that read their own rows, besides planning: the refresh write (of n_new rows, which
+// it still needs itself), the table, and the row tiles of BM rows of a launch without a plan: first query token and
+// rows of the stream (0: no tile), first row, kv head, frontier (the last cache entry that the last row sees, inside those
+// that the stream defines; -1: none), stream.
+template <int BM>
+__global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) {
+  __shared__ int s_tiles[64];
+  OwnMove<64>().all(p);
+  const int64_t n_entries = static_cast<int64_t>(p.n_streams) * p.max_blocks;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x; i < n_entries; i += static_cast<int64_t>(gridDim.x) * 64) {
+    const int s = static_cast<int>(i / p.max_blocks), first = static_cast<int>(i - static_cast<int64_t>(s) * p.max_blocks) * CS_KV_BLOCK;
+    const int len = p.kv_len[s] - first;
+    if (len <= 0) continue;              // the stream's row of the block table ends before
+    const int q0 = p.cu_q[s], q1 = p.cu_q[s + 1];
+    int lo = q0, hi = q1;                // the first query at or past the block
+    while (lo < hi) {
+      const int mid = lo + (hi - lo) / 2;
+      if (p.q_pos[mid] < first) lo = mid + 1;
+      else hi = mid;
+    }
+    uint32_t mask = 0;
+    for (int t = lo; t < min(q1, lo + CS_KV_BLOCK); ++t) {
+      const int at = p.q_pos[t] - first;
+      if (at >= CS_KV_BLOCK) break;
+      mask |= 1u << at;
+    }
+    if (len < CS_KV_BLOCK && (~mask & ((1u << len) - 1)) == 0) mask = 0xffffu;
+    p.ws_own[i] = OwnEntry::packed(p.block_table[i], lo - q0, mask);
+  }
+  const int64_t n_tiles = ((p.n_q * p.group) / BM + p.n_streams) * p.n_kv_heads;
+  for (int64_t b = blockIdx.x; b < n_tiles; b += gridDim.x) {
+    RowTile t = {};
+    int frontier = -1;
+    if (find_row_tile<BM, 1>(p, static_cast<int>(b), s_tiles, t)) {
+      const int cap = min(p.kv_len[t.s], p.max_blocks * CS_KV_BLOCK) - 1;
+      frontier = min(p.q_pos[t.q0 + (min(t.r_tile + BM, t.rows_total) - 1) / p.group], cap);
+    }
+    if (threadIdx.x == 0) {
+      int32_t* d = p.ws_tiles + b * 8;
+      d[0] = t.q0; d[1] = t.rows_total; d[2] = t.r_tile; d[3] = t.kvh; d[4] = frontier; d[5] = t.s;
+    }
+    __syncthreads();
+  }
+  wait_scalar();                         // (no scalar load is left in flight)
 }
 
 // =============================================================================================
@@ -1453,11 +1655,6 @@ __device__ __forceinline__ void launch_barrier(int32_t* sync, int32_t* status, i
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// ---- loads of data that does not change during the launch: through the constant address space they are scalar loads
-typedef const __attribute__((address_space(4))) i32x8 const_i32x8;
-__device__ __forceinline__ i32x8 const_load8(const int32_t* at) { return *(const_i32x8*)reinterpret_cast<uintptr_t>(at); }
-// A scalar load that the compiler knows of turns every wait for an LDS read into a wait for all: it is waited for on the spot.
-__device__ __forceinline__ void wait_scalar() { __builtin_amdgcn_s_waitcnt(0xc07f); }
 
 // f(Begin), f(Begin + 1), ... f(End - 1) with the index as a compile-time constant.
 template <int Begin, int End, typename F>
@@ -2914,14 +3111,28 @@ template <int D, int ROWW, int KG, int STAGES>
 int launch_tiles(const AttnParams& p, hipStream_t st) {
   const int64_t tiles = ((p.n_q * p.group) / (32 * ROWW) + p.n_streams) * p.n_kv_heads;      // upper bound
   if (tiles > 0x7fffffffll) return CS_EUNSUPPORTED;
-  hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES>), dim3(static_cast<unsigned>(tiles)),
-                     dim3(64 * ROWW * KG), 0, st, p);
+  const dim3 grid(static_cast<unsigned>(tiles)), block(64 * ROWW * KG);
+  if (p.ws_own) hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES, false, true>), grid, block, 0, st, p);
+  else hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES>), grid, block, 0, st, p);
+  return cs::note_hip(hipGetLastError());
+}
+
+int launch_own_rows(const AttnParams& p, int bm, hipStream_t st) {
+  const int64_t rows = (p.n_new * p.row_vecs + 63) / 64, tiles = ((p.n_q * p.group) / bm + p.n_streams) * p.n_kv_heads;
+  const int64_t entries = (static_cast<int64_t>(p.n_streams) * p.max_blocks + 63) / 64;
+  int64_t grid = rows > tiles ? rows : tiles;
+  grid = grid > entries ? grid : entries;
+  const dim3 blocks(static_cast<unsigned>(grid < (1 << 16) ? grid : 1 << 16));
+  if (bm == 128) hipLaunchKernelGGL(window_attn_own_rows_kernel<128>, blocks, dim3(64), 0, st, p);
+  else hipLaunchKernelGGL(window_attn_own_rows_kernel<64>, blocks, dim3(64), 0, st, p);
   return cs::note_hip(hipGetLastError());
 }
 
 int launch_split_tiles(const AttnParams& p, hipStream_t st) {
   const int64_t tiles = ((p.n_q * p.group) / p.bm + p.n_streams) * p.n_kv_heads;
-  hipLaunchKernelGGL((window_attn_bf16_tile_kernel<128, 2, 4, 1, true>), dim3(static_cast<unsigned>(tiles * p.pieces)), dim3(512), 0, st, p);
+  const dim3 grid(static_cast<unsigned>(tiles * p.pieces));
+  if (p.ws_own) hipLaunchKernelGGL((window_attn_bf16_tile_kernel<128, 2, 4, 1, true, true>), grid, dim3(512), 0, st, p);
+  else hipLaunchKernelGGL((window_attn_bf16_tile_kernel<128, 2, 4, 1, true>), grid, dim3(512), 0, st, p);
   const int e = cs::note_hip(hipGetLastError());
   if (e != CS_OK) return e;
   hipLaunchKernelGGL(window_attn_merge_kernel, dim3(static_cast<unsigned>(tiles * (p.bm / 8))), dim3(256), 0, st, p);
@@ -2941,6 +3152,15 @@ extern "C" size_t cs_window_prefill_attn_workspace(int64_t n_q, int32_t n_stream
 }
 
 namespace {
+
+// What calls with CS_ATTN_OWN_ROWS keep behind the workspace of the others: the table of own rows, then the row tiles of a
+// launch without a plan (of 64 rows or more).
+size_t own_table_bytes(int32_t n_streams, int32_t max_blocks) {
+  return (static_cast<size_t>(n_streams) * max_blocks * sizeof(cs::u32x2) + 255) & ~static_cast<size_t>(255);
+}
+size_t own_bytes(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int32_t max_blocks) {
+  return own_table_bytes(n_streams, max_blocks) + static_cast<size_t>((n_q * group / 64 + n_streams) * n_kv_heads) * 8 * sizeof(int32_t);
+}
 
 // The attention call; with k_new != nullptr the launch first writes the new K/V rows into the cache
 // (bf16 / head_dim 128: inside the same launch; other shapes: the caller has already queued the
@@ -2984,7 +3204,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
               int32_t n_kv_heads, int32_t head_dim, int64_t stride_slot,
               int64_t stride_head, float softmax_scale, int32_t dtype,
               void* workspace, size_t workspace_bytes, int32_t plan_mode,
-              const void* k_new, const void* v_new, const int32_t* new_slot, int64_t n_new,
+              const void* k_new, const void* v_new, const int32_t* new_slot, int64_t n_new, cs::u32x2* own,
               void* stream) {
   const int checked = attn_validate(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks,
                                     block_size, out, n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot,
@@ -3019,10 +3239,22 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
   p.n_new = n_new;
   p.head_vecs = head_dim / 8;
   p.row_vecs = n_kv_heads * p.head_vecs;
+  p.ws_own = nullptr;
+  p.ws_tiles = nullptr;
   p.ws_sync = nullptr;
   p.ws_status = nullptr;
   p.clear_status = 0;
   hipStream_t st = cs::as_stream(stream);
+  // before a call with own rows, of row tiles of bm rows
+  auto own_rows = [&](int bm) -> int {
+    p.ws_own = own;
+    p.ws_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(own) + own_table_bytes(n_streams, max_blocks));
+    if (plan_mode == CS_ATTN_PLAN_REUSE) return CS_OK;
+    if (plan_mode == CS_ATTN_PLAN_ONLY && head_dim == 128) p.n_new = 0;
+    const int e = launch_own_rows(p, bm, st);
+    p.ws_own = nullptr;                  // (its own attention reads the cache)
+    return e;
+  };
   if (dtype == CS_BF16) {
     if (head_dim == 128) {
       if (n_kv_heads > 256 || n_streams >= (1 << 23)) return CS_EUNSUPPORTED;
@@ -3046,8 +3278,11 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       // Without a plan the refresh write is a launch of its own, and so it is for whole sweeps of few row tiles: the launch-wide
       // barrier takes 4-9 us more than that launch (10 streams of 420 tokens, 610 keys, us a layer of a graph 47.9 / 42.0).
       const bool few = a.rt_cap < 1024;
-      const bool one_launch = fuse && route == TileRoute::kNone && (a.span || !few) && !a.solo;
-      if (fuse && !one_launch && plan_mode != CS_ATTN_PLAN_ONLY) {
+      const bool one_launch = fuse && !own && route == TileRoute::kNone && (a.span || !few) && !a.solo;
+      if (own && route != TileRoute::kNone) {
+        const int e = own_rows(route == TileRoute::kRows128 ? 128 : 64);
+        if (e != CS_OK) return e;
+      } else if (fuse && !one_launch && plan_mode != CS_ATTN_PLAN_ONLY) {
         const int e = cs_kv_refresh_scatter(k_new, v_new, new_slot, const_cast<void*>(k_cache_layer),
                                             const_cast<void*>(v_cache_layer), n_new, n_kv_heads, head_dim, stride_slot,
                                             stride_head, dtype, stream);
@@ -3124,6 +3359,10 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       // are resident together, 1,024 of them with one group).  One group / two, us a layer in a step: 4 streams,
       // 28/4 heads 25.3 / 23.1; 12 streams, 16/4 heads 30.5 / 26.9; 32 streams 57.3 / 58.4 (the merge is extra work).
       const int64_t tiles = ((n_q * group) / kBM + n_streams) * n_kv_heads;
+      if (own) {
+        const int e = own_rows(kBM);
+        if (e != CS_OK) return e;
+      }
       if (tiles <= 1024) return launch_tiles<64, 4, 2, 2>(p, st);
       return launch_tiles<64, 4, 1, 1>(p, st);
     }
@@ -3151,7 +3390,15 @@ extern "C" int cs_window_prefill_attn(const void* q, const void* k_cache_layer, 
                                       void* stream) {
   return attn_call(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks, block_size, out,
                    n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot, stride_head, softmax_scale, dtype,
-                   workspace, workspace_bytes, plan_mode, nullptr, nullptr, nullptr, 0, stream);
+                   workspace, workspace_bytes, plan_mode, nullptr, nullptr, nullptr, 0, nullptr, stream);
+}
+
+extern "C" size_t cs_refresh_prefill_attn_workspace(int64_t n_q, int32_t n_streams, int32_t n_q_heads,
+                                                    int32_t n_kv_heads, int32_t head_dim, int32_t max_blocks,
+                                                    int32_t dtype) {
+  const size_t attn = cs_window_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype);
+  if (dtype != CS_BF16 || n_q <= 0 || n_streams <= 0 || max_blocks <= 0 || n_kv_heads < 1 || n_q_heads < n_kv_heads) return attn;
+  return attn + own_bytes(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, max_blocks);
 }
 
 extern "C" int cs_refresh_prefill_attn(const void* k_new, const void* v_new, const int32_t* slot, int64_t n_tok,
@@ -3164,6 +3411,31 @@ extern "C" int cs_refresh_prefill_attn(const void* k_new, const void* v_new, con
                                        void* workspace, size_t workspace_bytes, int32_t plan_mode,
                                        void* stream) {
   if (n_tok < 0) return CS_EINVAL;
+  // The rows are the queries' own: what finds them is made by the call that plans and read by those that follow it.  Where the
+  // cache is laid out as the rows are, so that the same offsets serve both; otherwise the call is as without the flag.
+  const int32_t mode = plan_mode & ~CS_ATTN_OWN_ROWS;
+  bool own = mode != plan_mode && (mode == CS_ATTN_PLAN_BUILD || mode == CS_ATTN_PLAN_REUSE || mode == CS_ATTN_PLAN_ONLY);
+  if (own) plan_mode = mode;
+  own = own && dtype == CS_BF16 && n_tok == n_q && n_tok > 0 && n_streams > 0 && max_blocks > 0 && stride_head == head_dim &&
+        stride_slot == static_cast<int64_t>(n_kv_heads) * head_dim && n_tok * stride_slot < (1ll << 34) &&
+        max_blocks <= (1 << kOwnRowBits) / CS_KV_BLOCK;
+  if (own) {
+    const int checked = attn_validate(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks,
+                                      block_size, out, n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot,
+                                      stride_head, softmax_scale, dtype, plan_mode);
+    if (checked < 0) return checked;
+    const size_t at = cs_window_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype);
+    if (!workspace || !cs::aligned16(workspace) ||
+        workspace_bytes < at + own_bytes(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, max_blocks))
+      return CS_EWORKSPACE;
+    cs::u32x2* table = reinterpret_cast<cs::u32x2*>(static_cast<char*>(workspace) + at);
+    const bool only = plan_mode == CS_ATTN_PLAN_ONLY && head_dim == 128;
+    if (!only && (!k_new || !v_new || !slot)) return CS_EINVAL;
+    if (!cs::aligned16(k_new) || !cs::aligned16(v_new)) return CS_EUNSUPPORTED;
+    return attn_call(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks, block_size, out, n_q,
+                     n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot, stride_head, softmax_scale, dtype, workspace,
+                     workspace_bytes, plan_mode, k_new, v_new, slot, n_tok, table, stream);
+  }
   const bool one_launch = dtype == CS_BF16 && head_dim == 128;
   const bool plan_only = plan_mode == CS_ATTN_PLAN_ONLY && one_launch;
   if (n_tok > 0 && !plan_only && (!k_new || !v_new || !slot)) return CS_EINVAL;
@@ -3183,9 +3455,9 @@ extern "C" int cs_refresh_prefill_attn(const void* k_new, const void* v_new, con
     }
     return attn_call(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks, block_size, out,
                      n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot, stride_head, softmax_scale, dtype,
-                     workspace, workspace_bytes, plan_mode, nullptr, nullptr, nullptr, 0, stream);
+                     workspace, workspace_bytes, plan_mode, nullptr, nullptr, nullptr, 0, nullptr, stream);
   }
   return attn_call(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks, block_size, out,
                    n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot, stride_head, softmax_scale, dtype,
-                   workspace, workspace_bytes, plan_mode, k_new, v_new, slot, n_tok, stream);
+                   workspace, workspace_bytes, plan_mode, k_new, v_new, slot, n_tok, nullptr, stream);
 }

@@ -172,14 +172,17 @@ class DeviceStep:
     (tests and comparison runs)."""
 
     def __init__(self, data: StepData, reuse_cap: Optional[int] = None, q_cap: Optional[int] = None,
-                 host_plan: bool = False, fused: bool = False, overlap: Optional[bool] = None,
+                 host_plan: bool = False, fused: Optional[bool] = None, overlap: Optional[bool] = None,
                  layers_per_rerotate: int = 4):
         import torch
         from . import binding as cs
         self.cs = cs
         self.data = data
         self.host_plan = host_plan
-        self.fused = fused             # refresh write inside the attention launch (cs_refresh_prefill_attn)
+        # refresh write and attention of a layer: one call (cs_refresh_prefill_attn; None: of the executed tokens' own
+        # rows, which a step's are; True: of any rows) or, False, two
+        self.fused = fused
+        self.own_rows = fused is None
         # overlap: the position correction runs on a second stream, a few layers per call, while the
         # layer loop proceeds; a layer's attention waits for the call that covers its layer
         # (decided below, once the capacities are known; None = by the size of the correction's traffic)
@@ -259,8 +262,8 @@ class DeviceStep:
         self.q, self.k_new, self.v_new = grow(data.q.to(dev)), grow(data.k_new.to(dev)), grow(data.v_new.to(dev))
         self.out = torch.zeros_like(self.q)
         self.n_q = self.q_cap
-        self.ws_d_bytes = cs.cs_window_prefill_attn_workspace(self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads,
-                                                              w.head_dim, self.max_blocks, self.dtype)
+        workspace = cs.cs_refresh_prefill_attn_workspace if self.own_rows else cs.cs_window_prefill_attn_workspace
+        self.ws_d_bytes = workspace(self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, self.max_blocks, self.dtype)
         self.ws_d = torch.zeros((max(8, self.ws_d_bytes),), dtype=torch.uint8, device=dev)
 
     def score_compact(self):
@@ -323,16 +326,20 @@ class DeviceStep:
                                        self.cs.CS_ATTN_PLAN_REUSE if reuse_plan else self.cs.CS_ATTN_PLAN_BUILD)
 
     def refresh_and_attention(self, layer: int, reuse_plan: bool = False):
-        """Refresh write + attention of one layer as one call (one launch for bf16 / head_dim 128)."""
+        """Refresh write + attention of one layer as one call."""
+        self._refresh_and_attention(self.k_new[layer], self.v_new[layer], self.k_pool[layer], self.v_pool[layer],
+                                    self.q[layer], self.out[layer], reuse_plan)
+
+    def _refresh_and_attention(self, k_new, v_new, k, v, q, out, reuse_plan):
         w = self.data.workload
-        self.cs.cs_refresh_prefill_attn(self.k_new[layer], self.v_new[layer], self.q_slot, self.n_q,
-                                        self.q[layer], self.k_pool[layer], self.v_pool[layer], self.cu_q,
+        mode = self.cs.CS_ATTN_PLAN_REUSE if reuse_plan else self.cs.CS_ATTN_PLAN_BUILD
+        self.cs.cs_refresh_prefill_attn(k_new, v_new, self.q_slot, self.n_q, q, k, v, self.cu_q,
                                         self.q_pos, self.kv_len, self.block_table, self.max_blocks,
-                                        self.cs.CS_KV_BLOCK, self.out[layer], self.n_q, w.n_streams,
+                                        self.cs.CS_KV_BLOCK, out, self.n_q, w.n_streams,
                                         w.n_q_heads, w.n_kv_heads, w.head_dim, self.stride_slot,
                                         self.stride_head, self.data.softmax_scale, self.dtype,
                                         self.ws_d if self.ws_d_bytes else None, self.ws_d_bytes,
-                                        self.cs.CS_ATTN_PLAN_REUSE if reuse_plan else self.cs.CS_ATTN_PLAN_BUILD)
+                                        mode | self.cs.CS_ATTN_OWN_ROWS if self.own_rows else mode)
 
     def attention_status(self) -> int:
         """Barrier status word of the fused launches (synchronises): 0 unless a launch's grid could not
@@ -373,20 +380,18 @@ class DeviceStep:
         else:
             self.rerotate()
         # (the views of all layers at once: indexing six tensors in every layer costs more than the two calls of a layer)
-        views = () if self.fused else [t.unbind(0) for t in (self.k_new, self.v_new, self.k_pool, self.v_pool, self.q, self.out)]
+        views = [t.unbind(0) for t in (self.k_new, self.v_new, self.k_pool, self.v_pool, self.q, self.out)]
         for layer in range(n_layers):
-            if layer in ready:
-                # the refresh write touches other rows than the correction, but the fused call reads the cache too
-                if self.fused:
-                    torch.cuda.current_stream().wait_event(ready[layer])
-            if self.fused:
-                self.refresh_and_attention(layer, reuse_plan=layer > 0)
-            else:
-                k_new, v_new, k, v, q, out = (t[layer] for t in views)
+            k_new, v_new, k, v, q, out = (t[layer] for t in views)
+            # the refresh write touches other rows than the correction, attention reads both
+            if self.fused is False:
                 self._refresh_scatter(k_new, v_new, k, v)
-                if layer in ready:
-                    torch.cuda.current_stream().wait_event(ready[layer])
+            if layer in ready:
+                torch.cuda.current_stream().wait_event(ready[layer])
+            if self.fused is False:
                 self._attention(q, k, v, out, layer > 0)
+            else:
+                self._refresh_and_attention(k_new, v_new, k, v, q, out, layer > 0)
         if ready:
             torch.cuda.current_stream().wait_stream(self.side)
 
@@ -519,8 +524,8 @@ class FrontEndStep:
         self.stride_layer, self.stride_slot, self.stride_head = (self.k_pool.stride(i) for i in range(3))
         self.q, self.k_new, self.v_new = data.q.to(dev), data.k_new.to(dev), data.v_new.to(dev)
         self.out = torch.zeros_like(self.q)
-        self.ws_d_bytes = cs.cs_window_prefill_attn_workspace(self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads,
-                                                              w.head_dim, self.max_blocks, self.dtype)
+        self.ws_d_bytes = cs.cs_refresh_prefill_attn_workspace(self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads,
+                                                               w.head_dim, self.max_blocks, self.dtype)
         self.ws_d = torch.zeros((max(8, self.ws_d_bytes),), dtype=torch.uint8, device=dev)
 
     def front_end(self):
@@ -550,15 +555,12 @@ class FrontEndStep:
                               w.n_layers, w.n_kv_heads, w.head_dim, self.stride_layer, self.stride_slot, self.stride_head,
                               w.rope_base, cs.CS_ROPE_HALF_SPLIT, self.dtype)
         for layer in range(w.n_layers):
-            cs.cs_kv_refresh_scatter(self.k_new[layer], self.v_new[layer], self.q_slot, self.k_pool[layer],
-                                     self.v_pool[layer], self.q_cap, w.n_kv_heads, w.head_dim, self.stride_slot,
-                                     self.stride_head, self.dtype)
-            cs.cs_window_prefill_attn(self.q[layer], self.k_pool[layer], self.v_pool[layer], self.cu_q, self.q_pos,
-                                      self.kv_len, self.bt_new, self.max_blocks, cs.CS_KV_BLOCK, self.out[layer],
-                                      self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, self.stride_slot,
-                                      self.stride_head, self.data.softmax_scale, self.dtype,
-                                      self.ws_d if self.ws_d_bytes else None, self.ws_d_bytes,
-                                      cs.CS_ATTN_PLAN_REUSE if layer > 0 else cs.CS_ATTN_PLAN_BUILD)
+            mode = cs.CS_ATTN_PLAN_REUSE if layer > 0 else cs.CS_ATTN_PLAN_BUILD
+            cs.cs_refresh_prefill_attn(self.k_new[layer], self.v_new[layer], self.q_slot, self.q_cap, self.q[layer], self.k_pool[layer],
+                                       self.v_pool[layer], self.cu_q, self.q_pos, self.kv_len, self.bt_new, self.max_blocks,
+                                       cs.CS_KV_BLOCK, self.out[layer], self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads,
+                                       w.head_dim, self.stride_slot, self.stride_head, self.data.softmax_scale, self.dtype,
+                                       self.ws_d if self.ws_d_bytes else None, self.ws_d_bytes, mode | cs.CS_ATTN_OWN_ROWS)
 
     def run(self):
         self.front_end()

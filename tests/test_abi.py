@@ -209,6 +209,19 @@ def test_host_side_argument_errors(lib):
     assert fused(d=96) == binding.CS_EUNSUPPORTED
     assert fused(nq=0, nt=0) == binding.CS_OK
 
+    # ... of the queries' own rows: a workspace of its own size, the same checks
+    own = binding.CS_ATTN_OWN_ROWS
+    size = L.cs_refresh_prefill_attn_workspace(8, 1, 4, 2, 128, 4, 1)
+    assert size >= need + 4 * 8 and L.cs_refresh_prefill_attn_workspace(8, 1, 4, 2, 128, 4, 0) == 0
+    assert fused(ws=one, wsb=need, mode=own) == binding.CS_EWORKSPACE
+    assert fused(ws=one, wsb=size - 1, mode=own | 1) == binding.CS_EWORKSPACE
+    assert fused(ws=one, wsb=size, mode=own | 3) == binding.CS_EINVAL
+    assert fused(ws=one, wsb=size, mode=own, scale=0.0) == binding.CS_EINVAL
+    assert fused(ws=one, wsb=size, mode=own | 1, vn=z) == binding.CS_EINVAL
+    assert fused(ws=one, wsb=size, mode=own, kn=ctypes.c_void_p(8)) == binding.CS_EUNSUPPORTED
+    assert fused(d=64, ss=128, sh=64, mode=own) == binding.CS_EWORKSPACE
+    assert fused(nq=0, nt=0, mode=own) == binding.CS_OK
+
     # the scoring call that allocates nothing serves up to 4,096 streams
     assert L.cs_score_compact_noalloc(one, z, z, one, one, z, 4097, 1, 16, 16, 1, 0, 0, 0, one, one, one, z) == binding.CS_EUNSUPPORTED
 

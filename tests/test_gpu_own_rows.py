@@ -1,0 +1,161 @@
+"""cs_refresh_prefill_attn with CS_ATTN_OWN_ROWS against the refresh write followed by attention: caches and results bit
+for bit, on every route such a call can take.  The slots of the new rows hold no number before the call, so a key read
+from the cache in place of the caller's rows shows."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import codecsight_oracle as oc
+from tests import helpers as hp
+from tests.test_gpu_parity import DEV, _pool, cs, say   # noqa: F401  (cs is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # Hq, Hkv, d, kv_lens, n_qs, pattern of the query positions
+    (28, 4, 128, [915], [425], "runs"),                        # 64-row tiles, four key groups
+    (28, 4, 128, [917], [425], "any"),
+    (16, 8, 128, [300], [130], "runs"),                        # two key groups
+    (28, 4, 128, [915, 1, 640, 77], [425, 1, 333, 0], "runs"),
+    (28, 4, 128, [1000 + 7 * i for i in range(6)], [421 + i for i in range(6)], "runs"),      # plan, made beside the first layer
+    (8, 2, 128, [3000, 700, 40], [257, 64, 40], "runs"),       # sweeps in pieces
+    (28, 4, 128, [13700], [18], "any"),
+    (32, 8, 128, [200 + i for i in range(66)], [31] * 66, "any"),       # one row tile of 128 a stream, more streams than lanes
+    (32, 8, 128, [200 + i for i in range(66)], [64] * 66, "runs"),      # row tiles are jobs
+    (28, 4, 128, [6033], [300], "runs"),                       # split sweeps and merge
+    (28, 4, 128, [1100 + 13 * i for i in range(32)], [380 + 5 * i for i in range(32)], "runs"),      # whole sweeps
+    (4, 4, 64, [200, 129, 16, 17, 15], [64, 129, 16, 1, 14], "any"),    # head_dim 64, few row tiles
+    (16, 4, 64, [900 + 11 * i for i in range(12)], [370 + i for i in range(12)], "runs"),
+    (16, 4, 64, [300 + 11 * i for i in range(40)], [250 + i % 7 for i in range(40)], "runs"),      # many
+    (8, 1, 64, [70] * 130, [3] * 130, "any"),
+]
+
+
+def _positions(rng, kv_len, n_q, pattern):
+    """Strictly increasing window positions: a few runs, the last one up to the end of the window, or any."""
+    if pattern == "any" or n_q < 8:
+        return np.sort(rng.choice(kv_len, size=n_q, replace=False))
+    first = n_q // 2
+    start = int(rng.integers(0, kv_len - n_q + 1))
+    return np.concatenate([np.arange(start, start + first), np.arange(kv_len - (n_q - first), kv_len)])
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_own_rows_equal_refresh_write_then_attention(cs, case):
+    hq, hkv, d, kv_lens, n_qs, pattern = CASES[case]
+    say(f"own rows case {case}: heads={hq}/{hkv} d={d} kv={kv_lens[:6]} n_q={n_qs[:6]} {pattern}")
+    rng = np.random.default_rng(8200 + case)
+    n_streams = len(kv_lens)
+    nb = [-(-n // 16) for n in kv_lens]
+    max_blocks = max(nb) + 1
+    ids = rng.permutation(sum(nb) + 3)
+    bt = np.full((n_streams, max_blocks), -5, np.int32)          # (entries past a stream's last: never looked at)
+    at = 0
+    for s in range(n_streams):
+        bt[s, : nb[s]] = ids[at: at + nb[s]]
+        at += nb[s]
+    pos = [_positions(rng, kv_lens[s], n_qs[s], pattern) for s in range(n_streams)]
+    cu = np.concatenate([[0], np.cumsum([p.size for p in pos])]).astype(np.int32)
+    q_pos = np.concatenate(pos).astype(np.int32)
+    slot = np.concatenate([bt[s, pos[s] // 16].astype(np.int64) * 16 + pos[s] % 16 for s in range(n_streams)]).astype(np.int32)
+    n_q, pad = int(q_pos.size), 37
+    n_all = n_q + pad
+    dev = lambda a: torch.from_numpy(a).to(DEV)
+    slot_p = dev(np.concatenate([slot, np.full(pad, -1, np.int32)]))
+    meta = (dev(cu), dev(np.concatenate([q_pos, np.full(pad, 7, np.int32)])), torch.tensor(kv_lens, dtype=torch.int32, device=DEV), dev(bt))
+    scale = 1.0 / math.sqrt(d)
+    plain_bytes = cs.cs_window_prefill_attn_workspace(n_all, n_streams, hq, hkv, d, max_blocks, cs.CS_BF16)
+    own_bytes = cs.cs_refresh_prefill_attn_workspace(n_all, n_streams, hq, hkv, d, max_blocks, cs.CS_BF16)
+    dirty = lambda n: torch.randint(0, 255, (max(64, n),), dtype=torch.uint8, device=DEV)
+    ws, ws_only, ws_two = dirty(own_bytes), dirty(own_bytes), dirty(plain_bytes)
+    n_slots = ids.size * 16
+    build, reuse, only = cs.CS_ATTN_PLAN_BUILD, cs.CS_ATTN_PLAN_REUSE, cs.CS_ATTN_PLAN_ONLY
+
+    def rest(workspace, n_bytes, mode):
+        return (n_all, n_streams, hq, hkv, d, hkv * d, d, scale, cs.CS_BF16, workspace, n_bytes, mode)
+
+    def own(data, workspace, mode, out, k, v):
+        kn, vn, q = data
+        cs.cs_refresh_prefill_attn(kn, vn, slot_p, n_all, q, k, v, *meta, max_blocks, 16, out,
+                                   *rest(workspace, own_bytes, mode | cs.CS_ATTN_OWN_ROWS))
+
+    for rep, (workspace, mode) in enumerate(((ws, build), (ws, reuse), (ws, reuse), (ws_only, only), (ws_only, reuse))):
+        if mode == only and d == 128:
+            own((None, None, None), workspace, only, None, None, None)
+            continue
+        kc, vc = _pool(rng, (n_slots, hkv, d), "bf16"), _pool(rng, (n_slots, hkv, d), "bf16")
+        kc[slot] = vc[slot] = float("nan")
+        data = [t.to(DEV) for t in (_pool(rng, (n_all, hkv, d), "bf16"), _pool(rng, (n_all, hkv, d), "bf16"), _pool(rng, (n_all, hq, d), "bf16"))]
+        k2, v2, k1, v1 = kc.to(DEV), vc.to(DEV), kc.to(DEV), vc.to(DEV)
+        out2 = torch.full((n_all, hq, d), 7.0, dtype=torch.bfloat16, device=DEV)
+        out1 = out2.clone()
+        cs.cs_kv_refresh_scatter(data[0], data[1], slot_p, k2, v2, n_all, hkv, d, hkv * d, d, cs.CS_BF16)
+        if rep == 4 and d == 128:
+            cs.cs_window_prefill_attn(None, None, None, *meta, max_blocks, 16, None, *rest(ws_two, plain_bytes, only))
+        cs.cs_window_prefill_attn(data[2], k2, v2, *meta, max_blocks, 16, out2, *rest(ws_two if plain_bytes else None, plain_bytes, mode))
+        own(data, workspace, mode, out1, k1, v1)
+        torch.cuda.synchronize()
+        raw = torch.int16
+        assert torch.equal(k1.view(raw), k2.view(raw)) and torch.equal(v1.view(raw), v2.view(raw)), f"cache, pass {rep}"
+        assert torch.equal(out1.view(raw), out2.view(raw)), f"results, pass {rep}"
+        assert torch.all(out1[n_q:].float() == 7.0)
+        if rep == 1:
+            ref = oc.window_attn(hp.f64(data[2][:n_q]), hp.f64(k2), hp.f64(v2), cu, q_pos, bt, hq, scale)
+            say(f"  {hp.check_attention(out1[:n_q].cpu(), ref, 'bf16')}")
+
+
+def test_own_rows_of_a_cache_in_another_layout(cs):
+    """Slots further apart than a row: the flag changes nothing."""
+    hq, hkv, d, kv_len, n_q = 28, 4, 128, 640, 200
+    say(f"own rows: cache rows with a gap, heads={hq}/{hkv} kv={kv_len} n_q={n_q}")
+    rng = np.random.default_rng(8301)
+    pos = _positions(rng, kv_len, n_q, "runs")
+    bt = rng.permutation(40).astype(np.int32)[None]
+    slot = (bt[0, pos // 16].astype(np.int64) * 16 + pos % 16).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).to(DEV)
+    meta = (dev(np.array([0, n_q], np.int32)), dev(pos.astype(np.int32)), dev(np.array([kv_len], np.int32)), dev(bt))
+    size = cs.cs_refresh_prefill_attn_workspace(n_q, 1, hq, hkv, d, 40, cs.CS_BF16)
+    kn, vn, q = (_pool(rng, (n_q, h, d), "bf16").to(DEV) for h in (hkv, hkv, hq))
+    pools = [_pool(rng, (640, hkv + 1, d), "bf16").to(DEV) for _ in range(2)]
+    results = []
+    for flag in (0, cs.CS_ATTN_OWN_ROWS):
+        k, v = (t.clone() for t in pools)
+        ws = torch.zeros(size, dtype=torch.uint8, device=DEV)
+        out = torch.zeros((n_q, hq, d), dtype=torch.bfloat16, device=DEV)
+        for mode in (cs.CS_ATTN_PLAN_BUILD, cs.CS_ATTN_PLAN_REUSE):
+            cs.cs_refresh_prefill_attn(kn, vn, dev(slot), n_q, q, k, v, *meta, 40, 16, out, n_q, 1, hq, hkv, d, k.stride(0), k.stride(1),
+                                       1.0 / math.sqrt(d), cs.CS_BF16, ws, size, mode | flag)
+        results.append((k, v, out))
+    torch.cuda.synchronize()
+    for a, b in zip(*results):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+def test_own_rows_step_under_capture(cs):
+    """A step of own-row calls replayed from a HIP graph equals the step of separate calls, every time."""
+    from paper_2604_06036_amd import engine, synth
+    w = synth.small_variant(synth.CFG2, n_streams=1, n_layers=4)
+    say(f"own rows: captured step, {w.name} streams={w.n_streams} layers={w.n_layers}")
+    data = engine.assemble_step(w, engine.hip_scorer, device="cpu")
+    caps = dict(reuse_cap=data.info["n_reuse"] + 64, q_cap=data.info["n_q"] + 64)
+    two, one = engine.DeviceStep(data, fused=False, **caps), engine.DeviceStep(data, **caps)
+    two.run()
+    k0, v0 = data.k_pool.to(DEV), data.v_pool.to(DEV)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        one.run()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        one.run()
+    for rep in range(3):
+        one.k_pool.copy_(k0); one.v_pool.copy_(v0); one.out.zero_(); one.ws_d.fill_(0xA5)
+        assert math.isfinite(torch.randn(1 << 20, device=DEV).sum().item())
+        graph.replay()
+        torch.cuda.synchronize()
+        for name in ("k_pool", "v_pool", "out"):
+            assert torch.equal(getattr(two, name).view(torch.int16), getattr(one, name).view(torch.int16)), (rep, name)
