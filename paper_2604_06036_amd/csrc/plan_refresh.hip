@@ -18,6 +18,7 @@
 //                           tokens are consecutive in the sequence and consecutive in their output
 //                           list, so every store is coalesced; the tail of the workgroups pads the
 //                           lists up to their capacities.
+// Small batches (one_launch) take one launch, which does without the prefix sums in memory.
 // A reused token's row in the previous window is its new sequence index plus the kept-token count
 // of the frames that left the window (the overlap keeps its order), so no second prefix sum over
 // the old window is needed.
@@ -165,6 +166,40 @@ __device__ __forceinline__ int slot_of(const int32_t* bt, int max_blocks, int se
   return bt[b] * CS_KV_BLOCK + seq % CS_KV_BLOCK;
 }
 
+// The rows of one frame (or text suffix) of stream s: list entries o0 onward, sequence positions seq0 onward; `head`: kept
+// tokens of the frames that left the window.  True: the block tables do not cover all of them.
+__device__ __forceinline__ bool fill_rows(const PlanRefreshParams& p, int lane, int s, int kind, int seq0, int cnt, int64_t o0, int head) {
+  const int32_t* btn = p.bt_new + static_cast<int64_t>(s) * p.max_blocks_new;
+  bool bad = false;
+  if (kind == kKindReuse) {
+    const int32_t* bto = p.bt_old + static_cast<int64_t>(s) * p.max_blocks_old;
+    for (int i = lane; i < cnt; i += 64) {
+      const int64_t o = o0 + i;
+      const int src = slot_of(bto, p.max_blocks_old, seq0 + i + head, &bad);
+      const int dst = slot_of(btn, p.max_blocks_new, seq0 + i, &bad);
+      if (o < p.reuse_cap) {
+        // a row with either slot missing is dropped as a whole
+        p.src_slot[o] = dst < 0 ? -1 : src;
+        p.dst_slot[o] = src < 0 ? -1 : dst;
+        p.delta[o] = p.shift;
+      }
+    }
+  } else {
+    for (int i = lane; i < cnt; i += 64) {
+      const int64_t o = o0 + i;
+      const int dst = slot_of(btn, p.max_blocks_new, seq0 + i, &bad);
+      if (o < p.q_cap) {
+        // a position the block-table row does not cover (flagged) is pulled back onto the row, so
+        // that attention queued behind this plan never indexes past the table
+        p.q_pos[o] = dst < 0 ? min(seq0 + i, p.max_blocks_new * CS_KV_BLOCK - 1) : seq0 + i;
+        p.q_slot[o] = dst;
+        p.q_kind[o] = static_cast<uint8_t>(kind);
+      }
+    }
+  }
+  return bad;
+}
+
 __global__ __launch_bounds__(256) void plan_fill_kernel(PlanRefreshParams p, int fill_blocks, int pad_r_blocks) {
   const int lane = threadIdx.x & 63;
   const int block = blockIdx.x;
@@ -184,39 +219,166 @@ __global__ __launch_bounds__(256) void plan_fill_kernel(PlanRefreshParams p, int
   if (unit >= static_cast<int64_t>(p.n_streams) * per_stream) return;
   const int s = static_cast<int>(unit / per_stream);
   const int4 r = p.rec[unit];
-  const int seq0 = r.x, cnt = r.z, kind = r.w;
-  const int32_t* btn = p.bt_new + static_cast<int64_t>(s) * p.max_blocks_new;
-  bool bad = false;
-  if (kind == kKindReuse) {
-    const int32_t* bto = p.bt_old + static_cast<int64_t>(s) * p.max_blocks_old;
-    const int head = p.st_head[s];
-    const int64_t o0 = static_cast<int64_t>(p.reuse_base[s]) + r.y;
-    for (int i = lane; i < cnt; i += 64) {
-      const int64_t o = o0 + i;
-      const int src = slot_of(bto, p.max_blocks_old, seq0 + i + head, &bad);
-      const int dst = slot_of(btn, p.max_blocks_new, seq0 + i, &bad);
-      if (o < p.reuse_cap) {
-        // a row with either slot missing is dropped as a whole
-        p.src_slot[o] = dst < 0 ? -1 : src;
-        p.dst_slot[o] = src < 0 ? -1 : dst;
-        p.delta[o] = p.shift;
-      }
+  const bool reuse = r.w == kKindReuse;
+  const int64_t o0 = static_cast<int64_t>(reuse ? p.reuse_base[s] : p.q_base[s]) + r.y;
+  if (fill_rows(p, lane, s, r.w, r.x, r.z, o0, reuse ? p.st_head[s] : 0)) atomicOr(p.totals + 2, kFlagBlockTable);
+}
+
+// ---- small batches: everything in one launch.  What bounds it is latency, three dependent launches being most of it, so
+// every wave finds the prefix sums that it needs by itself: over the overlap frames of the streams before its own (kept
+// tokens of the new frames come as differences of kept_off), two loads a frame, from L2.  The first workgroup writes what is
+// kept a stream or a frame, the next ones a (stream, frame) record a wave, the last ones pad the lists.
+struct FlatSums {
+  int reuse, anchor, own;      // reused rows, anchor rows, rows of records from own_from on
+};
+
+// Sums over the first n records, record i being overlap frame i % keep of stream i / keep.  All lanes take the result.
+__device__ __forceinline__ FlatSums flat_sums(const PlanRefreshParams& p, int lane, int n, int own_from) {
+  const int keep = p.window - p.stride;
+  FlatSums t = {0, 0, 0};
+  for (int i0 = lane; i0 < n; i0 += 256) {
+    int type[4], cnt[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = min(i0 + 64 * u, n - 1);
+      const int s = i / keep;
+      const int64_t at = static_cast<int64_t>(s) * p.window + p.stride + (i - s * keep);
+      type[u] = p.old_types[at];
+      cnt[u] = p.old_counts[at];
     }
-  } else {
-    const int64_t o0 = static_cast<int64_t>(p.q_base[s]) + r.y;
-    for (int i = lane; i < cnt; i += 64) {
-      const int64_t o = o0 + i;
-      const int dst = slot_of(btn, p.max_blocks_new, seq0 + i, &bad);
-      if (o < p.q_cap) {
-        // a position the block-table row does not cover (flagged) is pulled back onto the row, so
-        // that attention queued behind this plan never indexes past the table
-        p.q_pos[o] = dst < 0 ? min(seq0 + i, p.max_blocks_new * CS_KV_BLOCK - 1) : seq0 + i;
-        p.q_slot[o] = dst;
-        p.q_kind[o] = static_cast<uint8_t>(kind);
-      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + 64 * u, c = i < n ? cnt[u] : 0;
+      const bool anchor = type[u] == CS_FRAME_I;
+      t.reuse += anchor ? 0 : c;
+      t.anchor += anchor ? c : 0;
+      t.own += i >= own_from ? c : 0;
     }
   }
-  if (bad) atomicOr(p.totals + 2, kFlagBlockTable);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    t.reuse += __shfl_xor(t.reuse, off);
+    t.anchor += __shfl_xor(t.anchor, off);
+    t.own += __shfl_xor(t.own, off);
+  }
+  return t;
+}
+
+constexpr int kPadPerWave = 256;         // list entries that a wave of the one launch pads
+
+__global__ __launch_bounds__(256) void plan_one_launch_kernel(PlanRefreshParams p, int fill_blocks, int pad_r_blocks) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int W = p.window, S = p.stride, keep = W - S;
+  if (blockIdx.x == 0) {
+    // a thread per stream: its frames one after the other
+    __shared__ int part_r[4], part_q[4];
+    __shared__ int any_bad;
+    if (threadIdx.x == 0) any_bad = 0;
+    const int s = threadIdx.x;
+    int seq = 0, reuse = 0;
+    bool bad = false;
+    const int64_t room_new = static_cast<int64_t>(p.max_blocks_new) * CS_KV_BLOCK, room_old = static_cast<int64_t>(p.max_blocks_old) * CS_KV_BLOCK;
+    if (s < p.n_streams) {
+      const uint8_t* ot = p.old_types + static_cast<int64_t>(s) * W;
+      const int32_t* oc = p.old_counts + static_cast<int64_t>(s) * W;
+      const int32_t* ko = p.kept_off + static_cast<int64_t>(s) * S;
+      // as slot_of finds it for the rows [seq, seq + cnt) of the window (and, reused ones, `ahead` rows further on in the old one)
+      auto covered = [](int64_t first, int cnt, int64_t room) { return cnt <= 0 || (first >= 0 && first + cnt <= room); };
+      const uint8_t* nt = p.new_types + static_cast<int64_t>(s) * S;
+      int head = 0;
+#pragma unroll 8
+      for (int f = 0; f < S; ++f) head += oc[f];
+      for (int f0 = 0; f0 < W; f0 += 8) {          // (all loads of eight frames before the first store)
+        int type[8], cnt[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int f = min(f0 + u, W - 1);
+          type[u] = f < keep ? ot[f + S] : nt[f - keep];
+          cnt[u] = f < keep ? oc[f + S] : ko[f - keep + 1] - ko[f - keep];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int f = f0 + u;
+          if (f >= W) break;
+          p.out_types[static_cast<int64_t>(s) * W + f] = static_cast<uint8_t>(type[u]);
+          p.out_counts[static_cast<int64_t>(s) * W + f] = cnt[u];
+          bad |= !covered(seq, cnt[u], room_new);
+          if (f < keep && type[u] != CS_FRAME_I) {
+            bad |= !covered(seq + head, cnt[u], room_old);
+            reuse += cnt[u];
+          }
+          seq += cnt[u];
+        }
+      }
+      bad |= !covered(seq, p.n_text, room_new);
+      p.kv_len[s] = seq + p.n_text;
+    }
+    const int q = s < p.n_streams ? seq - reuse + p.n_text : 0;
+    const int r_inc = wave_inclusive_scan(reuse, lane), q_inc = wave_inclusive_scan(q, lane);
+    if (lane == 63) { part_r[wave] = r_inc; part_q[wave] = q_inc; }
+    __syncthreads();
+    if (bad) any_bad = 1;
+    int base_q = 0, all_q = 0, all_r = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if (w < wave) base_q += part_q[w];
+      all_q += part_q[w];
+      all_r += part_r[w];
+    }
+    if (s < p.n_streams) p.cu_q[s] = static_cast<int>(min(static_cast<int64_t>(base_q + q_inc - q), p.q_cap));
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      p.cu_q[p.n_streams] = static_cast<int>(min(static_cast<int64_t>(all_q), p.q_cap));
+      p.totals[0] = all_r;
+      p.totals[1] = all_q;
+      p.totals[2] = (all_r > p.reuse_cap ? kFlagReuseCap : 0) | (all_q > p.q_cap ? kFlagQueryCap : 0) | (any_bad ? kFlagBlockTable : 0);
+      p.totals[3] = 0;
+    }
+    return;
+  }
+  const int block = blockIdx.x - 1;
+  const int32_t* ko = p.kept_off;
+  if (block >= fill_blocks) {
+    const FlatSums t = flat_sums(p, lane, p.n_streams * keep, 0);
+    const bool pads_r = block < fill_blocks + pad_r_blocks;
+    const int64_t first = (static_cast<int64_t>(block - fill_blocks - (pads_r ? 0 : pad_r_blocks)) * 4 + wave) * kPadPerWave + lane;
+    const int total = pads_r ? t.reuse : t.anchor + ko[p.n_streams * S] - ko[0] + p.n_streams * p.n_text;
+#pragma unroll
+    for (int u = 0; u < kPadPerWave / 64; ++u) {
+      const int64_t i = first + 64 * u;
+      if (i < total) continue;
+      if (pads_r) {
+        if (i < p.reuse_cap) { p.src_slot[i] = -1; p.dst_slot[i] = -1; p.delta[i] = 0; }
+      } else {
+        if (i < p.q_cap) { p.q_pos[i] = 0; p.q_slot[i] = -1; p.q_kind[i] = 0xff; }
+      }
+    }
+    return;
+  }
+  const int unit = block * 4 + wave;
+  if (unit >= p.n_streams * (W + 1)) return;
+  const int s = unit / (W + 1), f = unit - s * (W + 1);
+  const int own_from = s * keep;
+  const FlatSums t = flat_sums(p, lane, own_from + min(f, keep), own_from);
+  // new frames of the streams before and, where the record is past the overlap, of its own
+  const int ko_s = ko[s * S], ko_f = f > keep ? ko[s * S + f - keep] : ko_s;
+  int kind = kKindText, cnt = p.n_text;
+  if (f < keep) {
+    const int64_t at = static_cast<int64_t>(s) * W + S + f;
+    cnt = p.old_counts[at];
+    kind = p.old_types[at] == CS_FRAME_I ? kKindAnchor : kKindReuse;
+  } else if (f < W) {
+    cnt = ko[s * S + f - keep + 1] - ko_f;
+    kind = kKindNew;
+  }
+  int head = 0;
+  if (kind == kKindReuse) {
+    for (int g = lane; g < S; g += 64) head += p.old_counts[static_cast<int64_t>(s) * W + g];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) head += __shfl_xor(head, off);
+  }
+  const int64_t o0 = kind == kKindReuse ? t.reuse : t.anchor + ko_f - ko[0] + s * p.n_text;
+  fill_rows(p, lane, s, kind, t.own + ko_f - ko_s, cnt, o0, head);      // (the first workgroup finds the flags)
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
@@ -236,6 +398,16 @@ PlanRefreshLayout layout_for(int64_t n_streams, int64_t window) {
   l.off_qbase = at;    at = align256(at + static_cast<size_t>(n_streams) * sizeof(int32_t));
   l.total = at;
   return l;
+}
+
+// One launch or three: the one repeats sums over the streams before in every wave, and a thread of its first workgroup walks a
+// stream's window alone.  us a call in a graph, three launches / one: 1 stream of 8 frames 7.5 / 3.8, 5 of 11 8.5 / 4.7, 64 of 8
+// 8.3 / 4.1, 64 of 16 (896 overlap frames) 8.4 / 5.3, 128 of 8 8.5 / 5.3, but 128 of 16 (1,920) 8.8 / 9.3, 256 of 8 (1,792)
+// 8.9 / 9.1, 4 of 64 8.1 / 13.2 (0.17 a frame of the window).
+constexpr int kOneLaunchStreams = 256, kOneLaunchRecords = 1024, kOneLaunchWindow = 24;
+bool one_launch(int32_t n_streams, int32_t window, int32_t stride) {
+  return n_streams > 0 && n_streams <= kOneLaunchStreams && window <= kOneLaunchWindow &&
+         static_cast<int64_t>(n_streams) * (window - stride) <= kOneLaunchRecords;
 }
 
 }  // namespace
@@ -308,6 +480,13 @@ extern "C" int cs_plan_refresh(const uint8_t* old_types, const int32_t* old_coun
   p.q_base = reinterpret_cast<int32_t*>(w + l.off_qbase);
 
   hipStream_t st = cs::as_stream(stream);
+  if (one_launch(n_streams, window, stride)) {
+    const int64_t fill_blocks = (units + 3) / 4, pad_r = (reuse_cap + 4 * kPadPerWave - 1) / (4 * kPadPerWave);
+    const int64_t blocks = 1 + fill_blocks + pad_r + (q_cap + 4 * kPadPerWave - 1) / (4 * kPadPerWave);
+    hipLaunchKernelGGL(plan_one_launch_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p,
+                       static_cast<int>(fill_blocks), static_cast<int>(pad_r));
+    return cs::note_hip(hipGetLastError());
+  }
   if (n_streams > 0) {
     hipLaunchKernelGGL(plan_frames_kernel, dim3((n_streams + 3) / 4), dim3(256), 0, st, p);
     const int e = cs::note_hip(hipGetLastError());
