@@ -18,6 +18,7 @@
 //   pass 2  take the ballot words of pass 1 back from LDS (or, past 128 words per wave, re-read
 //           the wave's own keep bytes), rank kept tokens inside each 64-token group with mbcnt,
 //           and write their dense ids at base + rank.
+// Small batches are one tile of up to 16 waves (wide_tile): no look-back, nothing to clear.
 // The look-back wait is bounded: after kSpinLimit polls a tile raises the error word in the
 // workspace and continues with a zero prefix, so every wave always exits.
 #include <mutex>
@@ -365,12 +366,12 @@ __device__ uint32_t look_back(const ScoreParams& p, uint32_t tile, uint32_t aggr
 // and tiles need no order at all when the prefix comes from a scan.
 constexpr int kFused = 0, kScoreOnly = 1, kEmitOnly = 2;
 
-template <int G, bool PK, int MODE>
-__global__ __launch_bounds__(kWavesPerTile * cs::kWave) void score_compact_kernel(ScoreParams p) {
+template <int G, bool PK, int MODE, int WAVES = kWavesPerTile>
+__global__ __launch_bounds__(WAVES * cs::kWave) void score_compact_kernel(ScoreParams p) {
   __shared__ uint32_t s_ticket;
-  __shared__ uint32_t s_total[kWavesPerTile];
+  __shared__ uint32_t s_total[WAVES];
   __shared__ uint32_t s_exclusive;
-  __shared__ uint64_t s_mask[MODE == kFused ? kWavesPerTile : 1][kMaskWords];
+  __shared__ uint64_t s_mask[MODE == kFused ? WAVES : 1][kMaskWords];
   const int lane = threadIdx.x & (cs::kWave - 1);
   const int wave = threadIdx.x / cs::kWave;
   if constexpr (MODE == kFused) {
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(kWavesPerTile * cs::kWave) void score_compact_kerne
   }
   const uint32_t tile = MODE == kFused ? s_ticket : blockIdx.x;
   uint64_t* my_masks = s_mask[MODE == kFused ? wave : 0];
-  const int s_begin = (static_cast<int>(tile) * kWavesPerTile + wave) * p.streams_per_wave;
+  const int s_begin = (static_cast<int>(tile) * WAVES + wave) * p.streams_per_wave;
   const int s_end = min(p.n_streams, s_begin + p.streams_per_wave);
   // The wave's frame ranges and frame types are fetched lane-parallel up front, so that the walk
   // over its streams does not pay a dependent memory round trip per stream for them.
@@ -449,14 +450,14 @@ __global__ __launch_bounds__(kWavesPerTile * cs::kWave) void score_compact_kerne
       cur = nxt;
     }
   }
-  const int64_t gw = static_cast<int64_t>(tile) * kWavesPerTile + wave;
+  const int64_t gw = static_cast<int64_t>(tile) * WAVES + wave;
   if constexpr (MODE == kScoreOnly) {
     if (lane == 0) { p.wave_total[gw] = total; s_total[wave] = total; }
     __syncthreads();
     if (threadIdx.x == 0) {
       uint32_t sum = 0;
 #pragma unroll
-      for (int w = 0; w < kWavesPerTile; ++w) sum += s_total[w];
+      for (int w = 0; w < WAVES; ++w) sum += s_total[w];
       p.wg_total[tile] = sum;
     }
     return;
@@ -468,7 +469,7 @@ __global__ __launch_bounds__(kWavesPerTile * cs::kWave) void score_compact_kerne
     if (wave == 0) {
       uint32_t aggregate = 0;
 #pragma unroll
-      for (int w = 0; w < kWavesPerTile; ++w) aggregate += s_total[w];
+      for (int w = 0; w < WAVES; ++w) aggregate += s_total[w];
       const uint32_t exclusive = p.single_tile ? 0u : look_back(p, tile, aggregate, lane);
       if (lane == 0) s_exclusive = exclusive;
     }
@@ -592,6 +593,17 @@ __global__ __launch_bounds__(kScanThreads) void scan_totals_kernel(uint64_t* fir
 // Above this many streams the call is three launches (see score_compact_kernel).
 constexpr int kFusedMaxStreams = 4096;
 
+// Batches of up to 16 streams with up to 32 sweeps are one tile, a wave to a stream: tiles of 4 waves would need a launch that
+// clears the look-back words first, and wait for each other's counts.  More waves than that, or longer walks, and the issue rate
+// of the one CU is the time.  us a call in a graph, tiles of 4 waves / one tile: 8 streams of 16 x 16 6.6 / 4.2, 12 6.7 / 4.6, 16
+// 6.7 / 5.2, 5 of 2 frames of 19 x 27 (30 sweeps) 16.4 / 14.1, but 32 streams 6.9 / 7.9, 64 6.8 / 13.5, 12 of 26 x 46 (60
+// sweeps) 11.8 / 12.3.  (group 2 stays with tiles of 4 waves: its sweeps hold four patches a lane, which 16 waves a workgroup
+// have no registers for.)
+constexpr int kWideWaves = 16, kWideSweeps = 32;
+bool wide_tile(int n_streams, int n_frames, int64_t n_tok, int group) {
+  return group == 1 && n_streams > kWavesPerTile && n_streams <= kWideWaves && n_frames * ((n_tok + kSweep - 1) / kSweep) <= kWideSweeps;
+}
+
 struct SplitPlan {
   int streams_per_wave;
   int64_t n_waves, n_wgs;
@@ -668,7 +680,8 @@ int score_compact_call(const int16_t* mv, const uint32_t* sad, const uint8_t* in
   const bool split = n_streams > kFusedMaxStreams;
   const SplitPlan sp = split_plan(n_streams);
   if (split && sp.n_wgs >= (1ll << 31)) return CS_EUNSUPPORTED;
-  const int n_tiles = split ? static_cast<int>(sp.n_wgs) : tiles_for(n_streams);
+  const bool wide = wide_tile(n_streams, n_frames, n_tok, group);
+  const int n_tiles = wide ? 1 : split ? static_cast<int>(sp.n_wgs) : tiles_for(n_streams);
   ScoreParams p;
   p.mv = reinterpret_cast<const uint32_t*>(mv);
   p.sad = sad;
@@ -715,7 +728,11 @@ int score_compact_call(const int16_t* mv, const uint32_t* sad, const uint8_t* in
     else                                                                                             \
       hipLaunchKernelGGL((score_compact_kernel<2, false, MODE>), grid, block, 0, st, p);             \
   } while (0)
-  if (!split) {
+  if (wide) {
+    const dim3 wide_block(kWideWaves * cs::kWave);
+    if (packed) hipLaunchKernelGGL((score_compact_kernel<1, true, kFused, kWideWaves>), grid, wide_block, 0, st, p);
+    else hipLaunchKernelGGL((score_compact_kernel<1, false, kFused, kWideWaves>), grid, wide_block, 0, st, p);
+  } else if (!split) {
     CS_LAUNCH_SCORE(kFused);
   } else {
     CS_LAUNCH_SCORE(kScoreOnly);
