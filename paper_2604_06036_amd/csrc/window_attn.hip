@@ -435,16 +435,21 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
     cap = min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK) - 1;
     wg_max = min(p.q_pos[q0 + (min(r_tile + BM, rows_total) - 1) / p.group], cap);
   }
-  const int lim = valid ? min(p.q_pos[tok], cap) : -1;
+  const int pos = p.q_pos[tok];
+  int lim, wave_min, wave_max;
+  auto frontiers = [&]() __attribute__((always_inline)) {
+    lim = valid ? min(pos, cap) : -1;
+    // positions do not decrease along the rows
+    const int rows_here = min(32, rows_total - w_first);
+    wave_min = rows_here > 0 ? __builtin_amdgcn_readlane(lim, 0) : -1;
+    wave_max = rows_here > 0 ? __builtin_amdgcn_readlane(lim, max(rows_here, 1) - 1) : -1;
+  };
+  if (STAGES == 1) frontiers();
   if (!SPLIT && wg_max < 0) {                           // the stream defines no cache entry: rows left untouched
     if constexpr (OWN) move.all(p);
     settle();
     return;
   }
-  // positions do not decrease along the rows
-  const int rows_here = min(32, rows_total - w_first);
-  const int wave_min = rows_here > 0 ? __builtin_amdgcn_readlane(lim, 0) : -1;
-  const int wave_max = rows_here > 0 ? __builtin_amdgcn_readlane(lim, max(rows_here, 1) - 1) : -1;
   const int n_key_tiles = wg_max / kBN + 1;
   const int last_blk = wg_max / CS_KV_BLOCK;
   // ---- this workgroup's key tiles [kt_begin, kt_end): pieces are whole trips of the groups
@@ -462,6 +467,21 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
     kt_begin = piece * len;
     kt_end = min(kt_begin + len, n_key_tiles);
   }
+
+  // ---- Q^T fragments: lane = (query n, half h) holds d-slice [16 step + 8 h, + 8).  With two stages they and the positions are
+  //      asked for before the cache blocks' ids have come, and the positions looked at behind the first tile's requests: the
+  //      compiler does not know of those, and where it waits for a load it waits for all of them.  us a step, 24 layers of
+  //      head_dim 64: one stream, 16/4 heads 424 / 415, 12 streams, 8/1 heads 508 / 494, 32 streams, 16/4 heads 1,607 / 1,594; 8 streams, 8/1
+  //      heads of 128 1,090 / 1,082.  With one stage the first K is what a sweep starts on, and Q in front of it 1 % slower.
+  const int64_t q_at = (static_cast<int64_t>(tok) * p.n_q_heads + head) * D;
+  const uint16_t* qrow = static_cast<const uint16_t*>(p.q) + q_at;
+  bf16x8 qf[STEPS];
+  auto load_queries = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st)
+      qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const cs::u32x4*>(qrow + 16 * st + 8 * h));
+  };
+  if (STAGES == 2) load_queries();
 
   // ---- tile requests.  This wave fetches rows [16 BPW rw, + 16 BPW) of its group's tiles; inside a cache block
   //      a lane's source offset is constant.  The tile that holds the frontier takes per-lane addresses: rows past
@@ -567,15 +587,7 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   }
   if (STAGES == 2) load_ids(kt + KG);
 
-  // ---- Q^T fragments: lane = (query n, half h) holds d-slice [16 step + 8 h, + 8)
-  const int64_t q_at = (static_cast<int64_t>(tok) * p.n_q_heads + head) * D;
-  const uint16_t* qrow = static_cast<const uint16_t*>(p.q) + q_at;
-  bf16x8 qf[STEPS];
-#pragma unroll
-  for (int st = 0; st < STEPS; ++st)
-    qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const cs::u32x4*>(qrow + 16 * st + 8 * h));
-
-
+  if (STAGES == 1) load_queries();
   if constexpr (OWN) move.load(p);
 
   // ---- LDS byte addresses of this lane's fragments
@@ -598,6 +610,11 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   const float slack = kMaxSlack / p.scale_log2e;          // in raw score units
 
   if (STAGES == 2) wait_ids();
+
+  if (STAGES == 2) {
+    wait_vmcnt<0>();
+    frontiers();
+  }
 
   // Four groups: a SIMD holds a wave of group g and one of g + 2.  The upper groups run one barrier behind, so that one of
   // the two is at its matrix instructions while the other forms weights (a barrier more here for them, behind the sweep for
