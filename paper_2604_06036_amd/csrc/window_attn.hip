@@ -68,6 +68,8 @@ struct AttnParams {
   int32_t row_vecs, head_vecs;   // 16-byte vectors per new row / per head
   cs::u32x2* ws_own;     // CS_ATTN_OWN_ROWS: where the rows of each cache block are (OwnEntry), [streams][max_blocks]
   int32_t* ws_tiles;     // and the row tiles of a launch without a plan, [workgroups][8] (window_attn_own_rows_kernel)
+  cs::u32x2* ws_warm;    // and of every stream its first query and how many cache entries its queries see
+  int32_t n_warm;        // workgroups ahead of the row tiles that bring keys and values into L2 (warm_l2)
   int32_t* ws_sync;      // counters of the fused launch's launch-wide barrier (see launch_barrier)
   int32_t* ws_status;    // its status word
   int32_t clear_status;  // the launch without a plan zeroes it
@@ -194,8 +196,9 @@ __device__ __forceinline__ T* uniform(T* ptr) {
 constexpr int kOwnIdBits = 27, kOwnRowBits = 21;      // (slots are 32-bit: ids below 2^27; windows of up to 2^21 entries)
 struct OwnEntry {
   uint32_t id, row, mask;
-  __device__ __forceinline__ OwnEntry(const i32x2& e) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(e.x), hi = __builtin_amdgcn_readfirstlane(e.y);
+  __device__ __forceinline__ OwnEntry(const i32x2& e)      // the same in all lanes
+      : OwnEntry(__builtin_amdgcn_readfirstlane(e.x), __builtin_amdgcn_readfirstlane(e.y)) {}
+  __device__ __forceinline__ OwnEntry(uint32_t lo, uint32_t hi) {
     id = lo & ((1u << kOwnIdBits) - 1);
     row = lo >> kOwnIdBits | hi >> 16 << (32 - kOwnIdBits);
     mask = hi & 0xffffu;
@@ -327,9 +330,10 @@ struct OwnMove {
   uint32_t rem = 0;
   __device__ __forceinline__ void load(const AttnParams& p) {
     const uint32_t n_units = static_cast<uint32_t>(p.n_new) * p.row_vecs;      // (below 2^31: the host checks)
-    const uint64_t apart = static_cast<uint64_t>(gridDim.x) * THREADS;
-    if (static_cast<uint64_t>(blockIdx.x) * THREADS + threadIdx.x >= n_units) return;
-    uint32_t unit = blockIdx.x * THREADS + threadIdx.x;
+    const uint64_t apart = static_cast<uint64_t>(gridDim.x - p.n_warm) * THREADS;
+    const uint32_t wg = blockIdx.x - p.n_warm;
+    if (static_cast<uint64_t>(wg) * THREADS + threadIdx.x >= n_units) return;
+    uint32_t unit = wg * THREADS + threadIdx.x;
     for (;;) {
       const uint32_t tok = unit / p.row_vecs;
       rem = unit - tok * p.row_vecs;
@@ -847,16 +851,78 @@ __device__ __forceinline__ void attend_row_tile(const AttnParams& p, int block, 
   }
 }
 
+// Launches that leave CUs idle put some workgroups ahead of the row tiles, up to kWarmPerXcd an XCD, that read a word of each
+// cache line of the keys and values past the first trip.  The row tiles of a (stream, kv head) sweep the same keys at the same
+// pace, and every trip waited for a line's way from memory twice (K, then V): with the tiles in L2 already (the same tile asked
+// for again and again) a step of one stream takes 506 us instead of 561, without any arithmetic 382 instead of 504.  What bounds it is its
+// own chain: where the stream's entries are, the lines' places, the lines.  Which XCD a workgroup runs on (they go round robin)
+// decides only whether this helps.  us a step of 28 layers, without / with: one
+// stream of 900 keys, 28/4 heads 561 / 533, 32/8 665 / 612, 8/1 526 / 504, of 1,800 keys 782 / 704, of 450 424 / 417, two of 1,300 keys,
+// 16/4 heads 848 / 792, of 900, 28/4 692 / 681; head_dim 64, one stream, 16/4 heads (24 layers) 414 / 412.
+// Asked for by the row tiles' own threads, a line each behind the first trip's requests, the gain was half of that, and launches
+// that fill the chip lost 2-5 %.
+constexpr int kWarmPerXcd = 4;
+template <int D, int KG, int THREADS>
+__device__ __forceinline__ void warm_l2(const AttnParams& p) {
+  constexpr int LINES = D * 4 / 128;     // 128-byte lines of a key and its value
+  constexpr int AT_ONCE = 4;
+  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, n_wg = p.n_warm >> 3;
+  const int heads_apart = min(8, p.n_kv_heads & -p.n_kv_heads);      // of the kv heads that an XCD's row tiles have
+  const int groups = min(n_wg, p.n_streams), parts = n_wg / groups, part = j / groups;
+  if (part >= parts) return;
+  uint32_t sum = 0;
+  for (int s = j % groups; s < p.n_streams; s += groups) {
+    const cs::u32x2 seen = p.ws_warm[s];
+    const int rows = static_cast<int>(seen.y);
+    const i32x2* own_t = reinterpret_cast<const i32x2*>(p.ws_own) + static_cast<int64_t>(s) * p.max_blocks;
+    for (int kvh = xcd % heads_apart; kvh < p.n_kv_heads; kvh += heads_apart) {
+      const uint16_t* kh = static_cast<const uint16_t*>(p.k) + static_cast<int64_t>(kvh) * p.stride_head;
+      const uint16_t* vh = static_cast<const uint16_t*>(p.v) + static_cast<int64_t>(kvh) * p.stride_head;
+      const int64_t own_at = static_cast<int64_t>(seen.x) * p.stride_slot + static_cast<int64_t>(kvh) * D;
+      const uint16_t* kn = static_cast<const uint16_t*>(p.k_new) + own_at;
+      const uint16_t* vn = static_cast<const uint16_t*>(p.v_new) + own_at;
+      const int step = parts * THREADS;
+      for (int i0 = KG * kBN * LINES + part * THREADS + static_cast<int>(threadIdx.x); i0 < rows * LINES; i0 += AT_ONCE * step) {
+        i32x2 e[AT_ONCE];
+        uint32_t got[AT_ONCE];
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) e[u] = own_t[min((i0 + u * step) / LINES, rows - 1) / CS_KV_BLOCK];
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) {
+          const int row = min((i0 + u * step) / LINES, rows - 1), line = (i0 + u * step) % LINES, r = row % CS_KV_BLOCK;
+          const OwnEntry at(static_cast<uint32_t>(e[u].x), static_cast<uint32_t>(e[u].y));
+          const bool v = line >= LINES / 2;
+          const uint16_t* src = at.own(r) ? (v ? vn : kn) + at.row_of(r) * p.stride_slot
+                                          : (v ? vh : kh) + (static_cast<int64_t>(at.id) * CS_KV_BLOCK + r) * p.stride_slot;
+          got[u] = *reinterpret_cast<const uint32_t*>(src + line % (LINES / 2) * 64);
+        }
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) sum |= got[u];
+      }
+    }
+  }
+  asm volatile("" :: "v"(sum));          // (the loads are not to be left out)
+}
+
 template <int D, int ROWW, int KG, int STAGES, bool SPLIT = false, bool OWN = false>
 __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_bf16_tile_kernel(AttnParams p) {
   __shared__ TileStages<D, KG, STAGES> stages;
-  attend_row_tile<D, ROWW, KG, STAGES, SPLIT, OWN>(p, blockIdx.x, stages);
+  int block = blockIdx.x;
+  if constexpr (OWN && !SPLIT && KG > 1) {
+    if (block < p.n_warm) {
+      warm_l2<D, KG, 64 * ROWW * KG>(p);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (no scalar load is left in flight)
+      return;
+    }
+    block -= p.n_warm;
+  }
+  attend_row_tile<D, ROWW, KG, STAGES, SPLIT, OWN>(p, block, stages);
 }
 
 // What the call that plans does for those that read their own rows, besides planning: the refresh write (of n_new rows, which
 // it still needs itself), the table, and the row tiles of BM rows of a launch without a plan: first query token and
 // rows of the stream (0: no tile), first row, kv head, frontier (the last cache entry that the last row sees, inside those
-// that the stream defines; -1: none), stream.
+// that the stream defines; -1: none), stream.  Of every stream, its first query and the cache entries up to its last frontier.
 template <int BM>
 __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) {
   __shared__ int s_tiles[64];
@@ -881,6 +947,11 @@ __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) 
     }
     if (len < CS_KV_BLOCK && (~mask & ((1u << len) - 1)) == 0) mask = 0xffffu;
     p.ws_own[i] = OwnEntry::packed(p.block_table[i], lo - q0, mask);
+  }
+  for (int64_t s = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x; s < p.n_streams; s += static_cast<int64_t>(gridDim.x) * 64) {
+    const int q0 = p.cu_q[s], q1 = p.cu_q[s + 1];
+    const int seen = q1 > q0 ? min(p.q_pos[q1 - 1] + 1, min(p.kv_len[s], p.max_blocks * CS_KV_BLOCK)) : 0;
+    p.ws_warm[s] = cs::u32x2{static_cast<uint32_t>(q0), static_cast<uint32_t>(seen)};
   }
   const int64_t n_tiles = ((p.n_q * p.group) / BM + p.n_streams) * p.n_kv_heads;
   for (int64_t b = blockIdx.x; b < n_tiles; b += gridDim.x) {
@@ -3129,8 +3200,14 @@ int launch_tiles(const AttnParams& p, hipStream_t st) {
   const int64_t tiles = ((p.n_q * p.group) / (32 * ROWW) + p.n_streams) * p.n_kv_heads;      // upper bound
   if (tiles > 0x7fffffffll) return CS_EUNSUPPORTED;
   const dim3 grid(static_cast<unsigned>(tiles)), block(64 * ROWW * KG);
-  if (p.ws_own) hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES, false, true>), grid, block, 0, st, p);
-  else hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES>), grid, block, 0, st, p);
+  if (p.ws_own) {
+    // workgroups that run at once: two a CU, with four key groups one
+    constexpr int kAtOnce = KG > 2 ? 256 : 512;
+    const int idle = tiles < kAtOnce ? static_cast<int>(kAtOnce - tiles) / 8 : 0;
+    AttnParams own = p;
+    own.n_warm = KG > 1 ? 8 * (idle < kWarmPerXcd ? idle : kWarmPerXcd) : 0;
+    hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES, false, true>), dim3(grid.x + own.n_warm), block, 0, st, own);
+  } else hipLaunchKernelGGL((window_attn_bf16_tile_kernel<D, ROWW, KG, STAGES>), grid, block, 0, st, p);
   return cs::note_hip(hipGetLastError());
 }
 
@@ -3171,12 +3248,15 @@ extern "C" size_t cs_window_prefill_attn_workspace(int64_t n_q, int32_t n_stream
 namespace {
 
 // What calls with CS_ATTN_OWN_ROWS keep behind the workspace of the others: the table of own rows, then the row tiles of a
-// launch without a plan (of 64 rows or more).
+// launch without a plan (of 64 rows or more), then a pair of words a stream.
 size_t own_table_bytes(int32_t n_streams, int32_t max_blocks) {
   return (static_cast<size_t>(n_streams) * max_blocks * sizeof(cs::u32x2) + 255) & ~static_cast<size_t>(255);
 }
+size_t own_tiles_bytes(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads) {
+  return static_cast<size_t>((n_q * group / 64 + n_streams) * n_kv_heads) * 8 * sizeof(int32_t);
+}
 size_t own_bytes(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int32_t max_blocks) {
-  return own_table_bytes(n_streams, max_blocks) + static_cast<size_t>((n_q * group / 64 + n_streams) * n_kv_heads) * 8 * sizeof(int32_t);
+  return own_table_bytes(n_streams, max_blocks) + own_tiles_bytes(n_q, n_streams, group, n_kv_heads) + static_cast<size_t>(n_streams) * sizeof(cs::u32x2);
 }
 
 // The attention call; with k_new != nullptr the launch first writes the new K/V rows into the cache
@@ -3258,6 +3338,8 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
   p.row_vecs = n_kv_heads * p.head_vecs;
   p.ws_own = nullptr;
   p.ws_tiles = nullptr;
+  p.ws_warm = nullptr;
+  p.n_warm = 0;
   p.ws_sync = nullptr;
   p.ws_status = nullptr;
   p.clear_status = 0;
@@ -3265,7 +3347,9 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
   // before a call with own rows, of row tiles of bm rows
   auto own_rows = [&](int bm) -> int {
     p.ws_own = own;
-    p.ws_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(own) + own_table_bytes(n_streams, max_blocks));
+    char* tiles = reinterpret_cast<char*>(own) + own_table_bytes(n_streams, max_blocks);
+    p.ws_tiles = reinterpret_cast<int32_t*>(tiles);
+    p.ws_warm = reinterpret_cast<cs::u32x2*>(tiles + own_tiles_bytes(n_q, n_streams, group, n_kv_heads));
     if (plan_mode == CS_ATTN_PLAN_REUSE) return CS_OK;
     if (plan_mode == CS_ATTN_PLAN_ONLY && head_dim == 128) p.n_new = 0;
     const int e = launch_own_rows(p, bm, st);
