@@ -923,9 +923,17 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 // it still needs itself), the table, and the row tiles of BM rows of a launch without a plan: first query token and
 // rows of the stream (0: no tile), first row, kv head, frontier (the last cache entry that the last row sees, inside those
 // that the stream defines; -1: none), stream.  Of every stream, its first query and the cache entries up to its last frontier.
+// More than kRankedTiles row tiles of up to 64 streams are listed by their key tiles, longest first, so that what starts late or
+// shares a CU is short (as find_row_tile has them, the last streams' longest sweeps start last).  us a step, by stream / by length,
+// head_dim 64, 16 layers: 319 row tiles (14 streams, 8/1 heads) 423 / 368, 411 455 / 402, 420 (9 streams, 16/4) 424 / 408, 736 680 / 578,
+// 1,491 (64 streams, 8/1) 1,058 / 908; head_dim 128: 368 of 64 rows 501 / 481, 500 525 / 481.  Fewer have a CU each, and are level
+// (144 319 / 317, 304 of 64 rows 397 / 398) or faster by stream (204 333 / 339, 271 336 / 359, 288 of 64 rows 404 / 416).
+constexpr int kRankedTiles = 300;
 template <int BM>
 __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) {
   __shared__ int s_tiles[64];
+  struct Listed { int first, q0, rows, cap; };
+  __shared__ Listed s_list[64];
   OwnMove<64>().all(p);
   const int64_t n_entries = static_cast<int64_t>(p.n_streams) * p.max_blocks;
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x; i < n_entries; i += static_cast<int64_t>(gridDim.x) * 64) {
@@ -954,15 +962,56 @@ __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) 
     p.ws_warm[s] = cs::u32x2{static_cast<uint32_t>(q0), static_cast<uint32_t>(seen)};
   }
   const int64_t n_tiles = ((p.n_q * p.group) / BM + p.n_streams) * p.n_kv_heads;
+  const int lane = threadIdx.x;
+  int n_found = 0;                       // row tiles of all streams, a kv head
+  if (p.n_streams <= 64 && blockIdx.x < n_tiles) {
+    Listed mine = {};
+    if (lane < p.n_streams) {
+      mine.q0 = p.cu_q[lane];
+      mine.rows = (p.cu_q[lane + 1] - mine.q0) * p.group;
+      mine.cap = min(p.kv_len[lane], p.max_blocks * CS_KV_BLOCK) - 1;
+    }
+    const int tiles = (mine.rows + BM - 1) / BM;
+    int incl = tiles;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int below = __shfl_up(incl, off);
+      incl += lane >= off ? below : 0;
+    }
+    mine.first = incl - tiles;
+    s_list[lane] = mine;
+    n_found = __shfl(incl, 63);
+    __syncthreads();
+  }
+  const bool ranked = static_cast<int64_t>(n_found) * p.n_kv_heads > kRankedTiles;
   for (int64_t b = blockIdx.x; b < n_tiles; b += gridDim.x) {
     RowTile t = {};
     int frontier = -1;
+    int64_t place = b;
     if (find_row_tile<BM, 1>(p, static_cast<int>(b), s_tiles, t)) {
       const int cap = min(p.kv_len[t.s], p.max_blocks * CS_KV_BLOCK) - 1;
       frontier = min(p.q_pos[t.q0 + (min(t.r_tile + BM, t.rows_total) - 1) / p.group], cap);
+      if (ranked) {
+        // how many of the others go first: those of more key tiles, or of as many and ahead of it
+        const int x = static_cast<int>(b / p.n_kv_heads);
+        int ahead = 0;
+        for (int o = lane; o < n_found; o += 64) {
+          int s = 0;                     // the last stream that begins at or before o
+#pragma unroll
+          for (int step = 32; step > 0; step >>= 1) s += s + step < p.n_streams && s_list[s + step].first <= o ? step : 0;
+          const Listed l = s_list[s];
+          const int r_tile = (l.first + (l.rows + BM - 1) / BM - 1 - o) * BM;
+          const int its = min(p.q_pos[l.q0 + (min(r_tile + BM, l.rows) - 1) / p.group], l.cap);
+          const int longer = max(its, -1) / kBN - max(frontier, -1) / kBN;
+          ahead += longer > 0 || (longer == 0 && o < x) ? 1 : 0;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) ahead += __shfl_xor(ahead, off);
+        place = static_cast<int64_t>(ahead) * p.n_kv_heads + t.kvh;
+      }
     }
     if (threadIdx.x == 0) {
-      int32_t* d = p.ws_tiles + b * 8;
+      int32_t* d = p.ws_tiles + place * 8;
       d[0] = t.q0; d[1] = t.rows_total; d[2] = t.r_tile; d[3] = t.kvh; d[4] = frontier; d[5] = t.s;
     }
     __syncthreads();

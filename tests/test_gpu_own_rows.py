@@ -30,6 +30,17 @@ CASES = [
     (16, 4, 64, [900 + 11 * i for i in range(12)], [370 + i for i in range(12)], "runs"),
     (16, 4, 64, [300 + 11 * i for i in range(40)], [250 + i % 7 for i in range(40)], "runs"),      # many
     (8, 1, 64, [70] * 130, [3] * 130, "any"),
+    # row tiles by length: 300 (by stream), 301, the most streams of a list by length with some that have no rows, one more
+    (8, 1, 64, [400] * 15, [320] * 15, "runs"),
+    (8, 1, 64, [400] * 15, [321] + [320] * 14, "runs"),
+    (16, 4, 64, [100 + 7 * i for i in range(64)], [33 if i % 9 else 0 for i in range(64)], "any"),
+    (16, 4, 64, [100 + 7 * i for i in range(65)], [33 if i % 9 else 0 for i in range(65)], "any"),
+    # workgroups that bring keys into L2: three kv heads, two, more streams than such workgroups, windows that end in the first trip
+    (12, 3, 128, [1100, 290, 333], [400, 133, 50], "any"),
+    (16, 2, 128, [1030], [500], "runs"),
+    (8, 1, 128, [900, 640, 500, 820, 930, 257], [200] * 6, "runs"),
+    (28, 4, 128, [256], [256], "any"),
+    (4, 1, 64, [129, 500], [100, 41], "any"),
 ]
 
 
