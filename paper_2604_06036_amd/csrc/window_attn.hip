@@ -3506,15 +3506,17 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       }
     } else {
       // Two key groups while the launch is so small that its longest sweep is what it takes (all of its row tiles
-      // are resident together, 1,024 of them with one group).  One group / two, us a layer in a step: 4 streams,
-      // 28/4 heads 25.3 / 23.1; 12 streams, 16/4 heads 30.5 / 26.9; 32 streams 57.3 / 58.4 (the merge is extra work).
+      // are resident together, 1,024 of them with one group).  One group / two, us a step of 16 layers (own rows): bound of 364 row tiles
+      // 426 / 336, 752 509 / 453, 992 571 / 578 (of 1,000 with 55 key tiles 1,519 / 1,434), 1,200 640 / 662, 1,408 750 / 776, 3,552 1,638 /
+      // 1,793.  One group with two stages, not one: the same order 1,200 730 / 640, 1,408 781 / 750, 1,856 1,005 / 953, 3,552 1,669 /
+      // 1,638 (one stage / two; without own rows 740 / 720, 831 / 831, 1,064 / 1,067, 1,787 / 1,744).
       const int64_t tiles = ((n_q * group) / kBM + n_streams) * n_kv_heads;
       if (own) {
         const int e = own_rows(kBM);
         if (e != CS_OK) return e;
       }
       if (tiles <= 1024) return launch_tiles<64, 4, 2, 2>(p, st);
-      return launch_tiles<64, 4, 1, 1>(p, st);
+      return launch_tiles<64, 4, 1, 2>(p, st);
     }
   } else {
     const int64_t tiles = ((n_q * group) / kF32Rows + n_streams) * n_kv_heads;       // upper bound on row tiles
