@@ -469,7 +469,9 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  * of k_new / v_new is query token t's, and slot[t] the slot that block_table gives position q_pos[t] of its stream; positions
  * increase strictly inside a stream; rows from cu_q[n_streams] on have a negative slot.  The workspace then takes
  * cs_refresh_prefill_attn_workspace() bytes, and a REUSE call follows a BUILD or ONLY call with the flag and the same cu_q,
- * q_pos, kv_len, block_table and shape arguments.  Same results, bit for bit.  What it allows (CS_BF16, caches with
+ * q_pos, kv_len, block_table and shape arguments.  Same caches and results, bit for bit, except that a REUSE call of up to 64
+ * streams with n_kv_heads * (n_q * n_q_heads / n_kv_heads / 128 + n_streams) from 441 to 850 may take another kernel than without
+ * the flag, whose results differ by rounding.  What the flag allows (CS_BF16, caches with
  * stride_head == head_dim and stride_slot == n_kv_heads * head_dim, shapes that run without a plan): a REUSE call is one launch
  * that reads the new keys and values where the caller has them and writes them to the cache beside its own work, so that
  * nothing waits for the write.  Other calls with the flag write first and attend then, as two launches.

@@ -3223,11 +3223,19 @@ struct TileChoice {
   int pieces;          // kSplit64Keys4: of a sweep
 };
 
-TileChoice tile_route_128(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int64_t row_tiles, int key_tiles) {
+// REUSE calls that read their own rows (`own`), of up to 64 streams: no refresh write goes ahead of the tile kernel, and its row
+// tiles are listed by length, so it stays the faster one further up.  us a step of 16 layers, plan and refresh write / kRows128 /
+// kRows64Keys2, 28/4 heads unless noted:
+//   kRows64Keys2 up to 590     T 520 634 / 608 / 603, 16/4 T 544 714 / 688 / 677, 8/1 T 496 - / 649 / 592, T 572 of 1,800 keys - / 999 / 891, 32/8
+//                              T 472 - / 594 / 536, but T 608 - / 648 / 721, T 636 701 / 683 / 733
+//   kRows128 up to 850         T 752 726 / 706, T 812 761 / 737, 16/4 T 784 774 / 738, 8/1 T 712 733 / 709, T 876 of 600 keys 598 / 591, but T 928
+//                              776 / 802, 8/1 T 878 846 / 849, 32/8 T 952 866 / 923
+TileChoice tile_route_128(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int64_t row_tiles, int key_tiles, bool own) {
+  const bool listed = own && n_streams <= 64;
   const int64_t rows = (n_q + n_streams - 1) / n_streams * group;                  // of a stream and kv head, if all are alike
   // 64-row tiles: as many as alike streams have, at most n_q * group / 64 + n_streams a kv head; the mean of the two
   const int64_t tiles64 = (((rows + 63) / 64 * n_streams + n_q * group / 64 + n_streams) * n_kv_heads + 1) / 2;
-  if (whole_sweeps(row_tiles, key_tiles, n_kv_heads))
+  if (whole_sweeps(row_tiles, key_tiles, n_kv_heads) && !(listed && row_tiles <= 850))
     return {n_q * group <= static_cast<int64_t>(kBM) * n_streams ? TileRoute::kRows128 : TileRoute::kNone, 1};
   const int64_t trips = (key_tiles + 3) / 4;
   const int pieces = static_cast<int>(256 / tiles64 < trips ? 256 / tiles64 : trips);
@@ -3240,7 +3248,8 @@ TileChoice tile_route_128(int64_t n_q, int32_t n_streams, int32_t group, int32_t
     if (2 * key_tiles > row_tiles && key_tiles > 20 + 3 * full_tiles / 8) return {TileRoute::kNone, 1};
     return {key_tiles > 8 ? TileRoute::kRows64Keys4 : TileRoute::kRows64Keys2, 1};
   }
-  if (row_tiles <= 440) return {key_tiles <= 48 ? TileRoute::kRows64Keys2 : TileRoute::kNone, 1};
+  if (row_tiles <= (listed ? 590 : 440) && key_tiles <= 48) return {TileRoute::kRows64Keys2, 1};
+  if (row_tiles <= 440) return {TileRoute::kNone, 1};
   return {TileRoute::kRows128, 1};
 }
 
@@ -3411,7 +3420,10 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       if (plan_mode != CS_ATTN_PLAN_BUILD && plan_mode != CS_ATTN_PLAN_REUSE && plan_mode != CS_ATTN_PLAN_ONLY)
         return CS_EINVAL;
       const AttnPlan a = plan_attn(n_q, n_streams, group, n_kv_heads, max_blocks);
-      const TileChoice choice = tile_route_128(n_q, n_streams, group, n_kv_heads, a.rt_cap, a.max_tiles);
+      // (a call that plans attends, and plans, as without own rows: any REUSE call may follow it)
+      const TileRoute own_route = own ? tile_route_128(n_q, n_streams, group, n_kv_heads, a.rt_cap, a.max_tiles, true).route : TileRoute::kNone;
+      const bool reads_own = own_route != TileRoute::kNone && plan_mode == CS_ATTN_PLAN_REUSE;
+      const TileChoice choice = tile_route_128(n_q, n_streams, group, n_kv_heads, a.rt_cap, a.max_tiles, reads_own);
       const TileRoute route = choice.route;
       if (a.items_cap * a.bm >= (1ll << 31)) return CS_EUNSUPPORTED;
       if (stride_slot >= (1ll << 26) || a.max_tiles >= (1 << 15)) return CS_EUNSUPPORTED;      // 32-bit byte offsets inside a cache block
@@ -3429,8 +3441,8 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       // barrier takes 4-9 us more than that launch (10 streams of 420 tokens, 610 keys, us a layer of a graph 47.9 / 42.0).
       const bool few = a.rt_cap < 1024;
       const bool one_launch = fuse && !own && route == TileRoute::kNone && (a.span || !few) && !a.solo;
-      if (own && route != TileRoute::kNone) {
-        const int e = own_rows(route == TileRoute::kRows128 ? 128 : 64);
+      if (own_route != TileRoute::kNone) {
+        const int e = own_rows(own_route == TileRoute::kRows128 ? 128 : 64);
         if (e != CS_OK) return e;
       } else if (fuse && !one_launch && plan_mode != CS_ATTN_PLAN_ONLY) {
         const int e = cs_kv_refresh_scatter(k_new, v_new, new_slot, const_cast<void*>(k_cache_layer),

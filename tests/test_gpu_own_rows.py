@@ -1,5 +1,5 @@
 """cs_refresh_prefill_attn with CS_ATTN_OWN_ROWS against the refresh write followed by attention: caches and results bit
-for bit, on every route such a call can take.  The slots of the new rows hold no number before the call, so a key read
+for bit, on every route such a call can take (results where it takes another kernel than the separate call: against the oracle).  The slots of the new rows hold no number before the call, so a key read
 from the cache in place of the caller's rows shows."""
 import math
 
@@ -30,6 +30,13 @@ CASES = [
     (16, 4, 64, [900 + 11 * i for i in range(12)], [370 + i for i in range(12)], "runs"),
     (16, 4, 64, [300 + 11 * i for i in range(40)], [250 + i % 7 for i in range(40)], "runs"),      # many
     (8, 1, 64, [70] * 130, [3] * 130, "any"),
+    # other lines with own rows: 64-row tiles up to 590 row tiles of 128, those up to 850, plan from there
+    (28, 4, 128, [900 + 7 * i for i in range(5)], [421 + i for i in range(5)], "runs"),
+    (16, 4, 128, [1000 + 7 * i for i in range(9)], [440] * 8 + [436], "runs"),
+    (16, 4, 128, [1000 + 7 * i for i in range(9)], [440] * 8 + [437 + 19], "any"),
+    (28, 4, 128, [1100 - 50 * i for i in range(7)], [421 + i for i in range(7)], "any"),
+    (8, 1, 128, [700 + i for i in range(33)], [395] * 33, "runs"),
+    (8, 1, 128, [700 + i for i in range(33)], [397] * 33, "runs"),
     # row tiles by length: 300 (by stream), 301, the most streams of a list by length with some that have no rows, one more
     (8, 1, 64, [400] * 15, [320] * 15, "runs"),
     (8, 1, 64, [400] * 15, [321] + [320] * 14, "runs"),
@@ -110,9 +117,10 @@ def test_own_rows_equal_refresh_write_then_attention(cs, case):
         torch.cuda.synchronize()
         raw = torch.int16
         assert torch.equal(k1.view(raw), k2.view(raw)) and torch.equal(v1.view(raw), v2.view(raw)), f"cache, pass {rep}"
-        assert torch.equal(out1.view(raw), out2.view(raw)), f"results, pass {rep}"
+        other_kernel = mode == reuse and d == 128 and n_streams <= 64 and 440 < hkv * (n_all * hq // hkv // 128 + n_streams) <= 850
+        assert other_kernel or torch.equal(out1.view(raw), out2.view(raw)), f"results, pass {rep}"
         assert torch.all(out1[n_q:].float() == 7.0)
-        if rep == 1:
+        if rep == 1 or other_kernel:
             ref = oc.window_attn(hp.f64(data[2][:n_q]), hp.f64(k2), hp.f64(v2), cu, q_pos, bt, hq, scale)
             say(f"  {hp.check_attention(out1[:n_q].cpu(), ref, 'bf16')}")
 
