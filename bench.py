@@ -441,7 +441,7 @@ def kernel_rooflines(w, work, t_a, t_plan, t_b, t_c, t_d, traffic_for):
                     traffic=None if t is None else t["read_bytes"] + t["write_bytes"])
     out = {
         "cs_score_compact": hbm("cs_score_compact", "score_compact_kernel (+ clear_words_kernel)", t_a, work["a_bytes"], 1),
-        "cs_plan_refresh": dict(kernel="plan_frames_kernel + plan_streams_kernel + plan_fill_kernel", bound="latency",
+        "cs_plan_refresh": dict(kernel="plan_one_launch_kernel (large batches: plan_frames_kernel + plan_streams_kernel + plan_fill_kernel)", bound="latency",
                                 ms=t_plan, launches_per_step=1),
         "cs_kv_rerotate": hbm("cs_kv_rerotate", "rerotate_kernel", t_b, work["b_bytes"], 1),
         "cs_kv_refresh_scatter": hbm("cs_kv_refresh_scatter", "scatter_kernel", t_c, work["c_bytes"], L),

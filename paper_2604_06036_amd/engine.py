@@ -172,17 +172,19 @@ class DeviceStep:
     (tests and comparison runs)."""
 
     def __init__(self, data: StepData, reuse_cap: Optional[int] = None, q_cap: Optional[int] = None,
-                 host_plan: bool = False, fused: Optional[bool] = None, overlap: Optional[bool] = None,
-                 layers_per_rerotate: int = 4):
+                 host_plan: bool = False, fused: bool = False, overlap: Optional[bool] = None,
+                 layers_per_rerotate: int = 4, own_rows: bool = True):
         import torch
         from . import binding as cs
         self.cs = cs
         self.data = data
         self.host_plan = host_plan
-        # refresh write and attention of a layer: one call (cs_refresh_prefill_attn; None: of the executed tokens' own
-        # rows, which a step's are; True: of any rows) or, False, two
+        # refresh write and attention of a layer are one call (cs_refresh_prefill_attn), told that the new rows are the
+        # executed tokens' own, as a step's are; fused: one call that takes any rows, one launch where it can be;
+        # own_rows=False: two calls
         self.fused = fused
-        self.own_rows = fused is None
+        self.own_rows = own_rows and not fused
+        self.two_calls = not own_rows and not fused
         # overlap: the position correction runs on a second stream, a few layers per call, while the
         # layer loop proceeds; a layer's attention waits for the call that covers its layer
         # (decided below, once the capacities are known; None = by the size of the correction's traffic)
@@ -326,11 +328,11 @@ class DeviceStep:
                                        self.cs.CS_ATTN_PLAN_REUSE if reuse_plan else self.cs.CS_ATTN_PLAN_BUILD)
 
     def refresh_and_attention(self, layer: int, reuse_plan: bool = False):
-        """Refresh write + attention of one layer as one call."""
+        """Refresh write + attention of one layer as one call (of any rows: it may follow any call that plans)."""
         self._refresh_and_attention(self.k_new[layer], self.v_new[layer], self.k_pool[layer], self.v_pool[layer],
-                                    self.q[layer], self.out[layer], reuse_plan)
+                                    self.q[layer], self.out[layer], reuse_plan, False)
 
-    def _refresh_and_attention(self, k_new, v_new, k, v, q, out, reuse_plan):
+    def _refresh_and_attention(self, k_new, v_new, k, v, q, out, reuse_plan, own_rows):
         w = self.data.workload
         mode = self.cs.CS_ATTN_PLAN_REUSE if reuse_plan else self.cs.CS_ATTN_PLAN_BUILD
         self.cs.cs_refresh_prefill_attn(k_new, v_new, self.q_slot, self.n_q, q, k, v, self.cu_q,
@@ -339,7 +341,7 @@ class DeviceStep:
                                         w.n_q_heads, w.n_kv_heads, w.head_dim, self.stride_slot,
                                         self.stride_head, self.data.softmax_scale, self.dtype,
                                         self.ws_d if self.ws_d_bytes else None, self.ws_d_bytes,
-                                        mode | self.cs.CS_ATTN_OWN_ROWS if self.own_rows else mode)
+                                        mode | self.cs.CS_ATTN_OWN_ROWS if own_rows else mode)
 
     def attention_status(self) -> int:
         """Barrier status word of the fused launches (synchronises): 0 unless a launch's grid could not
@@ -384,14 +386,14 @@ class DeviceStep:
         for layer in range(n_layers):
             k_new, v_new, k, v, q, out = (t[layer] for t in views)
             # the refresh write touches other rows than the correction, attention reads both
-            if self.fused is False:
+            if self.two_calls:
                 self._refresh_scatter(k_new, v_new, k, v)
             if layer in ready:
                 torch.cuda.current_stream().wait_event(ready[layer])
-            if self.fused is False:
+            if self.two_calls:
                 self._attention(q, k, v, out, layer > 0)
             else:
-                self._refresh_and_attention(k_new, v_new, k, v, q, out, layer > 0)
+                self._refresh_and_attention(k_new, v_new, k, v, q, out, layer > 0, self.own_rows)
         if ready:
             torch.cuda.current_stream().wait_stream(self.side)
 

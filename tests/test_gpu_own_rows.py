@@ -159,7 +159,7 @@ def test_own_rows_step_under_capture(cs):
     say(f"own rows: captured step, {w.name} streams={w.n_streams} layers={w.n_layers}")
     data = engine.assemble_step(w, engine.hip_scorer, device="cpu")
     caps = dict(reuse_cap=data.info["n_reuse"] + 64, q_cap=data.info["n_q"] + 64)
-    two, one = engine.DeviceStep(data, fused=False, **caps), engine.DeviceStep(data, **caps)
+    two, one = engine.DeviceStep(data, own_rows=False, **caps), engine.DeviceStep(data, **caps)
     two.run()
     k0, v0 = data.k_pool.to(DEV), data.v_pool.to(DEV)
     side = torch.cuda.Stream()
@@ -178,3 +178,30 @@ def test_own_rows_step_under_capture(cs):
         torch.cuda.synchronize()
         for name in ("k_pool", "v_pool", "out"):
             assert torch.equal(getattr(two, name).view(torch.int16), getattr(one, name).view(torch.int16)), (rep, name)
+
+
+def test_public_calls_of_a_step_follow_any_call_that_plans(cs):
+    """`refresh_and_attention` and `attention` of a step that runs own-row calls itself: behind a plan without own rows, and
+    behind `run`, the same results as the step's."""
+    from paper_2604_06036_amd import engine, synth
+    for n_streams in (1, 7):
+        w = synth.small_variant(synth.CFG2, n_streams=n_streams, n_layers=3)
+        say(f"own rows: public calls, {w.name} streams={w.n_streams}")
+        data = engine.assemble_step(w, engine.hip_scorer, device="cpu")
+        caps = dict(reuse_cap=data.info["n_reuse"] + 64, q_cap=data.info["n_q"] + 64)
+        two, one = engine.DeviceStep(data, own_rows=False, **caps), engine.DeviceStep(data, **caps)
+        two.run()
+        one.ws_d.fill_(0xA5)
+        one.prepare()
+        one.rerotate()
+        for layer in range(w.n_layers):
+            one.refresh_and_attention(layer, reuse_plan=layer > 0)
+        torch.cuda.synchronize()
+        assert torch.equal(two.out.view(torch.int16), one.out.view(torch.int16))
+        one.run()
+        one.out.zero_()
+        for layer in range(w.n_layers):
+            one.attention(layer, reuse_plan=True)
+            two.attention(layer, reuse_plan=True)
+        torch.cuda.synchronize()
+        assert torch.equal(two.out.view(torch.int16), one.out.view(torch.int16))
