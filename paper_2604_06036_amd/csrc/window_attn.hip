@@ -974,8 +974,9 @@ __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) 
     }
     uint32_t mask = 0;
     if (there && lo + l16 < q1) {
+      // (a row without a slot, its position pulled back to the last that the stream's table covers, is not that entry's)
       const int at = p.q_pos[lo + l16] - first;
-      mask = at < CS_KV_BLOCK ? 1u << at : 0u;
+      mask = at < CS_KV_BLOCK && (!p.new_slot || p.new_slot[lo + l16] >= 0) ? 1u << at : 0u;
     }
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) mask |= __shfl_xor(mask, off);

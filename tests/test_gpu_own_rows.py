@@ -152,6 +152,44 @@ def test_own_rows_of_a_cache_in_another_layout(cs):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
+@pytest.mark.parametrize("hq, hkv, d, n_streams", [(28, 4, 128, 1), (16, 4, 64, 1), (28, 4, 128, 5)])
+def test_own_rows_past_a_block_table_row(cs, hq, hkv, d, n_streams):
+    """Rows that the block-table row has no slot for (slot -1, position pulled back to the row's last, as cs_plan_refresh leaves
+    them) do not stand in for that position's key: it is a reused row's, in the cache, or an earlier row's."""
+    room, n_own = 640, 300
+    say(f"own rows: rows past the block table, heads={hq}/{hkv} d={d} streams={n_streams}")
+    rng = np.random.default_rng(8302)
+    bt = rng.permutation(40 * n_streams).astype(np.int32).reshape(n_streams, 40)
+    pos, slot = [], []
+    for s in range(n_streams):
+        p = np.sort(rng.choice(room - 1, size=n_own, replace=False))
+        if s % 2:
+            p[-1] = room - 1                                     # executed itself
+        n_past = 21 + s
+        pos += [p, np.full(n_past, room - 1)]
+        slot += [bt[s, p // 16].astype(np.int64) * 16 + p % 16, np.full(n_past, -1)]
+    cu = np.concatenate([[0], np.cumsum([a.size for a in pos])[1::2]]).astype(np.int32)
+    n_q = int(cu[-1])
+    dev = lambda a: torch.from_numpy(a).to(DEV)
+    slot = dev(np.concatenate(slot).astype(np.int32))
+    meta = (dev(cu), dev(np.concatenate(pos).astype(np.int32)), torch.full((n_streams,), room + 21, dtype=torch.int32, device=DEV), dev(bt))
+    size = cs.cs_refresh_prefill_attn_workspace(n_q, n_streams, hq, hkv, d, 40, cs.CS_BF16)
+    kn, vn, q = (_pool(rng, (n_q, h, d), "bf16").to(DEV) for h in (hkv, hkv, hq))
+    pools = [_pool(rng, (640 * n_streams, hkv, d), "bf16").to(DEV) for _ in range(2)]
+    results = []
+    for flag in (0, cs.CS_ATTN_OWN_ROWS):
+        ws = torch.zeros(size, dtype=torch.uint8, device=DEV)
+        for mode in (cs.CS_ATTN_PLAN_BUILD, cs.CS_ATTN_PLAN_REUSE):
+            k, v = (t.clone() for t in pools)
+            out = torch.zeros((n_q, hq, d), dtype=torch.bfloat16, device=DEV)
+            cs.cs_refresh_prefill_attn(kn, vn, slot, n_q, q, k, v, *meta, 40, 16, out, n_q, n_streams, hq, hkv, d, k.stride(0), k.stride(1),
+                                       1.0 / math.sqrt(d), cs.CS_BF16, ws, size, mode | flag)
+        results.append((k, v, out))
+    torch.cuda.synchronize()
+    for a, b in zip(*results):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
 def test_own_rows_step_under_capture(cs):
     """A step of own-row calls replayed from a HIP graph equals the step of separate calls, every time."""
     from paper_2604_06036_amd import engine, synth
