@@ -3332,7 +3332,11 @@ extern "C" size_t cs_window_prefill_attn_workspace(int64_t n_q, int32_t n_stream
 namespace {
 
 // What calls with CS_ATTN_OWN_ROWS keep behind the workspace of the others: the table of own rows, then the row tiles of a
-// launch without a plan (of 64 rows or more), then a pair of words a stream.
+// launch without a plan (of 64 rows or more), then a pair of words a stream.  Where the others need no workspace (head_dim 64),
+// a header goes ahead of it that holds the status word.
+constexpr size_t kOwnHeaderBytes = 256;
+static_assert(kHdrStatus * sizeof(int32_t) == CS_ATTN_STATUS_OFFSET && CS_ATTN_STATUS_OFFSET < kOwnHeaderBytes, "the status word is in the header");
+size_t own_offset(size_t attn_bytes) { return attn_bytes ? attn_bytes : kOwnHeaderBytes; }
 size_t own_table_bytes(int32_t n_streams, int32_t max_blocks) {
   return (static_cast<size_t>(n_streams) * max_blocks * sizeof(cs::u32x2) + 255) & ~static_cast<size_t>(255);
 }
@@ -3552,6 +3556,8 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       if (own) {
         const int e = own_rows(kBM);
         if (e != CS_OK) return e;
+        p.ws_status = static_cast<int32_t*>(workspace) + kHdrStatus;
+        p.clear_status = plan_mode == CS_ATTN_PLAN_REUSE ? 0 : 1;
       }
       if (tiles <= 1024) return launch_tiles<64, 4, 2, 2>(p, st);
       return launch_tiles<64, 4, 1, 2>(p, st);
@@ -3588,7 +3594,7 @@ extern "C" size_t cs_refresh_prefill_attn_workspace(int64_t n_q, int32_t n_strea
                                                     int32_t dtype) {
   const size_t attn = cs_window_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype);
   if (dtype != CS_BF16 || n_q <= 0 || n_streams <= 0 || max_blocks <= 0 || n_kv_heads < 1 || n_q_heads < n_kv_heads) return attn;
-  return attn + own_bytes(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, max_blocks);
+  return own_offset(attn) + own_bytes(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, max_blocks);
 }
 
 extern "C" int cs_refresh_prefill_attn(const void* k_new, const void* v_new, const int32_t* slot, int64_t n_tok,
@@ -3614,7 +3620,7 @@ extern "C" int cs_refresh_prefill_attn(const void* k_new, const void* v_new, con
                                       block_size, out, n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot,
                                       stride_head, softmax_scale, dtype, plan_mode);
     if (checked < 0) return checked;
-    const size_t at = cs_window_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype);
+    const size_t at = own_offset(cs_window_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype));
     if (!workspace || !cs::aligned16(workspace) ||
         workspace_bytes < at + own_bytes(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, max_blocks))
       return CS_EWORKSPACE;

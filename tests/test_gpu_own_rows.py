@@ -243,3 +243,17 @@ def test_public_calls_of_a_step_follow_any_call_that_plans(cs):
             two.attention(layer, reuse_plan=True)
         torch.cuda.synchronize()
         assert torch.equal(two.out.view(torch.int16), one.out.view(torch.int16))
+
+
+@pytest.mark.parametrize("hq, hkv, d, n_streams", [(28, 4, 128, 1), (16, 4, 64, 1), (16, 4, 64, 12), (28, 4, 128, 7)])
+def test_own_rows_step_reports_no_failed_barrier(cs, hq, hkv, d, n_streams):
+    """The status word of a default step's workspace is 0 behind a good step, whatever the workspace held: for head_dim 64 too."""
+    from dataclasses import replace
+    from paper_2604_06036_amd import engine, synth
+    w = replace(synth.small_variant(synth.CFG2, n_streams=n_streams, n_layers=2), n_q_heads=hq, n_kv_heads=hkv, head_dim=d)
+    say(f"own rows: status word, heads={hq}/{hkv} d={d} streams={n_streams}")
+    step = engine.DeviceStep(engine.assemble_step(w, engine.hip_scorer, device="cpu"))
+    step.ws_d.fill_(0xA5)
+    for _ in range(2):
+        step.run()
+        assert step.attention_status() == 0
