@@ -469,8 +469,8 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  * of k_new / v_new is query token t's, and slot[t] the slot that block_table gives position q_pos[t] of its stream; positions
  * increase strictly inside a stream, apart from rows of a negative slot that repeat its last position (cs_plan_refresh has them
  * where a block-table row is too short; a CS_ATTN_PLAN_ONLY call takes slot to tell them); rows from cu_q[n_streams] on have a
- * negative slot; no stream's window holds another stream's new rows (it would read them from the cache while they are
- * written).  The workspace then takes
+ * negative slot; no stream's window holds another stream's new rows, or one of its own at a second position (it would read
+ * them from the cache while they are written).  The workspace then takes
  * cs_refresh_prefill_attn_workspace() bytes (and has the status word for either head_dim: 0 after a call that plans and has no barrier), and a REUSE call follows a BUILD or ONLY call with the flag and the same cu_q,
  * q_pos, kv_len, block_table and shape arguments.  Same caches and results, bit for bit, except that a REUSE call of up to 64
  * streams with n_kv_heads * (n_q * n_q_heads / n_kv_heads / 128 + n_streams) from 441 to 850 may take another kernel than without

@@ -169,7 +169,12 @@ class DeviceStep:
     They are sized to capacities the caller budgets (`reuse_cap`, `q_cap`; default: the step's own
     row counts); the consumers are launched over the capacities and skip the padding.
     `host_plan=True` uploads the NumPy planner's lists instead and `run` skips the planning call
-    (tests and comparison runs)."""
+    (tests and comparison runs).
+
+    `run` tells the layers' calls that the new rows are the executed tokens' own (CS_ATTN_OWN_ROWS) where `own_rows` allows it and no
+    cache block of the new windows stands in two places: a window that holds another stream's new rows, or a row of its own at two
+    positions, would read them while they are written.  Such a step, and one whose `block_table` is overwritten later with tables that
+    share blocks (build it with `own_rows=False`), writes a layer's rows first and attends then."""
 
     def __init__(self, data: StepData, reuse_cap: Optional[int] = None, q_cap: Optional[int] = None,
                  host_plan: bool = False, fused: bool = False, overlap: Optional[bool] = None,
@@ -181,10 +186,10 @@ class DeviceStep:
         self.host_plan = host_plan
         # refresh write and attention of a layer are one call (cs_refresh_prefill_attn), told that the new rows are the
         # executed tokens' own, as a step's are; fused: one call that takes any rows, one launch where it can be;
-        # own_rows=False: two calls
+        # otherwise two calls
         self.fused = fused
-        self.own_rows = own_rows and not fused
-        self.two_calls = not own_rows and not fused
+        self.own_rows = own_rows and not fused and planner.blocks_apart(data.new_layout.block_table, data.new_layout.seq_len)
+        self.two_calls = not self.own_rows and not fused
         # overlap: the position correction runs on a second stream, a few layers per call, while the
         # layer loop proceeds; a layer's attention waits for the call that covers its layer
         # (decided below, once the capacities are known; None = by the size of the correction's traffic)
@@ -483,9 +488,9 @@ def assemble_frontend_step(w: synth.Workload, scorer: Scorer, device="cpu", tau_
 class FrontEndStep:
     """The whole chain on the GPU, queued without a host round trip: block projection and residual
     proxy (decoder output -> per-patch metadata), scoring + compaction, refresh plan, position
-    correction of the reused rows, then per layer refresh write and attention."""
+    correction of the reused rows, then per layer refresh write and attention (`own_rows`: as in DeviceStep)."""
 
-    def __init__(self, data: FrontEndData):
+    def __init__(self, data: FrontEndData, own_rows: bool = True):
         import torch
         from . import binding as cs
         self.cs, self.data = cs, data
@@ -526,8 +531,10 @@ class FrontEndStep:
         self.stride_layer, self.stride_slot, self.stride_head = (self.k_pool.stride(i) for i in range(3))
         self.q, self.k_new, self.v_new = data.q.to(dev), data.k_new.to(dev), data.v_new.to(dev)
         self.out = torch.zeros_like(self.q)
-        self.ws_d_bytes = cs.cs_refresh_prefill_attn_workspace(self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads,
-                                                               w.head_dim, self.max_blocks, self.dtype)
+        longest = old.counts[:, w.stride:].sum(axis=1) + w.stride * t_per + w.n_text
+        self.own_rows = own_rows and planner.blocks_apart(data.bt_new, longest)
+        workspace = cs.cs_refresh_prefill_attn_workspace if self.own_rows else cs.cs_window_prefill_attn_workspace
+        self.ws_d_bytes = workspace(self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, self.max_blocks, self.dtype)
         self.ws_d = torch.zeros((max(8, self.ws_d_bytes),), dtype=torch.uint8, device=dev)
 
     def front_end(self):
@@ -558,11 +565,16 @@ class FrontEndStep:
                               w.rope_base, cs.CS_ROPE_HALF_SPLIT, self.dtype)
         for layer in range(w.n_layers):
             mode = cs.CS_ATTN_PLAN_REUSE if layer > 0 else cs.CS_ATTN_PLAN_BUILD
-            cs.cs_refresh_prefill_attn(self.k_new[layer], self.v_new[layer], self.q_slot, self.q_cap, self.q[layer], self.k_pool[layer],
-                                       self.v_pool[layer], self.cu_q, self.q_pos, self.kv_len, self.bt_new, self.max_blocks,
-                                       cs.CS_KV_BLOCK, self.out[layer], self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads,
-                                       w.head_dim, self.stride_slot, self.stride_head, self.data.softmax_scale, self.dtype,
-                                       self.ws_d if self.ws_d_bytes else None, self.ws_d_bytes, mode | cs.CS_ATTN_OWN_ROWS)
+            k_new, v_new, k, v = self.k_new[layer], self.v_new[layer], self.k_pool[layer], self.v_pool[layer]
+            attention = (self.q[layer], k, v, self.cu_q, self.q_pos, self.kv_len, self.bt_new, self.max_blocks, cs.CS_KV_BLOCK,
+                         self.out[layer], self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, self.stride_slot,
+                         self.stride_head, self.data.softmax_scale, self.dtype, self.ws_d if self.ws_d_bytes else None, self.ws_d_bytes)
+            if self.own_rows:
+                cs.cs_refresh_prefill_attn(k_new, v_new, self.q_slot, self.q_cap, *attention, mode | cs.CS_ATTN_OWN_ROWS)
+            else:
+                cs.cs_kv_refresh_scatter(k_new, v_new, self.q_slot, k, v, self.q_cap, w.n_kv_heads, w.head_dim, self.stride_slot,
+                                         self.stride_head, self.dtype)
+                cs.cs_window_prefill_attn(*attention, mode)
 
     def run(self):
         self.front_end()

@@ -58,6 +58,13 @@ def blocks_needed(seq_len) -> np.ndarray:
     return (np.asarray(seq_len, dtype=np.int64) + KV_BLOCK - 1) // KV_BLOCK
 
 
+def blocks_apart(block_table: np.ndarray, seq_len) -> bool:
+    """Whether no cache block stands in two places of the windows that a batch's block tables describe."""
+    nb = np.minimum(blocks_needed(seq_len), block_table.shape[1])
+    used = block_table[np.arange(block_table.shape[1]) < nb[:, None]]
+    return np.unique(used).size == used.size
+
+
 def _slots(block_row: np.ndarray, seq_idx: np.ndarray) -> np.ndarray:
     return block_row[seq_idx // KV_BLOCK].astype(np.int64) * KV_BLOCK + seq_idx % KV_BLOCK
 

@@ -257,3 +257,46 @@ def test_own_rows_step_reports_no_failed_barrier(cs, hq, hkv, d, n_streams):
     for _ in range(2):
         step.run()
         assert step.attention_status() == 0
+
+
+def test_windows_that_share_a_cache_block(cs):
+    """A window that holds another stream's new rows, under both step classes: they are written before anything attends."""
+    from paper_2604_06036_amd import engine, synth
+    w = synth.small_variant(synth.CFG2, n_streams=2, n_layers=4)
+    say(f"own rows: shared cache block, {w.name} streams={w.n_streams} layers={w.n_layers}")
+    data = engine.assemble_step(w, engine.hip_scorer, device="cpu")
+    plan, table = data.plan, data.new_layout.block_table
+    def whole_blocks(s, executed):
+        rows = np.zeros(table.shape[1] * 16, bool)
+        rows[plan.q_pos[plan.cu_q[s]: plan.cu_q[s + 1]]] = True
+        rows = rows[: plan.kv_len[s] // 16 * 16].reshape(-1, 16)
+        return np.flatnonzero((rows if executed else ~rows).all(axis=1))
+    assert engine.DeviceStep(data).own_rows
+    table[1, whole_blocks(1, False)[1]] = table[0, whole_blocks(0, True)[1]]
+    data._plan = None
+    two, step = engine.DeviceStep(data, own_rows=False), engine.DeviceStep(data)
+    assert not step.own_rows
+    for one in (two, step):
+        one.run()
+    torch.cuda.synchronize()
+    for name in ("k_pool", "v_pool", "out"):
+        assert torch.equal(getattr(two, name).view(torch.int16), getattr(step, name).view(torch.int16)), name
+
+    front = engine.assemble_frontend_step(w, engine.hip_scorer, device="cpu")
+    assert engine.FrontEndStep(front).own_rows
+    front.bt_new[1, 3] = front.bt_new[0, 4]
+    assert not engine.FrontEndStep(front).own_rows
+
+
+def test_front_end_step_of_two_calls_a_layer(cs):
+    """A front-end step without own rows against the default one (of few row tiles: the same kernels, so bit for bit)."""
+    from paper_2604_06036_amd import engine, synth
+    w = synth.small_variant(synth.CFG2, n_streams=1, n_layers=3)
+    say(f"own rows: front-end step of two calls a layer, {w.name} streams={w.n_streams} layers={w.n_layers}")
+    data = engine.assemble_frontend_step(w, engine.hip_scorer, device="cpu")
+    steps = [engine.FrontEndStep(data, own_rows=own) for own in (False, True)]
+    for one in steps:
+        one.run()
+    torch.cuda.synchronize()
+    for name in ("k_pool", "v_pool", "out"):
+        assert torch.equal(*(getattr(one, name).view(torch.int16) for one in steps)), name

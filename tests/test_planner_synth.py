@@ -324,3 +324,13 @@ def test_plan_batch_is_plan_stream_per_stream():
         assert got["cu_q"][s] == at_q and got["cu_q"][s + 1] == at_q + n_q and got["kv_len"][s] == one["kv_len"]
         at_r, at_q = at_r + n_r, at_q + n_q
     assert len(got["src_slot"]) == at_r and len(got["q_pos"]) == at_q
+
+
+def test_blocks_apart():
+    """Blocks count up to a window's end, inside one window as between two; what a row holds past its window does not."""
+    table = np.array([[4, 1, 7, 0], [2, 3, 0, 0]], np.int32)
+    assert planner.blocks_apart(table, [33, 32])                 # 4 1 7 and 2 3
+    assert not planner.blocks_apart(table, [49, 33])             # the 0 of both
+    assert not planner.blocks_apart(table, [33, 64])             # 0 twice in one window
+    assert planner.blocks_apart(table, [100, 17]) and planner.blocks_apart(table, [0, 0])      # (a window past its row)
+    assert planner.blocks_apart(table[:0], np.zeros(0, np.int32))
