@@ -475,7 +475,9 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  * q_pos, kv_len, block_table and shape arguments.  Same caches and results, bit for bit, except that a REUSE call of up to 64
  * streams with n_kv_heads * (n_q * n_q_heads / n_kv_heads / 128 + n_streams) from 441 to 850 may take another kernel than without
  * the flag, whose results differ by rounding.  What the flag allows (CS_BF16, caches with
- * stride_head == head_dim and stride_slot == n_kv_heads * head_dim, shapes that run without a plan): a REUSE call is one launch
+ * stride_head == head_dim and stride_slot == n_kv_heads * head_dim, shapes that run without a plan, but not long sweeps over many row
+ * tiles; the lines are measured and may move: cs_refresh_prefill_attn_workspace() is larger than cs_window_prefill_attn_workspace()
+ * for the shapes meant): a REUSE call is one launch
  * that reads the new keys and values where the caller has them and writes them to the cache beside its own work, so that
  * nothing waits for the write.  Other calls with the flag write first and attend then, as two launches.
  *

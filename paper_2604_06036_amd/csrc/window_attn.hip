@@ -3337,6 +3337,26 @@ namespace {
 constexpr size_t kOwnHeaderBytes = 256;
 static_assert(kHdrStatus * sizeof(int32_t) == CS_ATTN_STATUS_OFFSET && CS_ATTN_STATUS_OFFSET < kOwnHeaderBytes, "the status word is in the header");
 size_t own_offset(size_t attn_bytes) { return attn_bytes ? attn_bytes : kOwnHeaderBytes; }
+
+// REUSE calls with the flag read their own rows in shapes that run without a plan, as long as T row tiles of 128 times K key
+// tiles are no more than this: the row tiles then hide a launch of 2-4 us and the refresh write, but ask for the place of every
+// cache block's rows, about 2 % of a sweep.  us a layer of REUSE calls, own rows / refresh write and attention:
+//   head_dim 128, streams of one row tile  T 1,968 with K 16 132.6 / 134.8, T 968 with 63 184 / 191, T 7,708 with 9 290 / 298 (69,000), but T
+//                 1,968 with 63 438 / 432 (124,000), with 125 837 / 825
+//   head_dim 64   64 streams of 8/1 heads T 5,244 with 47 210 / 220, 9,655 with 47 532 / 564 (454,000), T 7,168 of 16/4 with 24 253 / 264, 5,048 of 4/4
+//                 with 47 313 / 359, but 19,247 with 94 2,095 / 1,826, 19,436 of 16/4 with 47 1,142 / 1,058, 21,232 of 32/8 with 32 897 / 866 (680,000),
+//                 one stream, 1,579 with 470 719 / 690
+constexpr int64_t kOwnWork128 = 100000, kOwnWork64 = 1 << 19;
+
+// Rows of the row tiles that such calls list; 0: a call with the flag attends as one without.
+int own_row_tile(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int32_t head_dim, int32_t max_blocks) {
+  const int64_t row_tiles = (n_q * group / kBM + n_streams) * n_kv_heads;
+  const int64_t key_tiles = (static_cast<int64_t>(max_blocks) * CS_KV_BLOCK + kBN - 1) / kBN;
+  if (row_tiles * key_tiles > (head_dim == 128 ? kOwnWork128 : kOwnWork64)) return 0;
+  if (head_dim == 64) return kBM;
+  const TileRoute route = tile_route_128(n_q, n_streams, group, n_kv_heads, row_tiles, static_cast<int>(key_tiles), true).route;
+  return route == TileRoute::kNone ? 0 : route == TileRoute::kRows128 ? 128 : 64;
+}
 size_t own_table_bytes(int32_t n_streams, int32_t max_blocks) {
   return (static_cast<size_t>(n_streams) * max_blocks * sizeof(cs::u32x2) + 255) & ~static_cast<size_t>(255);
 }
@@ -3389,7 +3409,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
               int32_t n_kv_heads, int32_t head_dim, int64_t stride_slot,
               int64_t stride_head, float softmax_scale, int32_t dtype,
               void* workspace, size_t workspace_bytes, int32_t plan_mode,
-              const void* k_new, const void* v_new, const int32_t* new_slot, int64_t n_new, cs::u32x2* own,
+              const void* k_new, const void* v_new, const int32_t* new_slot, int64_t n_new, bool own,
               void* stream) {
   const int checked = attn_validate(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks,
                                     block_size, out, n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot,
@@ -3432,15 +3452,17 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
   p.ws_status = nullptr;
   p.clear_status = 0;
   hipStream_t st = cs::as_stream(stream);
-  // before a call with own rows, of row tiles of bm rows
-  auto own_rows = [&](int bm) -> int {
-    p.ws_own = own;
-    char* tiles = reinterpret_cast<char*>(own) + own_table_bytes(n_streams, max_blocks);
+  // before a call with own rows
+  const int own_bm = own ? own_row_tile(n_q, n_streams, group, n_kv_heads, head_dim, max_blocks) : 0;
+  auto own_rows = [&](size_t attn_bytes) -> int {
+    char* table = static_cast<char*>(workspace) + own_offset(attn_bytes);
+    char* tiles = table + own_table_bytes(n_streams, max_blocks);
+    p.ws_own = reinterpret_cast<cs::u32x2*>(table);
     p.ws_tiles = reinterpret_cast<int32_t*>(tiles);
     p.ws_warm = reinterpret_cast<cs::u32x2*>(tiles + own_tiles_bytes(n_q, n_streams, group, n_kv_heads));
     if (plan_mode == CS_ATTN_PLAN_REUSE) return CS_OK;
     if (plan_mode == CS_ATTN_PLAN_ONLY && head_dim == 128) p.n_new = 0;
-    const int e = launch_own_rows(p, bm, st);
+    const int e = launch_own_rows(p, own_bm, st);
     p.ws_own = nullptr;                  // (its own attention reads the cache)
     return e;
   };
@@ -3451,8 +3473,7 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
         return CS_EINVAL;
       const AttnPlan a = plan_attn(n_q, n_streams, group, n_kv_heads, max_blocks);
       // (a call that plans attends, and plans, as without own rows: any REUSE call may follow it)
-      const TileRoute own_route = own ? tile_route_128(n_q, n_streams, group, n_kv_heads, a.rt_cap, a.max_tiles, true).route : TileRoute::kNone;
-      const bool reads_own = own_route != TileRoute::kNone && plan_mode == CS_ATTN_PLAN_REUSE;
+      const bool reads_own = own_bm && plan_mode == CS_ATTN_PLAN_REUSE;
       const TileChoice choice = tile_route_128(n_q, n_streams, group, n_kv_heads, a.rt_cap, a.max_tiles, reads_own);
       const TileRoute route = choice.route;
       if (a.items_cap * a.bm >= (1ll << 31)) return CS_EUNSUPPORTED;
@@ -3471,8 +3492,8 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       // barrier takes 4-9 us more than that launch (10 streams of 420 tokens, 610 keys, us a layer of a graph 47.9 / 42.0).
       const bool few = a.rt_cap < 1024;
       const bool one_launch = fuse && !own && route == TileRoute::kNone && (a.span || !few) && !a.solo;
-      if (own_route != TileRoute::kNone) {
-        const int e = own_rows(own_route == TileRoute::kRows128 ? 128 : 64);
+      if (own_bm) {
+        const int e = own_rows(a.total);
         if (e != CS_OK) return e;
       } else if (fuse && !one_launch && plan_mode != CS_ATTN_PLAN_ONLY) {
         const int e = cs_kv_refresh_scatter(k_new, v_new, new_slot, const_cast<void*>(k_cache_layer),
@@ -3553,8 +3574,8 @@ int attn_call(const void* q, const void* k_cache_layer, const void* v_cache_laye
       // 1,793.  One group with two stages, not one: the same order 1,200 730 / 640, 1,408 781 / 750, 1,856 1,005 / 953, 3,552 1,669 /
       // 1,638 (one stage / two; without own rows 740 / 720, 831 / 831, 1,064 / 1,067, 1,787 / 1,744).
       const int64_t tiles = ((n_q * group) / kBM + n_streams) * n_kv_heads;
-      if (own) {
-        const int e = own_rows(kBM);
+      if (own_bm) {
+        const int e = own_rows(0);
         if (e != CS_OK) return e;
         p.ws_status = static_cast<int32_t*>(workspace) + kHdrStatus;
         p.clear_status = plan_mode == CS_ATTN_PLAN_REUSE ? 0 : 1;
@@ -3586,14 +3607,17 @@ extern "C" int cs_window_prefill_attn(const void* q, const void* k_cache_layer, 
                                       void* stream) {
   return attn_call(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks, block_size, out,
                    n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot, stride_head, softmax_scale, dtype,
-                   workspace, workspace_bytes, plan_mode, nullptr, nullptr, nullptr, 0, nullptr, stream);
+                   workspace, workspace_bytes, plan_mode, nullptr, nullptr, nullptr, 0, false, stream);
 }
 
 extern "C" size_t cs_refresh_prefill_attn_workspace(int64_t n_q, int32_t n_streams, int32_t n_q_heads,
                                                     int32_t n_kv_heads, int32_t head_dim, int32_t max_blocks,
                                                     int32_t dtype) {
   const size_t attn = cs_window_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype);
-  if (dtype != CS_BF16 || n_q <= 0 || n_streams <= 0 || max_blocks <= 0 || n_kv_heads < 1 || n_q_heads < n_kv_heads) return attn;
+  if (dtype != CS_BF16 || (head_dim != 64 && head_dim != 128) || n_q <= 0 || n_streams <= 0 || max_blocks <= 0 || n_kv_heads < 1 ||
+      n_q_heads < n_kv_heads || n_q_heads % n_kv_heads || n_q * n_q_heads >= (1ll << 31))
+    return attn;
+  if (!own_row_tile(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, head_dim, max_blocks)) return attn;
   return own_offset(attn) + own_bytes(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, max_blocks);
 }
 
@@ -3620,17 +3644,18 @@ extern "C" int cs_refresh_prefill_attn(const void* k_new, const void* v_new, con
                                       block_size, out, n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot,
                                       stride_head, softmax_scale, dtype, plan_mode);
     if (checked < 0) return checked;
-    const size_t at = own_offset(cs_window_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype));
+    own = head_dim == 128 || own_row_tile(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, head_dim, max_blocks);
+  }
+  if (own) {
     if (!workspace || !cs::aligned16(workspace) ||
-        workspace_bytes < at + own_bytes(n_q, n_streams, n_q_heads / n_kv_heads, n_kv_heads, max_blocks))
+        workspace_bytes < cs_refresh_prefill_attn_workspace(n_q, n_streams, n_q_heads, n_kv_heads, head_dim, max_blocks, dtype))
       return CS_EWORKSPACE;
-    cs::u32x2* table = reinterpret_cast<cs::u32x2*>(static_cast<char*>(workspace) + at);
     const bool only = plan_mode == CS_ATTN_PLAN_ONLY && head_dim == 128;
     if (!only && (!k_new || !v_new || !slot)) return CS_EINVAL;
     if (!cs::aligned16(k_new) || !cs::aligned16(v_new)) return CS_EUNSUPPORTED;
     return attn_call(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks, block_size, out, n_q,
                      n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot, stride_head, softmax_scale, dtype, workspace,
-                     workspace_bytes, plan_mode, k_new, v_new, slot, n_tok, table, stream);
+                     workspace_bytes, plan_mode, k_new, v_new, slot, n_tok, true, stream);
   }
   const bool one_launch = dtype == CS_BF16 && head_dim == 128;
   const bool plan_only = plan_mode == CS_ATTN_PLAN_ONLY && one_launch;
@@ -3651,9 +3676,9 @@ extern "C" int cs_refresh_prefill_attn(const void* k_new, const void* v_new, con
     }
     return attn_call(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks, block_size, out,
                      n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot, stride_head, softmax_scale, dtype,
-                     workspace, workspace_bytes, plan_mode, nullptr, nullptr, nullptr, 0, nullptr, stream);
+                     workspace, workspace_bytes, plan_mode, nullptr, nullptr, nullptr, 0, false, stream);
   }
   return attn_call(q, k_cache_layer, v_cache_layer, cu_q, q_pos, kv_len, block_table, max_blocks, block_size, out,
                    n_q, n_streams, n_q_heads, n_kv_heads, head_dim, stride_slot, stride_head, softmax_scale, dtype,
-                   workspace, workspace_bytes, plan_mode, k_new, v_new, slot, n_tok, nullptr, stream);
+                   workspace, workspace_bytes, plan_mode, k_new, v_new, slot, n_tok, false, stream);
 }

@@ -222,6 +222,13 @@ def test_host_side_argument_errors(lib):
     assert fused(d=64, ss=128, sh=64, mode=own) == binding.CS_EWORKSPACE
     assert fused(nq=0, nt=0, mode=own) == binding.CS_OK
 
+    # own rows cost workspace only where a launch reads them: not with a plan, nor on long sweeps over many row tiles
+    extra = lambda *shape: L.cs_refresh_prefill_attn_workspace(*shape, 1) - L.cs_window_prefill_attn_workspace(*shape, 1)
+    assert extra(400, 1, 28, 4, 128, 64) > 0 and extra(13000, 32, 28, 4, 128, 70) == 0
+    assert extra(1200, 1100, 1, 1, 128, 360) > 0 and extra(1200, 1100, 1, 1, 128, 361) == 0
+    assert extra(153600, 64, 8, 1, 64, 215) > 0 and extra(153600, 64, 8, 1, 64, 217) == 0
+    assert extra(400, 1, 28, 4, 96, 64) == 0 and extra(400, 1, 27, 4, 128, 64) == 0
+
     # the scoring call that allocates nothing serves up to 4,096 streams
     assert L.cs_score_compact_noalloc(one, z, z, one, one, z, 4097, 1, 16, 16, 1, 0, 0, 0, one, one, one, z) == binding.CS_EUNSUPPORTED
 

@@ -48,6 +48,11 @@ CASES = [
     (8, 1, 128, [900, 640, 500, 820, 930, 257], [200] * 6, "runs"),
     (28, 4, 128, [256], [256], "any"),
     (4, 1, 64, [129, 500], [100, 41], "any"),
+    # long sweeps over many row tiles (by the longest window): as without the flag; just below the line
+    (1, 1, 128, [6033] + [20 + i % 40 for i in range(1099)], [7] + [1 + i % 2 for i in range(1099)], "any"),
+    (1, 1, 128, [5600] + [20 + i % 40 for i in range(1099)], [7] + [1 + i % 2 for i in range(1099)], "any"),
+    (1, 1, 64, [16800] + [20 + i % 40 for i in range(1999)], [7] + [1] * 1999, "any"),
+    (1, 1, 64, [16300] + [20 + i % 40 for i in range(1999)], [7] + [1] * 1999, "any"),
 ]
 
 
