@@ -3252,12 +3252,16 @@ struct TileChoice {
 };
 
 // REUSE calls that read their own rows (`own`), of up to 64 streams: no refresh write goes ahead of the tile kernel, and its row
-// tiles are listed by length, so it stays the faster one further up.  us a step of 16 layers, plan and refresh write / kRows128 /
-// kRows64Keys2, 28/4 heads unless noted:
-//   kRows64Keys2 up to 590     T 520 634 / 608 / 603, 16/4 T 544 714 / 688 / 677, 8/1 T 496 - / 649 / 592, T 572 of 1,800 keys - / 999 / 891, 32/8
-//                              T 472 - / 594 / 536, but T 608 - / 648 / 721, T 636 701 / 683 / 733
-//   kRows128 up to 850         T 752 726 / 706, T 812 761 / 737, 16/4 T 784 774 / 738, 8/1 T 712 733 / 709, T 876 of 600 keys 598 / 591, but T 928
-//                              776 / 802, 8/1 T 878 846 / 849, 32/8 T 952 866 / 923
+// tiles are listed by length, so it stays the faster one further up.  us a layer, REUSE calls of two launches / kRows128 /
+// kRows64Keys2, with budgets 2 and 35 % above the rows (the row tiles that are there decide which of the two is the faster, the host
+// knows the budget):
+//   kRows64Keys2 up to 510     K 23 to 41, T 440 to 504: tight budgets 0.80 to 0.95 of two launches / 0.83 to 0.98, loose ones 0.81 to 0.95 / 0.71 to
+//   row tiles T, 20 key tiles  0.92 (16/4 heads T 448 49.0 / 42.6 / 34.8, one stream of 32/8 T 496 63.2 / 64.5 / 55.0); but K 7 to 15 tight 0.78 to 0.93 / 0.93
+//   K and more                 to 1.08, loose 0.76 to 0.90 / 0.84 to 0.95, and T 512 to 590 tight 0.77 to 1.03 / 0.94 to 1.23 (8/1 heads T 588, K 15
+//                              36.6 / 34.8 / 47.9), loose 0.78 to 0.99 / 0.81 to 1.09
+//   kRows128 up to 850         K 7 and 8 0.74 to 0.99; K 15 T 590 to 850 tight 0.73 to 1.03, loose 0.78 to 1.01; K 24 tight 0.88 to 1.06 (16/2 heads T 750 56.0
+//                              / 59.3), loose 0.79 to 1.02; K 37 to 41 tight 0.79 to 1.03, loose 0.79 to 0.97; but 28/4 T 928 of 900 keys 776 / 802 a step
+//                              of 16 layers, 8/1 T 878 846 / 849, 32/8 T 952 866 / 923
 TileChoice tile_route_128(int64_t n_q, int32_t n_streams, int32_t group, int32_t n_kv_heads, int64_t row_tiles, int key_tiles, bool own) {
   const bool listed = own && n_streams <= 64;
   const int64_t rows = (n_q + n_streams - 1) / n_streams * group;                  // of a stream and kv head, if all are alike
@@ -3276,7 +3280,7 @@ TileChoice tile_route_128(int64_t n_q, int32_t n_streams, int32_t group, int32_t
     if (2 * key_tiles > row_tiles && key_tiles > 20 + 3 * full_tiles / 8) return {TileRoute::kNone, 1};
     return {key_tiles > 8 ? TileRoute::kRows64Keys4 : TileRoute::kRows64Keys2, 1};
   }
-  if (row_tiles <= (listed ? 590 : 440) && key_tiles <= 48) return {TileRoute::kRows64Keys2, 1};
+  if (row_tiles <= (listed && key_tiles >= 20 ? 510 : 440) && key_tiles <= 48) return {TileRoute::kRows64Keys2, 1};
   if (row_tiles <= 440) return {TileRoute::kNone, 1};
   return {TileRoute::kRows128, 1};
 }

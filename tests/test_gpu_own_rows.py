@@ -30,7 +30,10 @@ CASES = [
     (16, 4, 64, [900 + 11 * i for i in range(12)], [370 + i for i in range(12)], "runs"),
     (16, 4, 64, [300 + 11 * i for i in range(40)], [250 + i % 7 for i in range(40)], "runs"),      # many
     (8, 1, 64, [70] * 130, [3] * 130, "any"),
-    # other lines with own rows: 64-row tiles up to 590 row tiles of 128, those up to 850, plan from there
+    # other lines with own rows: 64-row tiles of longer sweeps up to 510 row tiles of 128, those up to 850, plan from there
+    (28, 4, 128, [1500 + 7 * i for i in range(5)], [421 + i for i in range(5)], "runs"),
+    (28, 4, 128, [1220 - 9 * i for i in range(5)], [420 - i for i in range(5)], "any"),
+    (28, 4, 128, [1190 - 9 * i for i in range(5)], [420 - i for i in range(5)], "any"),
     (28, 4, 128, [900 + 7 * i for i in range(5)], [421 + i for i in range(5)], "runs"),
     (16, 4, 128, [1000 + 7 * i for i in range(9)], [440] * 8 + [436], "runs"),
     (16, 4, 128, [1000 + 7 * i for i in range(9)], [440] * 8 + [437 + 19], "any"),
@@ -122,7 +125,9 @@ def test_own_rows_equal_refresh_write_then_attention(cs, case):
         torch.cuda.synchronize()
         raw = torch.int16
         assert torch.equal(k1.view(raw), k2.view(raw)) and torch.equal(v1.view(raw), v2.view(raw)), f"cache, pass {rep}"
-        other_kernel = mode == reuse and d == 128 and n_streams <= 64 and 440 < hkv * (n_all * hq // hkv // 128 + n_streams) <= 850
+        row_tiles, key_tiles = hkv * (n_all * hq // hkv // 128 + n_streams), -(-max_blocks // 4)
+        other_kernel = mode == reuse and d == 128 and n_streams <= 64 and (
+            (440 < row_tiles <= 510 and 20 <= key_tiles <= 48) or ((768 if hkv > 4 else 512) <= row_tiles <= 850 and 8 < key_tiles <= 32))
         assert other_kernel or torch.equal(out1.view(raw), out2.view(raw)), f"results, pass {rep}"
         assert torch.all(out1[n_q:].float() == 7.0)
         if rep == 1 or other_kernel:
