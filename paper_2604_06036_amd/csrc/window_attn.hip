@@ -175,6 +175,7 @@ __device__ __forceinline__ int32_t sload1(const void* ptr) {
 }
 
 typedef __attribute__((ext_vector_type(2))) int32_t i32x2;
+typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
 __device__ __forceinline__ i32x2 sload2(const void* ptr) {
   i32x2 v;
   asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=&s"(v) : "s"(ptr));
@@ -920,13 +921,15 @@ __global__ __launch_bounds__(64 * ROWW * KG, D == 128 ? 2 : 4) void window_attn_
 }
 
 // The parts of window_attn_own_rows_kernel, in workgroups.
+constexpr int kListedStreams = 64;       // up to here a workgroup lists 16 row tiles of all kv heads, beyond one of one kv head
 struct OwnParts {
-  int64_t moves, entries, streams, tiles;
+  int64_t moves, entries, streams, row_tiles, tiles;
   __host__ __device__ __forceinline__ OwnParts(const AttnParams& p, int bm) {
     moves = (p.n_new * p.row_vecs + 63) / 64;
     entries = (static_cast<int64_t>(p.n_streams) * p.max_blocks + 3) / 4;
     streams = (p.n_streams + 63) / 64;
-    tiles = (p.n_q * p.group / bm + p.n_streams) * p.n_kv_heads;
+    row_tiles = p.n_q * p.group / bm + p.n_streams;       // of a kv head
+    tiles = p.n_streams <= kListedStreams ? (row_tiles + 15) / 16 : row_tiles * p.n_kv_heads;
   }
 };
 
@@ -939,12 +942,18 @@ struct OwnParts {
 // head_dim 64, 16 layers: 319 row tiles (14 streams, 8/1 heads) 423 / 368, 411 455 / 402, 420 (9 streams, 16/4) 424 / 408, 736 680 / 578,
 // 1,491 (64 streams, 8/1) 1,058 / 908; head_dim 128: 368 of 64 rows 501 / 481, 500 525 / 481.  Fewer have a CU each, and are level
 // (144 319 / 317, 304 of 64 rows 397 / 398) or faster by stream (204 333 / 339, 271 336 / 359, 288 of 64 rows 404 / 416).
+// A tile's place is how many of the others go first: those of more key tiles, or of as many and ahead of it, which makes each
+// place one tile's whatever the positions are.  A workgroup has the numbers to compare in LDS, and each lane counts a quarter of them for one
+// of 16 tiles.  us that a call which plans takes more than refresh write and attention, a workgroup for each tile and kv head / this,
+// head_dim 64: 64 streams of 8/1 heads 1,792 row tiles 15 / 10.5, 3,260 46 / 24, 9,655 174 / 47, of 16/4 7,168 34 / 2, 16 of 8/1 353 3.0 / 2.0.
 constexpr int kRankedTiles = 300;
+constexpr int kRankKeys = 1024;          // numbers in LDS at once
 template <int BM>
 __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) {
   __shared__ int s_tiles[64];
   struct Listed { int first, q0, rows, cap; };
-  __shared__ Listed s_list[64];
+  __shared__ Listed s_list[kListedStreams];
+  __shared__ __attribute__((aligned(16))) uint32_t s_key[kRankKeys];
   const int lane = threadIdx.x, l16 = lane & 15, group16 = lane >> 4;
   // The parts are chains of dependent loads, so they go to workgroups of their own: the refresh write to the first, then four
   // entries of the table a workgroup, then the streams, then the row tiles (round again where the grid is smaller than that).
@@ -991,8 +1000,20 @@ __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) 
     p.ws_warm[s] = cs::u32x2{static_cast<uint32_t>(q0), static_cast<uint32_t>(seen)};
   }
   const int64_t first_tile = first_of(parts.moves + parts.entries + parts.streams);
-  int n_found = 0;                       // row tiles of all streams, a kv head
-  if (p.n_streams <= 64 && first_tile < parts.tiles) {
+  auto list = [&](int64_t place, int q0, int rows, int r_tile, int kvh, int frontier, int s) {
+    i32x4* d = reinterpret_cast<i32x4*>(p.ws_tiles + place * 8);
+    d[0] = i32x4{q0, rows, r_tile, kvh};
+    d[1] = i32x4{frontier, s, 0, 0};
+  };
+  if (p.n_streams > kListedStreams) {
+    for (int64_t b = first_tile; b < parts.tiles; b += gridDim.x) {
+      RowTile t = {};
+      int frontier = -1;
+      if (find_row_tile<BM, 1>(p, static_cast<int>(b), s_tiles, t)) frontier = tile_frontier<BM>(p, t);
+      if (lane == 0) list(b, t.q0, t.rows_total, t.r_tile, t.kvh, frontier, t.s);
+      __syncthreads();
+    }
+  } else if (first_tile < parts.tiles) {
     Listed mine = {};
     if (lane < p.n_streams) {
       mine.q0 = p.cu_q[lane];
@@ -1008,41 +1029,68 @@ __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) 
     }
     mine.first = incl - tiles;
     s_list[lane] = mine;
-    n_found = __shfl(incl, 63);
+    const int row_tiles = static_cast<int>(parts.row_tiles), n_found = min(__shfl(incl, 63), row_tiles);
+    const bool ranked = static_cast<int64_t>(n_found) * p.n_kv_heads > kRankedTiles;
     __syncthreads();
-  }
-  const bool ranked = static_cast<int64_t>(n_found) * p.n_kv_heads > kRankedTiles;
-  for (int64_t b = first_tile; b < parts.tiles; b += gridDim.x) {
-    RowTile t = {};
-    int frontier = -1;
-    int64_t place = b;
-    if (find_row_tile<BM, 1>(p, static_cast<int>(b), s_tiles, t)) {
-      const int cap = min(p.kv_len[t.s], p.max_blocks * CS_KV_BLOCK) - 1;
-      frontier = min(p.q_pos[t.q0 + (min(t.r_tile + BM, t.rows_total) - 1) / p.group], cap);
+    // the query of the last row of the tile that begins at r_tile
+    auto last_query = [&](int q0, int rows, int r_tile) { return q0 + (min(r_tile + BM, rows) - 1) / p.group; };
+    struct Found { int s, q0, rows, r_tile, frontier; };
+    auto find = [&](int x) {               // row tile x of all streams, the last of a stream's rows first
+      int s = 0;                           // the last stream that begins at or before x
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1) s += s + step < p.n_streams && s_list[s + step].first <= x ? step : 0;
+      const Listed l = s_list[s];
+      const int r_tile = (l.first + (l.rows + BM - 1) / BM - 1 - x) * BM;
+      return Found{s, l.q0, l.rows, r_tile, min(p.q_pos[last_query(l.q0, l.rows, r_tile)], l.cap)};
+    };
+    // to rank: tile j of stream i % lanes is number i of its round, j going up with i / lanes
+    const int lanes = p.n_streams > 1 ? 1 << (32 - __clz(p.n_streams - 1)) : 1, apart = 64 / lanes;
+    const Listed of = s_list[lane % lanes];
+    const int of_tiles = (of.rows + BM - 1) / BM;
+    int most = of_tiles;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off));
+    // (ranked: row tiles times key tiles are below 2^20, own_row_tile)
+    auto key_of = [](int x, int frontier) { return static_cast<uint32_t>(max(frontier, -1) / kBN) << 20 | (0xfffffu - x); };
+    for (int64_t b = first_tile; b < parts.tiles; b += gridDim.x) {
+      const int x = static_cast<int>(b) * 16 + l16;
+      Found t = {0, 0, 0, 0, -1};
+      if (x < n_found) t = find(x);
+      int place = x;
       if (ranked) {
-        // how many of the others go first: those of more key tiles, or of as many and ahead of it
-        const int x = static_cast<int>(b / p.n_kv_heads);
+        constexpr int AT_ONCE = 4;
+        const uint32_t key = key_of(x, t.frontier);
         int ahead = 0;
-        for (int o = lane; o < n_found; o += 64) {
-          int s = 0;                     // the last stream that begins at or before o
+        for (int j0 = 0; j0 < most; j0 += kRankKeys / lanes) {
+          const int n = min(kRankKeys, (most - j0) * lanes);
+          __syncthreads();
+          for (int i = lane; i < n + lane; i += 64 * AT_ONCE) {      // (all positions asked for before the first store)
+            int its[AT_ONCE];
 #pragma unroll
-          for (int step = 32; step > 0; step >>= 1) s += s + step < p.n_streams && s_list[s + step].first <= o ? step : 0;
-          const Listed l = s_list[s];
-          const int r_tile = (l.first + (l.rows + BM - 1) / BM - 1 - o) * BM;
-          const int its = min(p.q_pos[l.q0 + (min(r_tile + BM, l.rows) - 1) / p.group], l.cap);
-          const int longer = max(its, -1) / kBN - max(frontier, -1) / kBN;
-          ahead += longer > 0 || (longer == 0 && o < x) ? 1 : 0;
+            for (int u = 0; u < AT_ONCE; ++u) {
+              const int j = j0 + i / lanes + u * apart;
+              its[u] = p.q_pos[j < of_tiles ? last_query(of.q0, of.rows, (of_tiles - 1 - j) * BM) : 0];
+            }
+#pragma unroll
+            for (int u = 0; u < AT_ONCE; ++u) {
+              const int j = j0 + i / lanes + u * apart, o = of.first + j;
+              if (i + 64 * u < kRankKeys) s_key[i + 64 * u] = j < of_tiles && o < n_found ? key_of(o, min(its[u], of.cap)) : 0u;
+            }
+          }
+          __syncthreads();
+#pragma unroll 4
+          for (int i = 4 * group16; i < n; i += 16) {
+            const cs::u32x4 o = *reinterpret_cast<const cs::u32x4*>(s_key + i);
+            ahead += (o.x > key ? 1 : 0) + (o.y > key ? 1 : 0) + (o.z > key ? 1 : 0) + (o.w > key ? 1 : 0);
+          }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) ahead += __shfl_xor(ahead, off);
-        place = static_cast<int64_t>(ahead) * p.n_kv_heads + t.kvh;
+        ahead += __shfl_xor(ahead, 16);
+        ahead += __shfl_xor(ahead, 32);
+        if (x < n_found) place = ahead;
       }
+      for (int kvh = group16; kvh < p.n_kv_heads && x < row_tiles; kvh += 4)
+        list(static_cast<int64_t>(place) * p.n_kv_heads + kvh, t.q0, t.rows, t.r_tile, kvh, t.frontier, t.s);
     }
-    if (threadIdx.x == 0) {
-      int32_t* d = p.ws_tiles + place * 8;
-      d[0] = t.q0; d[1] = t.rows_total; d[2] = t.r_tile; d[3] = t.kvh; d[4] = frontier; d[5] = t.s;
-    }
-    __syncthreads();
   }
   wait_scalar();                         // (no scalar load is left in flight)
 }

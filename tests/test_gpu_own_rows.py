@@ -45,6 +45,11 @@ CASES = [
     (8, 1, 64, [400] * 15, [321] + [320] * 14, "runs"),
     (16, 4, 64, [100 + 7 * i for i in range(64)], [33 if i % 9 else 0 for i in range(64)], "any"),
     (16, 4, 64, [100 + 7 * i for i in range(65)], [33 if i % 9 else 0 for i in range(65)], "any"),
+    # ... one stream, two, streams whose tiles take several rounds of numbers to rank, of alike and of unlike streams
+    (16, 1, 64, [2600], [2500], "runs"),
+    (16, 1, 64, [1500, 1400], [1250, 1300], "any"),
+    (16, 1, 64, [2600] + [40 + i for i in range(39)], [2500] + [i for i in range(39)], "runs"),
+    (16, 2, 64, [340 + i for i in range(33)], [330 + i % 5 for i in range(33)], "runs"),
     # workgroups that bring keys into L2: three kv heads, two, more streams than such workgroups, windows that end in the first trip
     (12, 3, 128, [1100, 290, 333], [400, 133, 50], "any"),
     (16, 2, 128, [1030], [500], "runs"),
