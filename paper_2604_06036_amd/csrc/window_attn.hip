@@ -192,8 +192,8 @@ __device__ __forceinline__ T* uniform(T* ptr) {
 
 // Where a call that reads its queries' own rows (CS_ATTN_OWN_ROWS) finds those of a cache block, two words a block of every
 // stream: the block's id (27 bits), the index, among the stream's queries, of the first of its rows that the call brings (21
-// bits), and which of its 16 rows those are (16 bits; all of them where every row that the stream defines is one).  They are
-// consecutive among the call's rows, queries being in order.
+// bits), and which of its 16 rows those are (16 bits: all of them stand for 16 rows that there are, also in a stream's last block).  They
+// are consecutive among the call's rows, queries being in order.
 constexpr int kOwnIdBits = 27, kOwnRowBits = 21;      // (slots are 32-bit: ids below 2^27; windows of up to 2^21 entries)
 struct OwnEntry {
   uint32_t id, row, mask;
@@ -989,7 +989,6 @@ __global__ __launch_bounds__(64) void window_attn_own_rows_kernel(AttnParams p) 
     }
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) mask |= __shfl_xor(mask, off);
-    if (len < CS_KV_BLOCK && (~mask & ((1u << max(len, 0)) - 1)) == 0) mask = 0xffffu;
     if (there && l16 == 0) p.ws_own[i] = OwnEntry::packed(p.block_table[i], lo - q0, mask);
   }
   for (int64_t w = first_of(parts.moves + parts.entries); w < parts.streams; w += gridDim.x) {

@@ -315,3 +315,24 @@ def test_front_end_step_of_two_calls_a_layer(cs):
     torch.cuda.synchronize()
     for name in ("k_pool", "v_pool", "out"):
         assert torch.equal(*(getattr(one, name).view(torch.int16) for one in steps)), name
+
+
+@pytest.mark.parametrize("kv_len", [5, 16, 37, 48])
+def test_a_full_block_of_own_rows_has_16_rows(cs, kv_len):
+    """A window that is executed whole: the table's entry of its last, part-filled block names the rows that there are."""
+    hq, hkv, d = 4, 1, 64
+    say(f"own rows: last block of {kv_len} executed rows")
+    dev = lambda a: torch.tensor(a, dtype=torch.int32, device=DEV)
+    n_blocks = -(-kv_len // 16)
+    kn, vn, q = (torch.randn((kv_len, h, d), device=DEV).to(torch.bfloat16) for h in (hkv, hkv, hq))
+    k, v = (torch.zeros((n_blocks * 16, hkv, d), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    size = cs.cs_refresh_prefill_attn_workspace(kv_len, 1, hq, hkv, d, n_blocks, cs.CS_BF16)
+    ws = torch.zeros(size, dtype=torch.uint8, device=DEV)
+    rows = list(range(kv_len))
+    cs.cs_refresh_prefill_attn(kn, vn, dev(rows), kv_len, q, k, v, dev([0, kv_len]), dev(rows), dev([kv_len]), dev(list(range(n_blocks))),
+                               n_blocks, 16, torch.zeros_like(q), kv_len, 1, hq, hkv, d, hkv * d, d, 0.125, cs.CS_BF16, ws, size,
+                               cs.CS_ATTN_PLAN_BUILD | cs.CS_ATTN_OWN_ROWS)
+    torch.cuda.synchronize()
+    # (behind a header of 256 bytes two words a block, the rows in the low half of the second)
+    table = ws[256: 256 + 8 * n_blocks].cpu().numpy().view(np.uint32).reshape(-1, 2)
+    assert [bin(int(m) & 0xffff).count("1") for m in table[:, 1]] == [min(16, kv_len - 16 * b) for b in range(n_blocks)]
