@@ -161,6 +161,16 @@ def assemble_step(w: synth.Workload, scorer: Scorer, device="cpu", with_tensors:
 OVERLAP_MIN_BYTES = 1 << 30     # bytes the position correction moves per step from which it runs beside the layer loop
 
 
+def _own_rows(cs, w: synth.Workload, wanted: bool, q_cap: int, max_blocks: int, dtype: int, block_table, seq_len):
+    """Whether a step's layers are called with CS_ATTN_OWN_ROWS, and the bytes of their workspace.  Not where windows share a block,
+    nor for a single layer: the lists that the first call leaves for the next ones would only cost (us a step, with / without: one stream
+    42.4 / 41.6, 12 and 32 of head_dim 64 64.9 / 63.3 and 101.8 / 95.9; of two layers 61.9 / 64.2, 91.7 / 95.2, 157 / 162)."""
+    shape = (q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, max_blocks, dtype)
+    plain, own = cs.cs_window_prefill_attn_workspace(*shape), cs.cs_refresh_prefill_attn_workspace(*shape)
+    taken = wanted and (w.n_layers > 1 or own == plain) and planner.blocks_apart(block_table, seq_len)
+    return taken, own if taken else plain
+
+
 class DeviceStep:
     """A step resident on the GPU; each method enqueues exactly one C-ABI call.
 
@@ -184,12 +194,7 @@ class DeviceStep:
         self.cs = cs
         self.data = data
         self.host_plan = host_plan
-        # refresh write and attention of a layer are one call (cs_refresh_prefill_attn), told that the new rows are the
-        # executed tokens' own, as a step's are; fused: one call that takes any rows, one launch where it can be;
-        # otherwise two calls
         self.fused = fused
-        self.own_rows = own_rows and not fused and planner.blocks_apart(data.new_layout.block_table, data.new_layout.seq_len)
-        self.two_calls = not self.own_rows and not fused
         # overlap: the position correction runs on a second stream, a few layers per call, while the
         # layer loop proceeds; a layer's attention waits for the call that covers its layer
         # (decided below, once the capacities are known; None = by the size of the correction's traffic)
@@ -269,8 +274,12 @@ class DeviceStep:
         self.q, self.k_new, self.v_new = grow(data.q.to(dev)), grow(data.k_new.to(dev)), grow(data.v_new.to(dev))
         self.out = torch.zeros_like(self.q)
         self.n_q = self.q_cap
-        workspace = cs.cs_refresh_prefill_attn_workspace if self.own_rows else cs.cs_window_prefill_attn_workspace
-        self.ws_d_bytes = workspace(self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, self.max_blocks, self.dtype)
+        # refresh write and attention of a layer are one call (cs_refresh_prefill_attn), told that the new rows are the
+        # executed tokens' own, as a step's are; fused: one call that takes any rows, one launch where it can be;
+        # otherwise two calls
+        self.own_rows, self.ws_d_bytes = _own_rows(cs, w, own_rows and not fused, self.q_cap, self.max_blocks, self.dtype,
+                                                   new.block_table, new.seq_len)
+        self.two_calls = not self.own_rows and not fused
         self.ws_d = torch.zeros((max(8, self.ws_d_bytes),), dtype=torch.uint8, device=dev)
 
     def score_compact(self):
@@ -532,9 +541,7 @@ class FrontEndStep:
         self.q, self.k_new, self.v_new = data.q.to(dev), data.k_new.to(dev), data.v_new.to(dev)
         self.out = torch.zeros_like(self.q)
         longest = old.counts[:, w.stride:].sum(axis=1) + w.stride * t_per + w.n_text
-        self.own_rows = own_rows and planner.blocks_apart(data.bt_new, longest)
-        workspace = cs.cs_refresh_prefill_attn_workspace if self.own_rows else cs.cs_window_prefill_attn_workspace
-        self.ws_d_bytes = workspace(self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, self.max_blocks, self.dtype)
+        self.own_rows, self.ws_d_bytes = _own_rows(cs, w, own_rows, self.q_cap, self.max_blocks, self.dtype, data.bt_new, longest)
         self.ws_d = torch.zeros((max(8, self.ws_d_bytes),), dtype=torch.uint8, device=dev)
 
     def front_end(self):

@@ -336,3 +336,19 @@ def test_a_full_block_of_own_rows_has_16_rows(cs, kv_len):
     # (behind a header of 256 bytes two words a block, the rows in the low half of the second)
     table = ws[256: 256 + 8 * n_blocks].cpu().numpy().view(np.uint32).reshape(-1, 2)
     assert [bin(int(m) & 0xffff).count("1") for m in table[:, 1]] == [min(16, kv_len - 16 * b) for b in range(n_blocks)]
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_a_single_layer_makes_no_lists(cs, head_dim):
+    """A step of one layer has no call that reads own rows: it takes the two calls, with no workspace for lists."""
+    from dataclasses import replace
+    from paper_2604_06036_amd import engine, synth
+    for n_layers in (1, 2):
+        w = replace(synth.small_variant(synth.CFG2, n_streams=1, n_layers=n_layers), n_q_heads=16, n_kv_heads=4, head_dim=head_dim)
+        say(f"own rows: {n_layers} layers, d={head_dim}")
+        steps = (engine.DeviceStep(engine.assemble_step(w, engine.hip_scorer, device="cpu")),
+                 engine.FrontEndStep(engine.assemble_frontend_step(w, engine.hip_scorer, device="cpu")))
+        for step in steps:
+            shape = (step.q_cap, 1, 16, 4, head_dim, step.max_blocks, cs.CS_BF16)
+            assert step.own_rows == (n_layers > 1)
+            assert step.ws_d_bytes == (cs.cs_refresh_prefill_attn_workspace if step.own_rows else cs.cs_window_prefill_attn_workspace)(*shape)
