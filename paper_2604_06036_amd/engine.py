@@ -161,13 +161,15 @@ def assemble_step(w: synth.Workload, scorer: Scorer, device="cpu", with_tensors:
 OVERLAP_MIN_BYTES = 1 << 30     # bytes the position correction moves per step from which it runs beside the layer loop
 
 
-def _own_rows(cs, w: synth.Workload, wanted: bool, q_cap: int, max_blocks: int, dtype: int, block_table, seq_len):
+def _own_rows(cs, w: synth.Workload, wanted: bool, q_cap: int, max_blocks: int, dtype: int, block_table, seq_len, beside: bool = False):
     """Whether a step's layers are called with CS_ATTN_OWN_ROWS, and the bytes of their workspace.  Not where windows share a block,
     nor for a single layer: the lists that the first call leaves for the next ones would only cost (us a step, with / without: one stream
-    42.4 / 41.6, 12 and 32 of head_dim 64 64.9 / 63.3 and 101.8 / 95.9; of two layers 61.9 / 64.2, 91.7 / 95.2, 157 / 162)."""
+    42.4 / 41.6, 12 and 32 of head_dim 64 64.9 / 63.3 and 101.8 / 95.9; of two layers 61.9 / 64.2, 91.7 / 95.2, 157 / 162).  With the
+    position correction beside the layer loop (`beside`) a call waits for its layer's rows, and no launch reads own rows where the
+    workspace is not larger: two calls then, of which the refresh write waits for nothing."""
     shape = (q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, max_blocks, dtype)
     plain, own = cs.cs_window_prefill_attn_workspace(*shape), cs.cs_refresh_prefill_attn_workspace(*shape)
-    taken = wanted and (w.n_layers > 1 or own == plain) and planner.blocks_apart(block_table, seq_len)
+    taken = wanted and (w.n_layers > 1 if own > plain else not beside) and planner.blocks_apart(block_table, seq_len)
     return taken, own if taken else plain
 
 
@@ -278,7 +280,7 @@ class DeviceStep:
         # executed tokens' own, as a step's are; fused: one call that takes any rows, one launch where it can be;
         # otherwise two calls
         self.own_rows, self.ws_d_bytes = _own_rows(cs, w, own_rows and not fused, self.q_cap, self.max_blocks, self.dtype,
-                                                   new.block_table, new.seq_len)
+                                                   new.block_table, new.seq_len, beside=self.overlap and self.reuse_cap > 0)
         self.two_calls = not self.own_rows and not fused
         self.ws_d = torch.zeros((max(8, self.ws_d_bytes),), dtype=torch.uint8, device=dev)
 
@@ -399,7 +401,7 @@ class DeviceStep:
         views = [t.unbind(0) for t in (self.k_new, self.v_new, self.k_pool, self.v_pool, self.q, self.out)]
         for layer in range(n_layers):
             k_new, v_new, k, v, q, out = (t[layer] for t in views)
-            # the refresh write touches other rows than the correction, attention reads both
+            # the refresh write touches other rows than the correction, attention reads both: only the latter waits
             if self.two_calls:
                 self._refresh_scatter(k_new, v_new, k, v)
             if layer in ready:

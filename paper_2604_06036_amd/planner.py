@@ -61,8 +61,8 @@ def blocks_needed(seq_len) -> np.ndarray:
 def blocks_apart(block_table: np.ndarray, seq_len) -> bool:
     """Whether no cache block stands in two places of the windows that a batch's block tables describe."""
     nb = np.minimum(blocks_needed(seq_len), block_table.shape[1])
-    used = block_table[np.arange(block_table.shape[1]) < nb[:, None]]
-    return np.unique(used).size == used.size
+    used = np.sort(block_table[np.arange(block_table.shape[1]) < nb[:, None]])
+    return not np.any(used[1:] == used[:-1])
 
 
 def _slots(block_row: np.ndarray, seq_idx: np.ndarray) -> np.ndarray:

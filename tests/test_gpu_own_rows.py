@@ -352,3 +352,38 @@ def test_a_single_layer_makes_no_lists(cs, head_dim):
             shape = (step.q_cap, 1, 16, 4, head_dim, step.max_blocks, cs.CS_BF16)
             assert step.own_rows == (n_layers > 1)
             assert step.ws_d_bytes == (cs.cs_refresh_prefill_attn_workspace if step.own_rows else cs.cs_window_prefill_attn_workspace)(*shape)
+
+
+@pytest.mark.parametrize("n_streams", [1, 32])
+def test_refresh_write_does_not_wait_for_the_correction(cs, n_streams):
+    """With the correction beside the layer loop, a step whose launches do not read own rows queues a layer's refresh write ahead of the
+    wait for the layer's corrected rows; one whose launches do waits once a layer."""
+    from paper_2604_06036_amd import engine, synth
+    w = synth.small_variant(synth.CFG2, n_streams=n_streams, n_layers=3)
+    say(f"own rows: correction beside the layer loop, streams={n_streams}")
+    step = engine.DeviceStep(engine.assemble_step(w, engine.hip_scorer, device="cpu"), overlap=True, layers_per_rerotate=1)
+    assert step.own_rows == (n_streams == 1)
+    main, order = torch.cuda.current_stream(), []
+    calls = ("cs_kv_refresh_scatter", "cs_window_prefill_attn", "cs_refresh_prefill_attn")
+
+    class Recorded:
+        def __getattr__(self, name):
+            def call(*args):
+                order.append(name)
+                return getattr(cs, name)(*args)
+            return call if name in calls else getattr(cs, name)
+    step.cs = Recorded()
+    wait = torch.cuda.Stream.wait_event
+
+    def recorded_wait(stream, event):
+        if stream == main:
+            order.append("wait")
+        return wait(stream, event)
+    torch.cuda.Stream.wait_event = recorded_wait
+    try:
+        step.run()
+    finally:
+        torch.cuda.Stream.wait_event = wait
+    torch.cuda.synchronize()
+    layer = ["wait", calls[2]] if n_streams == 1 else [calls[0], "wait", calls[1]]
+    assert order[: 3 * len(layer)] == 3 * layer
