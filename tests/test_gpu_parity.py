@@ -965,18 +965,22 @@ def test_refresh_prefill_attn_equals_scatter_then_attention(cs, case):
 
 def test_fused_step_equals_the_step_of_separate_calls(cs):
     """The whole device-planned step with the refresh write inside the attention launch: cache and
-    outputs bit-equal to the step that queues the two calls, also when replayed from a HIP graph."""
+    outputs bit-equal to the step that queues the two calls, also when replayed from a HIP graph.  So is the default step, whose
+    calls bring the executed tokens' own rows."""
     w = synth.small_variant(synth.CFG2, n_streams=3, n_layers=3)
     say(f"fused step: {w.name} streams={w.n_streams} layers={w.n_layers}")
     data = engine.assemble_step(w, engine.hip_scorer, device="cpu")
     n_reuse, n_q = data.info["n_reuse"], data.info["n_q"]
-    plain = engine.DeviceStep(data, reuse_cap=n_reuse + 64, q_cap=n_q + 64)
+    plain = engine.DeviceStep(data, reuse_cap=n_reuse + 64, q_cap=n_q + 64, own_rows=False)
     fused = engine.DeviceStep(data, reuse_cap=n_reuse + 64, q_cap=n_q + 64, fused=True)
-    plain.run()
-    fused.run()
-    assert fused.attention_status() == 0
+    own = engine.DeviceStep(data, reuse_cap=n_reuse + 64, q_cap=n_q + 64)
+    assert plain.two_calls and fused.fused and own.own_rows
+    for step in (plain, fused, own):
+        step.run()
+    assert fused.attention_status() == 0 and own.attention_status() == 0
     for name in ("k_pool", "v_pool", "out"):
-        assert torch.equal(getattr(plain, name).view(torch.int16), getattr(fused, name).view(torch.int16)), name
+        for step in (fused, own):
+            assert torch.equal(getattr(plain, name).view(torch.int16), getattr(step, name).view(torch.int16)), name
     k0, v0 = data.k_pool.to(DEV), data.v_pool.to(DEV)
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
