@@ -4,7 +4,7 @@
 A "step" is one pass of the whole hot path over one batch of synthetic streams, with nothing
 passing through the host in between:
   cs_score_compact -> cs_plan_refresh -> cs_kv_rerotate (all layers) -> per layer:
-  cs_kv_refresh_scatter, cs_window_prefill_attn.
+  cs_kv_refresh_scatter, cs_window_prefill_attn, or cs_refresh_prefill_attn where a launch reads the executed tokens' own rows.
 Inputs are resident in HBM before the timed region starts.  The step is captured once in a HIP
 graph and the timed region replays it K times.
 
@@ -429,9 +429,11 @@ def cpu_baseline(w, data, step, k_rows_before, pick, torch):
                 all_threads=multi, single_thread=single, workload=w.name)
 
 
-def kernel_rooflines(w, work, t_a, t_plan, t_b, t_c, t_d, traffic_for):
+def kernel_rooflines(w, work, t_a, t_plan, t_b, t_c, t_d, traffic_for, t_own=None):
     """Per-kernel figures of one workload: algorithmic bytes or flops per launch over the event-timed
-    launch duration, against the published peak that bounds the kernel."""
+    launch duration, against the published peak that bounds the kernel.  With `t_own` a layer of the step is one
+    call that reads the executed tokens' own rows (`t_own` ms); the refresh write and attention as two calls, which the step
+    does not make, are then returned apart."""
     L = w.n_layers
     def hbm(name, kernel, ms, nbytes, launches):
         ach = nbytes / ms / 1e6
@@ -459,7 +461,16 @@ def kernel_rooflines(w, work, t_a, t_plan, t_b, t_c, t_d, traffic_for):
                                          achieved=ach, peak=PEAK_MFMA_BF16_TFLOPS, unit="TFLOP/s",
                                          frac=ach / PEAK_MFMA_BF16_TFLOPS, TFLOPs=ach,
                                          GBps=work["d_bytes"] / t_d / 1e6, traffic=traffic)
-    return out
+    if t_own is None:
+        return out, None
+    apart = {call: out.pop(call) for call in ("cs_kv_refresh_scatter", "cs_window_prefill_attn")}
+    ach, nbytes = work["d_flops"] / t_own / 1e9, work["c_bytes"] + work["d_bytes"]
+    out["cs_refresh_prefill_attn"] = dict(kernel="window_attn_bf16_tile_kernel with own rows (+ window_attn_own_rows_kernel and the kernel "
+                                          "without them in the first layer)", bound="mfma", ms=t_own, launches_per_step=L,
+                                          flops_per_launch=work["d_flops"], algorithmic_bytes=nbytes, achieved=ach,
+                                          peak=PEAK_MFMA_BF16_TFLOPS, unit="TFLOP/s", frac=ach / PEAK_MFMA_BF16_TFLOPS,
+                                          TFLOPs=ach, GBps=nbytes / t_own / 1e6, traffic=None)
+    return out, apart
 
 
 def measure_workload(w, args, torch, binding, engine, keep_for_cpu, probe_power=False):
@@ -530,7 +541,10 @@ def measure_workload(w, args, torch, binding, engine, keep_for_cpu, probe_power=
             traffic_commit = doc.get("_commit")
         except Exception:
             per_wl = {}
-    kernels = kernel_rooflines(w, work, t_a, t_plan, t_b, t_c, t_d, lambda name: per_wl.get(name))
+    t_own = None
+    if step.reads_own_rows:
+        t_own = event_time(torch, lambda: [step.refresh_and_attention(l, reuse_plan=l > 0, own_rows=True) for l in range(L)], reps) / L
+    kernels, apart = kernel_rooflines(w, work, t_a, t_plan, t_b, t_c, t_d, lambda name: per_wl.get(name), t_own)
     share = {k: v["ms"] * v["launches_per_step"] for k, v in kernels.items()}
     dominant = max(share, key=share.get)
     roofline = dict(kernels[dominant])
@@ -545,6 +559,8 @@ def measure_workload(w, args, torch, binding, engine, keep_for_cpu, probe_power=
                executed_tokens=info["n_q"], reused_rows=info["n_reuse"], window_tokens=info["kv_len_total"],
                reuse_cap=step.reuse_cap, q_cap=step.q_cap, kernels=kernels, roofline=roofline,
                kernel_ms_sum=sum(share.values()))
+    if apart:
+        res["calls_the_step_does_not_make"] = apart
     if sustained:
         res["sustained"] = sustained
     res["rerotate_schedule"] = (f"second stream beside the layer loop, {step.layers_per_rerotate} layers per call"

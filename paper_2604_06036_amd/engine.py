@@ -282,6 +282,9 @@ class DeviceStep:
         self.own_rows, self.ws_d_bytes = _own_rows(cs, w, own_rows and not fused, self.q_cap, self.max_blocks, self.dtype,
                                                    new.block_table, new.seq_len, beside=self.overlap and self.reuse_cap > 0)
         self.two_calls = not self.own_rows and not fused
+        # (whether launches read them)
+        self.reads_own_rows = self.own_rows and self.ws_d_bytes > cs.cs_window_prefill_attn_workspace(
+            self.q_cap, w.n_streams, w.n_q_heads, w.n_kv_heads, w.head_dim, self.max_blocks, self.dtype)
         self.ws_d = torch.zeros((max(8, self.ws_d_bytes),), dtype=torch.uint8, device=dev)
 
     def score_compact(self):
@@ -343,10 +346,11 @@ class DeviceStep:
                                        self.ws_d if self.ws_d_bytes else None, self.ws_d_bytes,
                                        self.cs.CS_ATTN_PLAN_REUSE if reuse_plan else self.cs.CS_ATTN_PLAN_BUILD)
 
-    def refresh_and_attention(self, layer: int, reuse_plan: bool = False):
-        """Refresh write + attention of one layer as one call (of any rows: it may follow any call that plans)."""
+    def refresh_and_attention(self, layer: int, reuse_plan: bool = False, own_rows: bool = False):
+        """Refresh write + attention of one layer as one call (of any rows: it may follow any call that plans).  `own_rows`: as `run` calls
+        it where `reads_own_rows`; then a call that reuses a plan follows one that made it with `own_rows`."""
         self._refresh_and_attention(self.k_new[layer], self.v_new[layer], self.k_pool[layer], self.v_pool[layer],
-                                    self.q[layer], self.out[layer], reuse_plan, False)
+                                    self.q[layer], self.out[layer], reuse_plan, own_rows and self.own_rows)
 
     def _refresh_and_attention(self, k_new, v_new, k, v, q, out, reuse_plan, own_rows):
         w = self.data.workload

@@ -963,11 +963,12 @@ def test_refresh_prefill_attn_equals_scatter_then_attention(cs, case):
         say(f"  pass {rep}: {hp.check_attention(out1[:n_q].cpu(), ref, dtype)}")
 
 
-def test_fused_step_equals_the_step_of_separate_calls(cs):
+@pytest.mark.parametrize("n_streams, n_layers", [(3, 3), (32, 2)])      # without a plan; with one, the launch with the barrier
+def test_fused_step_equals_the_step_of_separate_calls(cs, n_streams, n_layers):
     """The whole device-planned step with the refresh write inside the attention launch: cache and
     outputs bit-equal to the step that queues the two calls, also when replayed from a HIP graph.  So is the default step, whose
     calls bring the executed tokens' own rows."""
-    w = synth.small_variant(synth.CFG2, n_streams=3, n_layers=3)
+    w = synth.small_variant(synth.CFG2, n_streams=n_streams, n_layers=n_layers)
     say(f"fused step: {w.name} streams={w.n_streams} layers={w.n_layers}")
     data = engine.assemble_step(w, engine.hip_scorer, device="cpu")
     n_reuse, n_q = data.info["n_reuse"], data.info["n_q"]
