@@ -11,12 +11,13 @@ graph and the timed region replays it K times.
 By default all five bf16 workloads are measured one after the other (the one-stream shape, the
 32-stream batch, both readings of the long window, the 64-stream batch); the top-level `value`,
 `ms_per_step`, `config` and `roofline` are those of the LAST one, the largest (64 streams, 32
-layers), and `workloads` carries the same figures for each.  `--workload NAME` measures one.
+layers), and `workloads` carries the step figures of each.  `--workload NAME` measures one.
 
-Printed: ONE JSON line with the whole-job throughput (executed tokens per second), a `roofline`
-object for the dominant kernel (event-timed on the launch stream), per-kernel rooflines, and a
-`cpu_baseline` object (the CPU oracle timed on this machine's host cores on a bounded sample of the
-headline workload, on all cores and on one).
+Printed: ONE JSON line, short enough for a log's tail: the whole-job throughput (executed tokens per
+second), a `roofline` object for the dominant kernel (event-timed on the launch stream), the step times of
+the workloads, and a `cpu_baseline` object (the CPU oracle timed on this machine's host cores on a bounded
+sample of the headline workload).  The whole record (per-kernel rooflines of every workload, the side legs,
+the parts of the CPU figure) goes to stderr as one line behind `[bench] record`, and to a file with `--record`.
 """
 from __future__ import annotations
 
@@ -66,7 +67,28 @@ def parse():
     ap.add_argument("--side-legs-workload", default="cfg2_qwen7b_32streams",
                     help="the workload whose shapes the side legs (scaled scoring, front end) use when "
                          "several workloads are measured")
+    ap.add_argument("--record", default=None, help="also write the whole record to this file")
     return ap.parse_args()
+
+
+def short_line(out):
+    """The record without what only a reader of all of it needs; floats to six digits."""
+    line = {k: v for k, v in out.items() if k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+                                                  "scaling", "vs_baseline", "dtype", "data", "config", "window_tokens_per_s")}
+    line["roofline"] = out["roofline"]
+    line["kernel_ms"] = {call: [k["ms"], k["launches_per_step"]] for call, k in out["kernels"].items()}
+    line["workloads"] = [{k: w[k] for k in ("workload", "ms_per_step", "tokens_per_s", "host_planned_ms_per_step") if k in w} for w in out["workloads"]]
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: v for k, v in out["cpu_baseline"].items() if k in ("value", "unit", "cores", "kind", "sample", "seconds_per_step",
+                                                                                     "cpu_model", "host_cpus", "workload")}
+    def rounded(v):
+        if isinstance(v, dict):
+            return {k: rounded(x) for k, x in v.items()}
+        if isinstance(v, list):
+            return [rounded(x) for x in v]
+        return float(f"{v:.6g}") if isinstance(v, float) else v
+    exact = ("value", "ms_per_step", "window_tokens_per_s")
+    return {k: v if k in exact else rounded(v) for k, v in line.items()}
 
 
 def kernel_bytes_flops(w, info, n_layers):
@@ -677,7 +699,11 @@ def main():
     out.update(side)
     if cpu is not None:
         out["cpu_baseline"] = cpu
-    print(json.dumps(out))
+    print("[bench] record " + json.dumps(out), file=sys.stderr, flush=True)
+    if args.record:
+        with open(args.record, "w") as fh:
+            json.dump(out, fh)
+    print(json.dumps(short_line(out)))
 
 
 if __name__ == "__main__":
