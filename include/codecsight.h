@@ -471,8 +471,9 @@ int cs_window_prefill_attn(const void* q, const void* k_cache_layer, const void*
  * where a block-table row is too short; a CS_ATTN_PLAN_ONLY call takes slot to tell them); rows from cu_q[n_streams] on have a
  * negative slot; no stream's window holds another stream's new rows, or one of its own at a second position (it would read
  * them from the cache while they are written).  The workspace then takes
- * cs_refresh_prefill_attn_workspace() bytes (and has the status word for either head_dim: 0 after a call that plans and has no barrier), and a REUSE call follows a BUILD or ONLY call with the flag and the same cu_q,
- * q_pos, kv_len, block_table and shape arguments.  Same caches and results, bit for bit, except that a REUSE call of up to 64
+ * cs_refresh_prefill_attn_workspace() bytes (unless 0 with the status word, for either head_dim: a call that plans leaves
+ * it 0), and a REUSE call follows a BUILD or ONLY call with the flag and the same cu_q, q_pos, kv_len, block_table and shape
+ * arguments.  Same caches and results, bit for bit, except that a REUSE call of up to 64
  * streams with T = n_kv_heads * (n_q * n_q_heads / n_kv_heads / 128 + n_streams) of 441 to 510 and 20 to 48 key tiles (of 64
  * entries of max_blocks * 16), or of 512 (768 with more than four kv heads) to 850 and 9 to 32 key tiles, takes another kernel
  * than without the flag, whose results differ by rounding.  What the flag allows (CS_BF16, caches with
